@@ -80,3 +80,40 @@ def test_sar_loss_of_a_sample_matches_oracle(shape_name, k):
         assert int(n.cpu()[0]) == len(terms)
         assert abs(float(loss.cpu()[0]) - sf.loss_sar(o_logits, ref)) < 2 * gc.LOGIT_TIGHT * len(terms)
         assert gm.device_faults() == 0
+
+
+@pytest.mark.parametrize("V,rows,offset", [(1000, 4099, 0),    # more rows than the summing kernel takes at once
+                                           (1000, 5, 1),       # logits that start on 4 bytes
+                                           (31999, 3, 0),      # rows of odd length: every alignment
+                                           (32772, 2, 0)])     # a row longer than what is held in registers
+def test_loss_at_the_edges_of_the_reduction(V, rows, offset):
+    """Row lengths, row counts and alignments where the two kernels change how they read, with masked (-inf)
+    logits: terms against float64 (bar: 2e-5, as above), and the sum is the float32 sum in row order, bit
+    for bit."""
+    torch = gc.require_gpu()
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=1, max_rows=36)
+    rng = np.random.default_rng(V + rows)
+    logits = (rng.standard_normal((rows, V)) * 3.0).astype(np.float32)
+    labels = rng.integers(0, V, size=rows).astype(np.int32)
+    logits[:, ::7] = -np.inf
+    labels[labels % 7 == 0] += 1
+    labels[rows // 2] = -1
+    flat = torch.empty(rows * V + offset, dtype=torch.float32, device="cuda")
+    lg = flat[offset:].view(rows, V)
+    lg.copy_(torch.from_numpy(logits))
+    row_loss = torch.empty(rows, dtype=torch.float32, device="cuda")
+    loss, n = gm.sar_loss(lg, torch.from_numpy(labels).cuda(), row_loss)
+    torch.cuda.synchronize()
+    x = logits.astype(np.float64)
+    mx = x.max(axis=1)
+    want = mx + np.log(np.exp(x - mx[:, None]).sum(axis=1)) - x[np.arange(rows), np.maximum(labels, 0)]
+    want[labels < 0] = 0.0
+    got = row_loss.cpu().numpy()
+    assert np.abs(got.astype(np.float64) - want).max() < 2e-5
+    tot = np.float32(0)
+    for t in got:
+        tot = np.float32(tot + t)
+    assert loss.cpu().numpy()[0] == tot and int(n.cpu()[0]) == int((labels >= 0).sum())
+    assert gm.device_faults() == 0

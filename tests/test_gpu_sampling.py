@@ -398,3 +398,51 @@ def test_sample_verify_error_paths(torch_mod):
         with pytest.raises(binding.SpaceError) as e:
             gm.sample_verify(P, t, lay, pc, u, out, **kw)
         assert e.value.code == binding.SPACE_EINVAL
+
+
+@pytest.mark.parametrize("V,top_k", [(40, 50), (250, 64), (1001, 64), (32000, 10), (32000, 64), (33000, 50)])
+def test_kept_lists_with_equal_and_masked_logits(torch_mod, V, top_k):
+    """The kept tokens of a row where the selection changes its path: vocabularies below top_k, below and
+    above what the threads hold, logits of a few distinct values (hundreds of equal ones), all equal, all
+    masked but a few, one row of NaN beside real values.  Ids in descending order with ties to the lowest id;
+    probabilities against float64 softmax (rel 1e-5: at most 64 float32 terms)."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    k = 8
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=1, max_rows=k + 1, max_ctx=64)
+    spec = lo.first_step_layout(k)
+    lay = gm.layout(spec)
+    rng = np.random.default_rng(V + top_k)
+    P = (rng.standard_normal((k + 1, V)) * 2.5).astype(np.float32)
+    P[1] = np.round(P[1])                                       # a few distinct values
+    P[2] = 0.25                                                 # all equal
+    P[3, rng.permutation(V)[min(7, V - 1):]] = -np.inf          # fewer tokens left than are kept
+    P[4] = np.minimum(P[4], 0.5)                                # a plateau at the top
+    P[5, V // 2:] = P[5, : V - V // 2]                          # every value twice
+    P[6] = np.where(rng.random(V) < 0.5, -0.0, 0.0)             # zeros of both signs are equal
+    P[7, rng.permutation(V)[: max(V // 3, 1)]] = np.nan         # never kept while numbers are left
+    P[8] = np.linspace(-1, 1, V, dtype=np.float32)              # all large values in neighbouring columns
+    u = rng.uniform(0.0, 1.0, size=(1, 1 + k)).astype(np.float32)
+    toks = np.full((1, k + 1), shape.mask_id, dtype=np.int32)
+    toks[0, 0] = 1
+    out = binding.SampleOut(gm, 1, 1, k, top_k)
+    gm.sample_verify(torch.from_numpy(P[None]).cuda(), torch.from_numpy(toks).cuda(), lay,
+                     torch.ones(1, k, device="cuda"), torch.from_numpy(u).cuda(), out, top_k=top_k, top_p=1.0)
+    torch.cuda.synchronize()
+    for j in range(k):
+        x = P[1 + j].astype(np.float64)
+        real = np.flatnonzero(~np.isnan(x))
+        order = real[np.lexsort((real, -x[real]))][: min(top_k, V)]
+        ids, probs = out.new_ids.cpu().numpy()[0, j], out.new_probs.cpu().numpy()[0, j]
+        n = int((ids >= 0).sum())
+        want = np.exp(x[order] - x[order[0]])
+        want /= want.sum()
+        assert np.all(ids[n:] == -1) and 1 <= n <= min(top_k, V)
+        if j == 6 and len(order) < min(top_k, V):
+            continue                                            # the places behind the last number are not defined
+        assert ids[:n].tolist() == order[:n].tolist(), j
+        # what is not kept has no mass left (float32 sums of up to 64 terms reach 1 within 64 ulp)
+        assert want[n:].sum() < 64 * 1.2e-7
+        np.testing.assert_allclose(probs[:n], want[:n], rtol=1e-5, atol=1e-30)

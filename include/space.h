@@ -344,6 +344,8 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *   attn=N   longest context, in 32-key chunks, that the one-launch attention kernel handles
  *            (0: always split over the key axis; 1000000 and more: always the one-launch kernel, also
  *            where a batch would put more than two of its workgroups on a compute unit);
+ *   resid=N  most rows (at most 48) for which O and down are computed without partial sums, norm included
+ *            (0: never);
  *   wide=N   fewest rows for the many-row projection kernel (default 193; 97 for QKV), widemask=M which projections
  *            may use it (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head);
  *   widecut=A:B:C:D:O   forces how that kernel cuts the rows of every launch whose rows make up exactly
@@ -398,7 +400,8 @@ int space_timing_read(space_ctx *ctx, void *stream, double *total_ms, int64_t *l
 /* Test hook: DEVICE address and size in bytes of one scratch buffer of ctx, as the last
  * space_step left it (with several layers: the last layer's contents).  Names:
  *   "x"        fp32 residual stream [rows, d_model];
- *   "xn", "attn_out", "h"  the operands of the projections (normalised rows; attention output,
+ *   "xn", "attn_out", "h"  the operands of the projections (normalised rows, in blocks of few rows short
+ *              of the row's factor 1 / rms, which the projection applies to its sums; attention output,
  *              n_heads*head_dim columns; SwiGLU product, ffn columns) as split-bf16 planes in tile
  *              order: [column tiles of 32][row tiles of 16][hi, lo][64 lanes][8], lane l holding
  *              row l%16 and columns 8*(l/16)..+8 of the tile; the last row tile keeps only its c

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdlib>
@@ -121,6 +122,10 @@ struct space_ctx {
     size_t part_stride = 0;
     int part_ld = 0;
     float* x = nullptr;
+    float* ss = nullptr;  // partial sums of squares of the rows (ResidLaunch)
+    // SPACE_TUNE="resid=N": up to N rows O and down are computed without a split of the contraction, norm
+    // included (0: never); -1: where step_impl's rule says so.
+    int resid_max_rows = -1;
     uint16_t* xn = nullptr;
     float* part = nullptr;
     uint16_t *q = nullptr, *kblk = nullptr, *vblk = nullptr, *attn_out = nullptr, *h = nullptr;
@@ -317,6 +322,9 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
         if (const char* p = strstr(e, "attn=")) {
             if (sscanf(p + 5, "%d", &n) == 1 && n >= 0) ctx->head_attn_max_chunks = n;
         }
+        if (const char* p = strstr(e, "resid=")) {
+            if (sscanf(p + 6, "%d", &n) == 1 && n >= 0) ctx->resid_max_rows = n;
+        }
         if (const char* p = strstr(e, "wideks=")) {
             if (sscanf(p + 7, "%d", &n) == 1 && n >= 0 && n <= 4) ctx->wide_ks = n;
         }
@@ -342,6 +350,7 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     const size_t rt = ctx->row_tiles_max;
     const size_t bh = (size_t)c.max_batch * c.n_heads;
     if ((rc = dev_alloc(ctx, &ctx->x, M * d, true))) return rc;
+    if ((rc = dev_alloc(ctx, &ctx->ss, (size_t)kResidMaxGroups * kResidMaxRows, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->xn, rt * ctx->kt_d * plane_tile, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->part, ctx->part_stride * ctx->part_splits_max, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->q, 2 * ctx->q_plane, true))) return rc;
@@ -431,7 +440,7 @@ void free_ctx(space_ctx* ctx) {
 int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t* x, int m, float* out, int ldo,
              size_t split_stride, uint16_t* h, int ffn, float* logits, hipStream_t s, int* splits_used = nullptr,
              int* groups_used = nullptr, int wide_from = 0, int cls = -1, const WideParts* force_parts = nullptr,
-             int force_ksplit = 0) {
+             int force_ksplit = 0, const float* ss = nullptr, int ss_n = 0) {
     const int pass_rows = 16 * kMaxRowTiles;
     GemmLaunch g{};
     g.w = w;
@@ -443,6 +452,12 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
     g.tiles_per_wave = gemm_tiles_per_wave(w, m);
     g.ldo = ldo;
     g.split_stride = split_stride;
+    if (ss) {  // rows without their norm factor (never with the many-row kernel: see step_impl)
+        g.ss = ss;
+        g.ss_n = ss_n;
+        g.norm_d = (float)ctx->cfg.d_model;
+        g.eps = ctx->cfg.rms_eps;
+    }
     if (epi == EPI_F32) g.out = out;
     if (epi == EPI_SWIGLU) {
         g.h = h;
@@ -702,13 +717,41 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const bool head_attn = L <= kHeadAttnMaxRows && ctx->head_attn_max_chunks > 0 &&
                            (attn_chunks <= head_chunks || (L <= 16 && B * c.n_heads >= 256));
 
+    // Few rows: O and down leave complete rows (residual added) as x * norm weights and the partial sums of
+    // squares, the projection behind them applies the norm factor; no norm launches.  Else split sums and
+    // a norm launch that adds them up.  (The many-row kernel, which a developer knob can force on few rows,
+    // does not apply factors.)
+    const int wide_from = std::min(ctx->wide_min_rows > 0 ? ctx->wide_min_rows : INT_MAX,
+                                   ctx->wide_min_rows_qkv > 0 ? ctx->wide_min_rows_qkv : INT_MAX);
+    const int groups_o = resid_groups(ctx->layers[0].o), groups_dn = resid_groups(ctx->layers[0].down);
+    // Where the line lies: a workgroup of that form reads the operand planes of all rows through its CU, 4
+    // bytes per element, and while weights stream from memory a CU gets through about 50 GB/s whatever
+    // part of it comes out of L2 (7B, 36 rows: O 16.9 us against 11.1 + 5.6 with its norm launch, down 38 against
+    // 21.9 + 5.6).  So: planes up to 100 KB (step of a 256-wide model of 2 layers, 25 rows: 66.3 -> 59.5 us; 512
+    // wide, 16 rows 70.7 -> 67.7, level at 25 rows = 137 KB), or 9 rows (two 7B layers 231.3 -> 226.0, 16 rows
+    // 236 -> 238; one 70B layer 370 -> 359), or 4 where too few workgroups would stream (two 13B layers, 160
+    // workgroups: 304.7 -> 304.0, 9 rows 308 -> 315).
+    const size_t plane_bytes = (size_t)M * kTileK * 4 * std::max(ctx->layers[0].o.k_tiles, ctx->layers[0].down.k_tiles);
+    const bool few = ctx->resid_max_rows >= 0 ? M <= ctx->resid_max_rows
+                                              : plane_bytes <= 100 * 1024 || M <= (groups_o >= 192 ? 9 : 4);
+    const bool resid = few && M <= kResidMaxRows && M < wide_from && groups_o > 0 && groups_dn > 0;
+    const float* ss = nullptr;  // set while xn holds rows without their factor
+    int ss_n = 0;
+    auto project_resid = [&](const PackedW& w, const uint16_t* in, const uint16_t* norm_w, int groups) {
+        ResidLaunch r{};
+        r.w = w; r.in = in; r.xs = xs; r.m = M; r.x = ctx->x; r.norm_w = norm_w; r.xn = ctx->xn; r.ss = ctx->ss;
+        ss = ctx->ss;
+        ss_n = groups;
+        return launch_gemm_resid(r, s);
+    };
+
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerPacked& lp = ctx->layers[l];
         int s_qkv = 1, s_o = 1, s_dn = 1;
         {
             TimedScope ts(ctx, SPACE_K_QKV, s);
             if ((rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, M, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0,
-                               nullptr, s, &s_qkv, nullptr, (ctx->wide_mask & 1) ? ctx->wide_min_rows_qkv : 0, 0)))
+                               nullptr, s, &s_qkv, nullptr, (ctx->wide_mask & 1) ? ctx->wide_min_rows_qkv : 0, 0, nullptr, 0, ss, ss_n)))
                 return rc;
         }
         uint16_t* kc_l = (uint16_t*)kv->k + kv_layer * l;
@@ -763,13 +806,16 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
             }
         }
 
-        {
+        if (resid) {
+            TimedScope ts(ctx, SPACE_K_O, s);
+            HIP_TRY(ctx, project_resid(lp.o, ctx->attn_out, lp.ffn_norm, groups_o));
+        } else {
             TimedScope ts(ctx, SPACE_K_O, s);
             if ((rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, M, ctx->part, d, ctx->part_stride, nullptr, 0,
                                nullptr, s, &s_o, nullptr, (ctx->wide_mask & 2) ? ctx->wide_min_rows : 0, 1)))
                 return rc;
         }
-        {
+        if (!resid) {
             TimedScope ts(ctx, SPACE_K_NORM, s);
             HIP_TRY(ctx, launch_resid_norm(ctx->x, ctx->part, s_o, ctx->part_stride, d, lp.ffn_norm, c.rms_eps, M, d,
                                            ctx->xn, xs, s));
@@ -777,8 +823,14 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_GATE_UP, s);
             if ((rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, M, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr,
-                               (ctx->wide_mask & 4) ? ctx->wide_min_rows : 0, 2)))
+                               (ctx->wide_mask & 4) ? ctx->wide_min_rows : 0, 2, nullptr, 0, ss, ss_n)))
                 return rc;
+        }
+        const uint16_t* next_norm = (l + 1 < c.n_layers) ? ctx->layers[l + 1].attn_norm : ctx->final_norm;
+        if (resid) {
+            TimedScope ts(ctx, SPACE_K_DOWN, s);
+            HIP_TRY(ctx, project_resid(lp.down, ctx->h, next_norm, groups_dn));
+            continue;
         }
         {
             TimedScope ts(ctx, SPACE_K_DOWN, s);
@@ -786,7 +838,6 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
                                s, &s_dn, nullptr, (ctx->wide_mask & 8) ? ctx->wide_min_rows : 0, 3)))
                 return rc;
         }
-        const uint16_t* next_norm = (l + 1 < c.n_layers) ? ctx->layers[l + 1].attn_norm : ctx->final_norm;
         {
             TimedScope ts(ctx, SPACE_K_NORM, s);
             HIP_TRY(ctx, launch_resid_norm(ctx->x, ctx->part, s_dn, ctx->part_stride, d, next_norm, c.rms_eps, M, d,
@@ -802,7 +853,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     {
         TimedScope ts(ctx, SPACE_K_LM_HEAD, s);
         if ((rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, M, nullptr, c.vocab, 0, nullptr, 0, out->logits, s, nullptr,
-                           &lm_groups, (ctx->wide_mask & 16) ? ctx->wide_min_rows : 0, 4)))
+                           &lm_groups, (ctx->wide_mask & 16) ? ctx->wide_min_rows : 0, 4, nullptr, 0, ss, ss_n)))
             return rc;
     }
 

@@ -72,7 +72,31 @@ struct GemmLaunch {
     float* arg_val;
     int32_t* arg_idx;
     int arg_groups;  // row stride of arg_val / arg_idx
+    // Rows that come as x * w without their RMSNorm factor (see ResidLaunch): the factor of row m is made of
+    // ss and applied to the sums.  nullptr: the rows are complete.  At most 48 rows, one pass.
+    const float* ss;  // [ss_n][round_up(m, 4)] partial sums of squares
+    int ss_n;
+    float norm_d, eps;  // factor = 1 / sqrt(sum / norm_d + eps)
 };
+
+// Projection onto the residual stream for at most kResidMaxRows rows, residual add and the next norm's
+// weights included: x += X W^T, xn = operand planes of x * norm_w, ss[workgroup][row] = sum of squares of the
+// workgroup's columns.  The row's factor 1 / sqrt(mean + eps) commutes with the projection behind it, which
+// applies it to its sums (GemmLaunch::ss).
+constexpr int kResidMaxRows = 48;
+constexpr int kResidMaxGroups = 256;
+struct ResidLaunch {
+    PackedW w;          // [d, k]
+    const uint16_t* in; // operand planes [m, k]
+    XtShape xs;         // shape of in and xn (both m rows)
+    int m;
+    float* x;           // [m, d]
+    const uint16_t* norm_w;
+    uint16_t* xn;
+    float* ss;          // [resid_groups(w)][round_up(m, 4)]
+};
+int resid_groups(const PackedW& w);  // workgroups (partial sums of squares per row); 0: not supported
+hipError_t launch_gemm_resid(const ResidLaunch& g, hipStream_t s);
 
 // Packs up to three row-major bf16 matrices with k columns each into w->data (w->bytes() bytes).
 // interleave == 0: rows are concatenated (s0 rows, then s1, then s2).  interleave == 1 (gate / up):

@@ -115,7 +115,7 @@ __device__ __forceinline__ u32x4 load_weight_tile(const u32x4* p) {
     return *p;
 }
 
-template <int T, int R, int EPI, int D>
+template <int T, int R, int EPI, int D, bool SCALED = false>
 __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int bx = blockIdx.x, s = blockIdx.y, pass = 0;
@@ -166,6 +166,19 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Norm factors of the rows, if they are still due: the partial sums of squares are requested in front of
+    // everything else and added up while the first weights are on their way.
+    constexpr int kSsLoads = SCALED ? (kResidMaxGroups + 20) / 21 : 1;  // 21 .. 32 groups of threads for at most 12 row quads
+    __shared__ float s_ss[SCALED ? 256 * 4 : 1], s_rs[SCALED ? 16 * T : 1];
+    const int ss_q = SCALED ? (g.m + 3) >> 2 : 1, ss_c = threadIdx.x % ss_q, ss_g = threadIdx.x / ss_q, ss_groups = min(256 / ss_q, 32);
+    f32x4 ss_p[kSsLoads];
+    if (SCALED) {
+#pragma unroll
+        for (int i = 0; i < kSsLoads; ++i)
+            ss_p[i] = ((const f32x4*)g.ss)[(size_t)min(ss_g + i * ss_groups, g.ss_n - 1) * ss_q + ss_c];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     {
         // Software pipeline of depth D.  Every load of the steady-state loop is unconditional (the
         // index is clamped to the range, a clamped load re-reads the last tile) so that the compiler
@@ -178,6 +191,23 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
             for (int r = 0; r < R; ++r) a[d][r] = load_weight_tile<T>(wp[r] + (size_t)(kt - kw0) * wstep);
 #pragma unroll
             for (int t = 0; t < 2 * T; ++t) b[d][t] = xp[kt * xkt + boff[t]];
+        }
+        if (SCALED) {
+            __builtin_amdgcn_sched_barrier(0);
+            f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kSsLoads; ++i)
+                if (ss_g + i * ss_groups < g.ss_n) sum += ss_p[i];
+            if (ss_g < ss_groups) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s_ss[ss_g * 4 * ss_q + 4 * ss_c + e] = sum[e];
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < g.m) {  // read behind the reduction's barrier below
+                float tot = 0.f;
+                for (int i = 0; i < min(ss_groups, g.ss_n); ++i) tot += s_ss[i * 4 * ss_q + threadIdx.x];
+                s_rs[threadIdx.x] = 1.0f / sqrtf(tot / g.norm_d + g.eps);
+            }
         }
         int kt = kw0;
         for (; kt + D <= kw1; kt += D) {
@@ -238,10 +268,11 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
             for (int i = threadIdx.x; i < RC * T * 64; i += 256) {
                 const int rt = i >> 6, l = i & 63;
                 const int r = rt / T, t = rt % T;
-                const f32x4 v = red[0][rt][l] + red[1][rt][l] + red[2][rt][l] + red[3][rt][l];
-                if (EPI == EPI_ARGMAX) red[0][rt][l] = v;
+                f32x4 v = red[0][rt][l] + red[1][rt][l] + red[2][rt][l] + red[3][rt][l];
                 const int nt = nt0 + rc0 + r;
                 const int tok = 16 * t + (l & 15);
+                if (SCALED) v *= s_rs[min(tok, m_rows - 1)];
+                if (EPI == EPI_ARGMAX) red[0][rt][l] = v;
                 if (nt >= g.w.n_tiles || tok >= m_rows || !outp) continue;
                 const int n = nt * 16 + 4 * (l >> 4);
                 float* o = outp + (size_t)tok * g.ldo + n;
@@ -280,8 +311,12 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
                 if (tok >= m_rows) continue;
                 const int m = row_tile0 * 16 + tok;
                 const int ga = (2 * p) * T + t, ua = (2 * p + 1) * T + t;
-                const f32x4 gt = red[0][ga][l] + red[1][ga][l] + red[2][ga][l] + red[3][ga][l];
-                const f32x4 up = red[0][ua][l] + red[1][ua][l] + red[2][ua][l] + red[3][ua][l];
+                f32x4 gt = red[0][ga][l] + red[1][ga][l] + red[2][ga][l] + red[3][ga][l];
+                f32x4 up = red[0][ua][l] + red[1][ua][l] + red[2][ua][l] + red[3][ua][l];
+                if (SCALED) {
+                    gt *= s_rs[tok];
+                    up *= s_rs[tok];
+                }
                 const int j = (((nt0 + rc0) >> 1) + p) * 16 + 4 * (l >> 4);
                 uint32_t hi[4], lo[4];
 #pragma unroll
@@ -327,6 +362,15 @@ int gemm_groups(const PackedW& w, int tiles_per_wave) { return w.groups * w.r_pa
 template <int EPI, int R, int D>
 static hipError_t launch_gemm_small(const GemmLaunch& g, hipStream_t s) {  // at most 3 row tiles
     const dim3 grid(gemm_groups(g.w, R), g.w.splits), block(256);
+    if (g.ss) {
+        switch (ceil_div(g.m, 16)) {
+            case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D, true>), grid, block, 0, s, g); break;
+            case 2: hipLaunchKernelGGL((gemm_skinny_kernel<2, R, EPI, D, true>), grid, block, 0, s, g); break;
+            case 3: hipLaunchKernelGGL((gemm_skinny_kernel<3, R, EPI, D, true>), grid, block, 0, s, g); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (ceil_div(g.m, 16)) {
         case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D>), grid, block, 0, s, g); break;
         case 2: hipLaunchKernelGGL((gemm_skinny_kernel<2, R, EPI, D>), grid, block, 0, s, g); break;
@@ -378,12 +422,193 @@ hipError_t launch_gemm(const GemmLaunch& g, GemmEpilogue epi, hipStream_t s) {
     if (epi != EPI_F32 && g.w.splits != 1) return hipErrorInvalidValue;
     if (g.row_tile0 < 0 || g.row_tile0 + ceil_div(g.m, 16) > g.xs.row_tiles || g.xs.last_cols < 1 || g.xs.last_cols > 16) return hipErrorInvalidValue;
     if (g.tiles_per_wave > g.w.r_pack || g.w.r_pack % g.tiles_per_wave) return hipErrorInvalidValue;
+    if (g.ss && (g.m > kResidMaxRows || g.passes != 1 || g.row_tile0 != 0 || g.ss_n < 1 || g.ss_n > kResidMaxGroups)) return hipErrorInvalidValue;
     switch (epi) {
         case EPI_F32: return launch_gemm_t<EPI_F32>(g, s);
         case EPI_SWIGLU: return launch_gemm_t<EPI_SWIGLU>(g, s);
         case EPI_ARGMAX: return launch_gemm_t<EPI_ARGMAX>(g, s);
     }
     return hipErrorInvalidValue;
+}
+
+// ------------------------------------------------------------------------------------------
+// projection onto the residual stream for few rows: sums complete in one workgroup, residual add, next norm
+// ------------------------------------------------------------------------------------------
+// With the contraction split over workgroups (gemm_skinny_kernel) the residual add and the RMSNorm need a
+// launch of their own behind the projection, because a row's statistic depends on all of them.  Two
+// things remove it.  A workgroup here owns 16 or 32 columns over the whole contraction -- its 8 waves
+// each take an eighth -- so its sums are complete and it can add the residual and write operand planes.  And
+// the row's factor is left out of them: it is a scalar per row, so the next projection applies it to its
+// sums, from the partial sums of squares that are written here.
+// The price: every workgroup reads all activation planes through its own CU.  A CU's vector loads come back
+// in order, so next to weights from memory (2 .. 3 us) planes out of L2 move no faster than these: about 50 GB/s
+// per CU in all, 82 .. 109 without weights from memory.  Worth it for few rows or short contractions; the rule
+// is in space_api.hip.  More loads in flight (7 tiles, 16 waves) change nothing.
+
+template <int T, int R, int D>
+__global__ __launch_bounds__(512, 2) void gemm_resid_kernel(ResidLaunch g) {
+    constexpr int W = 8;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nt0 = blockIdx.x * R;
+    const int d = g.w.n;
+
+    // what the epilogue adds to: one item (tile, lane) per thread, requested first
+    const int e_rt = threadIdx.x >> 6, e_r = e_rt / T, e_tok = 16 * (e_rt % T) + (lane & 15);
+    const int e_n = (nt0 + min(e_r, R - 1)) * 16 + 4 * (lane >> 4);
+    const bool e_on = e_rt < R * T && e_tok < g.m;
+    const f32x4 x_old = *(const f32x4*)(g.x + (size_t)min(e_tok, g.m - 1) * d + e_n);
+    const u32x2 w_norm = *(const u32x2*)(g.norm_w + e_n);
+
+    const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc((void*)g.w.data, 0, -1, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc((void*)g.in, 0, 0x7fffffff, 0x00020000);
+    const int xkt = ((g.xs.row_tiles - 1) * 128 + 8 * g.xs.last_cols) * 16;  // bytes of a contraction tile's planes
+    int boff[2 * T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int c = t == g.xs.row_tiles - 1 ? g.xs.last_cols : 16;
+        boff[2 * t] = (t * 128 + (lane >> 4) * c + min(lane & 15, c - 1)) * 16;
+        boff[2 * t + 1] = boff[2 * t] + 64 * c;
+    }
+    // The packed matrix cuts the contraction into 4 * splits ranges of lq tiles, and tiles of the same place
+    // in all ranges lie together.  The waves take the ranges in turn (halves of them if there are only
+    // four), all at the same place at the same time: what the grid reads at a time is then contiguous.
+    const uint32_t wstep = (uint32_t)g.w.splits * g.w.groups * 4 * g.w.r_pack * kTileBytes;
+    const uint32_t nt_off = (uint32_t)((nt0 / g.w.r_pack) * 4 * g.w.r_pack + nt0 % g.w.r_pack) * kTileBytes;
+    const int halves = g.w.splits == 1 ? 2 : 1, n_part = 4 * g.w.splits * halves, part = (g.w.lq + halves - 1) / halves;
+    auto part_first = [&](int q) { return (q / halves) * g.w.lq + (q % halves) * part; };
+    auto part_len = [&](int q) {  // real tiles (the packed ranges are padded)
+        const int k0 = part_first(q);
+        return max(min(min(part, g.w.lq - (q % halves) * part), g.w.k_tiles - k0), 0);
+    };
+    auto part_off = [&](int q) -> uint32_t {
+        const int rq = q / halves;
+        return ((uint32_t)(rq >> 2) * g.w.groups * 4 + (rq & 3)) * g.w.r_pack * kTileBytes + nt_off + (uint32_t)((q % halves) * part) * wstep;
+    };
+    int steps = 0;
+    for (int q = wave; q < n_part; q += W) steps += part_len(q);
+    int s_q = wave, s_left = part_len(wave), s_kt = part_first(wave);  // the tile requested next (parts in front are longest: never empty first)
+    uint32_t w_off = __builtin_amdgcn_readfirstlane(part_off(wave));
+    auto next_tile = [&]() {  // behind the last one: that one again
+        const bool inside = s_left > 1;
+        const int q = s_q + W;
+        const bool more = inside || (q < n_part && part_len(q) > 0);
+        const uint32_t off = inside ? w_off + wstep : part_off(q);
+        const int left = inside ? s_left - 1 : part_len(q), kt = inside ? s_kt + 1 : part_first(q);
+        w_off = more ? off : w_off;
+        s_left = more ? left : s_left;
+        s_kt = more ? kt : s_kt;
+        s_q = more && !inside ? q : s_q;
+    };
+
+    f32x4 acc[R][T];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (steps > 0) {  // (short contractions leave waves without work)
+        u32x4 a[D][R], b[D][2 * T];
+        auto load = [&](u32x4(&al)[R], u32x4(&bl)[2 * T]) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)  // read once on the chip: non-temporal
+                al[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16 + r * kTileBytes, (int)w_off, 2));
+#pragma unroll
+            for (int t = 0; t < 2 * T; ++t)
+                bl[t] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, boff[t], s_kt * xkt, 0));
+            next_tile();
+        };
+        auto products = [&](const u32x4(&al)[R], const u32x4(&bl)[2 * T]) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int t = 0; t < T; ++t) acc[r][t] = mfma16(al[r], bl[2 * t + p], acc[r][t]);
+        };
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+            load(a[i], b[i]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int n = 0;
+        for (; n + D <= steps; n += D) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                products(a[i], b[i]);
+                load(a[i], b[i]);
+                __builtin_amdgcn_sched_barrier(0);  // the refill of slot i right behind its products
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if (n + i < steps) products(a[i], b[i]);
+    }
+
+    // the waves' sums in wave order, then everything behind the projection
+    __shared__ f32x4 red[W][R * T][64];
+    __shared__ float s_sq[R][T * 16];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < T; ++t) red[wave][r * T + t][lane] = acc[r][t];
+    __syncthreads();
+    if (e_rt < R * T) {  // whole waves
+        f32x4 sum = red[0][e_rt][lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) sum += red[w][e_rt][lane];
+        const f32x4 v = x_old + sum;
+        const float sq = row_groups_sum(v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]);
+        if (lane < 16) s_sq[e_r][e_tok] = sq;
+        if (e_on) {
+            *(f32x4*)(g.x + (size_t)e_tok * d + e_n) = v;
+            const float wf[4] = {bf2f((uint16_t)(w_norm[0] & 0xFFFF)), bf2f((uint16_t)(w_norm[0] >> 16)),
+                                 bf2f((uint16_t)(w_norm[1] & 0xFFFF)), bf2f((uint16_t)(w_norm[1] >> 16))};
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float y = v[e] * wf[e];
+                const uint16_t h = f2bf(y);
+                hi[e] = h;
+                lo[e] = f2bf(y - bf2f(h));
+            }
+            *(u32x2*)(g.xn + xt_index(e_tok, e_n, g.xs, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+            *(u32x2*)(g.xn + xt_index(e_tok, e_n, g.xs, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+        }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < g.m) {
+        float sq = s_sq[0][threadIdx.x];
+#pragma unroll
+        for (int r = 1; r < R; ++r) sq += s_sq[r][threadIdx.x];
+        g.ss[(size_t)blockIdx.x * ((g.m + 3) & ~3) + threadIdx.x] = sq;
+    }
+}
+
+// 16 columns per workgroup while that makes at most one workgroup per CU, 32 beyond.
+int resid_groups(const PackedW& w) {
+    if (w.n % 32 || w.n_tiles > 2 * kResidMaxGroups || w.r_pack % 2 || w.bytes() >= ((size_t)1 << 32)) return 0;
+    return w.n_tiles <= kResidMaxGroups ? w.n_tiles : w.n_tiles / 2;
+}
+
+template <int R>
+static hipError_t launch_gemm_resid_r(const ResidLaunch& g, hipStream_t s) {
+    const dim3 grid(g.w.n_tiles / R), block(512);
+    constexpr int D = R == 1 ? 6 : 5;
+    switch (g.xs.row_tiles) {
+        case 1: hipLaunchKernelGGL((gemm_resid_kernel<1, R, D>), grid, block, 0, s, g); break;
+        case 2: hipLaunchKernelGGL((gemm_resid_kernel<2, R, D>), grid, block, 0, s, g); break;
+        case 3: hipLaunchKernelGGL((gemm_resid_kernel<3, R, D>), grid, block, 0, s, g); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_resid(const ResidLaunch& g, hipStream_t s) {
+    const int groups = resid_groups(g.w);
+    if (groups < 1 || g.m < 1 || g.m > kResidMaxRows || g.xs.row_tiles != ceil_div(g.m, 16) ||
+        g.xs.last_cols != g.m - 16 * (g.xs.row_tiles - 1) || g.w.k_tiles < 1)
+        return hipErrorInvalidValue;
+    return groups == g.w.n_tiles ? launch_gemm_resid_r<1>(g, s) : launch_gemm_resid_r<2>(g, s);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -109,6 +109,7 @@ struct space_ctx {
     // measured it; key = class << 32 | rows.  Without an entry: pieces of 128 rows and one for the rest.
     struct WideTuned { WideParts parts; int ksplit; };  // ksplit 0: the plan's own
     std::map<uint64_t, WideTuned> wide_parts;
+    std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
     // wide_cut_groups groups of two row tiles (0: none)
     WideParts wide_cut{};
@@ -477,14 +478,22 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
             const auto it = ctx->wide_parts.find(((uint64_t)cls << 32) | (uint32_t)m);
             if (it != ctx->wide_parts.end()) tuned = &it->second;
         }
-        WidePlan p = plan_gemm_wide(w, m, epi, ctx->part_splits_max,
-                                    force_parts ? force_ksplit : ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0);
-        if (force_parts) {
-            p.parts = *force_parts;
-        } else if (tuned) {
-            p.parts = tuned->parts;
-        } else if (ctx->wide_cut_groups > 0 && ctx->wide_cut_groups == ceil_div(ceil_div(m, 16), 2)) {
-            p.parts = ctx->wide_cut;
+        const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)m;
+        WidePlan p;
+        const auto known = !force_parts && cls >= 0 ? ctx->wide_plans.find(key) : ctx->wide_plans.end();
+        if (known != ctx->wide_plans.end()) {
+            p = known->second;
+        } else {
+            const bool knob = ctx->wide_cut_groups > 0 && ctx->wide_cut_groups == ceil_div(ceil_div(m, 16), 2);
+            p = plan_gemm_wide(w, m, epi, ctx->part_splits_max,
+                               force_parts ? force_ksplit : ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0,
+                               force_parts ? force_parts : tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr);
+            if (!force_parts && cls >= 0) {
+                try {
+                    ctx->wide_plans[key] = p;
+                } catch (...) {  // no room to remember it: made again next time
+                }
+            }
         }
         if (splits_used) *splits_used = p.ksplit;
         if (groups_used) *groups_used = p.n_groups;
@@ -1067,7 +1076,8 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         if (left == 3) ++b; else if (left == 2) ++cc; else if (left == 1) return add(a, b, cc, 1);
         add(a, b, cc, 0);
     };
-    rest(groups / 4, 0, 0, groups % 4);                                   // pieces of 128 rows: cands[0] is what an unmeasured launch uses
+    cands.push_back(WideParts{});                                         // cands[0]: what an unmeasured launch uses, per projection below
+    rest(groups / 4, 0, 0, groups % 4);                                   // pieces of 128 rows
     rest(0, groups / 3, 0, groups % 3);                                   // of 96 rows
     add(0, 0, groups / 2, groups % 2);                                    // of 64 rows
     { const int a = groups / 8; add(a, 0, (groups - 4 * a) / 2, (groups - 4 * a) % 2); }           // half of them large
@@ -1085,13 +1095,19 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         // work, the norm kernels) pays for each of them, which a measurement of the projection alone does
         // not show: the time to read the extra partial sums once is put on top.
         const bool plain = cls == 0 || cls == 1 || cls == 3;
+        WidePlan own;
+        {
+            const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
+            own = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max);
+            cands[0] = own.parts;
+        }
         const int ks_cands[4] = {0, 1, 2, 4};
         float best_ms = 0.f, default_ms = 0.f;
         int best = -1, best_ks = 0;
         for (int kc = 0; kc < (plain ? 4 : 1) && rc == SPACE_OK; ++kc)
         for (int i = 0; i < (int)cands.size() && rc == SPACE_OK; ++i) {
-            const int ks = ks_cands[kc];
-            if (ks > ctx->part_splits_max) continue;
+            const int ks = kc == 0 ? own.ksplit : ks_cands[kc];
+            if (ks > ctx->part_splits_max || (kc > 0 && ks == own.ksplit)) continue;
             float ms_min = 0.f;
             for (int rep = 0; rep < 4 && rc == SPACE_OK; ++rep) {  // the first one warms up
                 if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(ctx, SPACE_EHIP, "hipEventRecord"); break; }
@@ -1113,7 +1129,7 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
             }
             if (plain) {  // every partial sum beyond the first is read once more, at about 4 TB/s
                 const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : have[0]->down;
-                const int used = plan_gemm_wide(pw, rows, EPI_F32, ctx->part_splits_max, ks).ksplit;
+                const int used = plan_gemm_wide(pw, rows, EPI_F32, ctx->part_splits_max, ks, &cands[i]).ksplit;
                 const int n_out = cls == 0 ? hd + 2 * ctx->hd_kv : d;
                 ms_min += (float)((double)(used - 1) * rows * n_out * 4.0 / 4.0e9);
             }
@@ -1122,7 +1138,8 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         }
         // Same projection back to back is not quite the step's own sequence of kernels: another cut (or
         // split) is taken only where it is clearly ahead.
-        if (rc == SPACE_OK && (best > 0 || best_ks > 0) && best_ms < 0.90f * default_ms)
+        ctx->wide_plans.erase(((uint64_t)cls << 32) | (uint32_t)rows);
+        if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms)
             ctx->wide_parts[((uint64_t)cls << 32) | (uint32_t)rows] = space_ctx::WideTuned{cands[best], best_ks};
     }
     (void)hipEventDestroy(e0);

@@ -128,8 +128,10 @@ struct WidePlan {
     int kt_per_split;    // contraction tiles per partial sum
 };
 // force_ksplit > 0: that many partial sums over the contraction instead of the cost model's choice
-// (plain-sum epilogue only; rounded down to what leaves every split at least one pipeline round)
-WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit = 0);
+// (plain-sum epilogue only; rounded down to what leaves every split at least one pipeline round); cut: this
+// cut of the rows instead of the model's
+WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit = 0,
+                        const WideParts* cut = nullptr);
 // g.passes and g.tiles_per_wave are ignored (the plan's pieces are used); g.row_tile0 must be 0.
 hipError_t launch_gemm_wide(const GemmLaunch& g, const WidePlan& p, GemmEpilogue epi, hipStream_t s);
 

@@ -114,11 +114,9 @@ struct space_ctx {
     // wide_cut_groups groups of two row tiles (0: none)
     WideParts wide_cut{};
     int wide_cut_groups = 0;
-    // Longest context, in 32-key chunks, that a lone sequence handles with one workgroup per (head, query
-    // tile); measured cross-over with the split over the key axis on a 7B-shaped model: between 1536
-    // (4.09 against 4.14 ms per step) and 2048 tokens (4.26 against 4.25).
-    // SPACE_TUNE="attn=N" overrides (0: always split over the key axis).
-    int head_attn_max_chunks = 36;
+    // SPACE_TUNE="attn=N": longest context, in 32-key chunks, that the one-launch attention handles (0: always
+    // split over the key axis); -1: what step_impl's rule says.
+    int head_attn_max_chunks = -1;
     int wide_ks = 0;      // SPACE_TUNE wideks=N: partial sums over the contraction in the many-row kernel (0: cost model / measurement)
     size_t part_stride = 0;
     int part_ld = 0;
@@ -706,25 +704,31 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     paging.table = kv->block_table;
     paging.table_stride = kv->table_stride;
     paging.n_pages = kv->n_pages;
-    // One workgroup per head (rotary, store and attention fused) while the context is short enough
-    // for a single CU to get through a head's keys; the split over the key axis beyond.
-    // (with one query tile and at least a workgroup per CU it also wins at any length; with several query
-    // tiles every tile's workgroup would read the head's K/V again, which long contexts do not forgive)
-    // In a batch the kernel with one workgroup per (sequence, head, query tile) puts several workgroups on
-    // a CU, each of which stages and reads the head's keys again, and beyond 256 workgroups it runs in two
-    // rounds.  Measured against the split (7B, k = 5, us per layer at 256 / 512 / 1024 cached positions):
-    // 2 sequences 9.0 / 13.3 / 22.7 against 15.4 / 19.2 / 25.3; 3 sequences (288 workgroups) 22.4 / 30.7 /
-    // 44.0 against 20.1 / 24.2 / 31.5; 4 sequences 17.2 / 27.8 / 41.6 against 20.9 / 26.2 / 32.9; 6 sequences
-    // lose at any length.  So: beyond one workgroup per CU only up to 12 chunks (the block's own two and
-    // about 320 cached positions), beyond two per CU never.
-    const long long head_wgs = (long long)B * c.n_heads * ceil_div(L, 16);
+    // One workgroup per (sequence, head, query tile) -- rotary, store, attention and output in one launch --
+    // while the context is short; cut over the key axis, with a merge launch behind, beyond.  Where the line
+    // lies depends on the query tiles: the cut form stages all rows of the block in every workgroup and merges
+    // them, which costs 9 us for one tile and 17 for three whatever the context, the other one pulls a head's keys
+    // through one CU per tile.  Measured at 7B, one launch / cut, us per layer:
+    //   one tile (4 rows), 320 / 400 / 518 / 768 / 1023 positions: 8.1 / 8.8, 9.7 / 9.1, 12.6 / 9.4, 14.7 / 9.4,
+    //     20.6 / 11.1 (9 rows); 2 sequences at 384: 9.8 / 9.1; 4 at 512: 12.8 / 12.8; 8 at 256 and 1024: 10.1 /
+    //     10.1, 26.1 / 23.8;
+    //   two tiles (25 rows), 518 / 640 / 900: 12.8 / 13.3, 14.9 / 12.3, 18.7 / 13.5; 4 sequences at 512 and 1024:
+    //     19.2 / 20.8, 27.6 / 27.3;
+    //   three tiles (36 rows), 768 / 900 / 1023: 16.1 / 16.9, 18.7 / 18.0, 20.2 / 19.5 (70B: 21.8 / 19.9); 2
+    //     sequences at 512 and 1024: 15.3 / 20.9, 22.6 / 23.1.
+    // Beyond 256 workgroups the one-launch form puts several on a CU, each of which stages and reads the head's
+    // keys again: only up to 12 chunks (the block's own two and about 320 positions; 4 sequences of three tiles at
+    // 256 / 512: 18.3 / 22.4, 27.7 / 24.9), beyond 384 never (8 sequences of two tiles, 512 workgroups, at 256:
+    // 22.7 / 16.0).
+    const int q_tiles = ceil_div(L, 16);
+    const long long head_wgs = (long long)B * c.n_heads * q_tiles;
     long long head_chunks = ctx->head_attn_max_chunks;
+    if (head_chunks < 0) head_chunks = q_tiles == 1 ? 12 : q_tiles == 2 ? (B == 1 ? 19 : 30) : (B == 1 ? 29 : 36);
     if (head_chunks < 1000000) {  // (1000000 and more: the developer knob that forces this kernel)
-        if (head_wgs > 512) head_chunks = 0;
+        if (head_wgs > 384) head_chunks = 0;
         else if (head_wgs > 256) head_chunks = std::min<long long>(head_chunks, 12);
     }
-    const bool head_attn = L <= kHeadAttnMaxRows && ctx->head_attn_max_chunks > 0 &&
-                           (attn_chunks <= head_chunks || (L <= 16 && B * c.n_heads >= 256));
+    const bool head_attn = L <= kHeadAttnMaxRows && attn_chunks <= head_chunks;
 
     // Few rows: O and down leave complete rows (residual added) as x * norm weights and the partial sums of
     // squares, the projection behind them applies the norm factor; no norm launches.  Else split sums and

@@ -812,6 +812,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
             at.batch = B; at.L = L; at.Lp = Lp; at.n_heads = c.n_heads; at.n_kv_heads = ctx->kv_heads; at.head_dim = dh;
             at.capacity = kv->capacity;
             at.n_wg = attn_wg;
+            at.cache_chunks = ceil_div(kv->host_len_bound, kAttnKeys);
             at.o_part = ctx->o_part; at.ml_part = ctx->ml_part; at.out = ctx->attn_out; at.out_shape = xs; at.paging = paging;
             {
                 TimedScope ts(ctx, SPACE_K_ATTN, s);

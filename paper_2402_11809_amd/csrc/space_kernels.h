@@ -199,6 +199,7 @@ struct AttnLaunch {
     const int32_t* info;
     int batch, L, Lp, n_heads, n_kv_heads, head_dim, capacity;
     int n_wg;        // workgroups along the key axis: attention_workgroups(upper bound of len, L, streams)
+    int cache_chunks = 0;  // upper bound of the cached 32-key chunks of a sequence (picks the query tiles per workgroup)
     float* o_part;   // [B][H][n_wg][L][dh]
     float* ml_part;  // [B][H][n_wg][L][2]
     uint16_t* out;   // operand planes of the attention output, [B*L rows, n_heads*head_dim]

@@ -2060,11 +2060,26 @@ int attention_workgroups(int len_bound, int L, int streams) {
     return want < cap ? want : cap;
 }
 
+// Query tiles per workgroup.  Three share every chunk of keys best (long blocks: 3 tiles 165 us, 2 tiles 184 us at
+// 1024 rows behind 3000 positions, 7B), two make more and shorter workgroups: better while all of them are on
+// the chip at once, two per CU (7B: 333 rows 17.1 -> 14.0, 400 rows 21.2 -> 16.8, 512 rows 23.0 -> 18.1 and behind
+// 1024 positions 48.7 -> 44.2; 70B: 256 rows 18.9 -> 14.1) -- unless three give every CU at most one and
+// the cached keys, which all workgroups read alike, outweigh the block's own (13B: 256 rows behind 1500
+// positions 41.0 against 48.1).  Where both make the same number of groups, two waste less on padding.
+static int attention_query_tiles(const AttnLaunch& a) {
+    const int tiles = ceil_div(a.L, 16);
+    if (tiles < 3 || a.qkv) return tiles < 3 ? tiles : 3;
+    const int per = a.batch * a.n_heads * a.n_wg, wgs3 = per * ceil_div(tiles, 3), wgs2 = per * ceil_div(tiles, 2);
+    if (wgs2 == wgs3) return 2;
+    if (wgs2 > 512) return 3;
+    return wgs3 <= 256 && wgs2 > 256 && a.cache_chunks > 2 * ceil_div(a.L, kAttnKeys) ? 3 : 2;
+}
+
 template <int DH, bool PAGED>
 static hipError_t launch_attention_dh(const AttnLaunch& a, hipStream_t s) {
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)DH));
     const int tiles = ceil_div(a.L, 16);
-    const int TQ = tiles >= 3 ? 3 : tiles;
+    const int TQ = attention_query_tiles(a);
     const int QG = ceil_div(tiles, TQ);
     const dim3 grid(a.n_wg, a.n_heads, a.batch * QG), block(4 * 64);
     if (a.qkv) {  // rotary and K/V staging inside the kernel: one query group, at most 48 rows

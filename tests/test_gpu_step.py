@@ -760,3 +760,18 @@ def test_residual_projections_with_the_norm_included(torch_mod, shape_name, B, k
     # k = 5); the bar stated for all logits holds
     tol = gc.LOGIT_TOL if shape_name == "wide-residual" else gc.LOGIT_TIGHT
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=4), B, k, tune, tol)
+
+
+@pytest.mark.parametrize("shape_name,B,k,ctxs", [
+    ("tiny", 1, 6, [0]),                   # 49 rows: a last query tile of one row, nothing cached
+    ("small128", 2, 7, [31, 700]),         # 64 rows: two full pairs of query tiles, cut over the key axis
+    ("gqa128", 3, 7, [1, 64, 333]),
+    ("gqa-small", 40, 8, "ragged"),        # 320 x 3 workgroups of two tiles would not fit the chip: three tiles
+])
+def test_query_tiles_per_workgroup_of_long_blocks(torch_mod, shape_name, B, k, ctxs):
+    """Blocks beyond 48 rows on both sides of the rule that gives a workgroup two or three query tiles; every
+    sequence against its own oracle step."""
+    shape = SHAPES[shape_name]
+    if ctxs == "ragged":
+        ctxs = [(37 * (b + 1)) % 220 for b in range(B)]
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=6), B, k, None, gc.LOGIT_TIGHT, ctxs=ctxs, capacity=736)

@@ -710,8 +710,8 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     // them, which costs 9 us for one tile and 17 for three whatever the context, the other one pulls a head's keys
     // through one CU per tile.  Measured at 7B, one launch / cut, us per layer:
     //   one tile (4 rows), 320 / 400 / 518 / 768 / 1023 positions: 8.1 / 8.8, 9.7 / 9.1, 12.6 / 9.4, 14.7 / 9.4,
-    //     20.6 / 11.1 (9 rows); 2 sequences at 384: 9.8 / 9.1; 4 at 512: 12.8 / 12.8; 8 at 256 and 1024: 10.1 /
-    //     10.1, 26.1 / 23.8;
+    //     20.6 / 11.1 (9 rows); 2 sequences at 384: 9.8 / 9.1; 3 and 4 at 512: 12.3 / 11.6, 12.8 / 12.8 (the
+    //     merge grows with the rows); 8 at 256 and 1024: 10.1 / 10.1, 26.1 / 23.8;
     //   two tiles (25 rows), 518 / 640 / 900: 12.8 / 13.3, 14.9 / 12.3, 18.7 / 13.5; 4 sequences at 512 and 1024:
     //     19.2 / 20.8, 27.6 / 27.3;
     //   three tiles (36 rows), 768 / 900 / 1023: 16.1 / 16.9, 18.7 / 18.0, 20.2 / 19.5 (70B: 21.8 / 19.9); 2
@@ -723,7 +723,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const int q_tiles = ceil_div(L, 16);
     const long long head_wgs = (long long)B * c.n_heads * q_tiles;
     long long head_chunks = ctx->head_attn_max_chunks;
-    if (head_chunks < 0) head_chunks = q_tiles == 1 ? 12 : q_tiles == 2 ? (B == 1 ? 19 : 30) : (B == 1 ? 29 : 36);
+    if (head_chunks < 0) head_chunks = q_tiles == 1 ? std::min(10 + 2 * B, 18) : q_tiles == 2 ? (B == 1 ? 20 : 30) : (B == 1 ? 29 : 36);
     if (head_chunks < 1000000) {  // (1000000 and more: the developer knob that forces this kernel)
         if (head_wgs > 384) head_chunks = 0;
         else if (head_wgs > 256) head_chunks = std::min<long long>(head_chunks, 12);

@@ -254,7 +254,9 @@ typedef struct space_sample_params {
 
 /* All pointers DEVICE and caller-owned.  B = batch, L / G = rows / groups of `layout`.
  * Inputs: logits, tokens, p_c, uniforms are required; draft_* only when residual != 0.
- * Outputs may be NULL (then not written) except accepted_len, extra, new_cands, new_pc. */
+ * Outputs may be NULL (then not written) except accepted_len, extra, new_cands, new_pc.  new_pc, new_ids and
+ * new_probs may be the buffers p_c, draft_ids and draft_probs (a loop that keeps one set), next_tokens may
+ * be tokens. */
 typedef struct space_sample_io {
     const float *logits;      /* [B, L, vocab] */
     const int32_t *tokens;    /* [B, L]  the block that produced the logits                       */

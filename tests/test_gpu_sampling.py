@@ -446,3 +446,48 @@ def test_kept_lists_with_equal_and_masked_logits(torch_mod, V, top_k):
         # what is not kept has no mass left (float32 sums of up to 64 terms reach 1 within 64 ulp)
         assert want[n:].sum() < 64 * 1.2e-7
         np.testing.assert_allclose(probs[:n], want[:n], rtol=1e-5, atol=1e-30)
+
+
+@pytest.mark.parametrize("k,top_k", [(1, 1), (4, 8), (8, 64)])
+def test_residual_rule_with_the_draft_lists_updated_in_place(torch_mod, k, top_k):
+    """A loop may keep one set of draft buffers: new_pc, new_ids and new_probs on p_c, draft_ids and
+    draft_probs.  All outputs equal those of separate buffers bit for bit.  The candidates are the likeliest
+    tokens of their rows with a p_c of two: every test rejects at least half of the time, so the residual rule applies."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    V, B = 2000, 8
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    spec = lo.paper_layout(k)
+    L, G = spec.n_rows, spec.n_groups
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=B, max_rows=L, max_ctx=128)
+    lay = gm.layout(spec)
+    rng = np.random.default_rng(100 * k + top_k)
+    P = (rng.standard_normal((B, L, V)) * 2.0).astype(np.float32)
+    top = np.argsort(-P, axis=2)[..., :top_k]
+    real = gc.real_rows(spec)
+    toks = np.full((B, L), shape.mask_id, dtype=np.int32)
+    toks[:, real[0]] = 1
+    d_ids = rng.integers(0, V, size=(B, k, top_k)).astype(np.int32)
+    for i in range(k):
+        d_ids[:, i, : top_k // 2 + 1] = top[:, real[i], : top_k // 2 + 1]
+        toks[:, real[i + 1]] = d_ids[:, i, 0]
+    d_pr = rng.dirichlet(np.ones(top_k), size=(B, k)).astype(np.float32)
+    u = rng.uniform(0, 1, size=(B, G + k)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    logits, tokens, uni = dev(P), dev(toks), dev(u)
+
+    def call(in_place):
+        ids, probs, pc = dev(d_ids), dev(d_pr), torch.full((B, k), 2.0, device="cuda")
+        out = binding.SampleOut(gm, B, G, k, top_k, next_rows=L)
+        if in_place:
+            out.new_ids, out.new_probs, out.new_pc = ids, probs, pc
+        gm.sample_verify(logits, tokens, lay, pc, uni, out, top_k=top_k, top_p=1.0, residual=True, draft_ids=ids,
+                         draft_probs=probs, next_layout=lay)
+        torch.cuda.synchronize()
+        return [getattr(out, n).cpu().numpy() for n in ("accepted_len", "extra", "new_cands", "new_pc", "new_ids", "new_probs", "next_tokens", "ratios")]
+
+    want = call(False)
+    assert (want[0] < k).any()
+    for x, y in zip(want, call(True)):
+        assert np.array_equal(x, y)

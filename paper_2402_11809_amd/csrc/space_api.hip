@@ -1143,9 +1143,12 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         }
         // Same projection back to back is not quite the step's own sequence of kernels: another cut (or
         // split) is taken only where it is clearly ahead.
-        ctx->wide_plans.erase(((uint64_t)cls << 32) | (uint32_t)rows);
+        const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)rows;
+        ctx->wide_plans.erase(key);
         if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms)
-            ctx->wide_parts[((uint64_t)cls << 32) | (uint32_t)rows] = space_ctx::WideTuned{cands[best], best_ks};
+            ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
+        else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
+            ctx->wide_plans[key] = own;  // what the next launch would plan again
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

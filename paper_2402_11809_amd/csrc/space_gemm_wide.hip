@@ -24,7 +24,6 @@
 #include "space_device.h"
 #include "space_kernels.h"
 
-#include <algorithm>
 #include <limits.h>
 #include <math.h>
 #include <stdlib.h>
@@ -41,8 +40,6 @@ namespace {
 constexpr int kWideStage = 2;   // contraction tiles per LDS stage
 constexpr int kWideWaves = 8;   // waves per workgroup
 constexpr int kWideTiles = 2;   // weight tiles per wave: a workgroup covers 256 weight rows
-constexpr int kWideDepth = 2;   // weight tiles in flight per wave and tile row
-constexpr int kWideSearchGroups = 32;  // longest blocks (in groups of 32 rows) whose cuts are compared
 
 template <int W, int R, int KS, int DA, int EPI>
 __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch g, int ksplit, int n_groups, int kt_per_split,
@@ -385,78 +382,14 @@ hipError_t launch_wide_r(const GemmLaunch& g, int ksplit, int n_groups, int kt_p
 
 }  // namespace
 
-// What a launch costs, in us: the work of its busiest CU.  A CU gets through one piece after the other, or
-// two at half speed each; workgroup i runs on XCD i % 8, the first two rounds on its 32 CUs in turn, later
-// ones where a place is free.  A piece of g groups over kt contraction tiles takes 17.4 us * (kt / 128 * (0.6 +
-// g) + 0.4), one of a single group 0.2 * kt / 128 more: fitted on 790 x 4 launches (224 .. 1024 rows at 7B and 13B
-// width, all projections, up to 26 cuts, both orders, 1, 2 and 4 partial sums; off by 7.9 % rms).
-static double wide_cost(const WideParts& parts, int gk8, int kt) {
-    constexpr int kCus = 32;
-    double piece[5], load[kCus] = {0.0}, top = 0.0;
-    for (int g = 1; g <= 4; ++g) piece[g] = 17.4 * (kt / 128.0 * (g + (g == 1 ? 0.8 : 0.6)) + 0.4);
-    int placed = 0;
-    auto place = [&](int g) {
-        int at = placed % kCus;
-        if (placed >= 2 * kCus) at = (int)(std::min_element(load, load + kCus) - load);
-        load[at] += piece[g];
-        ++placed;
-    };
-    if (parts.by_size) {
-        for (int c = 0; c < 4; ++c)
-            for (int i = 0; i < gk8 * parts.count[c]; ++i) place(4 - c);
-    } else {
-        for (int i = 0; i < gk8; ++i)
-            for (int c = 0; c < 4; ++c)
-                for (int n = 0; n < parts.count[c]; ++n) place(4 - c);
-    }
-    for (double l : load) top = l > top ? l : top;
-    return top;
-}
-
-// Cut of the rows and number of partial sums with the lowest cost, a partial sum beyond the first charged
-// with the time to read it.  Pieces of 128 rows and one for the rest, large ones first, unless another cut is
-// ahead by more than 5 % (the model's picks are 2 % above the best cut measured, on average).  Why it matters:
-// gate / up at 333 rows and 7B width makes 258 workgroups of 128 and 96 rows, i.e. two CUs with two of them,
-// 140 us; the cut picked here 120.  O and down at 224 rows 28 -> 21 and 63 -> 45 us.  Beyond 1024 rows there are many
-// rounds and the cut matters little.
 WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit, const WideParts* cut) {
     WidePlan p{};
-    const int row_tiles = ceil_div(m, 16), groups = ceil_div(row_tiles, 2);
     p.tiles_per_wave = kWideTiles;
     p.n_groups = ceil_div(w.n_tiles, kWideWaves * kWideTiles);
     const int smax = (epi == EPI_F32) ? (max_splits < 4 ? max_splits : 4) : 1;
-    WideParts plain{};
-    plain.count[0] = groups / 4;
-    if (groups % 4) plain.count[4 - groups % 4] = 1;
-    plain.by_size = 1;
-    double best = 1e30;
-    p.ksplit = 1;
-    p.parts = cut ? *cut : plain;
-    for (int ks = 1; ks <= smax && !(cut && force_ksplit > 0); ks *= 2) {
-        if (force_ksplit > 0 && ks != (force_ksplit < smax ? force_ksplit : smax)) continue;
-        if (force_ksplit <= 0 && ks > 1 && w.k_tiles / ks < 16) break;
-        const int gk8 = ceil_div(p.n_groups * ks, 8), kt = round_up(ceil_div(w.k_tiles, ks), kWideDepth);
-        WideParts parts = cut ? *cut : plain;
-        double cost = wide_cost(parts, gk8, kt);
-        double bar = 0.95 * cost;
-        for (int a = groups <= kWideSearchGroups && !cut ? groups / 4 : -1; a >= 0; --a)
-            for (int b = (groups - 4 * a) / 3; b >= 0; --b) {
-                const int rest = groups - 4 * a - 3 * b;
-                for (int order = 0; order < 2; ++order) {
-                    const WideParts c{{a, b, rest / 2, rest % 2}, order};
-                    const double t = wide_cost(c, gk8, kt);
-                    if (t < bar) { bar = cost = t; parts = c; }
-                }
-            }
-        cost += (ks - 1) * (double)m * w.n * 4.0 / 4.5e6;
-        if (cost < best) {
-            best = cost;
-            p.ksplit = ks;
-            p.parts = parts;
-        }
-    }
-    if (force_ksplit > 0 && epi == EPI_F32) p.ksplit = force_ksplit < smax ? force_ksplit : smax;
-    p.kt_per_split = round_up(ceil_div(w.k_tiles, p.ksplit), kWideDepth);
+    const WideCut c = plan_wide_cut(p.n_groups, w.n, w.k_tiles, m, smax, epi == EPI_F32 ? force_ksplit : 0, cut);
+    p.parts = c.parts;
+    p.kt_per_split = round_up(ceil_div(w.k_tiles, c.ksplit), kWideDepth);
     p.ksplit = ceil_div(w.k_tiles, p.kt_per_split);  // no empty split
     return p;
 }

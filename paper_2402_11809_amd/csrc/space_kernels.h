@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "space_wide_plan.h"
+
 namespace space {
 
 constexpr int kTileN = 16;        // weight rows per MFMA tile
@@ -11,9 +13,6 @@ constexpr int kTileBytes = 1024;  // one packed 16x32 bf16 tile
 constexpr int kMaxRowTiles = 6;   // 96 rows per projection pass; also the longest block the verification handles
 constexpr int kMaxBlockRows = 1024;  // longest block of one sequence (prompt chunks; no verification beyond 96 rows)
 constexpr int kAttnKeys = 32;     // keys per attention chunk; V is stored transposed in runs of 32
-
-inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
-inline int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
 enum GemmEpilogue { EPI_F32 = 0, EPI_SWIGLU = 1, EPI_ARGMAX = 2 };
 
@@ -114,12 +113,6 @@ int gemm_groups(const PackedW& w, int tiles_per_wave);  // workgroups along the 
 // EPI_F32, a split of the contraction into ksplit partial sums out[s] (at most max_splits; the caller
 // adds them up as it does the skinny kernel's).
 constexpr int kWideRowTiles = 8;  // at most 128 rows per workgroup
-// How the rows of every weight group are cut: count[c] pieces of 4 - c groups of two row tiles (8, 6, 4,
-// 2 row tiles), laid end to end in this order; the groups add up to ceil(ceil(m / 16) / 2).
-struct WideParts {
-    int count[4];
-    int by_size;  // launch order: 0 = weight group by weight group, 1 = all pieces of a size before any smaller one
-};
 struct WidePlan {
     WideParts parts;
     int tiles_per_wave;  // 2

@@ -87,12 +87,19 @@ struct WideCut {
     int ksplit;  // partial sums over the contraction
 };
 
+// By how much another cut has to be ahead of pieces of 128 rows and one for the rest, in percent of their cost.
+// Measured at 7B, 13B and 70B width (97 .. 1024 rows, all projections): 115 picks more than 9 % ahead are 10 %
+// faster on average and at most 1.3 % slower; 19 picks 5 .. 9 % ahead where the matrix has up to 512 MB are 1.7 %
+// faster on average (7B LM head at 648 rows 273 -> 258 us) and at most 5 % slower; 6 of them at 940 MB (70B gate /
+// up) are 2.4 % slower on average (480 rows 1381 -> 1538 us, whole 70B layers 3.5 .. 5.8 % slower): every size in a
+// launch streams the matrix again, there from memory and not from a cache, which the model knows nothing of.
+inline int wide_cut_bar(int n, int k_tiles) { return (int64_t)n * k_tiles * 64 > ((int64_t)512 << 20) ? 91 : 95; }
+
 // Cut of the rows and number of partial sums with the lowest cost, a partial sum beyond the first charged
 // with the time to read it.  Pieces of 128 rows and one for the rest, large ones first, unless another cut is
-// ahead by more than 5 % (the model's picks are 2 % above the best cut measured, on average).  Why it matters:
-// gate / up at 333 rows and 7B width makes 258 workgroups of 128 and 96 rows, i.e. two CUs with two of them,
-// 140 us; the cut picked here 120.  O and down at 224 rows 28 -> 21 and 63 -> 45 us.  Beyond 1024 rows there are many
-// rounds and the cut matters little.
+// ahead (wide_cut_bar).  Why it matters: gate / up at 333 rows and 7B width makes 258 workgroups of 128 and 96 rows,
+// i.e. two CUs with two of them, 140 us; the cut picked here 120.  O and down at 224 rows 28 -> 21 and 63 -> 45 us.
+// Beyond 1024 rows there are many rounds and the cut matters little.
 //   n_groups, n, k_tiles  the matrix: weight groups (workgroups along its rows), rows, contraction tiles
 //   m                     rows of the launch
 //   smax                  most partial sums (1 .. 4); force_ksplit > 0: that many; cut: that cut
@@ -110,7 +117,7 @@ inline WideCut plan_wide_cut(int n_groups, int n, int k_tiles, int m, int smax, 
         const int gk8 = ceil_div(n_groups * ks, 8), kt = round_up(ceil_div(k_tiles, ks), kWideDepth);
         WideParts parts = cut ? *cut : plain;
         int64_t cost = wide_cost(parts, gk8, kt);
-        int64_t bar = cost * 95 / 100;
+        int64_t bar = cost * wide_cut_bar(n, k_tiles) / 100;
         for (int a = groups <= kWideSearchGroups && !cut ? groups / 4 : -1; a >= 0; --a)
             for (int b = (groups - 4 * a) / 3; b >= 0; --b) {
                 const int rest = groups - 4 * a - 3 * b;

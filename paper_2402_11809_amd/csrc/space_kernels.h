@@ -122,7 +122,7 @@ struct WidePlan {
 };
 // force_ksplit > 0: that many partial sums over the contraction instead of the cost model's choice
 // (plain-sum epilogue only; rounded down to what leaves every split at least one pipeline round); cut: this
-// cut of the rows instead of the model's
+// cut of the rows instead of the model's, with the partial sums that the model's has
 WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit = 0,
                         const WideParts* cut = nullptr);
 // g.passes and g.tiles_per_wave are ignored (the plan's pieces are used); g.row_tile0 must be 0.

@@ -102,23 +102,25 @@ inline int wide_cut_bar(int n, int k_tiles) { return (int64_t)n * k_tiles * 64 >
 // Beyond 1024 rows there are many rounds and the cut matters little.
 //   n_groups, n, k_tiles  the matrix: weight groups (workgroups along its rows), rows, contraction tiles
 //   m                     rows of the launch
-//   smax                  most partial sums (1 .. 4); force_ksplit > 0: that many; cut: that cut
+//   smax                  most partial sums (1 .. 4); force_ksplit > 0: that many
+//   cut                   that cut; the partial sums are still those of the plan without it, so that a cut
+//                         alone changes no sum's order
 inline WideCut plan_wide_cut(int n_groups, int n, int k_tiles, int m, int smax, int force_ksplit, const WideParts* cut) {
     const int groups = ceil_div(ceil_div(m, 16), 2);
     WideParts plain{};
     plain.count[0] = groups / 4;
     if (groups % 4) plain.count[4 - groups % 4] = 1;
     plain.by_size = 1;
-    WideCut p{cut ? *cut : plain, 1};
+    WideCut p{plain, 1};
     int64_t best = INT64_MAX;
     for (int ks = 1; ks <= smax && !(cut && force_ksplit > 0); ks *= 2) {
         if (force_ksplit > 0 && ks != (force_ksplit < smax ? force_ksplit : smax)) continue;
         if (force_ksplit <= 0 && ks > 1 && k_tiles / ks < 16) break;
         const int gk8 = ceil_div(n_groups * ks, 8), kt = round_up(ceil_div(k_tiles, ks), kWideDepth);
-        WideParts parts = cut ? *cut : plain;
+        WideParts parts = plain;
         int64_t cost = wide_cost(parts, gk8, kt);
         int64_t bar = cost * wide_cut_bar(n, k_tiles) / 100;
-        for (int a = groups <= kWideSearchGroups && !cut ? groups / 4 : -1; a >= 0; --a)
+        for (int a = groups <= kWideSearchGroups ? groups / 4 : -1; a >= 0; --a)
             for (int b = (groups - 4 * a) / 3; b >= 0; --b) {
                 const int rest = groups - 4 * a - 3 * b;
                 for (int order = 0; order < 2; ++order) {
@@ -137,6 +139,7 @@ inline WideCut plan_wide_cut(int n_groups, int n, int k_tiles, int m, int smax, 
         }
     }
     if (force_ksplit > 0) p.ksplit = force_ksplit < smax ? force_ksplit : smax;
+    if (cut) p.parts = *cut;
     return p;
 }
 

@@ -775,3 +775,30 @@ def test_query_tiles_per_workgroup_of_long_blocks(torch_mod, shape_name, B, k, c
     if ctxs == "ragged":
         ctxs = [(37 * (b + 1)) % 220 for b in range(B)]
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=6), B, k, None, gc.LOGIT_TIGHT, ctxs=ctxs, capacity=736)
+
+
+@pytest.mark.parametrize("cut", ["2:0:0:1:0", "0:3:0:0:1", "0:0:4:1:0", "0:0:0:9:1", "1:1:1:0:0"])
+def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
+    """As the test with contractions that are never split, at 1024 wide (32 and 43 contraction tiles): 288 rows,
+    where the planner takes two partial sums for QKV, O and down.  A forced cut keeps the partial sums of the default
+    one, so logits, indices and accepted counts are equal bit for bit."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES["gqa128"]
+    w = all_weights(shape, seed=6)
+    B, k = 8, 5
+    spec = lo.paper_layout(k)
+    L = spec.n_rows
+    toks = np.random.default_rng(14).integers(0, shape.vocab, size=(B, L)).astype(np.int32)
+    om = gc.oracle_model(shape, w)
+    okvs = [gc.synthetic_oracle_kv(om, seed=80 + b, ctx=9 * b + 4, std=0.5) for b in range(B)]
+    got = []
+    for tune in (None, "widecut=" + cut):
+        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune=tune)
+        cache = gm.kv_cache(B, 160)
+        for b in range(B):
+            gc.upload_oracle_kv(torch, cache, b, okvs[b])
+        out = _run_step(torch, gm, cache, spec, toks, batch=B)
+        got.append((out.logits.cpu().numpy().copy(), out.argmax.cpu().numpy().copy(), out.accepted_len.cpu().numpy().copy()))
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)

@@ -2528,13 +2528,21 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_verify_kernel(Sample
         for (int i = 1 + threadIdx.x; i < G; i += blockDim.x)
             v.ratios[(size_t)b * (G - 1) + (i - 1)] = (!rejected || i <= rejected) ? s_ratio[i] : -1.f;
     const int last = __builtin_amdgcn_readfirstlane(s_real[acc]), nm = __builtin_amdgcn_readfirstlane(s_nmask[acc]);
-    SampleList l = {-1, 0.f, 0};  // wave 0: the list of the extra token
-    if (wave == 0) l = list_of(last);
-    if (v.residual && rejected && v.draft_ids && v.draft_probs) {
-        if (wave == 0) {
+    // new_ids / new_probs may lie on draft_ids / draft_probs: what is needed of these is read before the other waves write
+    const bool use_residual = v.residual && rejected && v.draft_ids && v.draft_probs;
+    int did = -1;
+    float dp = 0.f;
+    if (use_residual) {
+        if (wave == 0 && lane < K) {
             const size_t d0 = ((size_t)b * v.max_cands + (rejected - 1)) * K;
-            const int did = lane < K ? v.draft_ids[d0 + lane] : -1;
-            const float dp = lane < K ? v.draft_probs[d0 + lane] : 0.f;
+            did = v.draft_ids[d0 + lane];
+            dp = v.draft_probs[d0 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {  // the extra token
+        SampleList l = list_of(last);
+        if (use_residual) {
             const uint64_t end = __builtin_amdgcn_ballot_w64(did < 0 || lane >= K);
             const int dn = end ? __builtin_ctzll(end) : 64;
             float d = 0.f;
@@ -2551,9 +2559,6 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_verify_kernel(Sample
             for (int j = 0; j < l.n; ++j) sum += lane_value(res, j);
             if (sum > 0.f) l.p = res / sum;
         }
-        __syncthreads();  // new_ids / new_probs may lie on draft_ids / draft_probs: read before the other waves write
-    }
-    if (wave == 0) {  // the extra token
         float p_extra;
         const int extra = sample_draw(l, s_u[G - 1], &p_extra);
         if (lane == 0) {
@@ -2577,15 +2582,15 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_verify_kernel(Sample
         for (int j = wave - 1; j < v.max_cands; j += kSampleWaves - 1) {
             int t = -1;
             float pt = 0.f;
-            SampleList c = {-1, 0.f, 0};
+            SampleList l = {-1, 0.f, 0};
             if (j < nm) {
-                c = list_of(last + 1 + j);
-                t = sample_draw(c, s_u[G + j], &pt);
+                l = list_of(last + 1 + j);
+                t = sample_draw(l, s_u[G + j], &pt);
             }
             const size_t o = ((size_t)b * v.max_cands + j) * K;
             if (lane < K) {
-                if (v.new_ids) v.new_ids[o + lane] = c.id;
-                if (v.new_probs) v.new_probs[o + lane] = c.p;
+                if (v.new_ids) v.new_ids[o + lane] = l.id;
+                if (v.new_probs) v.new_probs[o + lane] = l.p;
             }
             if (lane == 0) {
                 v.new_cands[(size_t)b * v.max_cands + j] = t;

@@ -2255,15 +2255,13 @@ hipError_t launch_verify(const VerifyLaunch& v, hipStream_t s) {
 // four threads) bounds the top_k-th largest element from below, so the elements at or above it -- about
 // top_k and a few more -- are all that has to be ordered: they go to LDS and each finds its place by
 // counting.  What that costs does not grow with top_k, unlike a round with two barriers per kept token.
-// Rows where more than 256 elements reach the bound (many equal logits: masked vocabularies) and rows with
-// NaN have paths of their own.  648 rows of 32000, 50 kept: 38 us (284 with a round per kept token); 36
-// rows, 10 kept: 10.8 (26.8).  Sums run sequentially in descending order: the result does not depend on the
-// launch shape.
+// Rows where more than 256 elements lie above the bound (large ones in the columns of few groups) or are equal to
+// it (masked vocabularies) take a path that is not inlined: 648 rows with large values in 50 groups, 64 kept, 150 us
+// against 53 for usual ones (1430 with a pass over the row per kept token); all but 7 elements masked, 10 kept, 48.
+// 648 rows of 32000, 50 kept: 38 us (284 with a round per kept token); 36 rows, 10 kept: 10.8 (26.8).  Sums run
+// sequentially in descending order: the result does not depend on the launch shape.
 constexpr int kTopGroups = 256, kTopCand = 256;
 
-__device__ __forceinline__ bool sample_after(float v, int i, float pv, int pi) {  // (v, i) comes after (pv, pi)
-    return v < pv || (v == pv && i > pi);
-}
 __device__ __forceinline__ bool sample_before(float v, int i, float bv, int bi) {
     return v > bv || (v == bv && i < bi);
 }
@@ -2280,96 +2278,171 @@ __device__ __forceinline__ float lane_value(float v, int lane) {  // lane: the s
 
 constexpr int kTopHeld = 32;  // elements of a row held per thread
 
+struct TopLds {
+    int count;
+    uint32_t bound;
+    __attribute__((aligned(16))) int word[16];
+    __attribute__((aligned(16))) float group[kTopGroups];
+    float c_v[kTopCand];  // the list
+    int c_i[kTopCand];
+    float top_v[kMaxTopK];  // the kept ones
+    int top_i[kMaxTopK];
+};
+__device__ __forceinline__ TopLds& top_lds() {  // also for functions that are not inlined: LDS addresses stay known
+    __shared__ __attribute__((aligned(16))) TopLds s;
+    return s;
+}
+
 // Every element of the list finds its place in the order; the first K are kept.
-__device__ __forceinline__ void topk_place(const float* c_v, const int* c_i, int n, int K, float* top_v, int* top_i) {
+__device__ __forceinline__ void topk_place(int n, int K) {
+    TopLds& s = top_lds();
     if ((int)threadIdx.x < n) {
-        const float v = c_v[threadIdx.x];
-        const int i = c_i[threadIdx.x];
+        const float v = s.c_v[threadIdx.x];
+        const int i = s.c_i[threadIdx.x];
         int place = 0;
-        for (int j = 0; j < n; ++j) place += sample_before(c_v[j], c_i[j], v, i);
-        if (place < K) { top_v[place] = v; top_i[place] = i; }
+        for (int j = 0; j < n; ++j) place += sample_before(s.c_v[j], s.c_i[j], v, i);
+        if (place < K) { s.top_v[place] = v; s.top_i[place] = i; }
     }
     __syncthreads();
 }
 
-// More elements reach the bound than the list holds: the ones above it are ordered as usual, the places
-// behind them go to elements equal to it by lowest id, found 1024 at a time from the front of the row.
-// false: also too many above it (left to the rounds).
-__device__ __noinline__ bool topk_many_equal(const float* __restrict__ x, int V, int K, float bound, float* c_v, int* c_i,
-                                             int* s_count, int* s_i, float* top_v, int* top_i) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    __syncthreads();
-    if (tid == 0) *s_count = 0;
-    __syncthreads();
-    for (int i = tid; i < V; i += 1024) {
-        const float v = x[i];
-        if (v > bound) {
-            const int at = atomicAdd(s_count, 1);
-            if (at < kTopCand) { c_v[at] = v; c_i[at] = i; }
-        }
+// A thread's elements of a row, eight requested at a time.
+template <class F>
+__device__ __forceinline__ void row_elements(const float* __restrict__ x, int V, F use) {
+    constexpr int kAtOnce = 8;
+    for (int i0 = threadIdx.x; i0 < V; i0 += kAtOnce * 1024) {
+        float v[kAtOnce];
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) v[e] = x[min(i0 + e * 1024, V - 1)];
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e)
+            if (i0 + e * 1024 < V) use(v[e], i0 + e * 1024);
     }
+}
+
+// The list of the elements above the bound, among those of the threads that may hold any (elsewhere the row is not
+// read again).  Returns how many there are; the first kTopCand are listed.
+__device__ __forceinline__ int topk_above(const float* __restrict__ x, int V, float bound, bool holds) {
+    TopLds& s = top_lds();
     __syncthreads();
-    const int n = *s_count;
-    if (n > kTopCand) return false;
-    topk_place(c_v, c_i, n, K, top_v, top_i);
-    int got = n;
-    for (int base = 0; base < V && got < K; base += 1024) {
-        const int i = base + tid;
-        const bool hit = i < V && x[i] == bound;
-        const uint64_t hits = __builtin_amdgcn_ballot_w64(hit);
-        if (lane == 0) s_i[wave] = __popcll(hits);
-        __syncthreads();
-        int at = got + __popcll(hits & ((1ull << lane) - 1)), all = 0;
-        for (int w = 0; w < 16; ++w) {
-            at += w < wave ? s_i[w] : 0;
-            all += s_i[w];
+    if (threadIdx.x == 0) s.count = 0;
+    __syncthreads();
+    if (holds)
+        row_elements(x, V, [&](float v, int i) {
+            if (v > bound) {
+                const int at = atomicAdd(&s.count, 1);
+                if (at < kTopCand) { s.c_v[at] = v; s.c_i[at] = i; }
+            }
+        });
+    __syncthreads();
+    return s.count;
+}
+
+// The places from `got` on go to elements equal to the bound by lowest id, found 8192 elements at a time from the
+// front of the row.
+__device__ __forceinline__ void topk_many_equal(const float* __restrict__ x, int V, int K, float bound, int got) {
+    TopLds& s = top_lds();
+    constexpr int kAtOnce = 8;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int base = 0; base < V && got < K; base += kAtOnce * 1024) {
+        const int i0 = base + wave * kAtOnce * 64 + lane;  // a wave's elements lie together
+        uint64_t hits[kAtOnce];
+        float v[kAtOnce];
+        int in_wave = 0;
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) v[e] = x[min(i0 + e * 64, V - 1)];
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) {
+            hits[e] = __builtin_amdgcn_ballot_w64(i0 + e * 64 < V && v[e] == bound);
+            in_wave += __popcll(hits[e]);
         }
-        if (hit && at < K) { top_v[at] = bound; top_i[at] = i; }
+        if (lane == 0) s.word[wave] = in_wave;
+        __syncthreads();
+        int at = got, all = 0;
+#pragma unroll 2
+        for (int w = 0; w < 16; ++w) {
+            at += w < wave ? s.word[w] : 0;
+            all += s.word[w];
+        }
+        if (in_wave) {
+#pragma unroll
+            for (int e = 0; e < kAtOnce; ++e) {
+                const int mine = at + __popcll(hits[e] & ((1ull << lane) - 1));
+                if ((hits[e] >> lane & 1) && mine < K) { s.top_v[mine] = bound; s.top_i[mine] = i0 + e * 64; }
+                at += __popcll(hits[e]);
+            }
+        }
         got += all;
         __syncthreads();
     }
-    return true;
 }
 
-// The rounds: the j-th largest is the maximum of the elements that come after the (j-1)-th in the order.
-__device__ __noinline__ void topk_rounds(const float* __restrict__ x, int V, int K, float* s_v, int* s_i, float* top_v, int* top_i) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float pv = INFINITY;
-    int pi = -1;
-    for (int k = 0; k < K; ++k) {
-        float bv = -INFINITY;
-        int bi = INT_MAX;
-        for (int i = tid; i < V; i += 1024) {
-            const float v = x[i];
-            if (sample_after(v, i, pv, pi) && sample_before(v, i, bv, bi)) { bv = v; bi = i; }
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float ov = __shfl_xor(bv, o, 64);
-            const int oi = __shfl_xor(bi, o, 64);
-            if (sample_before(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-        }
-        if (lane == 0) { s_v[wave] = bv; s_i[wave] = bi; }
+// More than the list holds lie above the bound (large values in columns of few groups): a higher bound from
+// counts of the elements above it in 256 equal ranges of their order, then of the range that holds the K-th
+// largest, at most four times (32 bits).  Returns the highest lower end of a range with K elements at or above it:
+// at most kTopCand of them, or all but fewer than K are equal to it.
+__device__ __forceinline__ float topk_narrow(const float* __restrict__ x, int V, int K, float bound, float largest) {
+    TopLds& s = top_lds();
+    int* hist = s.c_i;
+    const int tid = threadIdx.x;
+    uint32_t first = float_order(bound) + 1, last = float_order(largest);
+    int above = 0;  // elements behind last
+    for (;;) {
+        const uint32_t span = last - first;
+        const int shift = span < 256 ? 0 : 24 - __clz(span);
         __syncthreads();
-        bv = s_v[0]; bi = s_i[0];
-        for (int w = 1; w < 16; ++w)
-            if (sample_before(s_v[w], s_i[w], bv, bi)) { bv = s_v[w]; bi = s_i[w]; }
-        if (tid == 0) { top_v[k] = bv; top_i[k] = bi; }
-        pv = bv; pi = bi;
+        if (tid < 256) hist[tid] = 0;
         __syncthreads();
+        row_elements(x, V, [&](float v, int) {
+            const uint32_t o = float_order(v);
+            if (v == v && o >= first && o <= last) atomicAdd(hist + ((o - first) >> shift), 1);
+        });
+        __syncthreads();
+        if (tid < 256) {
+            int from = above;
+#pragma unroll 4
+            for (int j = 0; j < 256; ++j) from += j >= tid ? hist[j] : 0;
+            if (from >= K && from - hist[tid] < K) {  // one thread
+                s.word[0] = tid;
+                s.word[1] = from;
+                s.word[2] = from - hist[tid];
+            }
+        }
+        __syncthreads();
+        first += (uint32_t)s.word[0] << shift;
+        above = s.word[2];
+        if (s.word[1] <= kTopCand || shift == 0) return float_from_order(first);
+        last = first + min(last - first, (1u << shift) - 1);
     }
 }
 
+// Fewer than K or more than kTopCand elements at or above the bound.
+__device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K, float bound, bool holds) {
+    TopLds& s = top_lds();
+    const int tid = threadIdx.x;
+    int n = s.count;
+    if (n < K) {  // fewer numbers than places, the rest of the row is NaN
+        if (tid >= n && tid < K) {
+            s.top_v[tid] = -INFINITY;
+            s.top_i[tid] = INT_MAX;
+        }
+        topk_place(n, K);
+        return;
+    }
+    n = topk_above(x, V, bound, holds);
+    if (n > kTopCand) {
+        float largest = s.group[0];
+#pragma unroll 4
+        for (int j = 1; j < kTopGroups; ++j) largest = fmaxf(largest, s.group[j]);
+        bound = topk_narrow(x, V, K, bound, largest);
+        n = topk_above(x, V, bound, true);  // at most kTopCand now
+    }
+    topk_place(n, K);
+    topk_many_equal(x, V, K, bound, n);
+}
+
 __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
-    __shared__ float s_v[16];
-    __shared__ int s_i[16];
-    __shared__ float top_v[kMaxTopK];
-    __shared__ int top_i[kMaxTopK];
-    __shared__ __attribute__((aligned(16))) float s_group[kTopGroups];
-    __shared__ float c_v[kTopCand];
-    __shared__ int c_i[kTopCand];
-    __shared__ uint32_t s_bound;
-    __shared__ int s_count;
+    TopLds& s = top_lds();
     const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const size_t row = (size_t)b * a.lay.L + r;
     const float* __restrict__ x = a.logits + row * a.vocab;
@@ -2382,8 +2455,8 @@ __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
         cache[j] = i < V ? x[i] : -INFINITY;
     }
     if (tid == 0) {
-        s_bound = 0xffffffffu;
-        s_count = 0;
+        s.bound = 0xffffffffu;
+        s.count = 0;
     }
     const int K = min(a.top_k, V);
     float mine = -INFINITY;
@@ -2393,26 +2466,26 @@ __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
     {
         float g = fmaxf(mine, __shfl_xor(mine, 1, 64));
         g = fmaxf(g, __shfl_xor(g, 2, 64));
-        if ((tid & 3) == 0) s_group[tid >> 2] = g;
+        if ((tid & 3) == 0) s.group[tid >> 2] = g;
     }
     __syncthreads();
     if (tid < kTopGroups) {  // the smallest group maximum with fewer than K larger ones
-        const float g = s_group[tid];
+        const float g = s.group[tid];
         int larger = 0;
 #pragma unroll 8
         for (int j = 0; j < kTopGroups / 4; ++j) {
-            const f32x4 q = *(const f32x4*)(s_group + 4 * j);
+            const f32x4 q = *(const f32x4*)(s.group + 4 * j);
             larger += (q[0] > g) + (q[1] > g) + (q[2] > g) + (q[3] > g);
         }
-        if (larger < K) atomicMin(&s_bound, float_order(g));
+        if (larger < K) atomicMin(&s.bound, float_order(g));
     }
     __syncthreads();
-    const float bound = float_from_order(s_bound);
+    const float bound = float_from_order(s.bound);
     if (mine >= bound) {
         auto take = [&](float v, int i) {
             if (v >= bound) {
-                const int at = atomicAdd(&s_count, 1);
-                if (at < kTopCand) { c_v[at] = v; c_i[at] = i; }
+                const int at = atomicAdd(&s.count, 1);
+                if (at < kTopCand) { s.c_v[at] = v; s.c_i[at] = i; }
             }
         };
 #pragma unroll
@@ -2421,14 +2494,14 @@ __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
         for (int i = tid + held; i < V; i += 1024) take(x[i], i);
     }
     __syncthreads();
-    const int n = s_count;
+    const int n = s.count;
     if (n >= K && n <= kTopCand)  // (the branches are taken by whole workgroups)
-        topk_place(c_v, c_i, n, K, top_v, top_i);
-    else if (n < K || !topk_many_equal(x, V, K, bound, c_v, c_i, &s_count, s_i, top_v, top_i))
-        topk_rounds(x, V, K, s_v, s_i, top_v, top_i);
+        topk_place(n, K);
+    else
+        topk_rare(x, V, K, bound, mine > bound);
     if (tid < 64) {  // lane j: the j-th kept token
         const int j = min(lane, K - 1);
-        const float e = expf(top_v[j] - top_v[0]);
+        const float e = expf(s.top_v[j] - s.top_v[0]);
         float total = 0.f;
         for (int q = 0; q < K; ++q) total += lane_value(e, q);
         const float p = e / total;
@@ -2440,7 +2513,7 @@ __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
         }
         for (int q = 0; q < keep; ++q) mass += lane_value(p, q);
         if (lane < keep) {
-            a.row_ids[row * kMaxTopK + lane] = top_i[lane];
+            a.row_ids[row * kMaxTopK + lane] = s.top_i[lane];
             a.row_probs[row * kMaxTopK + lane] = p / mass;
         }
         if (lane == 0) a.row_n[row] = keep;

@@ -491,3 +491,54 @@ def test_residual_rule_with_the_draft_lists_updated_in_place(torch_mod, k, top_k
     assert (want[0] < k).any()
     for x, y in zip(want, call(True)):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("V,top_k", [(1500, 64), (32000, 33), (32000, 64), (40000, 64)])
+def test_kept_lists_with_large_logits_in_few_column_groups(torch_mod, V, top_k):
+    """Rows where hundreds of elements lie strictly above what the group maxima promise: large values only in the
+    columns of fewer groups (four columns of 1024) than tokens are kept.  All distinct, beside one outlier or
+    +inf (a first range that holds everything else), spread over thirty orders of magnitude, with hundreds equal to the
+    last kept value, negative throughout; and rows with fewer numbers than places.  Ids against a sort in
+    full, probabilities against float64 softmax (rel 1e-5: at most 64 float32 terms)."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    k = 8
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=1, max_rows=k + 1, max_ctx=64)
+    spec = lo.first_step_layout(k)
+    lay = gm.layout(spec)
+    rng = np.random.default_rng(V + top_k)
+    few = np.flatnonzero(np.arange(V) % 1024 < 4 * (top_k // 2 - 1))  # the columns of too few groups
+    assert len(few) < 256 or V > 1500
+    P = rng.standard_normal((k + 1, V)).astype(np.float32)
+    P[1, few] = 5.0 + rng.permutation(len(few)).astype(np.float32) / len(few)
+    P[2] = P[1]
+    P[2, few[len(few) // 2]] = 3e38
+    P[3] = P[1]
+    P[3, few[::97]] += 40.0
+    P[4, few] = np.exp(rng.uniform(2.0, 60.0, size=len(few))).astype(np.float32)
+    P[5, few] = 7.0
+    P[5, few[rng.permutation(len(few))[: top_k - 5]]] = 8.0
+    P[6] = P[1] - 200.0
+    P[7, rng.permutation(V)[top_k - 3:]] = np.nan
+    P[8] = np.nan
+    P[8, V - 1] = -3.0
+    u = rng.uniform(0.0, 1.0, size=(1, 1 + k)).astype(np.float32)
+    toks = np.full((1, k + 1), shape.mask_id, dtype=np.int32)
+    toks[0, 0] = 1
+    out = binding.SampleOut(gm, 1, 1, k, top_k)
+    gm.sample_verify(torch.from_numpy(P[None]).cuda(), torch.from_numpy(toks).cuda(), lay,
+                     torch.ones(1, k, device="cuda"), torch.from_numpy(u).cuda(), out, top_k=top_k, top_p=1.0)
+    torch.cuda.synchronize()
+    for j in range(k):
+        x = P[1 + j].astype(np.float64)
+        real = np.flatnonzero(~np.isnan(x))
+        order = real[np.lexsort((real, -x[real]))][:top_k]
+        ids, probs = out.new_ids.cpu().numpy()[0, j], out.new_probs.cpu().numpy()[0, j]
+        n = min(int((ids >= 0).sum()), len(order))
+        want = np.exp(x[order] - x[order[0]])
+        want /= want.sum()
+        assert n >= 1 and ids[:n].tolist() == order[:n].tolist(), j
+        assert want[n:].sum() < 64 * 1.2e-7  # what is not kept has no mass left in float32
+        np.testing.assert_allclose(probs[:n], want[:n], rtol=1e-5, atol=1e-30)

@@ -2142,12 +2142,13 @@ __global__ __launch_bounds__(1024) void verify_kernel(VerifyLaunch v) {
     }
     if (v.next_tokens)
         for (int i = threadIdx.x; i < v.next.L; i += blockDim.x) s_next[i] = v.next.info[i];
-    // Three rows per wave at a time, up to 256 partials of each, everything requested before anything is
+    // Up to three rows per wave at a time, up to 256 partials of each, everything requested before anything is
     // compared: the partials were written on all XCDs, so every dependent trip here goes out to memory.  One
-    // 36-row block with 250 partials per row: 9.1 -> 6.0 us (row after row, one partial per lane at a time).
-    constexpr int kRowsAtOnce = 3;
-    auto argmax_rows = [&](auto parts_tag, int r0) {
-        constexpr int kPartsAtOnce = decltype(parts_tag)::value;
+    // 36-row block with 250 partials per row: 9.1 -> 6.0 us (row after row, one partial per lane at a time).  No
+    // more rows than the waves have, or the merges of missing ones are waited for: 16 rows of 4 sequences 5.7 us row
+    // after row, 6.3 with three at once, 5.0 with one (16 partials per row: 3.3, 4.5, 3.4).
+    auto argmax_rows = [&](auto rows_tag, auto parts_tag, int r0) {
+        constexpr int kRowsAtOnce = decltype(rows_tag)::value, kPartsAtOnce = decltype(parts_tag)::value;
         float best[kRowsAtOnce];
         int bi[kRowsAtOnce];
 #pragma unroll
@@ -2192,10 +2193,15 @@ __global__ __launch_bounds__(1024) void verify_kernel(VerifyLaunch v) {
             }
         }
     };
-    for (int r0 = wave; r0 < L; r0 += nwaves * kRowsAtOnce) {
-        if (v.n_groups_used <= 64) argmax_rows(std::integral_constant<int, 1>{}, r0);
-        else argmax_rows(std::integral_constant<int, 4>{}, r0);
-    }
+    auto all_rows = [&](auto rows_tag) {
+        for (int r0 = wave; r0 < L; r0 += nwaves * decltype(rows_tag)::value) {
+            if (v.n_groups_used <= 64) argmax_rows(rows_tag, std::integral_constant<int, 1>{}, r0);
+            else argmax_rows(rows_tag, std::integral_constant<int, 4>{}, r0);
+        }
+    };
+    if (L <= nwaves) all_rows(std::integral_constant<int, 1>{});
+    else if (L <= 2 * nwaves) all_rows(std::integral_constant<int, 2>{});
+    else all_rows(std::integral_constant<int, 3>{});
     __syncthreads();
     if (threadIdx.x == 0) {
         int acc = 0;

@@ -802,3 +802,27 @@ def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
         got.append((out.logits.cpu().numpy().copy(), out.argmax.cpu().numpy().copy(), out.accepted_len.cpu().numpy().copy()))
     for x, y in zip(*got):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane
+@pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 96])
+def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, vocab):
+    """The verification merges one, two or three rows per wave and trip (16 waves): the argmax of every row of
+    two sequences is that of its own logits (lowest id of equal ones), the extra token that of the first row."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=vocab, n_layers=1)
+    B = 2
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=3), max_batch=B, max_rows=rows, max_ctx=128)
+    spec = lo.first_step_layout(rows - 1)
+    assert spec.n_rows == rows
+    cache = gm.kv_cache(B, 128)
+    toks = np.random.default_rng(rows).integers(0, vocab, size=(B, rows)).astype(np.int32)
+    out = binding.StepOut(gm, B, rows, max(rows - 1, 1))
+    gm.step(torch.from_numpy(toks).cuda(), gm.layout(spec), cache, out)
+    torch.cuda.synchronize()
+    want = out.logits.cpu().numpy().reshape(B, rows, vocab).argmax(2)
+    assert np.array_equal(out.argmax.cpu().numpy().reshape(B, rows), want)
+    assert out.bonus.cpu().numpy().tolist() == want[:, 0].tolist()
+    assert out.accepted_len.cpu().numpy().tolist() == [0, 0]

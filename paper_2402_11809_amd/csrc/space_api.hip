@@ -716,6 +716,9 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     //     19.2 / 20.8, 27.6 / 27.3;
     //   three tiles (36 rows), 768 / 900 / 1023: 16.1 / 16.9, 18.7 / 18.0, 20.2 / 19.5 (70B: 21.8 / 19.9); 2
     //     sequences at 512 and 1024: 15.3 / 20.9, 22.6 / 23.1.
+    // Heads of 64 elements have half the bytes to pull and the same merge: level at 768 positions for one and two
+    // tiles (step of a 256-wide model of 2 layers, 4 rows, 384 / 518 / 768 / 1023 positions: 54.8 / 57.1, 56.4 / 58.6,
+    // 58.7 / 58.8, 64.3 / 57.0; 25 rows at 518 and 768: 64.1 / 69.0, 66.3 / 67.9).
     // Beyond 256 workgroups the one-launch form puts several on a CU, each of which stages and reads the head's
     // keys again: only up to 12 chunks (the block's own two and about 320 positions; 4 sequences of three tiles at
     // 256 / 512: 18.3 / 22.4, 27.7 / 24.9), beyond 384 never (8 sequences of two tiles, 512 workgroups, at 256:
@@ -724,6 +727,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const long long head_wgs = (long long)B * c.n_heads * q_tiles;
     long long head_chunks = ctx->head_attn_max_chunks;
     if (head_chunks < 0) head_chunks = q_tiles == 1 ? std::min(10 + 2 * B, 18) : q_tiles == 2 ? (B == 1 ? 20 : 30) : (B == 1 ? 29 : 36);
+    if (ctx->head_attn_max_chunks < 0 && dh <= 64) head_chunks = std::max<long long>(head_chunks, 24);
     if (head_chunks < 1000000) {  // (1000000 and more: the developer knob that forces this kernel)
         if (head_wgs > 384) head_chunks = 0;
         else if (head_wgs > 256) head_chunks = std::min<long long>(head_chunks, 12);

@@ -826,3 +826,11 @@ def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, 
     assert np.array_equal(out.argmax.cpu().numpy().reshape(B, rows), want)
     assert out.bonus.cpu().numpy().tolist() == want[:, 0].tolist()
     assert out.accepted_len.cpu().numpy().tolist() == [0, 0]
+
+
+@pytest.mark.parametrize("shape_name,k,ctx", [("tiny", 1, 703), ("tiny", 3, 736), ("tiny", 3, 737), ("gqa-small", 4, 704), ("gqa-small", 4, 705)])
+def test_attention_of_64_element_heads_around_its_line(torch_mod, shape_name, k, ctx):
+    """Heads of 64 elements take the one-launch attention up to 24 chunks of 32 keys (the cached ones and the
+    block's), the cut over the key axis beyond: one and two query tiles on both sides of the line against the oracle."""
+    shape = SHAPES[shape_name]
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=8), 1, k, None, gc.LOGIT_TIGHT, ctxs=[ctx], capacity=768)

@@ -720,16 +720,18 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     // tiles (step of a 256-wide model of 2 layers, 4 rows, 384 / 518 / 768 / 1023 positions: 54.8 / 57.1, 56.4 / 58.6,
     // 58.7 / 58.8, 64.3 / 57.0; 25 rows at 518 and 768: 64.1 / 69.0, 66.3 / 67.9).
     // Beyond 256 workgroups the one-launch form puts several on a CU, each of which stages and reads the head's
-    // keys again: only up to 12 chunks (the block's own two and about 320 positions; 4 sequences of three tiles at
-    // 256 / 512: 18.3 / 22.4, 27.7 / 24.9), beyond 384 never (8 sequences of two tiles, 512 workgroups, at 256:
-    // 22.7 / 16.0).
+    // keys again.  One tile: never (7B, 12 sequences of 4 rows at 40 / 256 / 1024 positions 12.6 / 7.6, 17.3 / 12.6,
+    // 45.9 / 34.7, 16 sequences of 16 rows 16.3 / 12.4, 24.5 / 21.4, 66.4 / 59.3; 70B, 5 of 4 rows 12.9 / 8.0, 16.4 / 12.5, 44.3 /
+    // 34.7; heads of 64 alike).  More tiles: up to 12 chunks (the block's own two and about 320 positions; 4 sequences of
+    // three tiles at 256 / 512: 18.3 / 22.4, 27.7 / 24.9), beyond 384 never (8 sequences of two tiles, 512
+    // workgroups, at 256: 22.7 / 16.0).
     const int q_tiles = ceil_div(L, 16);
     const long long head_wgs = (long long)B * c.n_heads * q_tiles;
     long long head_chunks = ctx->head_attn_max_chunks;
     if (head_chunks < 0) head_chunks = q_tiles == 1 ? std::min(10 + 2 * B, 18) : q_tiles == 2 ? (B == 1 ? 20 : 30) : (B == 1 ? 29 : 36);
     if (ctx->head_attn_max_chunks < 0 && dh <= 64) head_chunks = std::max<long long>(head_chunks, 24);
     if (head_chunks < 1000000) {  // (1000000 and more: the developer knob that forces this kernel)
-        if (head_wgs > 384) head_chunks = 0;
+        if (head_wgs > (q_tiles == 1 ? 256 : 384)) head_chunks = 0;
         else if (head_wgs > 256) head_chunks = std::min<long long>(head_chunks, 12);
     }
     const bool head_attn = L <= kHeadAttnMaxRows && attn_chunks <= head_chunks;

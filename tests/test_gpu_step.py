@@ -834,3 +834,11 @@ def test_attention_of_64_element_heads_around_its_line(torch_mod, shape_name, k,
     block's), the cut over the key axis beyond: one and two query tiles on both sides of the line against the oracle."""
     shape = SHAPES[shape_name]
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=8), 1, k, None, gc.LOGIT_TIGHT, ctxs=[ctx], capacity=768)
+
+
+@pytest.mark.parametrize("B", [32, 33])
+def test_one_tile_attention_on_both_sides_of_a_workgroup_per_cu(torch_mod, B):
+    """Blocks of one query tile take the one-launch attention up to 256 (sequence, head) pairs and the cut over the key
+    axis beyond: 32 and 33 sequences of 8 heads with short ragged contexts against the oracle."""
+    shape = SHAPES["gqa-small"]
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=9), B, 1, None, gc.LOGIT_TIGHT)

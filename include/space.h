@@ -345,14 +345,15 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *                                             and S partial sums over the contraction (1..8; gu and lm: 1);
  *   attn=N   longest context, in 32-key chunks, that the one-launch attention kernel handles
  *            (0: always split over the key axis; 1000000 and more: always the one-launch kernel, also
- *            where a batch would put more than two of its workgroups on a compute unit);
+ *            where a batch has so many of its workgroups that it would otherwise not be taken);
  *   resid=N  most rows (at most 48) for which O and down are computed without partial sums, norm included
  *            (0: never);
  *   wide=N   fewest rows for the many-row projection kernel (default 193; 97 for QKV), widemask=M which projections
  *            may use it (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head);
  *   widecut=A:B:C:D:O   forces how that kernel cuts the rows of every launch whose rows make up exactly
  *            4A + 3B + 2C + D groups of 32 rows: A pieces of 128 rows, B of 96, C of 64, D of 32, launched
- *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1).
+ *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1); the
+ *            partial sums over the contraction stay those of the cut it replaces;
  *   wideks=N   that kernel sums the contraction in N parts (1, 2 or 4; plain-sum projections only) instead of
  *            what its cost model or space_tune_rows picked.
  * Results do not depend on it beyond the order of floating-point sums; the tests use it to force every

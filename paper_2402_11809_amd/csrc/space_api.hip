@@ -105,9 +105,9 @@ struct space_ctx {
     // rows 205 -> 224 (QKV level), 208 rows 286 -> 238, 288 rows 296 -> 260, 384 rows 381 -> 340, 512 rows
     // 521 -> 370, 1024 rows 1015 -> 640: from the third 96-row pass on, and for QKV from the second.
     int wide_min_rows = 193, wide_min_rows_qkv = 97, wide_mask = 31;
-    // How the many-row kernel cuts the rows of (projection class, row count), where space_tune_rows has
-    // measured it; key = class << 32 | rows.  Without an entry: pieces of 128 rows and one for the rest.
-    struct WideTuned { WideParts parts; int ksplit; };  // ksplit 0: the plan's own
+    // How the many-row kernel cuts the rows of (projection class, row count) and in how many parts it sums the
+    // contraction, where space_tune_rows has found something faster than the planner's choice; key = class << 32 | rows.
+    struct WideTuned { WideParts parts; int ksplit; };
     std::map<uint64_t, WideTuned> wide_parts;
     std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
@@ -746,10 +746,10 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     // Where the line lies: a workgroup of that form reads the operand planes of all rows through its CU, 4
     // bytes per element, and while weights stream from memory a CU gets through about 50 GB/s whatever
     // part of it comes out of L2 (7B, 36 rows: O 16.9 us against 11.1 + 5.6 with its norm launch, down 38 against
-    // 21.9 + 5.6).  So: planes up to 100 KB (step of a 256-wide model of 2 layers, 25 rows: 66.3 -> 59.5 us; 512
-    // wide, 16 rows 70.7 -> 67.7, level at 25 rows = 137 KB), or 9 rows (two 7B layers 231.3 -> 226.0, 16 rows
-    // 236 -> 238; one 70B layer 370 -> 359), or 4 where too few workgroups would stream (two 13B layers, 160
-    // workgroups: 304.7 -> 304.0, 9 rows 308 -> 315).
+    // 21.9 + 5.6).  So: planes up to 100 KB (steps of 2 layers, 256 wide, 4 / 16 / 25 rows: 53.9 -> 51.6, 54.7 -> 52.4,
+    // 59.3 -> 59.0 us; 512 wide, 16 rows 66.2 -> 65.8; 1024 wide, 16 rows 74.6 -> 71.4), or 9 rows (two 7B layers 227.4 ->
+    // 223.2, 16 rows level; one 70B layer 366.9 -> 358.2), or 4 where too few workgroups would stream (two 13B layers,
+    // 160 workgroups: level, 9 rows 308 -> 315).
     const size_t plane_bytes = (size_t)M * kTileK * 4 * std::max(ctx->layers[0].o.k_tiles, ctx->layers[0].down.k_tiles);
     const bool few = ctx->resid_max_rows >= 0 ? M <= ctx->resid_max_rows
                                               : plane_bytes <= 100 * 1024 || M <= (groups_o >= 192 ? 9 : 4);

@@ -16,7 +16,7 @@
 //   * a CU gets through one such workgroup per unit of time however many it holds (two fit: 119
 //     registers, 64 KB of LDS), so what a launch costs is the work of its busiest CU.  The rows of a
 //     weight group are therefore cut into pieces of 8, 6, 4 or 2 row tiles (WideParts, chosen by the
-//     host: by default pieces of 8 and one for the rest, else what space_tune_rows measured);
+//     host: by the cost model of space_wide_plan.h, else what space_tune_rows measured);
 //   * the pieces of one weight group get workgroup indices that differ by 8 (same XCD, about the same
 //     time), so the weights cross HBM once and the siblings hit L2.
 // Per contraction tile a full workgroup moves 16 KB of weights and 16 KB of activation planes for

@@ -1151,10 +1151,13 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         // split) is taken only where it is clearly ahead.
         const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)rows;
         ctx->wide_plans.erase(key);
-        if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms)
-            ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
-        else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
-            ctx->wide_plans[key] = own;  // what the next launch would plan again
+        try {
+            if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms)
+                ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
+            else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
+                ctx->wide_plans[key] = own;  // what the next launch would plan again
+        } catch (...) {  // no room to remember it: planned again
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -2256,16 +2256,16 @@ hipError_t launch_verify(const VerifyLaunch& v, hipStream_t s) {
 // verification by rejection sampling (Algorithm 1 as printed; appendix "Random Sampling")
 // ------------------------------------------------------------------------------------------
 // Kernel 1, one workgroup per block row: the top_k largest logits in descending order (ties: lowest
-// id), softmax over them, the shortest prefix whose mass reaches top_p, renormalised.  A thread keeps
-// its first 32 elements in registers.  The top_k-th largest of 256 group maxima (a group: the elements of
-// four threads) bounds the top_k-th largest element from below, so the elements at or above it -- about
-// top_k and a few more -- are all that has to be ordered: they go to LDS and each finds its place by
-// counting.  What that costs does not grow with top_k, unlike a round with two barriers per kept token.
+// id), softmax over them, the shortest prefix whose mass reaches top_p, renormalised.  The top_k-th largest of 256
+// group maxima (a group: the elements of two or four threads) bounds the top_k-th largest element from below, so the
+// elements at or above it -- about top_k and a few more -- are all that has to be ordered: they go to LDS and each
+// finds its place by counting.  What that costs does not grow with top_k, unlike a round with two barriers per kept
+// token.  Every phase behind the reading is a chain of LDS or lane operations with few waves busy, so their
+// comparisons are shared by all threads and the sums, which run sequentially in descending order (the result does
+// not depend on the launch shape), are straight code over the lanes: 36 rows of 32000, 10 kept, 10.5 -> 8.5 us.
 // Rows where more than 256 elements lie above the bound (large ones in the columns of few groups) or are equal to
 // it (masked vocabularies) take a path that is not inlined: 648 rows with large values in 50 groups, 64 kept, 150 us
 // against 53 for usual ones (1430 with a pass over the row per kept token); all but 7 elements masked, 10 kept, 48.
-// 648 rows of 32000, 50 kept: 38 us (284 with a round per kept token); 36 rows, 10 kept: 10.8 (26.8).  Sums run
-// sequentially in descending order: the result does not depend on the launch shape.
 constexpr int kTopGroups = 256, kTopCand = 256;
 
 __device__ __forceinline__ bool sample_before(float v, int i, float bv, int bi) {
@@ -2280,6 +2280,34 @@ __device__ __forceinline__ float float_from_order(uint32_t o) {
 }
 __device__ __forceinline__ float lane_value(float v, int lane) {  // lane: the same in all lanes
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+
+// f(0) .. f(n - 1) and on to the next multiple of 8 (n <= 64, the same in all lanes): straight code, the lanes are
+// constants.  A loop over readlane and a branch per lane took 30 - 40 cycles a lane.
+template <class F>
+__device__ __forceinline__ void for_lanes(int n, F f) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+        if (8 * c < n) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) f(8 * c + e);
+            __builtin_amdgcn_sched_barrier(0);  // or the masks of all lanes are made at once and spill
+        }
+}
+// Sum of the first n lanes in lane order, and the sums up to every lane.  v: 0 in the lanes from n on.
+__device__ __forceinline__ float lanes_sum(float v, int n) {
+    float sum = 0.f;
+    for_lanes(n, [&](int q) { sum += lane_value(v, q); });
+    return sum;
+}
+__device__ __forceinline__ float lanes_prefix(float v, int n) {
+    const int lane = threadIdx.x & 63;
+    float run = 0.f;
+    for_lanes(n, [&](int q) {
+        const float vq = lane_value(v, q);
+        run += lane >= q ? vq : 0.f;
+    });
+    return run;
 }
 
 constexpr int kTopHeld = 32;  // elements of a row held per thread
@@ -2299,42 +2327,50 @@ __device__ __forceinline__ TopLds& top_lds() {  // also for functions that are n
     return s;
 }
 
-// Every element of the list finds its place in the order; the first K are kept.
+// Every element of the list finds its place in the order, its comparisons shared by NT / 256 threads; the first K
+// are kept.
+template <int NT>
 __device__ __forceinline__ void topk_place(int n, int K) {
     TopLds& s = top_lds();
-    if ((int)threadIdx.x < n) {
-        const float v = s.c_v[threadIdx.x];
-        const int i = s.c_i[threadIdx.x];
+    constexpr int P = NT / kTopCand;
+    const int c = threadIdx.x / P;
+    if (c < n) {
+        const float v = s.c_v[c];
+        const int i = s.c_i[c];
         int place = 0;
-        for (int j = 0; j < n; ++j) place += sample_before(s.c_v[j], s.c_i[j], v, i);
-        if (place < K) { s.top_v[place] = v; s.top_i[place] = i; }
+#pragma unroll 4
+        for (int j = threadIdx.x % P; j < n; j += P) place += sample_before(s.c_v[j], s.c_i[j], v, i);
+#pragma unroll
+        for (int o = 1; o < P; o <<= 1) place += __shfl_xor(place, o, 64);
+        if (threadIdx.x % P == 0 && place < K) { s.top_v[place] = v; s.top_i[place] = i; }
     }
     __syncthreads();
 }
 
-// A thread's elements of a row, eight requested at a time.
-template <class F>
-__device__ __forceinline__ void row_elements(const float* __restrict__ x, int V, F use) {
+// A thread's elements of a row (every NT-th from element `from` + its index on), eight requested at a time.
+template <int NT, class F>
+__device__ __forceinline__ void row_elements(const float* __restrict__ x, int from, int V, F use) {
     constexpr int kAtOnce = 8;
-    for (int i0 = threadIdx.x; i0 < V; i0 += kAtOnce * 1024) {
+    for (int i0 = from + threadIdx.x; i0 < V; i0 += kAtOnce * NT) {
         float v[kAtOnce];
 #pragma unroll
-        for (int e = 0; e < kAtOnce; ++e) v[e] = x[min(i0 + e * 1024, V - 1)];
+        for (int e = 0; e < kAtOnce; ++e) v[e] = x[min(i0 + e * NT, V - 1)];
 #pragma unroll
         for (int e = 0; e < kAtOnce; ++e)
-            if (i0 + e * 1024 < V) use(v[e], i0 + e * 1024);
+            if (i0 + e * NT < V) use(v[e], i0 + e * NT);
     }
 }
 
 // The list of the elements above the bound, among those of the threads that may hold any (elsewhere the row is not
 // read again).  Returns how many there are; the first kTopCand are listed.
+template <int NT>
 __device__ __forceinline__ int topk_above(const float* __restrict__ x, int V, float bound, bool holds) {
     TopLds& s = top_lds();
     __syncthreads();
     if (threadIdx.x == 0) s.count = 0;
     __syncthreads();
     if (holds)
-        row_elements(x, V, [&](float v, int i) {
+        row_elements<NT>(x, 0, V, [&](float v, int i) {
             if (v > bound) {
                 const int at = atomicAdd(&s.count, 1);
                 if (at < kTopCand) { s.c_v[at] = v; s.c_i[at] = i; }
@@ -2344,13 +2380,14 @@ __device__ __forceinline__ int topk_above(const float* __restrict__ x, int V, fl
     return s.count;
 }
 
-// The places from `got` on go to elements equal to the bound by lowest id, found 8192 elements at a time from the
-// front of the row.
+// The places from `got` on go to elements equal to the bound by lowest id, found 8 a thread at a time from the front
+// of the row.
+template <int NT>
 __device__ __forceinline__ void topk_many_equal(const float* __restrict__ x, int V, int K, float bound, int got) {
     TopLds& s = top_lds();
     constexpr int kAtOnce = 8;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int base = 0; base < V && got < K; base += kAtOnce * 1024) {
+    for (int base = 0; base < V && got < K; base += kAtOnce * NT) {
         const int i0 = base + wave * kAtOnce * 64 + lane;  // a wave's elements lie together
         uint64_t hits[kAtOnce];
         float v[kAtOnce];
@@ -2366,7 +2403,7 @@ __device__ __forceinline__ void topk_many_equal(const float* __restrict__ x, int
         __syncthreads();
         int at = got, all = 0;
 #pragma unroll 2
-        for (int w = 0; w < 16; ++w) {
+        for (int w = 0; w < NT / 64; ++w) {
             at += w < wave ? s.word[w] : 0;
             all += s.word[w];
         }
@@ -2387,6 +2424,7 @@ __device__ __forceinline__ void topk_many_equal(const float* __restrict__ x, int
 // counts of the elements above it in 256 equal ranges of their order, then of the range that holds the K-th
 // largest, at most four times (32 bits).  Returns the highest lower end of a range with K elements at or above it:
 // at most kTopCand of them, or all but fewer than K are equal to it.
+template <int NT>
 __device__ __forceinline__ float topk_narrow(const float* __restrict__ x, int V, int K, float bound, float largest) {
     TopLds& s = top_lds();
     int* hist = s.c_i;
@@ -2399,7 +2437,7 @@ __device__ __forceinline__ float topk_narrow(const float* __restrict__ x, int V,
         __syncthreads();
         if (tid < 256) hist[tid] = 0;
         __syncthreads();
-        row_elements(x, V, [&](float v, int) {
+        row_elements<NT>(x, 0, V, [&](float v, int) {
             const uint32_t o = float_order(v);
             if (v == v && o >= first && o <= last) atomicAdd(hist + ((o - first) >> shift), 1);
         });
@@ -2423,6 +2461,7 @@ __device__ __forceinline__ float topk_narrow(const float* __restrict__ x, int V,
 }
 
 // Fewer than K or more than kTopCand elements at or above the bound.
+template <int NT>
 __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K, float bound, bool holds) {
     TopLds& s = top_lds();
     const int tid = threadIdx.x;
@@ -2432,58 +2471,96 @@ __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K
             s.top_v[tid] = -INFINITY;
             s.top_i[tid] = INT_MAX;
         }
-        topk_place(n, K);
+        topk_place<NT>(n, K);
         return;
     }
-    n = topk_above(x, V, bound, holds);
+    n = topk_above<NT>(x, V, bound, holds);
     if (n > kTopCand) {
         float largest = s.group[0];
 #pragma unroll 4
         for (int j = 1; j < kTopGroups; ++j) largest = fmaxf(largest, s.group[j]);
-        bound = topk_narrow(x, V, K, bound, largest);
-        n = topk_above(x, V, bound, true);  // at most kTopCand now
+        bound = topk_narrow<NT>(x, V, K, bound, largest);
+        n = topk_above<NT>(x, V, bound, true);  // at most kTopCand now
     }
-    topk_place(n, K);
-    topk_many_equal(x, V, K, bound, n);
+    topk_place<NT>(n, K);
+    topk_many_equal<NT>(x, V, K, bound, n);
 }
 
-__global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
+// HELD: 1024 threads keep the first 32768 elements of the row in registers, two rows to a CU.  Else 512 threads keep
+// the maxima of the eighths of their first 64 elements and read those eighths again that reach the bound (out of
+// L2 or the cache behind it, 1 - 2 us): four rows to a CU, so that up to 1024 rows read at the same time.  648 rows, 50
+// kept: 37.8 -> 25.6 us (1.3 rounds of the first form).  The rule, rows up to 512, is where the first form needs a
+// second round (both launches of a call, first / second form: 486 rows, 10 kept, 21.8 / 23.1; 36 rows 12.0 / 13.2; 567
+// rows, 50 kept, 43.8 / 31.0).
+template <int NT, bool HELD>
+__global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
     TopLds& s = top_lds();
     const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const size_t row = (size_t)b * a.lay.L + r;
     const float* __restrict__ x = a.logits + row * a.vocab;
     const int V = a.vocab;
-    constexpr int held = kTopHeld * 1024;
-    float cache[kTopHeld];
+    constexpr int kSub = 8, kSubElems = 8;  // !HELD
+    constexpr int held = HELD ? kTopHeld * NT : kSub * kSubElems * NT;
+    static_assert(!HELD || NT == 1024, "registers");
+    float cache[HELD ? kTopHeld : kSub];  // elements; maxima
+    float mine = -INFINITY;
+    if (HELD) {
 #pragma unroll
-    for (int j = 0; j < kTopHeld; ++j) {
-        const int i = tid + j * 1024;
-        cache[j] = i < V ? x[i] : -INFINITY;
+        for (int j = 0; j < kTopHeld; ++j) {
+            const int i = tid + j * NT;
+            cache[j] = i < V ? x[i] : -INFINITY;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kSub; j += 2) {  // two at a time
+            float v[2][kSubElems];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int e = 0; e < kSubElems; ++e) {
+                    const int i = tid + ((j + q) * kSubElems + e) * NT;
+                    v[q][e] = i < V ? x[i] : -INFINITY;
+                }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                cache[j + q] = -INFINITY;
+#pragma unroll
+                for (int e = 0; e < kSubElems; ++e) cache[j + q] = fmaxf(cache[j + q], v[q][e]);
+            }
+        }
     }
     if (tid == 0) {
         s.bound = 0xffffffffu;
         s.count = 0;
     }
     const int K = min(a.top_k, V);
-    float mine = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < kTopHeld; ++j) mine = fmaxf(mine, cache[j]);
-    for (int i = tid + held; i < V; i += 1024) mine = fmaxf(mine, x[i]);
+    for (int j = 0; j < (HELD ? kTopHeld : kSub); ++j) mine = fmaxf(mine, cache[j]);
+    row_elements<NT>(x, held, V, [&](float v, int) { mine = fmaxf(mine, v); });
+    constexpr int P = NT / kTopGroups;  // threads of a group
     {
-        float g = fmaxf(mine, __shfl_xor(mine, 1, 64));
-        g = fmaxf(g, __shfl_xor(g, 2, 64));
-        if ((tid & 3) == 0) s.group[tid >> 2] = g;
+        float g = mine;
+#pragma unroll
+        for (int o = 1; o < P; o <<= 1) g = fmaxf(g, __shfl_xor(g, o, 64));
+        if (tid % P == 0) s.group[tid / P] = g;
     }
     __syncthreads();
-    if (tid < kTopGroups) {  // the smallest group maximum with fewer than K larger ones
-        const float g = s.group[tid];
+    {  // the smallest group maximum with fewer than K larger ones; a group's threads share its comparisons
+        constexpr int kQuads = kTopGroups / 4 / P;
+        const float g = s.group[tid / P];
+        const int part = tid % P;
         int larger = 0;
 #pragma unroll 8
-        for (int j = 0; j < kTopGroups / 4; ++j) {
-            const f32x4 q = *(const f32x4*)(s.group + 4 * j);
+        for (int j = 0; j < kQuads; ++j) {  // (each part starts elsewhere: other LDS banks)
+            const f32x4 q = *(const f32x4*)(s.group + 4 * (part * kQuads + ((j + 2 * part) & (kQuads - 1))));
             larger += (q[0] > g) + (q[1] > g) + (q[2] > g) + (q[3] > g);
         }
-        if (larger < K) atomicMin(&s.bound, float_order(g));
+#pragma unroll
+        for (int o = 1; o < P; o <<= 1) larger += __shfl_xor(larger, o, 64);
+        uint32_t low = larger < K ? float_order(g) : 0xffffffffu;
+#pragma unroll
+        for (int o = P; o < 64; o <<= 1) low = min(low, (uint32_t)__shfl_xor((int)low, o, 64));
+        if (lane == 0 && low != 0xffffffffu) atomicMin(&s.bound, low);
     }
     __syncthreads();
     const float bound = float_from_order(s.bound);
@@ -2494,30 +2571,40 @@ __global__ __launch_bounds__(1024, 8) void topk_warp_kernel(SampleLaunch a) {
                 if (at < kTopCand) { s.c_v[at] = v; s.c_i[at] = i; }
             }
         };
+        if (HELD) {
 #pragma unroll
-        for (int j = 0; j < kTopHeld; ++j)
-            if (tid + j * 1024 < V) take(cache[j], tid + j * 1024);
-        for (int i = tid + held; i < V; i += 1024) take(x[i], i);
+            for (int j = 0; j < kTopHeld; ++j)
+                if (tid + j * NT < V) take(cache[j], tid + j * NT);
+        } else {
+            unsigned again = 0;
+#pragma unroll
+            for (int j = 0; j < kSub; ++j) again |= (unsigned)(cache[j] >= bound) << j;
+            while (again) {
+                const int i0 = tid + __builtin_ctz(again) * kSubElems * NT;
+                again &= again - 1;
+                float v[kSubElems];
+#pragma unroll
+                for (int e = 0; e < kSubElems; ++e) v[e] = x[min(i0 + e * NT, V - 1)];
+#pragma unroll
+                for (int e = 0; e < kSubElems; ++e)
+                    if (i0 + e * NT < V) take(v[e], i0 + e * NT);
+            }
+        }
+        row_elements<NT>(x, held, V, take);
     }
     __syncthreads();
     const int n = s.count;
     if (n >= K && n <= kTopCand)  // (the branches are taken by whole workgroups)
-        topk_place(n, K);
+        topk_place<NT>(n, K);
     else
-        topk_rare(x, V, K, bound, mine > bound);
+        topk_rare<NT>(x, V, K, bound, mine > bound);
     if (tid < 64) {  // lane j: the j-th kept token
-        const int j = min(lane, K - 1);
-        const float e = expf(s.top_v[j] - s.top_v[0]);
-        float total = 0.f;
-        for (int q = 0; q < K; ++q) total += lane_value(e, q);
-        const float p = e / total;
-        int keep = K;
-        float run = 0.f, mass = 0.f;
-        for (int q = 0; q < K; ++q) {
-            run += lane_value(p, q);
-            if (run >= a.top_p) { keep = q + 1; break; }
-        }
-        for (int q = 0; q < keep; ++q) mass += lane_value(p, q);
+        const float e = lane < K ? expf(s.top_v[min(lane, K - 1)] - s.top_v[0]) : 0.f;
+        const float p = e / lanes_sum(e, K);
+        const float run = lanes_prefix(lane < K ? p : 0.f, K);
+        const uint64_t reached = __builtin_amdgcn_ballot_w64(lane < K && run >= a.top_p);
+        const int keep = reached ? __builtin_ctzll(reached) + 1 : K;
+        const float mass = lane_value(run, __builtin_amdgcn_readfirstlane(keep - 1));
         if (lane < keep) {
             a.row_ids[row * kMaxTopK + lane] = s.top_i[lane];
             a.row_probs[row * kMaxTopK + lane] = p / mass;
@@ -2544,7 +2631,7 @@ __device__ __forceinline__ float sample_prob_of(const SampleList& l, int token) 
 __device__ __forceinline__ int sample_draw(const SampleList& l, float u, float* p_out) {
     float run = 0.f;
     int at = l.n - 1;
-    for (int j = 0; j < l.n; ++j) {
+    for (int j = 0; j < l.n; ++j) {  // (mostly a few: the likely tokens are in front)
         run += lane_value(l.p, j);
         if (u < run) { at = j; break; }
     }
@@ -2626,16 +2713,15 @@ __global__ __launch_bounds__(64 * kSampleWaves) void sample_verify_kernel(Sample
             const int dn = end ? __builtin_ctzll(end) : 64;
             float d = 0.f;
             bool found = false;
-            for (int q = 0; q < dn; ++q) {
-                const bool hit = !found && __builtin_amdgcn_readlane(did, q) == l.id;
+            for_lanes(dn, [&](int q) {
+                const bool hit = !found && q < dn && __builtin_amdgcn_readlane(did, q) == l.id;
                 const float pq = lane_value(dp, q);
                 d = hit ? pq : d;
                 found |= hit;
-            }
+            });
             float res = l.p - d;
             res = (lane < l.n && res > 0.f) ? res : 0.f;
-            float sum = 0.f;
-            for (int j = 0; j < l.n; ++j) sum += lane_value(res, j);
+            const float sum = lanes_sum(res, l.n);
             if (sum > 0.f) l.p = res / sum;
         }
         float p_extra;
@@ -2696,7 +2782,9 @@ hipError_t launch_sample_verify(const SampleLaunch& v, hipStream_t s) {
         return hipErrorInvalidValue;
     // both kernels keep per-row facts in LDS arrays of 96 entries (uniforms: 192): check before either is enqueued
     if (v.lay.L > 16 * kMaxRowTiles || v.lay.G + v.max_cands > 2 * 16 * kMaxRowTiles) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(topk_warp_kernel, dim3(v.lay.L, v.batch), dim3(1024), 0, s, v);
+    const dim3 rows(v.lay.L, v.batch);
+    if (v.lay.L * v.batch <= 512) hipLaunchKernelGGL((topk_warp_kernel<1024, true>), rows, dim3(1024), 0, s, v);
+    else hipLaunchKernelGGL((topk_warp_kernel<512, false>), rows, dim3(512), 0, s, v);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sample_verify_kernel, dim3(v.batch), dim3(64 * kSampleWaves), 0, s, v);

@@ -541,3 +541,45 @@ def test_kept_lists_with_large_logits_in_few_column_groups(torch_mod, V, top_k):
         assert n >= 1 and ids[:n].tolist() == order[:n].tolist(), j
         assert want[n:].sum() < 64 * 1.2e-7  # what is not kept has no mass left in float32
         np.testing.assert_allclose(probs[:n], want[:n], rtol=1e-5, atol=1e-30)
+
+
+@pytest.mark.parametrize("V,top_k", [(40, 50), (4097, 64), (16391, 10), (33000, 64)])
+def test_more_rows_than_are_held_at_once(torch_mod, V, top_k):
+    """More than 512 rows take the kernel that reads its candidates again instead of holding the row: the same
+    bits as the same sequences in two calls of at most 512 rows, which the tests above check against a full
+    sort.  Vocabularies below, between and above what the maxima of a thread cover; rows with plateaus, masked
+    and NaN elements, large values in the columns of a few threads."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    k, B = 8, 57
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=B, max_rows=k + 1, max_ctx=64)
+    spec = lo.first_step_layout(k)
+    lay = gm.layout(spec)
+    g = torch.Generator(device="cuda").manual_seed(V)
+    P = torch.randn((B, k + 1, V), generator=g, device="cuda") * 2.5
+    col = torch.arange(V, device="cuda")
+    drop = torch.rand((B, V), generator=g, device="cuda")
+    P[:, 1] = P[:, 1].round()
+    P[:, 2, :] = 0.25
+    P[:, 3][drop > 8.0 / V] = -float("inf")
+    P[:, 4][drop > 0.6] = float("nan")
+    P[:, 5] = torch.where(col % 512 < 9, P[:, 5].abs() + 20.0, P[:, 5])
+    P[:, 6] = torch.where(col % 512 == 3, torch.full_like(P[:, 6], 9.0), P[:, 6])
+    P[:, 7] = col / V
+    u = torch.rand((B, 1 + k), generator=g, device="cuda")
+    toks = torch.full((B, k + 1), shape.mask_id, dtype=torch.int32, device="cuda")
+    toks[:, 0] = 1
+    pc = torch.ones(B, k, device="cuda")
+
+    def call(lo_, hi):
+        out = binding.SampleOut(gm, hi - lo_, 1, k, top_k)
+        s = slice(lo_, hi)
+        gm.sample_verify(P[s].contiguous(), toks[s].contiguous(), lay, pc[s].contiguous(), u[s].contiguous(), out, top_k=top_k, top_p=0.9)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (out.new_ids, out.new_probs, out.extra, out.new_cands, out.new_pc)]
+
+    assert B * (k + 1) > 512
+    for whole, a, b in zip(call(0, B), call(0, 28), call(28, B)):
+        assert whole.tobytes() == np.concatenate([a, b]).tobytes()

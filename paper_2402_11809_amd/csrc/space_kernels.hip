@@ -2508,7 +2508,7 @@ __global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
 #pragma unroll
         for (int j = 0; j < kTopHeld; ++j) {
             const int i = tid + j * NT;
-            cache[j] = i < V ? x[i] : -INFINITY;
+            cache[j] = i < V ? __builtin_nontemporal_load(x + i) : -INFINITY;  // (both launches, 486 rows, 10 kept: 22.0 -> 20.9 us)
         }
     } else {
 #pragma unroll
@@ -2795,20 +2795,25 @@ hipError_t launch_sample_verify(const SampleLaunch& v, hipStream_t s) {
 // losses of SAR-SFT (Methods, "Semi-Autoregressive Finetuning"): -log softmax(row)[label] per row
 // ------------------------------------------------------------------------------------------
 // Both L_AR and L_SAR are sums of such terms; which rows and labels enter is the caller's (the
-// dataloader's) business.  One workgroup per row: maximum, sum of exponentials (each thread over its
-// own elements, then a fixed tree: the result does not depend on timing), then the term.  A second
-// launch adds the rows up in row order.
+// dataloader's) business.  One workgroup per row, a thread over its own elements, then a fixed tree: the result does
+// not depend on timing.  A second launch adds the rows up in row order.
 //
-// Bound by reading the logits once: a row's first 32768 logits stay in the registers of its 1024
-// threads between the maximum and the sum (two workgroups per CU, 256 KB in flight); what lies beyond is
-// read a second time.  VEC: rows that start on 16 bytes (vocabulary a multiple of 4) take float4 loads.
-// 1366 rows of 32000: 33.5 us = 5.2 TB/s (75 us when maximum and sum each read the row).
-constexpr int kNllHeld = 32;  // logits of a row held per thread
+// Bound by reading the logits once, next to about 35 cycles of arithmetic an element: every thread keeps a running
+// maximum and the sum of exponentials below it, 32 elements at a time, so that nothing waits for the row's maximum
+// and four rows run on a CU, some reading while others compute (rows held in registers up to their maximum, two to
+// a CU, with the library's expf: 32.3 us for 1366 rows of 32000, here 27).  The exponential is the hardware's of
+// a rounded product: the terms' errors against 64 bits are 0.95 - 0.98 of what they were.  The loads are non-temporal:
+// read once, and from memory that holds more than the caches 36.0 against 40.2 us for both launches.  256 threads are
+// level there and slower from 300 rows of 32000 on down (11.2 against 10.4), 1024 slower on short rows.  VEC: rows
+// that start on 16 bytes (vocabulary a multiple of 4) take float4 loads.
+constexpr int kNllThreads = 512, kNllHeld = 32;  // logits of a row a thread takes at a time
 
 template <bool VEC>
-__global__ __launch_bounds__(1024, 8) void nll_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                           int vocab, float* __restrict__ row_loss, int32_t* faults) {
-    __shared__ float sh[2][16];
+__global__ __launch_bounds__(kNllThreads, 8) void nll_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
+                                                                  int vocab, float* __restrict__ row_loss, int32_t* faults) {
+    constexpr int W = kNllThreads / 64;
+    constexpr float kLog2e = 1.4426950408889634f;
+    __shared__ float s_max[W], s_sum[W];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int label = labels[row];
     if (label < 0 || label >= vocab) {  // ignored row (negative) or a label outside the vocabulary (counted)
@@ -2819,96 +2824,107 @@ __global__ __launch_bounds__(1024, 8) void nll_rows_kernel(const float* __restri
         return;
     }
     const float* __restrict__ x = logits + (size_t)row * vocab;
-    constexpr int held = kNllHeld * 1024;
-    float v[kNllHeld];
-    if (VEC) {
+    const float at_label = x[label];
+    float mx = -INFINITY, sum = 0.f;
+    for (int base = 0; base < vocab; base += kNllThreads * kNllHeld) {
+        float v[kNllHeld];
+        if (VEC) {
 #pragma unroll
-        for (int j = 0; j < kNllHeld / 4; ++j) {
-            const int i = 4 * (tid + j * 1024);  // vocab % 4 == 0: a vector lies in the row or behind it
-            f32x4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-            if (i < vocab) q = *(const f32x4*)(x + i);
+            for (int j = 0; j < kNllHeld / 4; ++j) {
+                const int i = base + 4 * (tid + j * kNllThreads);  // vocab % 4 == 0: a vector lies in the row or behind it
+                f32x4 q = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                if (i < vocab) q = __builtin_nontemporal_load((const f32x4*)(x + i));
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * j + e] = q[e];
+                for (int e = 0; e < 4; ++e) v[4 * j + e] = q[e];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kNllHeld; ++j) {
+                const int i = base + tid + j * kNllThreads;
+                v[j] = i < vocab ? __builtin_nontemporal_load(x + i) : -INFINITY;
+            }
         }
-    } else {
+        float m = mx;
 #pragma unroll
-        for (int j = 0; j < kNllHeld; ++j) {
-            const int i = tid + j * 1024;
-            v[j] = i < vocab ? x[i] : -INFINITY;
-        }
+        for (int j = 0; j < kNllHeld; ++j) m = fmaxf(m, v[j]);
+        const float m_use = m == -INFINITY ? 0.f : m;  // nothing but masked logits so far: exp2(-inf), not of a NaN
+        sum *= __builtin_amdgcn_exp2f((mx - m_use) * kLog2e);
+        mx = m;
+        float part[2] = {0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < kNllHeld; ++j) part[j & 1] += __builtin_amdgcn_exp2f((v[j] - m_use) * kLog2e);
+        sum += part[0] + part[1];
     }
-    float mx = -INFINITY;
+    float all = mx;
 #pragma unroll
-    for (int j = 0; j < kNllHeld; ++j) mx = fmaxf(mx, v[j]);
-    for (int i = held + tid; i < vocab; i += 1024) mx = fmaxf(mx, x[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) sh[0][wave] = mx;
+    for (int o = 32; o > 0; o >>= 1) all = fmaxf(all, __shfl_xor(all, o, 64));
+    if (lane == 0) s_max[wave] = all;
     __syncthreads();
-    mx = sh[0][0];
 #pragma unroll
-    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, sh[0][w]);
-    float sum = 0.f;
-#pragma unroll
-    for (int j = 0; j < kNllHeld; ++j) {
-        const int i = VEC ? 4 * (tid + (j >> 2) * 1024) : tid + j * 1024;
-        if (i < vocab) sum += expf(v[j] - mx);
-    }
-    for (int i = held + tid; i < vocab; i += 1024) sum += expf(x[i] - mx);
+    for (int w = 0; w < W; ++w) all = fmaxf(all, s_max[w]);
+    sum *= __builtin_amdgcn_exp2f((mx - (all == -INFINITY ? 0.f : all)) * kLog2e);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (lane == 0) sh[1][wave] = sum;
+    if (lane == 0) s_sum[wave] = sum;
     __syncthreads();
     if (tid == 0) {
         float tot = 0.f;
-        for (int w = 0; w < 16; ++w) tot += sh[1][w];
-        row_loss[row] = -(x[label] - mx - logf(tot));
+#pragma unroll
+        for (int w = 0; w < W; ++w) tot += s_sum[w];
+        row_loss[row] = -(at_label - all - logf(tot));
     }
 }
 
-// The sum over the rows is a chain of additions in row order by contract.  All threads fetch the terms,
-// one wave adds them up out of LDS, where the next terms are a few cycles away instead of a trip to
-// memory each (rows that do not count hold a zero term, which changes no sum): 2048 rows 187 -> 9 us.
+// The sum over the rows is a chain of additions in row order by contract.  All threads fetch the terms; those of rows
+// that count are put side by side in LDS (the others are zero and change no sum), where one wave adds them up: the
+// next terms are a few cycles away instead of a trip to memory each.  2048 rows, 1366 that count: 9.3 -> 7.7 us, 3 of
+// them the additions.
 __global__ __launch_bounds__(1024) void nll_sum_kernel(const float* __restrict__ row_loss, const int32_t* __restrict__ labels,
                                                        int rows, int vocab, float* loss_sum, int32_t* n_terms) {
-    constexpr int kChunk = 4096;
-    __shared__ f32x4 buf[kChunk / 4];
-    __shared__ int s_n[16];
-    const int tid = threadIdx.x;
+    constexpr int kRounds = 4, kChunk = kRounds * 1024;
+    __shared__ f32x4 buf[kChunk / 4 + 1];  // (zeros behind the last term)
+    __shared__ int s_n[kRounds * 16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float tot = 0.f;
     int n = 0;
     for (int base = 0; base < rows; base += kChunk) {
+        float t[kRounds];
+        uint64_t on[kRounds];
 #pragma unroll
-        for (int j = 0; j < kChunk / 1024; ++j) {
-            const int r = base + tid + j * 1024;
-            float t = 0.f;
-            if (r < rows) {
-                const int label = labels[r];
-                t = row_loss[r];
-                n += label >= 0 && label < vocab;
-            }
-            ((float*)buf)[tid + j * 1024] = t;
+        for (int j = 0; j < kRounds; ++j) {
+            const int r = min(base + tid + j * 1024, rows - 1), label = labels[r];
+            t[j] = row_loss[r];
+            on[j] = __builtin_amdgcn_ballot_w64(base + tid + j * 1024 < rows && label >= 0 && label < vocab);
+            if (lane == 0) s_n[j * 16 + wave] = __popcll(on[j]);
         }
         __syncthreads();
+        int before = s_n[lane];  // terms up to the lane-th wave of the chunk, that one included
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int lower = __shfl_up(before, o, 64);
+            before += lane >= o ? lower : 0;
+        }
+        const int here = __builtin_amdgcn_readlane(before, 63);
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) {
+            const int at = __builtin_amdgcn_readlane(before, j * 16 + __builtin_amdgcn_readfirstlane(wave)) - __popcll(on[j] >> lane);
+            if (on[j] >> lane & 1) ((float*)buf)[at] = t[j];
+        }
+        if (tid < 3) ((float*)buf)[here + tid] = 0.f;
+        __syncthreads();
         if (tid < 64) {
-            const int n4 = (min(rows - base, kChunk) + 3) >> 2;  // the chunk's rest is zero
 #pragma unroll 8
-            for (int i = 0; i < n4; ++i) {
+            for (int i = 0; i < (here + 3) >> 2; ++i) {
                 const f32x4 q = buf[i];
                 tot += q[0]; tot += q[1]; tot += q[2]; tot += q[3];
             }
         }
+        n += here;
         __syncthreads();
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
-    if ((tid & 63) == 0) s_n[tid >> 6] = n;
-    __syncthreads();
     if (tid == 0) {
         *loss_sum = tot;
-        int all = 0;
-        for (int w = 0; w < 16; ++w) all += s_n[w];
-        if (n_terms) *n_terms = all;
+        if (n_terms) *n_terms = n;
     }
 }
 
@@ -2916,9 +2932,9 @@ hipError_t launch_nll(const float* logits, const int32_t* labels, int rows, int 
                       int32_t* n_terms, int32_t* faults, hipStream_t s) {
     if (rows < 1 || vocab < 1) return hipErrorInvalidValue;
     if ((vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0)
-        hipLaunchKernelGGL(nll_rows_kernel<true>, dim3(rows), dim3(1024), 0, s, logits, labels, vocab, row_loss, faults);
+        hipLaunchKernelGGL(nll_rows_kernel<true>, dim3(rows), dim3(kNllThreads), 0, s, logits, labels, vocab, row_loss, faults);
     else
-        hipLaunchKernelGGL(nll_rows_kernel<false>, dim3(rows), dim3(1024), 0, s, logits, labels, vocab, row_loss, faults);
+        hipLaunchKernelGGL(nll_rows_kernel<false>, dim3(rows), dim3(kNllThreads), 0, s, logits, labels, vocab, row_loss, faults);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(nll_sum_kernel, dim3(1), dim3(1024), 0, s, row_loss, labels, rows, vocab, loss_sum, n_terms);

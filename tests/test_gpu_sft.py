@@ -117,3 +117,50 @@ def test_loss_at_the_edges_of_the_reduction(V, rows, offset):
         tot = np.float32(tot + t)
     assert loss.cpu().numpy()[0] == tot and int(n.cpu()[0]) == int((labels >= 0).sum())
     assert gm.device_faults() == 0
+
+
+@pytest.mark.parametrize("V,rows,kept", [(16384, 6, 1.0), (16388, 6, 0.7), (16383, 6, 0.7), (40, 4096, 0.6), (40, 8193, 0.4),
+                                         (40, 1025, 0.0), (1000, 3, 1.0)])
+def test_loss_where_the_running_maximum_and_the_row_sum_change_course(V, rows, kept):
+    """Rows of one and just over one pass of a workgroup's threads, logits that are masked (-inf) up to the last
+    column, in the whole first pass or everywhere but at the label, an ascending row (the maximum moves in every
+    step), infinite and NaN logits; and row counts around the summing kernel's chunk with few or no rows that
+    count.  Terms against float64 (2e-5 absolute, as above, or 4 ulp of the logits), the sum bit for bit."""
+    torch = gc.require_gpu()
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=1, max_rows=36)
+    rng = np.random.default_rng(V + rows)
+    logits = (rng.standard_normal((rows, V)) * 3.0).astype(np.float32)
+    labels = rng.integers(0, V, size=rows).astype(np.int32)
+    labels[rng.random(rows) >= kept] = -1
+    special = rows < 10
+    if special:
+        labels[:3] = V - 1
+        logits[0, : V - 1] = -np.inf
+        logits[1, : min(V - 2, 16384)] = -np.inf
+        logits[2] = np.linspace(-80.0, 80.0, V, dtype=np.float32)
+    row_loss = torch.empty(rows, dtype=torch.float32, device="cuda")
+
+    def call():
+        loss, n = gm.sar_loss(torch.from_numpy(logits).cuda(), torch.from_numpy(labels).cuda(), row_loss)
+        torch.cuda.synchronize()
+        return loss.cpu().numpy()[0], int(n.cpu()[0]), row_loss.cpu().numpy()
+
+    loss, n, got = call()
+    x = logits.astype(np.float64)
+    mx = x.max(axis=1)
+    want = mx + np.log(np.exp(x - mx[:, None]).sum(axis=1)) - x[np.arange(rows), np.maximum(labels, 0)]
+    want[labels < 0] = 0.0
+    assert np.abs(got.astype(np.float64) - want).max() < 2e-5
+    tot = np.float32(0)
+    for t in got:
+        tot = np.float32(tot + t)
+    assert loss == tot and n == int((labels >= 0).sum())
+    if special:  # what made a term NaN or infinite still does
+        logits[0] = -np.inf
+        logits[1, V // 2] = np.nan
+        logits[2, V // 3] = np.inf
+        _, _, got = call()
+        assert np.isnan(got[:3]).all() and np.isfinite(got[3:]).all()
+    assert gm.device_faults() == 0

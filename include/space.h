@@ -352,8 +352,11 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *            may use it (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head);
  *   widecut=A:B:C:D:O   forces how that kernel cuts the rows of every launch whose rows make up exactly
  *            4A + 3B + 2C + D groups of 32 rows: A pieces of 128 rows, B of 96, C of 64, D of 32, launched
- *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1); the
- *            partial sums over the contraction stay those of the cut it replaces;
+ *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1) or any
+ *            larger one (O = 2); the partial sums over the contraction stay those of the cut it replaces, and no
+ *            piece is cut over the contraction;
+ *   widetail=P:N   where a projection has complete sums, its last P pieces per XCD are cut over the contraction into N
+ *            workgroups each (P * N up to 32) as far as it has that many; widetail=0: never by the library's own choice;
  *   wideks=N   that kernel sums the contraction in N parts (1, 2 or 4; plain-sum projections only) instead of
  *            what its cost model or space_tune_rows picked.
  * Results do not depend on it beyond the order of floating-point sums; the tests use it to force every
@@ -365,9 +368,11 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  * rows of the layout), a handful of ways to cut the rows into workgroups of 128, 96, 64 or 32 rows on the
  * context's own scratch buffers and the loaded layers' weights in turn -- and, for the projections whose
  * output is a plain sum (QKV, O, down), in how many parts the contraction is summed (1, 2 or 4) -- and
- * remembers the fastest for later space_step / space_prefill calls with that row count.  The cut of the rows
+ * remembers the fastest for later space_step / space_prefill calls with that row count.  Where the cost model would
+ * cut the last pieces over the contraction (their sums are added up inside the kernel), that is kept only if it
+ * measures 5 % ahead.  The cut of the rows
  * changes no result (every output element is computed by the same instructions in the same order); the
- * number of partial sums changes the order of the fp32 additions, i.e. results of a tuned context can
+ * number of partial sums and pieces cut over the contraction change the order of the fp32 additions, i.e. results of a tuned context can
  * differ from an untuned one's in the last bits, as they do between any two tilings.  Unlike the other calls it waits for the
  * stream (a few tens of milliseconds) and must not be called on a stream that is being captured
  * (SPACE_EINVAL).  rows: 1..max_batch*max_rows, else SPACE_ESHAPE.  Row counts below the many-row kernel's

@@ -109,6 +109,11 @@ struct space_ctx {
     // contraction, where space_tune_rows has found something faster than the planner's choice; key = class << 32 | rows.
     struct WideTuned { WideParts parts; int ksplit; };
     std::map<uint64_t, WideTuned> wide_parts;
+    // SPACE_TUNE widetail=: 0 = no pieces that are cut over the contraction, P:N = the last P pieces per XCD in N parts
+    int wide_tail = 1;
+    WideTail wide_tail_force{};
+    float* tail_sums = nullptr;  // their sums and arrival counts (GemmLaunch)
+    int32_t* tail_count = nullptr;
     std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
     // wide_cut_groups groups of two row tiles (0: none)
@@ -333,17 +338,26 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
         if (const char* p = strstr(e, "widemask=")) {
             if (sscanf(p + 9, "%d", &n) == 1 && n >= 0) ctx->wide_mask = n;
         }
+        if (const char* p = strstr(e, "widetail=")) {
+            int parts = 0;
+            const int got = sscanf(p + 9, "%d:%d", &n, &parts);
+            if (got == 2 && n >= 1 && n <= kWideTailSlots && parts >= 2 && n * parts <= kWideTailSlots) ctx->wide_tail_force = WideTail{n, parts};
+            else if (got == 1 && (n == 0 || n == 1)) ctx->wide_tail = n;
+        }
         if (const char* p = strstr(e, "widecut=")) {
             WideParts w{};
             if (sscanf(p + 8, "%d:%d:%d:%d:%d", &w.count[0], &w.count[1], &w.count[2], &w.count[3], &w.by_size) == 5 &&
-                w.count[0] >= 0 && w.count[1] >= 0 && w.count[2] >= 0 && w.count[3] >= 0 && (w.by_size == 0 || w.by_size == 1)) {
+                w.count[0] >= 0 && w.count[1] >= 0 && w.count[2] >= 0 && w.count[3] >= 0 && w.by_size >= 0 && w.by_size <= 2) {
                 ctx->wide_cut = w;
                 ctx->wide_cut_groups = 4 * w.count[0] + 3 * w.count[1] + 2 * w.count[2] + w.count[3];
             }
         }
     }
-    if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv))
+    if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv)) {
         max_splits = std::max(max_splits, 4);
+        if ((rc = dev_alloc(ctx, &ctx->tail_count, (size_t)8 * kWideTailSlots, true))) return rc;
+        if (dev_alloc(ctx, &ctx->tail_sums, 8 * kWideTailSlots * kWideTailFloats, false)) ctx->err.clear();  // 32 MB; no tails without
+    }
     ctx->part_splits_max = max_splits;
     const size_t plane_tile = 2 * 64 * 8;  // hi + lo plane of one 16 x 32 activation tile, in elements
     const size_t rt = ctx->row_tiles_max;
@@ -438,8 +452,8 @@ void free_ctx(space_ctx* ctx) {
 // (EPI_ARGMAX: *groups_used).
 int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t* x, int m, float* out, int ldo,
              size_t split_stride, uint16_t* h, int ffn, float* logits, hipStream_t s, int* splits_used = nullptr,
-             int* groups_used = nullptr, int wide_from = 0, int cls = -1, const WideParts* force_parts = nullptr,
-             int force_ksplit = 0, const float* ss = nullptr, int ss_n = 0) {
+             int* groups_used = nullptr, int wide_from = 0, int cls = -1, const WidePlan* force_plan = nullptr,
+             const float* ss = nullptr, int ss_n = 0) {
     const int pass_rows = 16 * kMaxRowTiles;
     GemmLaunch g{};
     g.w = w;
@@ -470,29 +484,34 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
     }
     if (wide_from > 0 && m >= wide_from) {  // wide_from: fewest rows for the many-row kernel, 0 = never
         // The cut of the rows changes no result, only the time; the number of partial sums over the
-        // contraction (measured too, for the plain-sum projections) changes the order of the fp32 sums.
-        const space_ctx::WideTuned* tuned = nullptr;
-        if (!force_parts && cls >= 0 && !(ctx->wide_cut_groups > 0 && ctx->wide_cut_groups == ceil_div(ceil_div(m, 16), 2))) {
-            const auto it = ctx->wide_parts.find(((uint64_t)cls << 32) | (uint32_t)m);
-            if (it != ctx->wide_parts.end()) tuned = &it->second;
-        }
+        // contraction (measured too, for the plain-sum projections) and a tail change the order of the fp32 sums.
         const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)m;
         WidePlan p;
-        const auto known = !force_parts && cls >= 0 ? ctx->wide_plans.find(key) : ctx->wide_plans.end();
-        if (known != ctx->wide_plans.end()) {
+        const auto known = cls >= 0 ? ctx->wide_plans.find(key) : ctx->wide_plans.end();
+        if (force_plan) {
+            p = *force_plan;
+        } else if (known != ctx->wide_plans.end()) {
             p = known->second;
         } else {
             const bool knob = ctx->wide_cut_groups > 0 && ctx->wide_cut_groups == ceil_div(ceil_div(m, 16), 2);
-            p = plan_gemm_wide(w, m, epi, ctx->part_splits_max,
-                               force_parts ? force_ksplit : ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0,
-                               force_parts ? force_parts : tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr);
-            if (!force_parts && cls >= 0) {
+            const auto it = cls >= 0 && !knob ? ctx->wide_parts.find(key) : ctx->wide_parts.end();
+            const space_ctx::WideTuned* tuned = it != ctx->wide_parts.end() ? &it->second : nullptr;
+            p = plan_gemm_wide(w, m, epi, ctx->part_splits_max, ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0,
+                               tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr, ctx->tail_sums && ctx->wide_tail);
+            if (ctx->wide_tail_force.pieces && p.ksplit == 1 && ctx->tail_sums) {
+                WidePlan f = p;
+                f.tail = ctx->wide_tail_force;
+                if (wide_tail_fits(w.k_tiles, f)) p = f;
+            }
+            if (cls >= 0) {
                 try {
                     ctx->wide_plans[key] = p;
                 } catch (...) {  // no room to remember it: made again next time
                 }
             }
         }
+        g.tail_sums = ctx->tail_sums;
+        g.tail_count = ctx->tail_count;
         if (splits_used) *splits_used = p.ksplit;
         if (groups_used) *groups_used = p.n_groups;
         HIP_TRY(ctx, launch_gemm_wide(g, p, epi, s));
@@ -692,7 +711,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         TimedScope ts(ctx, SPACE_K_EMBED, s);
         HIP_TRY(ctx, launch_embed(tokens, ctx->embed, c.vocab, d, lay, kv->len, B, ctx->cos_tab, ctx->sin_tab, ctx->n_pos, dh,
                                   ctx->x, ctx->pos, ctx->cos_t, ctx->sin_t, ctx->faults, ctx->layers[0].attn_norm, c.rms_eps,
-                                  ctx->xn, xs, s));
+                                  ctx->xn, xs, ctx->tail_count, 8 * kWideTailSlots, s));
     }
     // the real lengths live on the device; the grid covers the host-side upper bound
     const int attn_chunks = ceil_div(kv->host_len_bound, kAttnKeys) + ceil_div(L, kAttnKeys);
@@ -770,7 +789,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_QKV, s);
             if ((rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, M, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0,
-                               nullptr, s, &s_qkv, nullptr, (ctx->wide_mask & 1) ? ctx->wide_min_rows_qkv : 0, 0, nullptr, 0, ss, ss_n)))
+                               nullptr, s, &s_qkv, nullptr, (ctx->wide_mask & 1) ? ctx->wide_min_rows_qkv : 0, 0, nullptr, ss, ss_n)))
                 return rc;
         }
         uint16_t* kc_l = (uint16_t*)kv->k + kv_layer * l;
@@ -843,7 +862,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_GATE_UP, s);
             if ((rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, M, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr,
-                               (ctx->wide_mask & 4) ? ctx->wide_min_rows : 0, 2, nullptr, 0, ss, ss_n)))
+                               (ctx->wide_mask & 4) ? ctx->wide_min_rows : 0, 2, nullptr, ss, ss_n)))
                 return rc;
         }
         const uint16_t* next_norm = (l + 1 < c.n_layers) ? ctx->layers[l + 1].attn_norm : ctx->final_norm;
@@ -873,7 +892,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     {
         TimedScope ts(ctx, SPACE_K_LM_HEAD, s);
         if ((rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, M, nullptr, c.vocab, 0, nullptr, 0, out->logits, s, nullptr,
-                           &lm_groups, (ctx->wide_mask & 16) ? ctx->wide_min_rows : 0, 4, nullptr, 0, ss, ss_n)))
+                           &lm_groups, (ctx->wide_mask & 16) ? ctx->wide_min_rows : 0, 4, nullptr, ss, ss_n)))
             return rc;
     }
 
@@ -1106,29 +1125,33 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         // work, the norm kernels) pays for each of them, which a measurement of the projection alone does
         // not show: the time to read the extra partial sums once is put on top.
         const bool plain = cls == 0 || cls == 1 || cls == 3;
-        WidePlan own;
+        WidePlan own, tail;  // an unmeasured launch's, without and with pieces cut over the contraction (if it has any)
         {
             const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
             own = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max);
+            tail = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, 0, nullptr, ctx->tail_sums && ctx->wide_tail);
             cands[0] = own.parts;
         }
         const int ks_cands[4] = {0, 1, 2, 4};
-        float best_ms = 0.f, default_ms = 0.f;
+        float best_ms = 0.f, default_ms = 0.f, tail_ms = 0.f;
         int best = -1, best_ks = 0;
         for (int kc = 0; kc < (plain ? 4 : 1) && rc == SPACE_OK; ++kc)
-        for (int i = 0; i < (int)cands.size() && rc == SPACE_OK; ++i) {
+        for (int i = 0; i < (int)cands.size() + (kc == 0 && tail.tail.pieces) && rc == SPACE_OK; ++i) {
+            const bool is_tail = i == (int)cands.size();
             const int ks = kc == 0 ? own.ksplit : ks_cands[kc];
             if (ks > ctx->part_splits_max || (kc > 0 && ks == own.ksplit)) continue;
+            const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
+            const WidePlan cand = is_tail ? tail : plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, ks, &cands[i]);
             float ms_min = 0.f;
             for (int rep = 0; rep < 4 && rc == SPACE_OK; ++rep) {  // the first one warms up
                 if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(ctx, SPACE_EHIP, "hipEventRecord"); break; }
                 const LayerPacked& lp = *have[turn++ % have.size()];
                 switch (cls) {
-                    case 0: rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, rows, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cands[i], ks); break;
-                    case 1: rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cands[i], ks); break;
-                    case 2: rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, rows, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr, 1, -1, &cands[i], ks); break;
-                    case 3: rc = run_gemm(ctx, lp.down, EPI_F32, ctx->h, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cands[i], ks); break;
-                    default: rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, rows, nullptr, c.vocab, 0, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cands[i], ks); break;
+                    case 0: rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, rows, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
+                    case 1: rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
+                    case 2: rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, rows, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
+                    case 3: rc = run_gemm(ctx, lp.down, EPI_F32, ctx->h, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
+                    default: rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, rows, nullptr, c.vocab, 0, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
                 }
                 if (rc != SPACE_OK) break;
                 float ms = 0.f;
@@ -1139,10 +1162,13 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
                 if (rep == 1 || (rep > 1 && ms < ms_min)) ms_min = ms;
             }
             if (plain) {  // every partial sum beyond the first is read once more, at about 4 TB/s
-                const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : have[0]->down;
-                const int used = plan_gemm_wide(pw, rows, EPI_F32, ctx->part_splits_max, ks, &cands[i]).ksplit;
+                const int used = cand.ksplit;
                 const int n_out = cls == 0 ? hd + 2 * ctx->hd_kv : d;
                 ms_min += (float)((double)(used - 1) * rows * n_out * 4.0 / 4.0e9);
+            }
+            if (is_tail) {
+                tail_ms = ms_min;
+                continue;
             }
             if (rc == SPACE_OK && kc == 0 && i == 0) default_ms = ms_min;
             if (rc == SPACE_OK && (best < 0 || ms_min < best_ms)) { best = i; best_ks = ks; best_ms = ms_min; }
@@ -1152,10 +1178,10 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)rows;
         ctx->wide_plans.erase(key);
         try {
-            if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms)
+            if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms && !(tail.tail.pieces && tail_ms <= best_ms))
                 ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
             else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
-                ctx->wide_plans[key] = own;  // what the next launch would plan again
+                ctx->wide_plans[key] = tail.tail.pieces && tail_ms < 0.95f * default_ms ? tail : own;  // (the tail's gain is smaller, and so is what it changes)
         } catch (...) {  // no room to remember it: planned again
         }
     }

@@ -43,7 +43,7 @@ constexpr int kWideTiles = 2;   // weight tiles per wave: a workgroup covers 256
 
 template <int W, int R, int KS, int DA, int EPI>
 __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch g, int ksplit, int n_groups, int kt_per_split,
-                                                                       WideParts parts) {
+                                                                       WideParts parts, WideTail tail) {
     constexpr int T = kWideRowTiles, TB = 2, GMAX = T / TB;
     static_assert(R % 2 == 0 && W == 8 && DA == KS && T == 8, "tile counts");
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub: the body is device code throughout (LDS address casts, inline assembly)
@@ -58,10 +58,19 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     const int n_gk = n_groups * ksplit, gk8 = (n_gk + 7) / 8 * 8;
     const int n_pieces = parts.count[0] + parts.count[1] + parts.count[2] + parts.count[3];
     int G = 0, row_tile0 = 0, gi;
+    // place of the piece among those of this XCD; the last tail.pieces of them have tail.parts workgroups each
+    int q = blockIdx.x >> 3, part = -1, tail_piece = 0;
+    const int whole = (gk8 >> 3) * n_pieces - tail.pieces;
+    if (tail.pieces && q >= whole) {
+        part = (q - whole) % tail.parts;
+        tail_piece = (q - whole) / tail.parts;
+        q = whole + tail_piece;
+    }
     if (parts.by_size) {
-        int idx = blockIdx.x, cnt = 1;
+        int idx = q * 8 + (blockIdx.x & 7), cnt = 1;
 #pragma unroll
-        for (int c = 0; c < GMAX; ++c) {
+        for (int i = 0; i < GMAX; ++i) {
+            const int c = parts.by_size == 1 ? i : GMAX - 1 - i;
             if (G == 0) {
                 const int size = gk8 * parts.count[c];
                 if (idx < size) {
@@ -69,16 +78,16 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
                     cnt = parts.count[c];
                 } else {
                     idx -= size;
-                    row_tile0 += parts.count[c] * TB * (GMAX - c);
                 }
             }
         }
         if (G == 0) return;  // whole workgroup, before any barrier
-        const int q = idx >> 3;
-        gi = (q / cnt) * 8 + (idx & 7);
-        row_tile0 += (q % cnt) * TB * G;
+#pragma unroll
+        for (int c = 0; c < GMAX; ++c) row_tile0 += GMAX - c > G ? parts.count[c] * TB * (GMAX - c) : 0;
+        const int qc = idx >> 3;
+        gi = (qc / cnt) * 8 + (idx & 7);
+        row_tile0 += (qc % cnt) * TB * G;
     } else {
-        const int q = blockIdx.x >> 3;
         gi = (q / n_pieces) * 8 + (blockIdx.x & 7);
         int piece = q % n_pieces;
 #pragma unroll
@@ -101,7 +110,12 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     const int t_run = (m_rows + 15) >> 4;
     // Contraction range of this split: a multiple of DA tiles (the host rounds; tiles past k_tiles exist
     // in the packed matrix as zeros, and the activation buffers are finite there).
-    const int k0 = s * kt_per_split, k1 = min(k0 + kt_per_split, (g.w.k_tiles + DA - 1) / DA * DA);
+    int k0 = s * kt_per_split, k1 = min(k0 + kt_per_split, (g.w.k_tiles + DA - 1) / DA * DA);
+    if (part >= 0) {  // (no split beside a tail, and no empty part: the host checks)
+        const int kt_part = ((k1 + tail.parts - 1) / tail.parts + DA - 1) / DA * DA;
+        k0 = part * kt_part;
+        k1 = min(k0 + kt_part, k1);
+    }
 
     // weights: tile (nt, kt) of the packed matrix sits at tile index ck(kt) + cr(nt)
     const int nt0 = (bx * W + wave) * R;
@@ -166,6 +180,7 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     // the argmax epilogue merges the waves through these (one copy, whatever the piece size)
     __shared__ float s_val[EPI == EPI_ARGMAX ? W : 1][EPI == EPI_ARGMAX ? T * 16 : 1];
     __shared__ int s_idx[EPI == EPI_ARGMAX ? W : 1][EPI == EPI_ARGMAX ? T * 16 : 1];
+    __shared__ int s_last;  // this workgroup is the last of its piece to arrive
     // The loop over the contraction for a piece of GC groups of two row tiles: nothing in it is
     // conditional, the LDS reads of a group are issued one group ahead of the MFMAs that use them.  A
     // last row tile that the matrix does not have is computed on copies of existing rows and dropped.
@@ -251,7 +266,44 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
             __builtin_amdgcn_s_barrier();
             buf ^= 1;
         }
-    
+
+        if (part >= 0) {
+            // A part of the contraction: the sums go to memory, and the workgroup of the piece that arrives last adds
+            // up all of them, in part order, and carries on with the epilogue.  Nobody waits for anybody.  The sums are
+            // written through to where all XCDs see them (sc1) and read back past the caches, so the hand-over needs no
+            // write-back or invalidation of an L2 (which cost tens of microseconds each): only that the stores are
+            // complete before the arrival is counted.
+            constexpr int kThrough = 16;  // sc1
+            const int slot = ((blockIdx.x & 7) * tail.pieces + tail_piece) * tail.parts;
+            const __amdgpu_buffer_rsrc_t ts = __builtin_amdgcn_make_buffer_rsrc((void*)g.tail_sums, 0, 0x7fffffff, 0x00020000);
+            auto at = [&](int p, int r, int t) { return (slot + p) * (int)(kWideTailFloats * 4) + ((wave * R + r) * T + t) * 1024; };
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int t = 0; t < TG; ++t)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[r][t]), ts, lane16, at(part, r, t), kThrough);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const int before = __hip_atomic_fetch_add(g.tail_count + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_last = before == tail.parts - 1;
+                if (s_last) __hip_atomic_store(g.tail_count + slot, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+            }
+            __syncthreads();
+            if (!s_last) return;
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int t = 0; t < TG; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int p = 0; p < tail.parts; ++p) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int t = 0; t < TG; ++t)
+                        acc[r][t] += __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ts, lane16, at(p, r, t), kThrough));
+            }
+        }
 
         // ---- epilogue out of registers: lane l holds, of tile (r, t), token 16 t + l%16 and the 4
         // weight rows 16 nt + 4 (l/16) .. + 3
@@ -372,33 +424,44 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
 }
 
 template <int W, int R, int EPI>
-hipError_t launch_wide_r(const GemmLaunch& g, int ksplit, int n_groups, int kt_per_split, const WideParts& parts, hipStream_t s) {
+hipError_t launch_wide_r(const GemmLaunch& g, const WidePlan& p, hipStream_t s) {
     int pieces = 0;
-    for (int c = 0; c < 4; ++c) pieces += parts.count[c];
-    const dim3 grid(8 * ceil_div(n_groups * ksplit, 8) * pieces), block(64 * W);
-    hipLaunchKernelGGL((gemm_wide_kernel<W, R, kWideStage, kWideDepth, EPI>), grid, block, 0, s, g, ksplit, n_groups, kt_per_split, parts);
+    for (int c = 0; c < 4; ++c) pieces += p.parts.count[c];
+    const dim3 grid(8 * (ceil_div(p.n_groups * p.ksplit, 8) * pieces + (p.tail.pieces ? p.tail.pieces * (p.tail.parts - 1) : 0))), block(64 * W);
+    hipLaunchKernelGGL((gemm_wide_kernel<W, R, kWideStage, kWideDepth, EPI>), grid, block, 0, s, g, p.ksplit, p.n_groups, p.kt_per_split,
+                       p.parts, p.tail);
     return hipGetLastError();
 }
 
 }  // namespace
 
-WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit, const WideParts* cut) {
+WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit, const WideParts* cut,
+                        bool may_tail) {
     WidePlan p{};
     p.tiles_per_wave = kWideTiles;
     p.n_groups = ceil_div(w.n_tiles, kWideWaves * kWideTiles);
     const int smax = (epi == EPI_F32) ? (max_splits < 4 ? max_splits : 4) : 1;
-    const WideCut c = plan_wide_cut(p.n_groups, w.n, w.k_tiles, m, smax, epi == EPI_F32 ? force_ksplit : 0, cut);
+    WideCut c = plan_wide_cut(p.n_groups, w.n, w.k_tiles, m, smax, epi == EPI_F32 ? force_ksplit : 0, cut);
+    if (may_tail && !cut && (force_ksplit <= 0 || epi != EPI_F32)) plan_wide_tail(p.n_groups, w.n, w.k_tiles, m, c, &c, &p.tail);
     p.parts = c.parts;
     p.kt_per_split = round_up(ceil_div(w.k_tiles, c.ksplit), kWideDepth);
     p.ksplit = ceil_div(w.k_tiles, p.kt_per_split);  // no empty split
     return p;
 }
 
+bool wide_tail_fits(int k_tiles, const WidePlan& p) {
+    int pieces = 0;
+    for (int c = 0; c < 4; ++c) pieces += p.parts.count[c];
+    const int kt = round_up(k_tiles, kWideDepth), t = p.tail.pieces, n = p.tail.parts;
+    return p.ksplit == 1 && t >= 1 && t <= kWideTailSlots && n >= 2 && n <= kWideTailSlots && t * n <= kWideTailSlots &&
+           t <= ceil_div(p.n_groups, 8) * pieces && (n - 1) * round_up(ceil_div(kt, n), kWideDepth) < kt;
+}
+
 hipError_t launch_gemm_wide(const GemmLaunch& g0, const WidePlan& p, GemmEpilogue epi, hipStream_t s) {
     GemmLaunch g = g0;
     int groups = 0;
     for (int c = 0; c < 4; ++c) {
-        if (p.parts.count[c] < 0 || (p.parts.by_size != 0 && p.parts.by_size != 1)) return hipErrorInvalidValue;
+        if (p.parts.count[c] < 0 || p.parts.by_size < 0 || p.parts.by_size > 2) return hipErrorInvalidValue;
         groups += p.parts.count[c] * (4 - c);
     }
     if (g.m < 1 || groups != ceil_div(ceil_div(g.m, 16), 2) || g.row_tile0 != 0 || g.w.k_tiles < 1 ||
@@ -412,10 +475,11 @@ hipError_t launch_gemm_wide(const GemmLaunch& g0, const WidePlan& p, GemmEpilogu
     if (g.w.bytes() >= ((size_t)1 << 32)) return hipErrorInvalidValue;  // the kernel addresses the matrix with 32-bit byte offsets
     if (epi == EPI_ARGMAX && p.n_groups > g.arg_groups) return hipErrorInvalidValue;
     if (p.tiles_per_wave != kWideTiles) return hipErrorInvalidValue;
+    if (p.tail.pieces && (!g.tail_sums || !g.tail_count || !wide_tail_fits(g.w.k_tiles, p))) return hipErrorInvalidValue;
     switch (epi) {
-        case EPI_F32: return launch_wide_r<kWideWaves, kWideTiles, EPI_F32>(g, p.ksplit, p.n_groups, p.kt_per_split, p.parts, s);
-        case EPI_SWIGLU: return launch_wide_r<kWideWaves, kWideTiles, EPI_SWIGLU>(g, p.ksplit, p.n_groups, p.kt_per_split, p.parts, s);
-        case EPI_ARGMAX: return launch_wide_r<kWideWaves, kWideTiles, EPI_ARGMAX>(g, p.ksplit, p.n_groups, p.kt_per_split, p.parts, s);
+        case EPI_F32: return launch_wide_r<kWideWaves, kWideTiles, EPI_F32>(g, p, s);
+        case EPI_SWIGLU: return launch_wide_r<kWideWaves, kWideTiles, EPI_SWIGLU>(g, p, s);
+        case EPI_ARGMAX: return launch_wide_r<kWideWaves, kWideTiles, EPI_ARGMAX>(g, p, s);
     }
     return hipErrorInvalidValue;
 }

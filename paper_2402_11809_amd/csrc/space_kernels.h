@@ -76,7 +76,12 @@ struct GemmLaunch {
     const float* ss;  // [ss_n][round_up(m, 4)] partial sums of squares
     int ss_n;
     float norm_d, eps;  // factor = 1 / sqrt(sum / norm_d + eps)
+    // Many-row kernel: sums and arrival counts of the pieces that are cut over the contraction (WideTail);
+    // nullptr: none may be.  The counts are zero between launches.
+    float* tail_sums;     // [8 * kWideTailSlots][kWideTailFloats]
+    int32_t* tail_count;  // [8 * kWideTailSlots]
 };
+constexpr size_t kWideTailFloats = 16 * 8 * 256;  // a piece of 16 weight tiles x 8 row tiles
 
 // Projection onto the residual stream for at most kResidMaxRows rows, residual add and the next norm's
 // weights included: x += X W^T, xn = operand planes of x * norm_w, ss[workgroup][row] = sum of squares of the
@@ -119,12 +124,16 @@ struct WidePlan {
     int n_groups;        // workgroups along the rows of W (EPI_ARGMAX: partials per row)
     int ksplit;          // partial sums over the contraction
     int kt_per_split;    // contraction tiles per partial sum
+    WideTail tail;       // (ksplit 1)
 };
 // force_ksplit > 0: that many partial sums over the contraction instead of the cost model's choice
 // (plain-sum epilogue only; rounded down to what leaves every split at least one pipeline round); cut: this
-// cut of the rows instead of the model's, with the partial sums that the model's has
+// cut of the rows instead of the model's, with the partial sums that the model's has; may_tail: pieces may be cut over
+// the contraction where neither is forced (GemmLaunch::tail_sums)
 WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit = 0,
-                        const WideParts* cut = nullptr);
+                        const WideParts* cut = nullptr, bool may_tail = false);
+// A tail's pieces lie in the launch, its slots in the buffers, and every part has contraction tiles.
+bool wide_tail_fits(int k_tiles, const WidePlan& p);
 // g.passes and g.tiles_per_wave are ignored (the plan's pieces are used); g.row_tile0 must be 0.
 hipError_t launch_gemm_wide(const GemmLaunch& g, const WidePlan& p, GemmEpilogue epi, hipStream_t s);
 
@@ -143,7 +152,8 @@ hipError_t launch_rope_table(float* cos_t, float* sin_t, int n_pos, int head_dim
 hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab, int d, const LayoutDev& lay,
                         const int32_t* kv_len, int batch, const float* cos_tab, const float* sin_tab, int n_pos,
                         int head_dim, float* x, int32_t* pos, float* cos_t, float* sin_t, int32_t* faults,
-                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, hipStream_t s);
+                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, hipStream_t s);
+// (counts: cleared; the arrival counts of the launches behind it, so that a forward never depends on how an earlier one ended)
 
 // x += sum_s part[s]; xn = operand planes of x * rsqrt(mean(x^2) + eps) * w
 hipError_t launch_resid_norm(float* x, const float* part, int splits, size_t split_stride, int ldp,

@@ -691,10 +691,12 @@ __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, cons
                                                      const float* __restrict__ sin_tab, int n_pos, int head_dim,
                                                      float* x, int32_t* pos_out, float* cos_t, float* sin_t, int32_t* faults,
                                                      const uint16_t* __restrict__ w, float eps, uint16_t* __restrict__ xn,
-                                                     XtShape xs) {
+                                                     XtShape xs, int32_t* counts, int n_counts) {
     __shared__ float sh[16];
     const int row = xcd_grouped_row(blockIdx.x), nvec = d >> 2, nthr = blockDim.x;
     if (row >= m) return;  // whole workgroup
+    if (row == 0)
+        for (int i = threadIdx.x; i < n_counts; i += nthr) counts[i] = 0;
     u32x2 wv[2];
     norm_w_load(w, d, wv);
     const int b = row / L, r = row % L;
@@ -735,13 +737,13 @@ __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, cons
 hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab, int d, const LayoutDev& lay,
                         const int32_t* kv_len, int batch, const float* cos_tab, const float* sin_tab, int n_pos,
                         int head_dim, float* x, int32_t* pos, float* cos_t, float* sin_t, int32_t* faults,
-                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, hipStream_t s) {
+                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, hipStream_t s) {
     if (d > 8192 || (d & 3) || n_pos < 1) return hipErrorInvalidValue;
     const int nvec = d >> 2;
     const int threads = nvec >= 1024 ? 1024 : round_up(nvec, 64);
     hipLaunchKernelGGL(embed_kernel, dim3(round_up(batch * lay.L, 64)), dim3(threads), 0, s, tokens, embed, vocab, d, lay.info,
                        lay.rel_pos, lay.L, batch * lay.L, kv_len, cos_tab, sin_tab, n_pos, head_dim, x, pos, cos_t, sin_t, faults,
-                       norm_w, eps, xn, xs);
+                       norm_w, eps, xn, xs, counts, counts ? n_counts : 0);
     return hipGetLastError();
 }
 

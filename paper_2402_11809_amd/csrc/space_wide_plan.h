@@ -15,7 +15,7 @@ constexpr int kWideSearchGroups = 32;  // longest blocks (in groups of 32 rows) 
 // 2 row tiles), laid end to end in this order; the groups add up to ceil(ceil(m / 16) / 2).
 struct WideParts {
     int count[4];
-    int by_size;  // launch order: 0 = weight group by weight group, 1 = all pieces of a size before any smaller one
+    int by_size;  // launch order: 0 = weight group by weight group, 1 = all pieces of a size before any smaller one, 2 = before any larger one (with a tail)
 };
 
 // What a launch costs: the work of its busiest CU, in units of 17.4 us / 1280.  A CU gets through one piece after
@@ -27,35 +27,28 @@ struct WideParts {
 constexpr double kWideUnitUs = 17.4 / 1280;
 inline int64_t wide_piece_cost(int g, int kt) { return (int64_t)kt * (10 * g + (g == 1 ? 8 : 6)) + 512; }
 
-// The cost, or any value >= bar once it is known not to lie below bar.  This runs in front of the first launch at
+// The load of the busiest CU once `runs` runs of equal pieces (cost_of(run) each, count_of(run) of them) are placed, or
+// any value >= bar once it is known not to lie below bar.  This runs in front of the first launch at
 // a row count, with the GPU idle, so the workgroups are not placed one by one: the CUs are kept as levels of equal
 // load, lowest first, and a run of equal pieces fills a level at a time.
-inline int64_t wide_cost(const WideParts& parts, int gk8, int kt, int64_t bar = INT64_MAX) {
-    constexpr int kCus = 32;
-    int64_t piece[4], total = 0;
-    for (int c = 0, pieces = 0; c < 4; ++c) {
-        piece[c] = wide_piece_cost(4 - c, kt);
-        total += piece[c] * parts.count[c] * gk8;
-        pieces += parts.count[c] * gk8;
-        if (ceil_div(pieces, kCus) * piece[c] >= bar) return bar;  // some CU has that many of at least this size
-    }
-    if (total / kCus >= bar) return bar;
-    const int n_runs = parts.by_size ? 4 : 4 * gk8, per_run = parts.by_size ? gk8 : 1;
-    int run = 0, left = parts.count[0] * per_run;
+constexpr int kWideCus = 32;  // per XCD
+template <class Cost, class Count>
+inline int64_t wide_place(int runs, Cost cost_of, Count count_of, int64_t bar) {
+    int run = 0, left = count_of(0);
     auto skip_empty = [&]() {  // to the next run with pieces left; false: none
         while (left == 0) {
-            if (++run >= n_runs) return false;
-            left = parts.count[run & 3] * per_run;
+            if (++run >= runs) return false;
+            left = count_of(run);
         }
         return true;
     };
     // the first two rounds
-    int64_t first[kCus] = {0};
-    for (int i = 0; i < 2 * kCus && skip_empty(); ++i, --left) first[i % kCus] += piece[run & 3];
+    int64_t first[kWideCus] = {0};
+    for (int i = 0; i < 2 * kWideCus && skip_empty(); ++i, --left) first[i % kWideCus] += cost_of(run);
     struct Level {
         int64_t load;
         int cus;
-    } level[kCus + 1];
+    } level[kWideCus + 1];
     int n = 0;  // levels, level[n - 1] the lowest
     auto insert = [&](int64_t load, int cus) {
         int at = n;
@@ -68,18 +61,33 @@ inline int64_t wide_cost(const WideParts& parts, int gk8, int kt, int64_t bar = 
         level[at] = Level{load, cus};
         ++n;
     };
-    for (int i = kCus - 1; i >= 0; --i) insert(first[i], 1);  // loads mostly fall with i
+    for (int i = kWideCus - 1; i >= 0; --i) insert(first[i], 1);  // loads mostly fall with i
     // the rest, where a place is free
     while (level[0].load < bar && skip_empty()) {
         Level& low = level[n - 1];
         const int take = left < low.cus ? left : low.cus;
-        const int64_t load = low.load + piece[run & 3];
+        const int64_t load = low.load + cost_of(run);
         left -= take;
         low.cus -= take;
         if (low.cus == 0) --n;
         insert(load, take);
     }
     return level[0].load;
+}
+
+// The cost, or any value >= bar once it is known not to lie below bar.
+inline int64_t wide_cost(const WideParts& parts, int gk8, int kt, int64_t bar = INT64_MAX) {
+    int64_t piece[4], total = 0;
+    for (int c = 0, pieces = 0; c < 4; ++c) {
+        piece[c] = wide_piece_cost(4 - c, kt);
+        total += piece[c] * parts.count[c] * gk8;
+        pieces += parts.count[c] * gk8;
+        if (ceil_div(pieces, kWideCus) * piece[c] >= bar) return bar;  // some CU has that many of at least this size
+    }
+    if (total / kWideCus >= bar) return bar;
+    const int per_run = parts.by_size ? gk8 : 1;
+    return wide_place(parts.by_size ? 4 : 4 * gk8, [&](int run) { return piece[run & 3]; },
+                      [&](int run) { return parts.count[run & 3] * per_run; }, bar);
 }
 
 struct WideCut {
@@ -141,6 +149,81 @@ inline WideCut plan_wide_cut(int n_groups, int n, int k_tiles, int m, int smax, 
     if (force_ksplit > 0) p.ksplit = force_ksplit < smax ? force_ksplit : smax;
     if (cut) p.parts = *cut;
     return p;
+}
+
+// The last `pieces` pieces of every XCD, in launch order, are cut over the contraction: `parts` workgroups each, whose sums
+// the one that ends last adds up in part order (same bits whichever that is) before the epilogue.  0: none.
+constexpr int kWideTailSlots = 32;  // most workgroups per XCD with a part of a piece (partial sums of 128 KB each)
+struct WideTail {
+    int pieces, parts;
+};
+
+// A part costs its share of the piece and 3 us to write the sums and count itself; the one that ends last another
+// 2 us, and 2 us to read each part's sums: a wave has room for one part's in flight.  (Measured at 7B: 256 rows, O and down, all
+// pieces in 8 parts 19 -> 35 and 42 -> 54 us; QKV at 208 rows, 12 of 18 pieces in 2 parts 49 -> 50; but gate / up, one piece
+// of 33 in 4 to 16 parts, 288 rows 89 -> 82 and 333 rows 107 -> 94: there all of it lies beside whole pieces.)
+inline int64_t wide_part_cost(int g, int kt, int parts, bool last) {
+    return wide_piece_cost(g, round_up(ceil_div(kt, parts), kWideDepth)) + 220 + (last ? 147 + 147 * parts : 0);
+}
+
+// Whether a tail is 10 % ahead of the cut `c` in this model (complete sums only), and which.  Rounds of workgroups that
+// are nearly empty are what it removes: gate / up at 333 rows and 7B width is 11 weight groups per XCD in pieces of 128, 128
+// and 96 rows, one piece more than an XCD has CUs, and either two pieces share a CU or smaller ones stream the
+// weights more often.  Two tails are tried with every cut: what exceeds whole rounds of workgroups, and all pieces of
+// the last size.  Measured, without / with: 7B gate / up at 208 and 224 rows 84 / 74 us, 333 and 352 rows 113 / 99, QKV at
+// 704 rows 118 / 113; 13B gate / up at 288 and 333 rows 133 / 122 and 159 / 148; 70B gate / up at 512 and 896 rows 688 /
+// 635 and 1203 / 1117.  5 to 10 % ahead in the model is within what cards differ by: 7B QKV at 648 and 1024 rows 102.4 / 101.7 and
+// 161 / 157 on one, 108.9 / 113.0 and level on another that holds a lower clock.
+inline bool plan_wide_tail(int n_groups, int n, int k_tiles, int m, const WideCut& c, WideCut* cut, WideTail* tail) {
+    const int groups = ceil_div(ceil_div(m, 16), 2), gk8 = ceil_div(n_groups, 8);
+    if (groups > kWideSearchGroups || k_tiles < 64) return false;  // (short contractions: a workgroup's fixed cost outweighs it)
+    const int kt_c = round_up(ceil_div(k_tiles, c.ksplit), kWideDepth), kt = round_up(k_tiles, kWideDepth);
+    const int64_t now = wide_cost(c.parts, ceil_div(n_groups * c.ksplit, 8), kt_c) +
+                        (int64_t)((c.ksplit - 1) * (double)m * n * 4.0 / (4.5e6 * kWideUnitUs));
+    int64_t bar = now * 90 / 100;
+    bool found = false;
+    int64_t piece[4];
+    for (int q = 0; q < 4; ++q) piece[q] = wide_piece_cost(4 - q, kt);
+    for (int a = groups / 4; a >= 0; --a)
+        for (int b = (groups - 4 * a) / 3; b >= 0; --b) {
+            const int rest = groups - 4 * a - 3 * b;
+            const WideParts w{{a, b, rest / 2, rest % 2}, 1};
+            int64_t total = 0;
+            int all = 0, big = -1, small = 0;  // largest and smallest size there is
+            for (int q = 0; q < 4; ++q) {
+                total += piece[q] * w.count[q] * gk8;
+                all += w.count[q] * gk8;
+                if (w.count[q]) {
+                    if (big < 0) big = q;
+                    small = q;
+                }
+            }
+            if (total / kWideCus >= bar) continue;
+            for (int order = 1; order <= 2; ++order) {
+                if (order == 2 && big == small) break;
+                const int last = order == 1 ? small : big;
+                const int sizes[2] = {all % kWideCus, w.count[last] * gk8};
+                for (int which = 0; which < 2; ++which) {
+                    const int t = sizes[which];
+                    if (t < 1 || t > w.count[last] * gk8 || 2 * t > kWideTailSlots || (which && t == sizes[0])) continue;
+                    for (int parts = 2; parts <= 8 && parts * t <= kWideTailSlots && kt / parts >= 16; parts += parts < 4 ? 1 : 2) {
+                        if ((parts - 1) * round_up(ceil_div(kt, parts), kWideDepth) >= kt) continue;  // an empty part
+                        const int64_t part = wide_part_cost(4 - last, kt, parts, false), end = wide_part_cost(4 - last, kt, parts, true);
+                        if ((total + t * ((parts - 1) * part + end - piece[last])) / kWideCus >= bar) continue;
+                        auto size_of = [&](int run) { return order == 1 ? run : 3 - run; };
+                        const int64_t cost = wide_place(6, [&](int run) { return run == 5 ? end : run == 4 ? part : piece[size_of(run)]; },
+                                                        [&](int run) { return run == 5 ? t : run == 4 ? t * (parts - 1) : w.count[size_of(run)] * gk8 - (size_of(run) == last ? t : 0); }, bar);
+                        if (cost < bar) {
+                            bar = cost;
+                            found = true;
+                            *cut = WideCut{{{w.count[0], w.count[1], w.count[2], w.count[3]}, order}, 1};
+                            *tail = WideTail{t, parts};
+                        }
+                    }
+                }
+            }
+        }
+    return found;
 }
 
 }  // namespace space

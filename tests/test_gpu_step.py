@@ -337,6 +337,28 @@ def test_many_row_projection_kernel_on_small_blocks(torch_mod, shape_name, B, k,
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=2), B, k, tune, gc.LOGIT_TIGHT)
 
 
+@pytest.mark.parametrize("shape_name,B,k,tail", [("small128", 1, 5, "1:2"), ("small128", 6, 5, "3:5"), ("gqa128", 2, 8, "2:8"), ("gqa128", 8, 5, "1:16"),
+                                                 ("gqa128", 5, 5, "8:2"), ("gqa-small", 5, 4, "32:1"), ("gqa-small", 5, 4, "5:3")])
+def test_pieces_cut_over_the_contraction(torch_mod, shape_name, B, k, tail):
+    """The last pieces of every XCD in several parts over the contraction, forced (SPACE_TUNE widetail=pieces:parts)
+    wherever a projection has that many pieces and contraction tiles: one part more than there are pipeline rounds to share, single
+    rounds, pieces of every size, all epilogues; "32:1" is malformed and ignored.  Against the oracle, and two steps
+    in a row on the same context give the same bits (the arrival counts are back at zero, the order of the sums does not
+    depend on who arrives last)."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name]
+    w = all_weights(shape, seed=11)
+    tune = "wide=1,widetail=" + tail
+    _batched_step_vs_oracle(torch, shape, w, B, k, tune, gc.LOGIT_TIGHT)
+    spec = lo.paper_layout(k)
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=spec.n_rows, tune=tune)
+    toks = np.random.default_rng(15).integers(0, shape.vocab, size=(B, spec.n_rows)).astype(np.int32)
+    cache = gm.kv_cache(B, 160)
+    got = [_run_step(torch, gm, cache, spec, toks, batch=B).logits.cpu().numpy().copy() for _ in range(3)]
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("shape_name,B,k", [("small128", 3, 5), ("small128", 6, 5), ("gqa128", 2, 8), ("small128", 8, 5)])
 def test_library_switches_between_the_projection_kernels_by_itself(torch_mod, shape_name, B, k):
     """Row counts on both sides of the library's own switch points, nothing forced: 108 and 162 rows (only

@@ -98,3 +98,79 @@ def test_planner_costs_and_the_time_a_plan_takes(tmp_path):
     assert int(compared) > 5000 and int(wrong) == 0
     assert int(plans) > 4000 and int(uncovered) == 0 and int(too_close) == 0 and int(moved) == 0
     assert float(worst) < 200, worst
+
+
+_TAIL_PROGRAM = r"""
+#include <algorithm>
+#include <chrono>
+#include <cstdio>
+#include <vector>
+#include "space_wide_plan.h"
+using namespace space;
+
+int main() {
+    const int shapes[][3] = {{768, 256, 1}, {1376, 1024, 0}, {2000, 1024, 0}, {12288, 4096, 1}, {4096, 4096, 1}, {22016, 4096, 0},
+                             {4096, 11008, 1}, {32000, 4096, 0}, {15360, 5120, 1}, {27648, 5120, 0}, {5120, 13824, 1},
+                             {10240, 8192, 1}, {57344, 8192, 0}, {8192, 28672, 1}, {32000, 8192, 0}};
+    long plans = 0, tails = 0, bad = 0, behind = 0;
+    double worst = 0;
+    for (const auto& s : shapes) {
+        const int n_groups = ceil_div(s[0], 256), k_tiles = ceil_div(s[1], 32), gk8 = ceil_div(n_groups, 8), kt = round_up(k_tiles, kWideDepth);
+        for (int m = 97; m <= 1090; m += 3) {
+            const WideCut c = plan_wide_cut(n_groups, s[0], k_tiles, m, s[2] ? 4 : 1, 0, nullptr);
+            WideCut cut{};
+            WideTail t{0, 0};
+            double us = 1e9;
+            bool found = false;
+            for (int rep = 0; rep < 3; ++rep) {
+                const auto t0 = std::chrono::steady_clock::now();
+                found = plan_wide_tail(n_groups, s[0], k_tiles, m, c, &cut, &t);
+                us = std::min(us, std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e6);
+            }
+            worst = std::max(worst, us);
+            ++plans;
+            if (!found) continue;
+            ++tails;
+            const int groups = ceil_div(ceil_div(m, 16), 2);
+            const int* n = cut.parts.count;
+            int step = round_up(ceil_div(kt, t.parts), kWideDepth);
+            bad += 4 * n[0] + 3 * n[1] + 2 * n[2] + n[3] != groups || cut.ksplit != 1 || t.pieces < 1 || t.parts < 2 ||
+                   t.pieces * t.parts > kWideTailSlots || t.pieces > gk8 * (n[0] + n[1] + n[2] + n[3]) || (t.parts - 1) * step >= kt;
+            // every workgroup placed by itself: pieces in launch order, the last t.pieces as parts
+            std::vector<int> size;
+            for (int q = 0; q < 4; ++q) {
+                const int sz = cut.parts.by_size == 1 ? q : 3 - q;
+                size.insert(size.end(), gk8 * n[sz], 4 - sz);
+            }
+            std::vector<int64_t> wg;
+            const int whole = (int)size.size() - t.pieces;
+            bad += size[whole] != size.back();
+            for (int i = 0; i < whole; ++i) wg.push_back(wide_piece_cost(size[i], kt));
+            for (int i = 0; i < t.pieces * t.parts; ++i) wg.push_back(wide_part_cost(size.back(), kt, t.parts, i >= t.pieces * (t.parts - 1)));
+            int64_t load[32] = {0};
+            for (size_t i = 0; i < wg.size(); ++i) load[i < 64 ? i % 32 : std::min_element(load, load + 32) - load] += wg[i];
+            const int64_t now = wide_cost(c.parts, ceil_div(n_groups * c.ksplit, 8), round_up(ceil_div(k_tiles, c.ksplit), kWideDepth)) +
+                                (int64_t)((c.ksplit - 1) * (double)m * s[0] * 4.0 / (4.5e6 * kWideUnitUs));
+            behind += *std::max_element(load, load + 32) * 100 >= now * 90;
+        }
+    }
+    printf("%ld %ld %ld %ld %.1f\n", plans, tails, bad, behind, worst);
+    return 0;
+}
+"""
+
+
+def test_tails_fit_and_are_ahead(tmp_path):
+    """A planned tail covers the rows, has as many pieces as the launch and work for every part, is taken from pieces of
+    one size, and the placement of every workgroup by itself puts it 10 % ahead of the plan without it; it is planned in
+    front of the first launch at a row count, so in well under 0.2 ms."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++")
+    src, exe = tmp_path / "tail.cpp", tmp_path / "tail"
+    src.write_text(_TAIL_PROGRAM)
+    subprocess.run([gxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2402_11809_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    plans, tails, bad, behind, worst = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
+    assert int(plans) > 4000 and int(tails) > 100 and int(bad) == 0 and int(behind) == 0
+    assert float(worst) < 200, worst

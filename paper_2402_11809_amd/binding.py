@@ -144,8 +144,9 @@ def _ptr(t) -> Optional[int]:
 
 def _stream(stream=None) -> Optional[int]:
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream) or None
+    if stream is None:  # (without the Stream object around it: 3 us a call)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    return int(stream.cuda_stream) or None
 
 
 class Layout:
@@ -374,17 +375,28 @@ class Model:
                       next_layout: Optional[Layout] = None, stream=None, static: bool = False) -> None:
         """space_sample_verify (static=True: space_sample_verify_static, same arguments): logits float32 [batch, L, vocab], tokens int32 [batch, L], p_c float32
         [batch, max_cands], uniforms float32 [batch, G + max_cands], all CUDA and contiguous."""
+        # A call is two launches of 8 and 4 us, so what stands in front of them counts: the struct is filled without a
+        # call per pointer, and a field that is not given costs a comparison.
         import torch
-        batch = tokens.shape[0]
-        for t, dt in ((logits, torch.float32), (tokens, torch.int32), (p_c, torch.float32), (uniforms, torch.float32)):
-            assert t.is_cuda and t.dtype == dt and t.is_contiguous()
+        f32, batch = torch.float32, tokens.shape[0]
+        assert logits.is_cuda and logits.dtype is f32 and logits.is_contiguous()
+        assert tokens.is_cuda and tokens.dtype is torch.int32 and tokens.is_contiguous()
+        assert p_c.is_cuda and p_c.dtype is f32 and p_c.is_contiguous()
+        assert uniforms.is_cuda and uniforms.dtype is f32 and uniforms.is_contiguous()
         assert p_c.shape == (batch, out.max_cands) and uniforms.shape == (batch, layout.spec.n_groups + out.max_cands)
         assert logits.shape == (batch, layout.n_rows, self.cfg.vocab)
         params = SpaceSampleParams(int(top_k), float(top_p), int(bool(residual)))
-        io = SpaceSampleIO(_ptr(logits), _ptr(tokens), _ptr(p_c), _ptr(uniforms), _ptr(draft_ids), _ptr(draft_probs),
-                           _ptr(out.accepted_len), _ptr(out.extra), _ptr(out.new_cands), _ptr(out.new_pc),
-                           out.max_cands, _ptr(out.new_ids), _ptr(out.new_probs), _ptr(out.next_tokens), _ptr(out.emit),
-                           _ptr(out.emit_len), out.emit_cap, _ptr(out.ratios), out.eos_id, _ptr(out.finished))
+        ids, probs, nxt, emit, emit_len, fin, ratios = (out.new_ids, out.new_probs, out.next_tokens, out.emit, out.emit_len,
+                                                        out.finished, out.ratios)
+        io = SpaceSampleIO(logits.data_ptr(), tokens.data_ptr(), p_c.data_ptr(), uniforms.data_ptr(),
+                           None if draft_ids is None else draft_ids.data_ptr(),
+                           None if draft_probs is None else draft_probs.data_ptr(),
+                           _ptr(out.accepted_len), _ptr(out.extra), _ptr(out.new_cands), _ptr(out.new_pc), out.max_cands,
+                           None if ids is None else ids.data_ptr(), None if probs is None else probs.data_ptr(),
+                           None if nxt is None else nxt.data_ptr(), None if emit is None else emit.data_ptr(),
+                           None if emit_len is None else emit_len.data_ptr(), out.emit_cap,
+                           None if ratios is None else ratios.data_ptr(), out.eos_id,
+                           None if fin is None else fin.data_ptr())
         fn = self.lib.space_sample_verify_static if static else self.lib.space_sample_verify
         rc = fn(self.ctx, batch, layout.handle, next_layout.handle if next_layout is not None else None,
                 C.byref(params), C.byref(io), _stream(stream))

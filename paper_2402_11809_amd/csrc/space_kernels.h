@@ -155,6 +155,11 @@ hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab,
                         const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, hipStream_t s);
 // (counts: cleared; the arrival counts of the launches behind it, so that a forward never depends on how an earlier one ended)
 
+// x += sum_s part[s]; xn = operand planes of x * w, ss[group][row] = sums of squares (as ResidLaunch leaves them); at most
+// kResidMaxRows rows
+int resid_part_groups(int d);
+hipError_t launch_resid_part(float* x, const float* part, int splits, size_t split_stride, int ldp, const uint16_t* w, int m, int d,
+                             uint16_t* xn, XtShape xs, float* ss, hipStream_t s);
 // x += sum_s part[s]; xn = operand planes of x * rsqrt(mean(x^2) + eps) * w
 hipError_t launch_resid_norm(float* x, const float* part, int splits, size_t split_stride, int ldp,
                              const uint16_t* w, float eps, int m, int d, uint16_t* xn, XtShape xs, hipStream_t s);

@@ -115,7 +115,9 @@ __device__ __forceinline__ u32x4 load_weight_tile(const u32x4* p) {
     return *p;
 }
 
-template <int T, int R, int EPI, int D, bool SCALED = false>
+// SCALED: the rows' norm factors are still due, made of at most kSsFew partial sums of squares (2) or more (1).
+constexpr int kSsFew = 16;
+template <int T, int R, int EPI, int D, int SCALED = 0>
 __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int bx = blockIdx.x, s = blockIdx.y, pass = 0;
@@ -167,15 +169,26 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
         for (int t = 0; t < T; ++t) acc[r][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Norm factors of the rows, if they are still due: the partial sums of squares are requested in front of
-    // everything else and added up while the first weights are on their way.
-    constexpr int kSsLoads = SCALED ? (kResidMaxGroups + 20) / 21 : 1;  // 21 .. 32 groups of threads for at most 12 row quads
-    __shared__ float s_ss[SCALED ? 256 * 4 : 1], s_rs[SCALED ? 16 * T : 1];
-    const int ss_q = SCALED ? (g.m + 3) >> 2 : 1, ss_c = threadIdx.x % ss_q, ss_g = threadIdx.x / ss_q, ss_groups = min(256 / ss_q, 32);
+    // everything else.  Many are added up while the first weights are on their way (behind the loop, with one
+    // more barrier there, a 7B step of 4 rows takes 221.7 us, not 218.8); few need neither LDS nor a barrier, a lane adds up
+    // its row's behind the loop (two layers 256 wide, 25 rows: 57.1 -> 55.0 us a step, 59.1 with loads for 256 sums).
+    constexpr int kSsLoads = SCALED == 1 ? (kResidMaxGroups + 20) / 21 : 1;  // 21 .. 32 groups of threads for at most 12 row quads
+    __shared__ float s_ss[SCALED == 1 ? 256 * 4 : 1], s_rs[SCALED ? 16 * T : 1];
+    float ss_few[SCALED == 2 ? kSsFew : 1];
+    if (SCALED == 2) {
+#pragma unroll
+        for (int i = 0; i < kSsFew; ++i)
+            if (i < kSsFew / 2 || g.ss_n > kSsFew / 2)  // (the same in all threads)
+                ss_few[i] = g.ss[(size_t)min(i, g.ss_n - 1) * ((g.m + 3) & ~3) + min((int)threadIdx.x, g.m - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const int ss_q = SCALED == 1 ? (g.m + 3) >> 2 : 1, ss_c = threadIdx.x % ss_q, ss_g = threadIdx.x / ss_q, ss_groups = min(256 / ss_q, 32);
     f32x4 ss_p[kSsLoads];
-    if (SCALED) {
+    if (SCALED == 1) {
 #pragma unroll
         for (int i = 0; i < kSsLoads; ++i)
-            ss_p[i] = ((const f32x4*)g.ss)[(size_t)min(ss_g + i * ss_groups, g.ss_n - 1) * ss_q + ss_c];
+            if (i == 0 || i * ss_groups < g.ss_n)  // (the same in all threads)
+                ss_p[i] = ((const f32x4*)g.ss)[(size_t)min(ss_g + i * ss_groups, g.ss_n - 1) * ss_q + ss_c];
         __builtin_amdgcn_sched_barrier(0);
     }
 
@@ -192,7 +205,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
 #pragma unroll
             for (int t = 0; t < 2 * T; ++t) b[d][t] = xp[kt * xkt + boff[t]];
         }
-        if (SCALED) {
+        if (SCALED == 1) {
             __builtin_amdgcn_sched_barrier(0);
             f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -243,6 +256,13 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
                     }
             }
         }
+    }
+
+    if (SCALED == 2 && (int)threadIdx.x < g.m) {  // read behind the reduction's barrier below
+        float tot = 0.f;
+#pragma unroll
+        for (int i = 0; i < kSsFew; ++i) tot += i < g.ss_n ? ss_few[i] : 0.f;
+        s_rs[threadIdx.x] = 1.0f / sqrtf(tot / g.norm_d + g.eps);
     }
 
     // Cross-wave reduction through LDS in a fixed order (wave 0 + 1 + 2 + 3): all R * T tiles at once
@@ -362,11 +382,20 @@ int gemm_groups(const PackedW& w, int tiles_per_wave) { return w.groups * w.r_pa
 template <int EPI, int R, int D>
 static hipError_t launch_gemm_small(const GemmLaunch& g, hipStream_t s) {  // at most 3 row tiles
     const dim3 grid(gemm_groups(g.w, R), g.w.splits), block(256);
+    if (g.ss && g.ss_n <= kSsFew) {
+        switch (ceil_div(g.m, 16)) {
+            case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D, 2>), grid, block, 0, s, g); break;
+            case 2: hipLaunchKernelGGL((gemm_skinny_kernel<2, R, EPI, D, 2>), grid, block, 0, s, g); break;
+            case 3: hipLaunchKernelGGL((gemm_skinny_kernel<3, R, EPI, D, 2>), grid, block, 0, s, g); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     if (g.ss) {
         switch (ceil_div(g.m, 16)) {
-            case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D, true>), grid, block, 0, s, g); break;
-            case 2: hipLaunchKernelGGL((gemm_skinny_kernel<2, R, EPI, D, true>), grid, block, 0, s, g); break;
-            case 3: hipLaunchKernelGGL((gemm_skinny_kernel<3, R, EPI, D, true>), grid, block, 0, s, g); break;
+            case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D, 1>), grid, block, 0, s, g); break;
+            case 2: hipLaunchKernelGGL((gemm_skinny_kernel<2, R, EPI, D, 1>), grid, block, 0, s, g); break;
+            case 3: hipLaunchKernelGGL((gemm_skinny_kernel<3, R, EPI, D, 1>), grid, block, 0, s, g); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -793,6 +822,63 @@ hipError_t launch_resid_norm(float* x, const float* part, int splits, size_t spl
     const int threads = nvec >= 1024 ? 1024 : round_up(nvec, 64);
     hipLaunchKernelGGL(resid_norm_kernel, dim3(round_up(m, 64)), dim3(threads), 0, s, x, part, splits, split_stride, ldp, w, eps,
                        m, d, xn, xs);
+    return hipGetLastError();
+}
+
+// The same for up to kResidMaxRows rows, without the row's factor (as gemm_resid_kernel leaves it): nothing has to wait
+// for the whole row, so a row is shared by workgroups of 1024 columns.  What bounds it is how fast one CU gets the row's
+// partial sums, 5 to 9 times 16 KB at 4096 columns.  Step of two 7B layers, 36 rows 277.8 -> 274.8 us (the launch 5.4 -> 4.4,
+// 0.3 more in the projections behind), 16 rows 238.7 -> 235.8, all 32 layers 3653 -> 3579; one 70B layer 419.6 ->
+// 416.1.
+constexpr int kScaleThreads = 256;
+__global__ __launch_bounds__(kScaleThreads) void resid_part_kernel(float* __restrict__ x, const float* __restrict__ part, int splits,
+                                                                   size_t split_stride, int ldp, const uint16_t* __restrict__ w, int m,
+                                                                   int d, uint16_t* __restrict__ xn, XtShape xs, float* __restrict__ ss) {
+    __shared__ float sh[kScaleThreads / 64];
+    const int rows64 = (m + 63) & ~63, row = xcd_grouped_row(blockIdx.x % rows64), col = blockIdx.x / rows64;
+    if (row >= m) return;  // whole workgroup
+    const int n = 4 * (col * kScaleThreads + threadIdx.x);
+    float sq = 0.f;
+    if (n < d) {
+        f32x4* xr = (f32x4*)(x + (size_t)row * d + n);
+        const u32x2 wv = *(const u32x2*)(w + n);
+        f32x4 v = *xr;
+        f32x4 p[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            p[s] = s < splits ? *(const f32x4*)(part + (size_t)s * split_stride + (size_t)row * ldp + n) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v += p[s];
+        *xr = v;
+        const float wf[4] = {bf2f((uint16_t)(wv[0] & 0xFFFF)), bf2f((uint16_t)(wv[0] >> 16)), bf2f((uint16_t)(wv[1] & 0xFFFF)),
+                             bf2f((uint16_t)(wv[1] >> 16))};
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float y = v[e] * wf[e];
+            const uint16_t h = f2bf(y);
+            hi[e] = h;
+            lo[e] = f2bf(y - bf2f(h));
+        }
+        *(u32x2*)(xn + xt_index(row, n, xs, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+        *(u32x2*)(xn + xt_index(row, n, xs, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+        sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) ss[(size_t)col * ((m + 3) & ~3) + row] = sh[0] + sh[1] + sh[2] + sh[3];
+}
+
+int resid_part_groups(int d) { return ceil_div(d, 4 * kScaleThreads); }
+
+hipError_t launch_resid_part(float* x, const float* part, int splits, size_t split_stride, int ldp, const uint16_t* w, int m, int d,
+                             uint16_t* xn, XtShape xs, float* ss, hipStream_t s) {
+    if (m < 1 || m > kResidMaxRows || (d & 3) || (ldp & 3) || splits < 1 || splits > 8 || resid_part_groups(d) > kResidMaxGroups)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(resid_part_kernel, dim3(round_up(m, 64) * resid_part_groups(d)), dim3(kScaleThreads), 0, s, x, part, splits,
+                       split_stride, ldp, w, m, d, xn, xs, ss);
     return hipGetLastError();
 }
 

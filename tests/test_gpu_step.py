@@ -826,6 +826,17 @@ def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
         assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("d,B,k", [(2080, 1, 1), (2080, 3, 3), (3104, 1, 5), (4096, 2, 3), (4128, 1, 4), (8192, 1, 5)])
+def test_norm_of_a_row_shared_by_workgroups(torch_mod, d, B, k):
+    """Up to 48 rows of models wider than 2048: residual add and norm in workgroups of 1024 columns, the row's factor
+    made of their 3 to 8 sums of squares by the projections behind.  Widths with a last workgroup of 32 to 1024 columns; 4, 16,
+    25, 32, 36 and 48 rows (all row tiles, ragged last ones); the form with the norm inside the projection is off.  Against the
+    oracle."""
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["tiny"], name="shared-rows", n_layers=2, d_model=d, n_heads=2, ffn=112, vocab=300)
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=12), B, k, "resid=0", gc.LOGIT_TOL)
+
+
 @pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane
 @pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 96])
 def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, vocab):

@@ -113,7 +113,7 @@ struct space_ctx {
     int wide_tail = 1;
     WideTail wide_tail_force{};
     float* tail_sums = nullptr;  // their sums and arrival counts (GemmLaunch)
-    int32_t* tail_count = nullptr;
+    int32_t* tail_count = nullptr;  // (within counts)
     std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
     // wide_cut_groups groups of two row tiles (0: none)
@@ -134,6 +134,10 @@ struct space_ctx {
     float* part = nullptr;
     uint16_t *q = nullptr, *kblk = nullptr, *vblk = nullptr, *attn_out = nullptr, *h = nullptr;
     float *o_part = nullptr, *ml_part = nullptr;
+    size_t o_part_rows = 0;  // rows of head_dim in o_part
+    int32_t* counts = nullptr;  // arrival counts: of the attention's parts, then tail_count; cleared at the head of every forward
+    int n_counts = 0;
+    KeyPart* key_plan = nullptr;
     int attn_wg_max = 1;
     float* arg_val = nullptr;
     int32_t* arg_idx = nullptr;
@@ -355,7 +359,6 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     }
     if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv)) {
         max_splits = std::max(max_splits, 4);
-        if ((rc = dev_alloc(ctx, &ctx->tail_count, (size_t)8 * kWideTailSlots, true))) return rc;
         if (dev_alloc(ctx, &ctx->tail_sums, 8 * kWideTailSlots * kWideTailFloats, false)) ctx->err.clear();  // 32 MB; no tails without
     }
     ctx->part_splits_max = max_splits;
@@ -383,6 +386,12 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     }
     if ((rc = dev_alloc(ctx, &ctx->o_part, bh * wg_rows * c.head_dim, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->ml_part, bh * wg_rows * 2, true))) return rc;
+    ctx->o_part_rows = bh * wg_rows;
+    const size_t n_attn = bh * ceil_div(c.max_rows, 16);  // (sequence, head, query group) triples
+    ctx->n_counts = (int)n_attn + 8 * kWideTailSlots;
+    if ((rc = dev_alloc(ctx, &ctx->counts, (size_t)ctx->n_counts, true))) return rc;
+    ctx->tail_count = ctx->counts + n_attn;
+    if ((rc = dev_alloc(ctx, &ctx->key_plan, (size_t)kMaxKeySlots, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->arg_val, M * ctx->arg_groups, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->arg_idx, M * ctx->arg_groups, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->cos_t, M * (c.head_dim / 2), true))) return rc;
@@ -707,12 +716,6 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const int Lp = round_up(L, kAttnKeys);
 
     const XtShape xs = xt_shape(M);
-    {
-        TimedScope ts(ctx, SPACE_K_EMBED, s);
-        HIP_TRY(ctx, launch_embed(tokens, ctx->embed, c.vocab, d, lay, kv->len, B, ctx->cos_tab, ctx->sin_tab, ctx->n_pos, dh,
-                                  ctx->x, ctx->pos, ctx->cos_t, ctx->sin_t, ctx->faults, ctx->layers[0].attn_norm, c.rms_eps,
-                                  ctx->xn, xs, ctx->tail_count, 8 * kWideTailSlots, s));
-    }
     // the real lengths live on the device; the grid covers the host-side upper bound
     const int attn_chunks = ceil_div(kv->host_len_bound, kAttnKeys) + ceil_div(L, kAttnKeys);
     const int attn_streams = B * c.n_heads * ceil_div(ceil_div(L, 16), 3);
@@ -755,12 +758,27 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     }
     const bool head_attn = L <= kHeadAttnMaxRows && attn_chunks <= head_chunks;
 
+    // The key-split attention of a batch: which workgroup takes what may go by length, from a table that is made with the embedding
+    AttnLaunch sched{};
+    sched.batch = B; sched.L = L; sched.n_heads = c.n_heads; sched.n_wg = attn_wg; sched.capacity = kv->capacity;
+    sched.cache_chunks = ceil_div(kv->host_len_bound, kAttnKeys);
+    sched.qkv = L <= kHeadAttnMaxRows ? ctx->part : nullptr;
+    sched.plan = ctx->key_plan; sched.part_rows = (long long)ctx->o_part_rows; sched.part_count = ctx->counts;
+    const KeyPlan key_plan = head_attn ? KeyPlan{} : schedule_attention(&sched);
+    const int wide_from = std::min(ctx->wide_min_rows > 0 ? ctx->wide_min_rows : INT_MAX,
+                                   ctx->wide_min_rows_qkv > 0 ? ctx->wide_min_rows_qkv : INT_MAX);
+    const bool counted = key_plan.slots > B || M >= wide_from;  // some launch of this forward counts arrivals
+    {
+        TimedScope ts(ctx, SPACE_K_EMBED, s);
+        HIP_TRY(ctx, launch_embed(tokens, ctx->embed, c.vocab, d, lay, kv->len, B, ctx->cos_tab, ctx->sin_tab, ctx->n_pos, dh,
+                                  ctx->x, ctx->pos, ctx->cos_t, ctx->sin_t, ctx->faults, ctx->layers[0].attn_norm, c.rms_eps,
+                                  ctx->xn, xs, ctx->counts, counted ? ctx->n_counts : 0, key_plan, s));
+    }
+
     // Few rows: O and down leave complete rows (residual added) as x * norm weights and the partial sums of
     // squares, the projection behind them applies the norm factor; no norm launches.  Else split sums and
     // a norm launch that adds them up.  (The many-row kernel, which a developer knob can force on few rows,
     // does not apply factors.)
-    const int wide_from = std::min(ctx->wide_min_rows > 0 ? ctx->wide_min_rows : INT_MAX,
-                                   ctx->wide_min_rows_qkv > 0 ? ctx->wide_min_rows_qkv : INT_MAX);
     const int groups_o = resid_groups(ctx->layers[0].o), groups_dn = resid_groups(ctx->layers[0].down);
     // Where the line lies: a workgroup of that form reads the operand planes of all rows through its CU, 4
     // bytes per element, and while weights stream from memory a CU gets through about 50 GB/s whatever
@@ -845,8 +863,9 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
             at.kv_len = kv->len; at.info = lay.info;
             at.batch = B; at.L = L; at.Lp = Lp; at.n_heads = c.n_heads; at.n_kv_heads = ctx->kv_heads; at.head_dim = dh;
             at.capacity = kv->capacity;
-            at.n_wg = attn_wg;
-            at.cache_chunks = ceil_div(kv->host_len_bound, kAttnKeys);
+            at.n_wg = sched.n_wg; at.slots = sched.slots; at.shared = sched.shared;
+            at.plan = sched.plan; at.part_rows = sched.part_rows; at.part_count = sched.part_count;
+            at.cache_chunks = sched.cache_chunks;
             at.o_part = ctx->o_part; at.ml_part = ctx->ml_part; at.out = ctx->attn_out; at.out_shape = xs; at.paging = paging;
             {
                 TimedScope ts(ctx, SPACE_K_ATTN, s);

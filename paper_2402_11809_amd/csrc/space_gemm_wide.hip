@@ -41,7 +41,7 @@ constexpr int kWideStage = 2;   // contraction tiles per LDS stage
 constexpr int kWideWaves = 8;   // waves per workgroup
 constexpr int kWideTiles = 2;   // weight tiles per wave: a workgroup covers 256 weight rows
 
-template <int W, int R, int KS, int DA, int EPI>
+template <int W, int R, int KS, int DA, int EPI, bool TAIL>
 __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch g, int ksplit, int n_groups, int kt_per_split,
                                                                        WideParts parts, WideTail tail) {
     constexpr int T = kWideRowTiles, TB = 2, GMAX = T / TB;
@@ -60,8 +60,8 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     int G = 0, row_tile0 = 0, gi;
     // place of the piece among those of this XCD; the last tail.pieces of them have tail.parts workgroups each
     int q = blockIdx.x >> 3, part = -1, tail_piece = 0;
-    const int whole = (gk8 >> 3) * n_pieces - tail.pieces;
-    if (tail.pieces && q >= whole) {
+    const int whole = (gk8 >> 3) * n_pieces - (TAIL ? tail.pieces : 0);
+    if (TAIL && q >= whole) {
         part = (q - whole) % tail.parts;
         tail_piece = (q - whole) / tail.parts;
         q = whole + tail_piece;
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     // Contraction range of this split: a multiple of DA tiles (the host rounds; tiles past k_tiles exist
     // in the packed matrix as zeros, and the activation buffers are finite there).
     int k0 = s * kt_per_split, k1 = min(k0 + kt_per_split, (g.w.k_tiles + DA - 1) / DA * DA);
-    if (part >= 0) {  // (no split beside a tail, and no empty part: the host checks)
+    if (TAIL && part >= 0) {  // (no split beside a tail, and no empty part: the host checks)
         const int kt_part = ((k1 + tail.parts - 1) / tail.parts + DA - 1) / DA * DA;
         k0 = part * kt_part;
         k1 = min(k0 + kt_part, k1);
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
             buf ^= 1;
         }
 
-        if (part >= 0) {
+        if (TAIL && part >= 0) {
             // A part of the contraction: the sums go to memory, and the workgroup of the piece that arrives last adds
             // up all of them, in part order, and carries on with the epilogue.  Nobody waits for anybody.  The sums are
             // written through to where all XCDs see them (sc1) and read back past the caches, so the hand-over needs no
@@ -428,8 +428,12 @@ hipError_t launch_wide_r(const GemmLaunch& g, const WidePlan& p, hipStream_t s) 
     int pieces = 0;
     for (int c = 0; c < 4; ++c) pieces += p.parts.count[c];
     const dim3 grid(8 * (ceil_div(p.n_groups * p.ksplit, 8) * pieces + (p.tail.pieces ? p.tail.pieces * (p.tail.parts - 1) : 0))), block(64 * W);
-    hipLaunchKernelGGL((gemm_wide_kernel<W, R, kWideStage, kWideDepth, EPI>), grid, block, 0, s, g, p.ksplit, p.n_groups, p.kt_per_split,
-                       p.parts, p.tail);
+    if (p.tail.pieces)
+        hipLaunchKernelGGL((gemm_wide_kernel<W, R, kWideStage, kWideDepth, EPI, true>), grid, block, 0, s, g, p.ksplit, p.n_groups, p.kt_per_split,
+                           p.parts, p.tail);
+    else
+        hipLaunchKernelGGL((gemm_wide_kernel<W, R, kWideStage, kWideDepth, EPI, false>), grid, block, 0, s, g, p.ksplit, p.n_groups,
+                           p.kt_per_split, p.parts, p.tail);
     return hipGetLastError();
 }
 

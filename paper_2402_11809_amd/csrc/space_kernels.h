@@ -145,6 +145,20 @@ struct LayoutDev {
     int L, G;
 };
 
+// A workgroup's share of a batch in the key-split attention: part `part` of n_parts over the keys of sequence b, `len` cached
+// ones; b < 0: none.  The table holds the parts of every (head, query group), largest first.
+constexpr int kMaxKeyParts = 16, kMaxKeySlots = 512;
+struct KeyPart {
+    int b, part, n_parts, len;
+};
+struct KeyPlan {
+    KeyPart* table;
+    int slots;  // entries, at least batch; 0: no plan
+    int batch;  // up to 64
+    int capacity, n_blk;  // chunks of the block
+    int streams;          // heads x query groups
+};
+
 // cos / sin of every position 0 .. n_pos-1 ([n_pos][head_dim/2] each), computed once
 hipError_t launch_rope_table(float* cos_t, float* sin_t, int n_pos, int head_dim, float rope_base, hipStream_t s);
 // Embedding rows -> x, position ids, the rows' rotary factors (copied out of the table; positions outside it are
@@ -152,8 +166,10 @@ hipError_t launch_rope_table(float* cos_t, float* sin_t, int n_pos, int head_dim
 hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab, int d, const LayoutDev& lay,
                         const int32_t* kv_len, int batch, const float* cos_tab, const float* sin_tab, int n_pos,
                         int head_dim, float* x, int32_t* pos, float* cos_t, float* sin_t, int32_t* faults,
-                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, hipStream_t s);
-// (counts: cleared; the arrival counts of the launches behind it, so that a forward never depends on how an earlier one ended)
+                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, const KeyPlan& plan,
+                        hipStream_t s);
+// (counts: cleared; the arrival counts of the launches behind it, so that a forward never depends on how an earlier one ended; plan:
+// made from the lengths)
 
 // x += sum_s part[s]; xn = operand planes of x * w, ss[group][row] = sums of squares (as ResidLaunch leaves them); at most
 // kResidMaxRows rows
@@ -227,9 +243,19 @@ struct AttnLaunch {
     uint16_t* kc_w = nullptr;
     uint16_t* vc_w = nullptr;
     int32_t* faults = nullptr;
+    // Batches dealt out by length (schedule_attention): the table that the embedding launch leaves, [slots]; room in o_part, in
+    // rows of head_dim, and arrival counts of every (sequence, head, query group), zero between launches.
+    KeyPart* plan = nullptr;
+    int slots = 0;   // workgroups per (head, query group); 0: n_wg for every sequence
+    int shared = 0;  // see attention_item
+    long long part_rows = 0;
+    int32_t* part_count = nullptr;
 };
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
 int attention_workgroups(int len_bound, int L, int streams);
+// Whether the workgroups of a batch are dealt out by length (batch, L, n_heads, n_wg, cache_chunks, capacity, qkv, plan and
+// part_* are set): sets slots, shared and n_wg and returns what the embedding launch has to make, or nothing (slots 0).
+KeyPlan schedule_attention(AttnLaunch* a);
 
 // Rotary, K/V store, attention and normalisation of a block of at most kHeadAttnMaxRows rows in one
 // launch, one workgroup per (sequence, head, tile of 16 query rows).  Reads the QKV projection's

@@ -711,21 +711,69 @@ __device__ __forceinline__ void norm_row_tail(const f32x4 (&v)[2], float ss, flo
     }
 }
 
+// How the key-split attention of a batch deals its workgroups out by length (KeyPlan); one wave, once per forward: made by every
+// workgroup for itself it cost them 1 - 2 us a layer.  Every sequence gets one part, or, with more slots than sequences, the
+// slots are dealt out so that the largest part is as small as they allow (a part has at least four chunks, so that no wave of it is
+// without one; at most kMaxKeyParts).  What a CU spends on a part is its chunks and, worth kPartStaging of these, the
+// staging of the block; beyond a workgroup per CU the mean over the CUs counts as well, and a cut has to be 8 % ahead of none.
+constexpr int kPartStaging = 16;
+__device__ __forceinline__ void make_key_plan(const KeyPlan& kp, const int32_t* kv_len) {
+    const int lane = threadIdx.x & 63, batch = kp.batch;
+    const int len = lane < batch ? min(max(kv_len[lane], 0), kp.capacity) : 0;
+    const int chunks = (len + kAttnKeys - 1) / kAttnKeys, w = lane < batch ? chunks + kp.n_blk : 0;
+    int longest = 0, total = 0;
+    for (int i = 0; i < batch; ++i) {
+        const int v = __builtin_amdgcn_readlane(w, i);
+        longest = max(longest, v);
+        total += v;
+    }
+    const int most = max(min(chunks >> 2, kMaxKeyParts), 1);
+    int size = max(total / kp.slots, 1), n = lane < batch ? 1 : 0, parts = batch;
+    if (kp.slots > batch) {
+        for (;;) {  // ends: at size >= longest every sequence has one part
+            n = lane < batch ? size >= longest ? 1 : min((w + size - 1) / size, most) : 0;
+            parts = 0;
+            for (int i = 0; i < batch; ++i) parts += __builtin_amdgcn_readlane(n, i);
+            if (size >= longest || parts <= kp.slots) break;
+            size += max(size >> 3, 1);
+        }
+        auto cost = [&](int k, int largest) {
+            return max(largest + kPartStaging, k * kp.streams > 256 ? (total + k * kPartStaging) * kp.streams / 232 : 0);
+        };
+        if (cost(parts, size) * 100 > cost(batch, longest) * 92) {
+            n = min(n, 1);
+            parts = batch;
+        }
+    }
+    const int part = n ? (w + n - 1) / n : 0;
+    int first = 0;  // parts of sequences with larger ones
+    for (int i = 0; i < batch; ++i) {
+        const int other = __builtin_amdgcn_readlane(part, i), others = __builtin_amdgcn_readlane(n, i);
+        first += other > part || (other == part && i < lane) ? others : 0;
+    }
+    for (int j = 0; j < n; ++j) kp.table[first + j] = KeyPart{lane, j, n, len};
+    for (int r = parts + lane; r < kp.slots; r += 64) kp.table[r].b = -1;
+}
+
 // One workgroup per block row: the embedding row (the mask embedding on mask rows) becomes the residual
 // stream, the row's position id and its rotary factors (out of the table) are noted, and the first
 // layer's RMSNorm goes with it -- one launch instead of two at the head of every step.
+template <bool PLAN>
 __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, const uint16_t* embed, int vocab, int d,
                                                      const int32_t* info, const int32_t* rel_pos, int L, int m,
                                                      const int32_t* kv_len, const float* __restrict__ cos_tab,
                                                      const float* __restrict__ sin_tab, int n_pos, int head_dim,
                                                      float* x, int32_t* pos_out, float* cos_t, float* sin_t, int32_t* faults,
                                                      const uint16_t* __restrict__ w, float eps, uint16_t* __restrict__ xn,
-                                                     XtShape xs, int32_t* counts, int n_counts) {
+                                                     XtShape xs, int32_t* counts, int n_counts, KeyPlan plan) {
     __shared__ float sh[16];
     const int row = xcd_grouped_row(blockIdx.x), nvec = d >> 2, nthr = blockDim.x;
     if (row >= m) return;  // whole workgroup
     if (row == 0)
         for (int i = threadIdx.x; i < n_counts; i += nthr) counts[i] = 0;
+    if constexpr (PLAN) {
+        if (row == 0 && threadIdx.x < 64) make_key_plan(plan, kv_len);
+    }
     u32x2 wv[2];
     norm_w_load(w, d, wv);
     const int b = row / L, r = row % L;
@@ -766,13 +814,13 @@ __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, cons
 hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab, int d, const LayoutDev& lay,
                         const int32_t* kv_len, int batch, const float* cos_tab, const float* sin_tab, int n_pos,
                         int head_dim, float* x, int32_t* pos, float* cos_t, float* sin_t, int32_t* faults,
-                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, hipStream_t s) {
-    if (d > 8192 || (d & 3) || n_pos < 1) return hipErrorInvalidValue;
+                        const uint16_t* norm_w, float eps, uint16_t* xn, XtShape xs, int32_t* counts, int n_counts, const KeyPlan& plan, hipStream_t s) {
+    if (d > 8192 || (d & 3) || n_pos < 1 || plan.batch > 64 || (plan.slots && plan.slots < plan.batch)) return hipErrorInvalidValue;
     const int nvec = d >> 2;
     const int threads = nvec >= 1024 ? 1024 : round_up(nvec, 64);
-    hipLaunchKernelGGL(embed_kernel, dim3(round_up(batch * lay.L, 64)), dim3(threads), 0, s, tokens, embed, vocab, d, lay.info,
+    hipLaunchKernelGGL(plan.slots ? embed_kernel<true> : embed_kernel<false>, dim3(round_up(batch * lay.L, 64)), dim3(threads), 0, s, tokens, embed, vocab, d, lay.info,
                        lay.rel_pos, lay.L, batch * lay.L, kv_len, cos_tab, sin_tab, n_pos, head_dim, x, pos, cos_t, sin_t, faults,
-                       norm_w, eps, xn, xs, counts, counts ? n_counts : 0);
+                       norm_w, eps, xn, xs, counts, counts ? n_counts : 0, plan);
     return hipGetLastError();
 }
 
@@ -1159,11 +1207,35 @@ __device__ __forceinline__ u32x4 chunk_load(const uint16_t* base, int lane_off, 
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, const_off, 0));
 }
 
+// 16 bytes at a uniform base + a byte offset per lane, written to and read from where every XCD sees them (sc1).
+__device__ __forceinline__ void store_through(float* base, int off, f32x4 v) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, off, 0, 16);
+}
+__device__ __forceinline__ f32x4 load_through(const float* base, int off) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00020000);
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 16));
+}
+
+// Batches with more workgroups than CUs and one workgroup for all keys of a (sequence, head, query group): who shares a
+// CU with whom, and who starts first, goes by length.  Workgroup 256 + i runs on the CU of workgroup i while all fit
+// (two per CU), each at half speed.  shared > 0: that many places at the end of the `places` share a CU with the
+// first ones; the longest sequences get the places between, alone, and of the others the longest go with the shortest.
+// shared < 0: more than fit at once, longest first.  Returns the place's rank by length (of its part).
+// (648 rows of 8 sequences, 458 to 3685 cached positions: in batch order 1377 and 3685 shared a CU, 87 us per layer, by length 79;
+// 70B, 8 ragged sequences of 81 rows, 1024 workgroups, 134 / 82.)
+__device__ __forceinline__ int attention_item(int place, int places, int shared) {
+    if (shared < 0) return place;
+    if (place < shared) return places - 2 * shared + place;
+    if (place >= places - shared) return places - 1 - (place - (places - shared));
+    return place - shared;
+}
 // WV waves per workgroup: 4, two workgroups to a CU (256 registers each, under half the LDS).  The kernel
 // is written for any count; 8 (one workgroup per CU) was measured and is not built: it was ahead only
 // while the 4-wave loop spilled registers, and is level with it since (one sequence of 4096 positions
 // beside seven short ones 65 against 67.6 us per layer, everything else equal or behind).
-template <int DH, int TQ, bool PAGED, bool FUSE, int WV>
+// DEALT: the workgroups of a batch are dealt out by length (AttnLaunch::plan).
+template <int DH, int TQ, bool PAGED, bool FUSE, int WV, bool DEALT>
 __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(AttnLaunch a, float scale_log2e) {
     constexpr int DS = DH / 32, DT = DH / 16;
     constexpr int kPass = DT < 4 ? DT : 4;  // output slices merged per LDS pass, one per wave (the first kPass)
@@ -1175,10 +1247,22 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     const int QG = (((L + 15) >> 4) + TQ - 1) / TQ;
     // query groups in descending order: the later a group sits in a long block the more in-block chunks
     // it has, and the workgroups that take longest should start first
-    const int b = blockIdx.z / QG, qg = QG - 1 - blockIdx.z % QG;
+    int b = blockIdx.z / QG, qg = QG - 1 - blockIdx.z % QG, n_wg = gridDim.x, wg = blockIdx.x, rank = 0, len;
+    if constexpr (DEALT) {
+        const int item = attention_item(blockIdx.z, gridDim.z, a.shared);
+        rank = item / QG;
+        qg = QG - 1 - item % QG;
+        const KeyPart kp = a.plan[rank];
+        if (kp.b < 0) return;  // whole workgroup: a slot that is left over
+        b = kp.b;
+        wg = kp.part;
+        n_wg = kp.n_parts;
+        len = kp.len;
+    } else {
+        len = min(max(a.kv_len[b], 0), a.capacity);
+    }
     const int r0 = qg * TQ * 16;
     const size_t bh = (size_t)b * H + h;
-    const int n_wg = gridDim.x, wg = blockIdx.x;
 
     constexpr int kQUnits = 2 * TQ * DS * 64, kRedUnits = WV * kPass * TQ * 64;
     // FUSE: the block's own keys and values stay in LDS (as in attn_head_kernel: padded rows)
@@ -1200,8 +1284,8 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     f32x4* const red = (f32x4*)pool;                               // merge buffer [wave][slice in pass][t][lane]
     __shared__ float m_sh[WV][TQ * 16], l_sh[WV][TQ * 16];
     __shared__ int s_info[FUSE ? 16 * kMaxRowTiles : kMaxBlockRows];
+    __shared__ int s_last;
 
-    const int len = min(max(a.kv_len[b], 0), a.capacity);
     // in-block keys past this group's last query row are invisible to all of its rows (Eq. 3 is causal):
     // long blocks (prompt chunks) skip those chunks altogether
     const int n_cache = (len + kAttnKeys - 1) / kAttnKeys, n_blk = (min(L, r0 + TQ * 16) + kAttnKeys - 1) / kAttnKeys;
@@ -1639,6 +1723,79 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     }
     __syncthreads();
     float m_all[TQ], l_all[TQ];
+    // Keys cut by length: where part p of this sequence leaves its sums (parts of a sequence lie one behind the other)
+    const size_t slot0 = ((size_t)h * QG + qg) * a.slots + (rank - wg);
+    auto slot_o = [&](int p) { return a.o_part + (slot0 + p) * (TQ * 16 * DH); };
+    auto slot_ml = [&](int p) { return a.ml_part + (slot0 + p) * (TQ * 16 * 2); };
+    // The workgroup that counts itself last merges the parts in part order, as attn_combine_kernel does.  Stores and loads go
+    // past the caches that other XCDs do not see, so nothing has to be written back or invalidated.
+    auto merge_last = [&]() {
+        constexpr int NTH = WV * 64, NROW = TQ * 16, NIT = NROW * (DH / 4) / NTH;
+        static_assert(NROW * (DH / 4) % NTH == 0 && kMaxKeyParts * NROW * 8 <= kPoolBytes, "items");
+        if (wave == 0 && g4 == 0) {
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) {
+                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2, m_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2 + 1, l_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        int32_t* const count = a.part_count + (bh * QG + qg);
+        if (threadIdx.x == 0) {
+            const int before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = before == n_wg - 1;
+            if (s_last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+        }
+        __syncthreads();
+        if (!s_last) return;
+        asm volatile("" ::: "memory");
+        float* const st = (float*)pool;  // [part][row][max, sum], then the part's weight in place of the sum
+        for (int u = threadIdx.x; u < n_wg * NROW * 2; u += NTH)
+            st[u] = __hip_atomic_load(slot_ml(0) + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        f32x4 num[NIT];
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) num[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+        __syncthreads();
+        if (threadIdx.x < NROW) {
+            float* const sr = st + threadIdx.x * 2;
+            float mx = -INFINITY, den = 0.f;
+            for (int p = 0; p < n_wg; ++p) mx = fmaxf(mx, sr[p * NROW * 2]);
+            for (int p = 0; p < n_wg; ++p) {
+                const float m = sr[p * NROW * 2], wgt = m == -INFINITY ? 0.f : exp2f(m - mx);
+                sr[p * NROW * 2] = wgt;
+                den += wgt * sr[p * NROW * 2 + 1];
+            }
+            for (int p = 0; p < n_wg; ++p) sr[p * NROW * 2 + 1] = den > 0.f ? sr[p * NROW * 2] / den : 0.f;
+        }
+        __syncthreads();
+        const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);
+        constexpr int kRowStep = NTH / (DH / 4);
+        for (int p = 0; p < n_wg; ++p) {
+            f32x4 v[NIT];
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) v[it] = load_through(slot_o(p), ((row0 + it * kRowStep) * DH + col) * 4);
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                const float wgt = st[(p * NROW + row0 + it * kRowStep) * 2 + 1];
+                if (wgt != 0.f) num[it] += wgt * v[it];
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int tok = r0 + row0 + it * kRowStep;
+            if (tok >= L) continue;
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint16_t hv = f2bf(num[it][e]);
+                hi[e] = hv;
+                lo[e] = f2bf(num[it][e] - bf2f(hv));
+            }
+            *(u32x2*)(a.out + xt_index(b * L + tok, h * DH + col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+            *(u32x2*)(a.out + xt_index(b * L + tok, h * DH + col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+        }
+    };
 #pragma unroll
     for (int t = 0; t < TQ; ++t) {
         float mx = -INFINITY;
@@ -1683,6 +1840,8 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
                     const int col = h * DH + 16 * dt + 4 * g4;
                     *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
                     *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+                } else if (DEALT) {
+                    store_through(slot_o(wg), ((tok - r0) * DH + 16 * dt + 4 * g4) * 4, sum);
                 } else {
                     const size_t base = (bh * n_wg + wg) * L + tok;
                     *(f32x4*)(a.o_part + base * DH + 16 * dt + 4 * g4) = sum;
@@ -1690,6 +1849,10 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
             }
         }
         __syncthreads();
+    }
+    if constexpr (DEALT) {
+        if (n_wg > 1) merge_last();
+        return;
     }
     if (n_wg > 1 && wave == 0 && g4 == 0) {
 #pragma unroll
@@ -2163,27 +2326,72 @@ static int attention_query_tiles(const AttnLaunch& a) {
     return wgs3 <= 256 && wgs2 > 256 && a.cache_chunks > 2 * ceil_div(a.L, kAttnKeys) ? 3 : 2;
 }
 
+// Workgroups per (head, query group) for a batch whose keys are cut by length; 0: not.  Where the same number of parts for every
+// sequence leaves one or two each and no CU has two of them, i.e. where a long sequence cannot be given more.  Attention in
+// us per layer, equal parts / by length (7B, 36 rows unless stated, 100 .. 4000 positions): 8 sequences 92 / 67, 6 of them 65 / 55, 5
+// of 25 rows 31.9 / 26.8, 4 of 81 rows 54 / 42, 3 of them 35.9 / 31.4; 13B, 3 and 6 of them 40.9 / 33.8, 60.9 / 55.4; of equal lengths
+// level (3 of them 30.8 / 30.6, 6 39.7 / 39.9, 8 47.1 / 47.8).  Not where the general form has four parts each anyway (2
+// sequences 33.0 / 34.9; 8 with 8 heads 23.7 / 25.6), two workgroups on a CU already (70B, 6 of 16 rows 64.5 / 67.0) or one query
+// tile (6 of 4 rows 14.7 / 15.5); these four were measured with the plan made in every workgroup, 1 - 2 us of each second figure.
+static int attention_slots(const AttnLaunch& a, int QG, int TQ) {
+    const int streams = a.n_heads * QG;
+    if (!a.part_count || a.cache_chunks < 16 || a.n_wg > 2 || TQ < 2 || a.batch * streams > 256) return 0;
+    const long long room = a.part_rows / (streams * TQ * 16);  // of the partial sums
+    const long long slots = std::min<long long>(256 / streams >= 2 * a.batch ? 256 / streams : 512 / streams, room);
+    return slots > a.batch ? (int)slots : 0;
+}
+
+KeyPlan schedule_attention(AttnLaunch* a) {
+    KeyPlan p{};
+    AttnLaunch one = *a;
+    one.n_wg = 1;  // as the launch will be
+    const int TQ = attention_query_tiles(one), QG = ceil_div(ceil_div(a->L, 16), TQ), streams = a->n_heads * QG;
+    a->slots = a->shared = 0;
+    if (!a->plan || a->batch < 2 || a->batch > 64) return p;
+    a->slots = attention_slots(*a, QG, TQ);
+    if (!a->slots && a->n_wg == 1 && a->batch * streams > 256) a->slots = a->batch;
+    if (!a->slots) return p;
+    a->n_wg = 1;
+    const int over = a->slots * streams - 256;  // workgroups that share a CU, or do not all fit
+    a->shared = over <= 0 ? 0 : over > 256 ? -1 : ceil_div(over, a->n_heads);
+    p.table = a->plan;
+    p.slots = a->slots;
+    p.batch = a->batch;
+    p.capacity = a->capacity;
+    p.n_blk = ceil_div(a->L, kAttnKeys);
+    p.streams = streams;
+    return p;
+}
+
 template <int DH, bool PAGED>
 static hipError_t launch_attention_dh(const AttnLaunch& a, hipStream_t s) {
     const float scale_log2e = (float)(1.4426950408889634 / sqrt((double)DH));
     const int tiles = ceil_div(a.L, 16);
     const int TQ = attention_query_tiles(a);
     const int QG = ceil_div(tiles, TQ);
-    const dim3 grid(a.n_wg, a.n_heads, a.batch * QG), block(4 * 64);
-    if (a.qkv) {  // rotary and K/V staging inside the kernel: one query group, at most 48 rows
-        if (QG != 1 || a.L > kHeadAttnMaxRows || a.splits < 1 || !a.cos_t || !a.sin_t || !a.pos || !a.kc_w || !a.vc_w || !a.faults)
+    dim3 grid(a.n_wg, a.n_heads, a.batch * QG);
+    const dim3 block(4 * 64);
+    if (a.slots) {  // whoever ends last merges
+        if (a.n_wg != 1 || a.slots < a.batch || !a.plan || (a.slots > a.batch && (!a.part_count || (long long)a.slots * a.n_heads * QG * TQ * 16 > a.part_rows)))
             return hipErrorInvalidValue;
-        switch (TQ) {
-            case 1: hipLaunchKernelGGL((attn_sar_kernel<DH, 1, PAGED, true, 4>), grid, block, 0, s, a, scale_log2e); break;
-            case 2: hipLaunchKernelGGL((attn_sar_kernel<DH, 2, PAGED, true, 4>), grid, block, 0, s, a, scale_log2e); break;
-            default: hipLaunchKernelGGL((attn_sar_kernel<DH, 3, PAGED, true, 4>), grid, block, 0, s, a, scale_log2e); break;
+        grid.z = a.slots * QG;
+    }
+    if (a.qkv && (QG != 1 || a.L > kHeadAttnMaxRows || a.splits < 1 || !a.cos_t || !a.sin_t || !a.pos || !a.kc_w || !a.vc_w || !a.faults))
+        return hipErrorInvalidValue;
+    auto launch = [&](auto tq) {
+        constexpr int T = decltype(tq)::value;
+        if (a.qkv) {  // rotary and K/V staging inside the kernel: one query group, at most 48 rows
+            if (a.slots) hipLaunchKernelGGL((attn_sar_kernel<DH, T, PAGED, true, 4, true>), grid, block, 0, s, a, scale_log2e);
+            else hipLaunchKernelGGL((attn_sar_kernel<DH, T, PAGED, true, 4, false>), grid, block, 0, s, a, scale_log2e);
+        } else {
+            if (a.slots) hipLaunchKernelGGL((attn_sar_kernel<DH, T, PAGED, false, 4, true>), grid, block, 0, s, a, scale_log2e);
+            else hipLaunchKernelGGL((attn_sar_kernel<DH, T, PAGED, false, 4, false>), grid, block, 0, s, a, scale_log2e);
         }
-    } else {
-        switch (TQ) {
-            case 1: hipLaunchKernelGGL((attn_sar_kernel<DH, 1, PAGED, false, 4>), grid, block, 0, s, a, scale_log2e); break;
-            case 2: hipLaunchKernelGGL((attn_sar_kernel<DH, 2, PAGED, false, 4>), grid, block, 0, s, a, scale_log2e); break;
-            default: hipLaunchKernelGGL((attn_sar_kernel<DH, 3, PAGED, false, 4>), grid, block, 0, s, a, scale_log2e); break;
-        }
+    };
+    switch (TQ) {
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 2: launch(std::integral_constant<int, 2>{}); break;
+        default: launch(std::integral_constant<int, 3>{}); break;
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_wg == 1) return e;  // a single workgroup along the keys writes the output itself

@@ -837,6 +837,42 @@ def test_norm_of_a_row_shared_by_workgroups(torch_mod, d, B, k):
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=12), B, k, "resid=0", gc.LOGIT_TOL)
 
 
+@pytest.mark.parametrize("shape_name,B,k,order", [("gqa-small", 33, 3, "up"), ("gqa-small", 40, 4, "up"), ("gqa-small", 64, 3, "down"), ("gqa-small", 64, 8, "mixed"),
+                                                  ("gqa-small", 65, 4, "mixed"), ("gqa-small", 33, 3, "equal"), ("gqa128", 17, 8, "mixed")])
+def test_workgroups_assigned_by_length(torch_mod, shape_name, B, k, order):
+    """Batches with more attention workgroups than CUs: 264 to 512 (the last places share a CU with the first), more
+    (longest first), 64 sequences and one more than are ordered; lengths ascending, descending, mixed with equal ones, all
+    equal, some empty.  Every sequence against its own oracle step."""
+    lens = {"up": [9 * b for b in range(B)], "down": [9 * (B - b) for b in range(B)], "mixed": [(211 * (b // 2)) % 500 for b in range(B)],
+            "equal": [77] * B}[order]
+    _batched_step_vs_oracle(torch_mod, SHAPES[shape_name], all_weights(SHAPES[shape_name], seed=13), B, k, "attn=0", gc.LOGIT_TIGHT, ctxs=lens, capacity=800)
+
+
+@pytest.mark.parametrize("shape_name,B,k,order", [("gqa-small", 16, 5, "ragged"), ("gqa-small", 20, 4, "one-long"), ("gqa-small", 32, 5, "ragged"),
+                                                  ("gqa-small", 11, 8, "ragged"), ("gqa-small", 31, 5, "equal"), ("small128", 33, 4, "one-long"),
+                                                  ("gqa128", 17, 5, "ragged"), ("gqa128", 16, 7, "one-long"), ("small128", 64, 3, "one-long")])
+def test_keys_of_a_batch_cut_by_length(torch_mod, shape_name, B, k, order):
+    """Batches whose workgroups are dealt out by length: sequences in one to sixteen parts, as many slots as the batch
+    needs and some left over, empty sequences beside 700 positions, equal lengths (no cut), two and three query tiles, two query
+    groups, heads of 64 and 128; the last batch has one query tile and is not cut.  Against the oracle, and three steps in a
+    row give the same bits (the parts are merged in part order by whoever ends last)."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name]
+    w = all_weights(shape, seed=14)
+    lens = {"ragged": [(67 * b * b) % 701 for b in range(B)], "one-long": [0, 5] + [31 + b for b in range(B - 3)] + [703], "equal": [640] * B}[order]
+    _batched_step_vs_oracle(torch, shape, w, B, k, "attn=0", gc.LOGIT_TIGHT, ctxs=lens, capacity=736)
+    spec = lo.paper_layout(k)
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=spec.n_rows, tune="attn=0")
+    om = gc.oracle_model(shape, w)
+    cache = gm.kv_cache(B, 736)
+    for b, c in enumerate(lens):
+        gc.upload_oracle_kv(torch, cache, b, gc.synthetic_oracle_kv(om, seed=70 + b, ctx=c, std=0.5))
+    toks = np.random.default_rng(16).integers(0, shape.vocab, size=(B, spec.n_rows)).astype(np.int32)
+    got = [_run_step(torch, gm, cache, spec, toks, batch=B).logits.cpu().numpy().copy() for _ in range(3)]
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane
 @pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 96])
 def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, vocab):

@@ -2327,15 +2327,16 @@ static int attention_query_tiles(const AttnLaunch& a) {
 }
 
 // Workgroups per (head, query group) for a batch whose keys are cut by length; 0: not.  Where the same number of parts for every
-// sequence leaves one or two each and no CU has two of them, i.e. where a long sequence cannot be given more.  Attention in
-// us per layer, equal parts / by length (7B, 36 rows unless stated, 100 .. 4000 positions): 8 sequences 92 / 67, 6 of them 65 / 55, 5
-// of 25 rows 31.9 / 26.8, 4 of 81 rows 54 / 42, 3 of them 35.9 / 31.4; 13B, 3 and 6 of them 40.9 / 33.8, 60.9 / 55.4; of equal lengths
-// level (3 of them 30.8 / 30.6, 6 39.7 / 39.9, 8 47.1 / 47.8).  Not where the general form has four parts each anyway (2
-// sequences 33.0 / 34.9; 8 with 8 heads 23.7 / 25.6), two workgroups on a CU already (70B, 6 of 16 rows 64.5 / 67.0) or one query
-// tile (6 of 4 rows 14.7 / 15.5); these four were measured with the plan made in every workgroup, 1 - 2 us of each second figure.
+// sequence leaves one or two each, i.e. where a long sequence cannot be given more, and the chip has room for more workgroups at
+// once.  Attention in us per layer, equal parts / by length (7B, 36 rows unless stated, 100 .. 4000 positions): 8 sequences
+// 92 / 67, 6 of them 65 / 55, 5 of 25 rows 31.9 / 26.8, 4 of 81 rows 54 / 42, 3 of them 35.9 / 31.4, 8 of 16 rows 44 / 30, 6 of 9 rows
+// 48 / 36; 13B, 3, 6 and 8 of them 40.9 / 33.8, 60.9 / 55.4, 51 / 38; 70B, 6 of 16 rows 36 / 30; of equal lengths level (3 of them
+// 30.8 / 30.6, 6 39.7 / 39.9, 8 47.1 / 47.8, 8 of 16 rows 37.5 / 38.1).  With four parts each anyway there is nothing to gain (2
+// sequences 24.9 / 25.1 and 23.5 / 24.5, 8 with 8 heads 23.3 / 23.8), and a lone sequence is better merged by all CUs
+// (attn_combine_kernel: 7B 23.5 / 26.8).
 static int attention_slots(const AttnLaunch& a, int QG, int TQ) {
     const int streams = a.n_heads * QG;
-    if (!a.part_count || a.cache_chunks < 16 || a.n_wg > 2 || TQ < 2 || a.batch * streams > 256) return 0;
+    if (!a.part_count || a.cache_chunks < 16 || a.n_wg > 2) return 0;
     const long long room = a.part_rows / (streams * TQ * 16);  // of the partial sums
     const long long slots = std::min<long long>(256 / streams >= 2 * a.batch ? 256 / streams : 512 / streams, room);
     return slots > a.batch ? (int)slots : 0;

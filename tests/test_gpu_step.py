@@ -850,11 +850,12 @@ def test_workgroups_assigned_by_length(torch_mod, shape_name, B, k, order):
 
 @pytest.mark.parametrize("shape_name,B,k,order", [("gqa-small", 16, 5, "ragged"), ("gqa-small", 20, 4, "one-long"), ("gqa-small", 32, 5, "ragged"),
                                                   ("gqa-small", 11, 8, "ragged"), ("gqa-small", 31, 5, "equal"), ("small128", 33, 4, "one-long"),
-                                                  ("gqa128", 17, 5, "ragged"), ("gqa128", 16, 7, "one-long"), ("small128", 64, 3, "one-long")])
+                                                  ("gqa128", 17, 5, "ragged"), ("gqa128", 16, 7, "one-long"), ("small128", 64, 3, "one-long"),
+                                                  ("gqa-small", 33, 1, "one-long"), ("gqa-small", 48, 5, "ragged"), ("gqa-small", 63, 3, "one-long")])
 def test_keys_of_a_batch_cut_by_length(torch_mod, shape_name, B, k, order):
     """Batches whose workgroups are dealt out by length: sequences in one to sixteen parts, as many slots as the batch
-    needs and some left over, empty sequences beside 700 positions, equal lengths (no cut), two and three query tiles, two query
-    groups, heads of 64 and 128; the last batch has one query tile and is not cut.  Against the oracle, and three steps in a
+    needs and some left over, empty sequences beside 700 positions, equal lengths (no cut), one to three query tiles, two query
+    groups, heads of 64 and 128, more sequences than a workgroup per CU allows (one slot to spare).  Against the oracle, and three steps in a
     row give the same bits (the parts are merged in part order by whoever ends last)."""
     torch = torch_mod
     from paper_2402_11809_amd import layout as lo

@@ -14,6 +14,7 @@
 // The contraction is order independent, so any assignment of slots to real indices is fine as
 // long as A and B agree.
 #include "space_kernels.h"
+#include "space_attn_plan.h"
 #include "space_device.h"
 
 #include <limits.h>
@@ -1217,19 +1218,6 @@ __device__ __forceinline__ f32x4 load_through(const float* base, int off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 16));
 }
 
-// Batches with more workgroups than CUs and one workgroup for all keys of a (sequence, head, query group): who shares a
-// CU with whom, and who starts first, goes by length.  Workgroup 256 + i runs on the CU of workgroup i while all fit
-// (two per CU), each at half speed.  shared > 0: that many places at the end of the `places` share a CU with the
-// first ones; the longest sequences get the places between, alone, and of the others the longest go with the shortest.
-// shared < 0: more than fit at once, longest first.  Returns the place's rank by length (of its part).
-// (648 rows of 8 sequences, 458 to 3685 cached positions: in batch order 1377 and 3685 shared a CU, 87 us per layer, by length 79;
-// 70B, 8 ragged sequences of 81 rows, 1024 workgroups, 134 / 82.)
-__device__ __forceinline__ int attention_item(int place, int places, int shared) {
-    if (shared < 0) return place;
-    if (place < shared) return places - 2 * shared + place;
-    if (place >= places - shared) return places - 1 - (place - (places - shared));
-    return place - shared;
-}
 // WV waves per workgroup: 4, two workgroups to a CU (256 registers each, under half the LDS).  The kernel
 // is written for any count; 8 (one workgroup per CU) was measured and is not built: it was ahead only
 // while the 4-wave loop spilled registers, and is level with it since (one sequence of 4096 positions
@@ -2353,8 +2341,7 @@ KeyPlan schedule_attention(AttnLaunch* a) {
     if (!a->slots && a->n_wg == 1 && a->batch * streams > 256) a->slots = a->batch;
     if (!a->slots) return p;
     a->n_wg = 1;
-    const int over = a->slots * streams - 256;  // workgroups that share a CU, or do not all fit
-    a->shared = over <= 0 ? 0 : over > 256 ? -1 : ceil_div(over, a->n_heads);
+    a->shared = attention_shared(a->slots * QG, a->n_heads);
     p.table = a->plan;
     p.slots = a->slots;
     p.batch = a->batch;

@@ -848,6 +848,16 @@ def test_workgroups_assigned_by_length(torch_mod, shape_name, B, k, order):
     _batched_step_vs_oracle(torch_mod, SHAPES[shape_name], all_weights(SHAPES[shape_name], seed=13), B, k, "attn=0", gc.LOGIT_TIGHT, ctxs=lens, capacity=800)
 
 
+@pytest.mark.parametrize("heads,kv_heads,B,k", [(24, 6, 21, 1), (20, 20, 25, 4), (20, 4, 14, 6), (56, 8, 9, 4)])
+def test_workgroups_by_length_where_heads_do_not_divide_the_chip(torch_mod, heads, kv_heads, B, k):
+    """480 to 504 workgroups of 20, 24 or 56 heads: those beyond 256 round up to more places than have a partner.  One to
+    three query tiles, ascending lengths.  Against the oracle."""
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["tiny"], name="odd-heads", n_heads=heads, n_kv_heads=kv_heads, vocab=300)
+    lens = [(9 * b) if b != B // 2 else 700 for b in range(B)]
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=15), B, k, "attn=0", gc.LOGIT_TIGHT, ctxs=lens, capacity=736)
+
+
 @pytest.mark.parametrize("shape_name,B,k,order", [("gqa-small", 16, 5, "ragged"), ("gqa-small", 20, 4, "one-long"), ("gqa-small", 32, 5, "ragged"),
                                                   ("gqa-small", 11, 8, "ragged"), ("gqa-small", 31, 5, "equal"), ("small128", 33, 4, "one-long"),
                                                   ("gqa128", 17, 5, "ragged"), ("gqa128", 16, 7, "one-long"), ("small128", 64, 3, "one-long"),

@@ -359,7 +359,8 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     }
     if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv)) {
         max_splits = std::max(max_splits, 4);
-        if (dev_alloc(ctx, &ctx->tail_sums, 8 * kWideTailSlots * kWideTailFloats, false)) ctx->err.clear();  // 32 MB; no tails without
+        const bool tails = ctx->wide_tail_force.pieces || (ctx->wide_tail && ceil_div(std::max(std::max(d, hd), f), kTileK) >= kWideTailMinK);
+        if (tails && dev_alloc(ctx, &ctx->tail_sums, 8 * kWideTailSlots * kWideTailFloats, false)) ctx->err.clear();  // 32 MB; no tails without
     }
     ctx->part_splits_max = max_splits;
     const size_t plane_tile = 2 * 64 * 8;  // hi + lo plane of one 16 x 32 activation tile, in elements
@@ -389,9 +390,10 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     ctx->o_part_rows = bh * wg_rows;
     const size_t n_attn = bh * ceil_div(c.max_rows, 16);  // (sequence, head, query group) triples
     ctx->n_counts = (int)n_attn + 8 * kWideTailSlots;
-    if ((rc = dev_alloc(ctx, &ctx->counts, (size_t)ctx->n_counts, true))) return rc;
+    const size_t count_parts = ceil_div(ctx->n_counts * (int)sizeof(int32_t), (int)sizeof(KeyPart));
+    if ((rc = dev_alloc(ctx, &ctx->key_plan, (size_t)kMaxKeySlots + count_parts, true))) return rc;
+    ctx->counts = (int32_t*)(ctx->key_plan + kMaxKeySlots);
     ctx->tail_count = ctx->counts + n_attn;
-    if ((rc = dev_alloc(ctx, &ctx->key_plan, (size_t)kMaxKeySlots, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->arg_val, M * ctx->arg_groups, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->arg_idx, M * ctx->arg_groups, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->cos_t, M * (c.head_dim / 2), true))) return rc;

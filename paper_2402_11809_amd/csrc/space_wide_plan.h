@@ -153,6 +153,7 @@ inline WideCut plan_wide_cut(int n_groups, int n, int k_tiles, int m, int smax, 
 
 // The last `pieces` pieces of every XCD, in launch order, are cut over the contraction: `parts` workgroups each, whose sums
 // the one that ends last adds up in part order (same bits whichever that is) before the epilogue.  0: none.
+constexpr int kWideTailMinK = 64;    // contraction tiles (shorter: a workgroup's fixed cost outweighs it)
 constexpr int kWideTailSlots = 32;  // most workgroups per XCD with a part of a piece (partial sums of 128 KB each)
 struct WideTail {
     int pieces, parts;
@@ -176,7 +177,7 @@ inline int64_t wide_part_cost(int g, int kt, int parts, bool last) {
 // 161 / 157 on one, 108.9 / 113.0 and level on another that holds a lower clock.
 inline bool plan_wide_tail(int n_groups, int n, int k_tiles, int m, const WideCut& c, WideCut* cut, WideTail* tail) {
     const int groups = ceil_div(ceil_div(m, 16), 2), gk8 = ceil_div(n_groups, 8);
-    if (groups > kWideSearchGroups || k_tiles < 64) return false;  // (short contractions: a workgroup's fixed cost outweighs it)
+    if (groups > kWideSearchGroups || k_tiles < kWideTailMinK) return false;
     const int kt_c = round_up(ceil_div(k_tiles, c.ksplit), kWideDepth), kt = round_up(k_tiles, kWideDepth);
     const int64_t now = wide_cost(c.parts, ceil_div(n_groups * c.ksplit, 8), kt_c) +
                         (int64_t)((c.ksplit - 1) * (double)m * n * 4.0 / (4.5e6 * kWideUnitUs));

@@ -1754,7 +1754,8 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
                 sr[p * NROW * 2] = wgt;
                 den += wgt * sr[p * NROW * 2 + 1];
             }
-            for (int p = 0; p < n_wg; ++p) sr[p * NROW * 2 + 1] = den > 0.f ? sr[p * NROW * 2] / den : 0.f;
+            // (a sum that is no number has to reach the output, as it does where one workgroup takes all keys)
+            for (int p = 0; p < n_wg; ++p) sr[p * NROW * 2 + 1] = den == 0.f ? 0.f : sr[p * NROW * 2] / den;
         }
         __syncthreads();
         const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);

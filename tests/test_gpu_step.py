@@ -884,6 +884,34 @@ def test_keys_of_a_batch_cut_by_length(torch_mod, shape_name, B, k, order):
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
 
 
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
+    """One sequence of a batch, long enough to be cut into parts, with one cached key element that is NaN or infinite: a score of the
+    softmax is no number then, so every logit of that sequence is NaN (as where one workgroup takes all keys), and
+    the other sequences' logits keep their bits."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES["gqa-small"]
+    B, k, long_one = 20, 4, 19
+    lens = [5 + b for b in range(B - 1)] + [703]
+    spec = lo.paper_layout(k)
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=14), max_batch=B, max_rows=spec.n_rows, tune="attn=0")
+    om = gc.oracle_model(shape, all_weights(shape, seed=14))
+    cache = gm.kv_cache(B, 736)
+    for b, c in enumerate(lens):
+        gc.upload_oracle_kv(torch, cache, b, gc.synthetic_oracle_kv(om, seed=70 + b, ctx=c, std=0.5))
+    cache.len.copy_(torch.tensor(lens, dtype=torch.int32))
+    cache.set_len_bound(max(lens))
+    toks = np.random.default_rng(17).integers(0, shape.vocab, size=(B, spec.n_rows)).astype(np.int32)
+    clean = _run_step(torch, gm, cache, spec, toks, batch=B).logits.cpu().numpy().copy()
+    cache.k_view()[0, long_one, :, 333, 0] = value
+    got = _run_step(torch, gm, cache, spec, toks, batch=B).logits.cpu().numpy()
+    assert np.isfinite(clean).all()
+    assert np.isnan(got[long_one]).all()
+    others = [b for b in range(B) if b != long_one]
+    assert np.array_equal(got[others], clean[others])
+
+
 @pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane
 @pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 96])
 def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, vocab):

@@ -3083,22 +3083,32 @@ hipError_t launch_sample_verify(const SampleLaunch& v, hipStream_t s) {
 // dataloader's) business.  One workgroup per row, a thread over its own elements, then a fixed tree: the result does
 // not depend on timing.  A second launch adds the rows up in row order.
 //
-// Bound by reading the logits once, next to about 35 cycles of arithmetic an element: every thread keeps a running
+// Bound by reading the logits once, next to about 45 cycles of arithmetic an element: every thread keeps a running
 // maximum and the sum of exponentials below it, 32 elements at a time, so that nothing waits for the row's maximum
 // and four rows run on a CU, some reading while others compute (rows held in registers up to their maximum, two to
-// a CU, with the library's expf: 32.3 us for 1366 rows of 32000, here 27).  The exponential is the hardware's of
-// a rounded product: the terms' errors against 64 bits are 0.95 - 0.98 of what they were.  The loads are non-temporal:
-// read once, and from memory that holds more than the caches 36.0 against 40.2 us for both launches.  256 threads are
-// level there and slower from 300 rows of 32000 on down (11.2 against 10.4), 1024 slower on short rows.  VEC: rows
-// that start on 16 bytes (vocabulary a multiple of 4) take float4 loads.
+// a CU, with the library's expf: both launches 41.1 us for 1366 rows of 32000, here 36.8 .. 37.3; 2048 short rows of 1000 32.4 / 14.2).
+// The sums of a thread's 16 exponentials are added up in 64 bits and the logarithm is taken there, once a row: the terms' rms
+// error against 64 bits is 0.2 - 0.6 of that form's where the label is likely (N(0, 2): 2.7e-7 -> 1.2e-7) and 0.4 - 0.9
+// where it is not (float32 rounding of the term).  The loads are non-temporal: read once, and from memory that holds more
+// than the caches 36.0 against 40.2 us for both launches.  256 threads are level there and slower from 300 rows of 32000 on
+// down (11.2 against 10.4), 1024 slower on short rows.  VEC: rows that start on 16 bytes (vocabulary a multiple of 4) take
+// float4 loads.
 constexpr int kNllThreads = 512, kNllHeld = 32;  // logits of a row a thread takes at a time
+
+// e^d for d <= 0 within about an ulp: p = d log2(e) is rounded to 32 bits, which alone would put up to 1e-6 on an
+// exponential of -20 and a bias on the sums; what it lost, d - p ln 2, goes back in behind the hardware's exponential (0.9 us
+// of the 37 above).  d = -inf (a masked logit) gives 0: the difference is no number there, and the maximum drops it; NaN stays NaN.
+__device__ __forceinline__ float exp_below(float d) {
+    const float p = d * 1.4426950408889634f, e = __builtin_amdgcn_exp2f(p);
+    return fmaf(e, fmaxf(fmaf(p, -0.6931471805599453f, d), -1.f), e);
+}
 
 template <bool VEC>
 __global__ __launch_bounds__(kNllThreads, 8) void nll_rows_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
                                                                   int vocab, float* __restrict__ row_loss, int32_t* faults) {
     constexpr int W = kNllThreads / 64;
-    constexpr float kLog2e = 1.4426950408889634f;
-    __shared__ float s_max[W], s_sum[W];
+    __shared__ float s_max[W];
+    __shared__ double s_sum[W];
     const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int label = labels[row];
     if (label < 0 || label >= vocab) {  // ignored row (negative) or a label outside the vocabulary (counted)
@@ -3110,7 +3120,8 @@ __global__ __launch_bounds__(kNllThreads, 8) void nll_rows_kernel(const float* _
     }
     const float* __restrict__ x = logits + (size_t)row * vocab;
     const float at_label = x[label];
-    float mx = -INFINITY, sum = 0.f;
+    float mx = -INFINITY;
+    double sum = 0.0;
     for (int base = 0; base < vocab; base += kNllThreads * kNllHeld) {
         float v[kNllHeld];
         if (VEC) {
@@ -3133,12 +3144,15 @@ __global__ __launch_bounds__(kNllThreads, 8) void nll_rows_kernel(const float* _
 #pragma unroll
         for (int j = 0; j < kNllHeld; ++j) m = fmaxf(m, v[j]);
         const float m_use = m == -INFINITY ? 0.f : m;  // nothing but masked logits so far: exp2(-inf), not of a NaN
-        sum *= __builtin_amdgcn_exp2f((mx - m_use) * kLog2e);
+        sum *= exp_below(mx - m_use);
         mx = m;
         float part[2] = {0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < kNllHeld; ++j) part[j & 1] += __builtin_amdgcn_exp2f((v[j] - m_use) * kLog2e);
-        sum += part[0] + part[1];
+        for (int j = 0; j < kNllHeld; ++j) {
+            if (j % 4 == 0 && base + j * kNllThreads >= vocab) break;  // (all threads)
+            part[j & 1] += exp_below(v[j] - m_use);
+        }
+        sum += (double)part[0] + part[1];
     }
     float all = mx;
 #pragma unroll
@@ -3147,16 +3161,16 @@ __global__ __launch_bounds__(kNllThreads, 8) void nll_rows_kernel(const float* _
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < W; ++w) all = fmaxf(all, s_max[w]);
-    sum *= __builtin_amdgcn_exp2f((mx - (all == -INFINITY ? 0.f : all)) * kLog2e);
+    sum *= exp_below(mx - (all == -INFINITY ? 0.f : all));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     if (lane == 0) s_sum[wave] = sum;
     __syncthreads();
     if (tid == 0) {
-        float tot = 0.f;
+        double tot = 0.0;
 #pragma unroll
         for (int w = 0; w < W; ++w) tot += s_sum[w];
-        row_loss[row] = -(at_label - all - logf(tot));
+        row_loss[row] = (float)(log(tot) - ((double)at_label - all));
     }
 }
 

@@ -164,3 +164,26 @@ def test_loss_where_the_running_maximum_and_the_row_sum_change_course(V, rows, k
         _, _, got = call()
         assert np.isnan(got[:3]).all() and np.isfinite(got[3:]).all()
     assert gm.device_faults() == 0
+
+
+def test_exponentials_carry_the_rounding_of_their_argument():
+    """Rows of one peak over 2047 equal logits d below it, d taken where the float32 product d log2(e) is rounded by 0.6 ulp
+    and more to one side (the rounded constant included): exponentials of the rounded product alone put 1.5e-7 on every term.
+    Allowed on the mean: half of 1 ulp of the exponential (the equal logits make up about half of the sum) plus half an
+    ulp of the term, 8e-8."""
+    torch = gc.require_gpu()
+    import dataclasses
+    V, rows = 2048, 256
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    gm = gc.make_gpu_model(shape, all_weights(shape, seed=0), max_batch=1, max_rows=36)
+    d = -(7.2 + 1.3 * np.random.default_rng(0).random(100000)).astype(np.float32)
+    p = d * np.float32(1.4426950408889634)
+    d = d[(p.astype(np.float64) - d.astype(np.float64) * 1.4426950408889634) / np.spacing(np.abs(p)) > 0.6][:rows]
+    assert len(d) == rows
+    logits = np.repeat(d[:, None], V, axis=1)
+    logits[:, 5] = 0.0
+    row_loss = torch.empty(rows, dtype=torch.float32, device="cuda")
+    gm.sar_loss(torch.from_numpy(logits).cuda(), torch.full((rows,), 5, dtype=torch.int32, device="cuda"), row_loss)
+    torch.cuda.synchronize()
+    err = row_loss.cpu().numpy().astype(np.float64) - np.log1p((V - 1) * np.exp(d.astype(np.float64)))
+    assert abs(err.mean()) < 8e-8, err.mean()

@@ -368,12 +368,12 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  * rows of the layout), a handful of ways to cut the rows into workgroups of 128, 96, 64 or 32 rows on the
  * context's own scratch buffers and the loaded layers' weights in turn -- and, for the projections whose
  * output is a plain sum (QKV, O, down), in how many parts the contraction is summed (1, 2 or 4) -- and
- * remembers the fastest for later space_step / space_prefill calls with that row count.  Where the cost model would
- * cut the last pieces over the contraction (their sums are added up inside the kernel), that is kept only if it
- * measures 5 % ahead.  The cut of the rows
- * changes no result (every output element is computed by the same instructions in the same order); the
- * number of partial sums and pieces cut over the contraction change the order of the fp32 additions, i.e. results of a tuned context can
- * differ from an untuned one's in the last bits, as they do between any two tilings.  Unlike the other calls it waits for the
+ * remembers the fastest for later space_step / space_prefill calls with that row count if it is 10 % ahead of what
+ * a context that was not tuned does (pieces cut over the contraction, whose sums are added up inside the kernel, included).
+ * The cut of the rows changes no result (every output element is computed by the same instructions in the same
+ * order); the number of partial sums and pieces cut over the contraction change the order of the fp32 additions, i.e.
+ * results of a tuned context can differ from an untuned one's in the last bits, as they do between any two tilings, where
+ * something is that far ahead.  Unlike the other calls it waits for the
  * stream (a few tens of milliseconds) and must not be called on a stream that is being captured
  * (SPACE_EINVAL).  rows: 1..max_batch*max_rows, else SPACE_ESHAPE.  Row counts below the many-row kernel's
  * switch points and contexts without a loaded layer return SPACE_OK without doing anything. */

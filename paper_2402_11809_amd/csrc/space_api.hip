@@ -1134,7 +1134,7 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         if (left == 3) ++b; else if (left == 2) ++cc; else if (left == 1) return add(a, b, cc, 1);
         add(a, b, cc, 0);
     };
-    cands.push_back(WideParts{});                                         // cands[0]: what an unmeasured launch uses, per projection below
+    cands.push_back(WideParts{});                                         // cands[0]: the planner's cut, per projection below
     rest(groups / 4, 0, 0, groups % 4);                                   // pieces of 128 rows
     rest(0, groups / 3, 0, groups % 3);                                   // of 96 rows
     add(0, 0, groups / 2, groups % 2);                                    // of 64 rows
@@ -1153,23 +1153,26 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         // work, the norm kernels) pays for each of them, which a measurement of the projection alone does
         // not show: the time to read the extra partial sums once is put on top.
         const bool plain = cls == 0 || cls == 1 || cls == 3;
-        WidePlan own, tail;  // an unmeasured launch's, without and with pieces cut over the contraction (if it has any)
+        // What a launch in a context that was not tuned does (pieces cut over the contraction included) is what everything else is
+        // measured against, and stays unless something is clearly ahead: a choice between two that are nearly level would
+        // differ from run to run, and with it the order of the sums.
+        WidePlan own, base;  // without such pieces; with them, where the planner cuts any
         {
             const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
             own = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max);
-            tail = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, 0, nullptr, ctx->tail_sums && ctx->wide_tail);
+            base = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, 0, nullptr, ctx->tail_sums && ctx->wide_tail);
             cands[0] = own.parts;
         }
+        const int first = base.tail.pieces ? -1 : 0;  // candidate that is base
         const int ks_cands[4] = {0, 1, 2, 4};
-        float best_ms = 0.f, default_ms = 0.f, tail_ms = 0.f;
+        float best_ms = 0.f, default_ms = 0.f;
         int best = -1, best_ks = 0;
         for (int kc = 0; kc < (plain ? 4 : 1) && rc == SPACE_OK; ++kc)
-        for (int i = 0; i < (int)cands.size() + (kc == 0 && tail.tail.pieces) && rc == SPACE_OK; ++i) {
-            const bool is_tail = i == (int)cands.size();
+        for (int i = kc == 0 ? first : 0; i < (int)cands.size() && rc == SPACE_OK; ++i) {
             const int ks = kc == 0 ? own.ksplit : ks_cands[kc];
             if (ks > ctx->part_splits_max || (kc > 0 && ks == own.ksplit)) continue;
             const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
-            const WidePlan cand = is_tail ? tail : plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, ks, &cands[i]);
+            const WidePlan cand = i < 0 ? base : plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, ks, &cands[i]);
             float ms_min = 0.f;
             for (int rep = 0; rep < 4 && rc == SPACE_OK; ++rep) {  // the first one warms up
                 if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(ctx, SPACE_EHIP, "hipEventRecord"); break; }
@@ -1194,22 +1197,18 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
                 const int n_out = cls == 0 ? hd + 2 * ctx->hd_kv : d;
                 ms_min += (float)((double)(used - 1) * rows * n_out * 4.0 / 4.0e9);
             }
-            if (is_tail) {
-                tail_ms = ms_min;
-                continue;
-            }
-            if (rc == SPACE_OK && kc == 0 && i == 0) default_ms = ms_min;
-            if (rc == SPACE_OK && (best < 0 || ms_min < best_ms)) { best = i; best_ks = ks; best_ms = ms_min; }
+            if (rc == SPACE_OK && kc == 0 && i == first) default_ms = ms_min;
+            else if (rc == SPACE_OK && (best < 0 || ms_min < best_ms)) { best = i; best_ks = ks; best_ms = ms_min; }
         }
         // Same projection back to back is not quite the step's own sequence of kernels: another cut (or
         // split) is taken only where it is clearly ahead.
         const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)rows;
         ctx->wide_plans.erase(key);
         try {
-            if (rc == SPACE_OK && (best > 0 || best_ks != own.ksplit) && best_ms < 0.90f * default_ms && !(tail.tail.pieces && tail_ms <= best_ms))
+            if (rc == SPACE_OK && best >= 0 && best_ms < 0.90f * default_ms)
                 ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
             else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
-                ctx->wide_plans[key] = tail.tail.pieces && tail_ms < 0.95f * default_ms ? tail : own;  // (the tail's gain is smaller, and so is what it changes)
+                ctx->wide_plans[key] = base;  // what the next launch would plan again
         } catch (...) {  // no room to remember it: planned again
         }
     }

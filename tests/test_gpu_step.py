@@ -912,6 +912,31 @@ def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
     assert np.array_equal(got[others], clean[others])
 
 
+def test_tuned_contexts_keep_the_planned_tail(torch_mod):
+    """288 rows at 7B width, where the planner cuts the last pieces of gate / up over the contraction (the logits differ from
+    those of a context without such pieces): measured, that form and the plan without it are within a few percent of each other, so
+    space_tune_rows must not choose between them by the clock.  Six tuned contexts give the untuned one's bits, and all are
+    within 1e-3 of the form without (the bar of the other tuning test)."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import layout as lo
+    shape = dataclasses.replace(SHAPES["7b"], name="7b-1l", n_layers=1, vocab=300)
+    w = all_weights(shape, seed=18, threads=16)
+    B, spec = 8, lo.paper_layout(5)
+    toks = np.random.default_rng(19).integers(0, shape.vocab, size=(B, spec.n_rows)).astype(np.int32)
+
+    def logits(tune=None, tuned=False):
+        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=spec.n_rows, max_ctx=128, tune=tune)
+        if tuned:
+            gm.tune_rows(B * spec.n_rows)
+        return _run_step(torch, gm, gm.kv_cache(B, 64), spec, toks, batch=B).logits.cpu().numpy()
+
+    plain, without = logits(), logits("widetail=0")
+    assert not np.array_equal(plain, without) and np.abs(plain - without).max() < 1e-3
+    for _ in range(6):
+        assert np.array_equal(logits(tuned=True), plain)
+
+
 @pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane
 @pytest.mark.parametrize("rows", [1, 16, 17, 32, 33, 48, 49, 96])
 def test_argmax_of_every_row_at_the_edges_of_the_rows_per_wave(torch_mod, rows, vocab):

@@ -1207,8 +1207,8 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         try {
             if (rc == SPACE_OK && best >= 0 && best_ms < 0.90f * default_ms)
                 ctx->wide_parts[key] = space_ctx::WideTuned{cands[best], best_ks};
-            else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_parts.count(key))
-                ctx->wide_plans[key] = base;  // what the next launch would plan again
+            else if (rc == SPACE_OK && ctx->wide_ks <= 0 && ctx->wide_cut_groups <= 0 && !ctx->wide_tail_force.pieces && !ctx->wide_parts.count(key))
+                ctx->wide_plans[key] = base;  // what the next launch would plan again (it applies the developer knobs)
         } catch (...) {  // no room to remember it: planned again
         }
     }

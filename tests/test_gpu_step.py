@@ -912,12 +912,9 @@ def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
     assert np.array_equal(got[others], clean[others])
 
 
-def test_tuned_contexts_keep_the_planned_tail(torch_mod):
-    """288 rows at 7B width, where the planner cuts the last pieces of gate / up over the contraction (the logits differ from
-    those of a context without such pieces): measured, that form and the plan without it are within a few percent of each other, so
-    space_tune_rows must not choose between them by the clock.  Six tuned contexts give the untuned one's bits, and all are
-    within 1e-3 of the form without (the bar of the other tuning test)."""
-    torch = torch_mod
+@pytest.fixture(scope="module")
+def one_layer_7b(torch_mod):
+    """logits(tune, tuned): 288 rows of one layer of 7B width, from a new context each time."""
     import dataclasses
     from paper_2402_11809_amd import layout as lo
     shape = dataclasses.replace(SHAPES["7b"], name="7b-1l", n_layers=1, vocab=300)
@@ -929,12 +926,28 @@ def test_tuned_contexts_keep_the_planned_tail(torch_mod):
         gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=spec.n_rows, max_ctx=128, tune=tune)
         if tuned:
             gm.tune_rows(B * spec.n_rows)
-        return _run_step(torch, gm, gm.kv_cache(B, 64), spec, toks, batch=B).logits.cpu().numpy()
+        return _run_step(torch_mod, gm, gm.kv_cache(B, 64), spec, toks, batch=B).logits.cpu().numpy()
 
-    plain, without = logits(), logits("widetail=0")
+    return logits
+
+
+def test_tuned_contexts_keep_the_planned_tail(one_layer_7b):
+    """288 rows at 7B width, where the planner cuts the last pieces of gate / up over the contraction (the logits differ from
+    those of a context without such pieces): measured, that form and the plan without it are within a few percent of each other, so
+    space_tune_rows must not choose between them by the clock.  Six tuned contexts give the untuned one's bits, and all are
+    within 1e-3 of the form without (the bar of the other tuning test)."""
+    plain, without = one_layer_7b(), one_layer_7b("widetail=0")
     assert not np.array_equal(plain, without) and np.abs(plain - without).max() < 1e-3
     for _ in range(6):
-        assert np.array_equal(logits(tuned=True), plain)
+        assert np.array_equal(one_layer_7b(tuned=True), plain)
+
+
+def test_forced_tail_holds_where_rows_are_tuned(one_layer_7b):
+    """SPACE_TUNE widetail=P:N is applied whether or not the row count was tuned (nothing else is 10 % ahead there: previous
+    test)."""
+    plain, forced = one_layer_7b(), one_layer_7b("widetail=6:2")
+    assert not np.array_equal(plain, forced) and np.abs(plain - forced).max() < 1e-3
+    assert np.array_equal(one_layer_7b("widetail=6:2", tuned=True), forced)
 
 
 @pytest.mark.parametrize("vocab", [1000, 32000])  # partials per row: fewer than a wave's lanes, several per lane

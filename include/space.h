@@ -354,7 +354,7 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *            4A + 3B + 2C + D groups of 32 rows: A pieces of 128 rows, B of 96, C of 64, D of 32, launched
  *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1) or any
  *            larger one (O = 2); the partial sums over the contraction stay those of the cut it replaces, and no
- *            piece is cut over the contraction;
+ *            piece is cut over the contraction (not by widetail= either);
  *   widetail=P:N   where a projection has complete sums, its last P pieces per XCD are cut over the contraction into N
  *            workgroups each (P * N up to 32) as far as it has that many; widetail=0: never by the library's own choice;
  *   wideks=N   that kernel sums the contraction in N parts (1, 2 or 4; plain-sum projections only) instead of

@@ -509,7 +509,7 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
             const space_ctx::WideTuned* tuned = it != ctx->wide_parts.end() ? &it->second : nullptr;
             p = plan_gemm_wide(w, m, epi, ctx->part_splits_max, ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0,
                                tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr, ctx->tail_sums && ctx->wide_tail);
-            if (ctx->wide_tail_force.pieces && p.ksplit == 1 && ctx->tail_sums) {
+            if (ctx->wide_tail_force.pieces && !knob && p.ksplit == 1 && ctx->tail_sums) {
                 WidePlan f = p;
                 f.tail = ctx->wide_tail_force;
                 if (wide_tail_fits(w.k_tiles, f)) p = f;

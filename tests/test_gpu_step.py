@@ -826,6 +826,24 @@ def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
         assert np.array_equal(x, y)
 
 
+def test_forced_cut_leaves_no_tail(torch_mod):
+    """widecut= and widetail= together: the forced cut has no piece cut over the contraction, i.e. the logits are those of the
+    default cut without tails, bit for bit; at another row count the forced tail still applies."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES["gqa128"]
+    w = all_weights(shape, seed=6)
+    spec = lo.paper_layout(5)
+    toks = np.random.default_rng(14).integers(0, shape.vocab, size=(8, spec.n_rows)).astype(np.int32)
+
+    def logits(B, tune):
+        gm = gc.make_gpu_model(shape, w, max_batch=8, max_rows=spec.n_rows, tune=tune)
+        return _run_step(torch, gm, gm.kv_cache(B, 160), spec, toks[:B], batch=B).logits.cpu().numpy()
+
+    assert np.array_equal(logits(8, "widecut=2:0:0:1:0,widetail=5:3"), logits(8, "widetail=0"))
+    assert not np.array_equal(logits(7, "widecut=2:0:0:1:0,widetail=5:3"), logits(7, "widetail=0"))
+
+
 @pytest.mark.parametrize("d,B,k", [(2080, 1, 1), (2080, 3, 3), (3104, 1, 5), (4096, 2, 3), (4128, 1, 4), (8192, 1, 5)])
 def test_norm_of_a_row_shared_by_workgroups(torch_mod, d, B, k):
     """Up to 48 rows of models wider than 2048: residual add and norm in workgroups of 1024 columns, the row's factor

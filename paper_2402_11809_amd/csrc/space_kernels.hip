@@ -758,7 +758,9 @@ __device__ __forceinline__ void make_key_plan(const KeyPlan& kp, const int32_t* 
 
 // One workgroup per block row: the embedding row (the mask embedding on mask rows) becomes the residual
 // stream, the row's position id and its rotary factors (out of the table) are noted, and the first
-// layer's RMSNorm goes with it -- one launch instead of two at the head of every step.
+// layer's RMSNorm goes with it -- one launch instead of two at the head of every step.  PLAN: one workgroup more, in front,
+// makes the table of the attention's workgroups beside the rows (in front of row 0's own work it lengthened the launch by
+// 2 - 3 us).
 template <bool PLAN>
 __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, const uint16_t* embed, int vocab, int d,
                                                      const int32_t* info, const int32_t* rel_pos, int L, int m,
@@ -768,13 +770,14 @@ __global__ __launch_bounds__(1024) void embed_kernel(const int32_t* tokens, cons
                                                      const uint16_t* __restrict__ w, float eps, uint16_t* __restrict__ xn,
                                                      XtShape xs, int32_t* counts, int n_counts, KeyPlan plan) {
     __shared__ float sh[16];
-    const int row = xcd_grouped_row(blockIdx.x), nvec = d >> 2, nthr = blockDim.x;
-    if (row >= m) return;  // whole workgroup
-    if (row == 0)
+    const int nvec = d >> 2, nthr = blockDim.x, row = xcd_grouped_row(blockIdx.x - PLAN);
+    if (PLAN ? blockIdx.x == 0 : row == 0)
         for (int i = threadIdx.x; i < n_counts; i += nthr) counts[i] = 0;
-    if constexpr (PLAN) {
-        if (row == 0 && threadIdx.x < 64) make_key_plan(plan, kv_len);
+    if (PLAN && blockIdx.x == 0) {
+        if (threadIdx.x < 64) make_key_plan(plan, kv_len);
+        return;
     }
+    if (row >= m) return;  // whole workgroup
     u32x2 wv[2];
     norm_w_load(w, d, wv);
     const int b = row / L, r = row % L;
@@ -819,7 +822,7 @@ hipError_t launch_embed(const int32_t* tokens, const uint16_t* embed, int vocab,
     if (d > 8192 || (d & 3) || n_pos < 1 || plan.batch > 64 || (plan.slots && plan.slots < plan.batch)) return hipErrorInvalidValue;
     const int nvec = d >> 2;
     const int threads = nvec >= 1024 ? 1024 : round_up(nvec, 64);
-    hipLaunchKernelGGL(plan.slots ? embed_kernel<true> : embed_kernel<false>, dim3(round_up(batch * lay.L, 64)), dim3(threads), 0, s, tokens, embed, vocab, d, lay.info,
+    hipLaunchKernelGGL(plan.slots ? embed_kernel<true> : embed_kernel<false>, dim3(round_up(batch * lay.L, 64) + (plan.slots ? 1 : 0)), dim3(threads), 0, s, tokens, embed, vocab, d, lay.info,
                        lay.rel_pos, lay.L, batch * lay.L, kv_len, cos_tab, sin_tab, n_pos, head_dim, x, pos, cos_t, sin_t, faults,
                        norm_w, eps, xn, xs, counts, counts ? n_counts : 0, plan);
     return hipGetLastError();

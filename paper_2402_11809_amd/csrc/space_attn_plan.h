@@ -1,5 +1,6 @@
-// Which workgroup of a batch's attention takes which place in the order by length: the same functions on the host and
-// in the kernel (constexpr functions are both), plain C++ so that they can be checked without a GPU.
+// How the key-split attention of a batch deals its workgroups out by length: into how many parts each sequence is cut,
+// where the parts lie in the table, and which workgroup takes which place of it.  The same functions on the host and in the
+// kernels (constexpr functions are both), plain C++ so that they can be checked without a GPU.
 #pragma once
 
 namespace space {
@@ -27,6 +28,71 @@ constexpr int attention_item(int place, int places, int shared) {
     if (place < shared) return places - 2 * shared + place;
     if (place >= places - shared) return places - 1 - (place - (places - shared));
     return place - shared;
+}
+
+// A workgroup's share of a batch: part `part` of n_parts over the keys of sequence b, `len` cached ones; b < 0: none.  The table
+// holds the parts that every (head, query group) has, largest first, the parts of a sequence one behind the other.
+constexpr int kMaxKeyParts = 16, kMaxKeySlots = 512;
+struct KeyPart {
+    int b, part, n_parts, len;
+};
+
+// Chunks of a sequence, the block's included (0: no sequence), and the most parts it may have: at least four cached chunks
+// each, so that no wave of a part is without one.
+struct KeySeq {
+    int chunks, most;
+};
+constexpr KeySeq key_seq(int cached_chunks, int block_chunks) {
+    const int most = cached_chunks / 4 < kMaxKeyParts ? cached_chunks / 4 : kMaxKeyParts;
+    return KeySeq{cached_chunks + block_chunks, most > 1 ? most : 1};
+}
+// Parts of a sequence if none is to have more than `size` chunks (as far as it may be cut); at size >= longest: one.
+constexpr int key_parts(const KeySeq& s, int size, int longest) {
+    if (s.chunks == 0) return 0;
+    if (size >= longest) return 1;
+    const int n = (s.chunks + size - 1) / size;
+    return n < s.most ? n : s.most;
+}
+constexpr int key_part_chunks(const KeySeq& s, int n) { return n ? (s.chunks + n - 1) / n : 0; }
+
+// What the busiest CU spends on `parts` parts of at most `largest` chunks: these and, worth kPartStaging chunks, the staging of
+// the block; beyond a workgroup per CU the mean over the CUs, of which 232 are taken to be busy, counts as well.
+constexpr int kPartStaging = 16;
+constexpr int key_cut_cost(int parts, int largest, int total, int streams) {
+    const int alone = largest + kPartStaging;
+    const int mean = parts * streams > 256 ? (total + parts * kPartStaging) * streams / 232 : 0;
+    return alone > mean ? alone : mean;
+}
+
+struct KeyCut {
+    int size;   // for key_parts
+    int parts;  // of all sequences
+};
+// The smallest largest part that the slots allow; no cut (size = longest) where it is not 8 % ahead of none.
+//   longest, total  chunks of the longest sequence and of all of them;  parts_at(size): parts of all sequences
+template <class PartsAt>
+constexpr KeyCut key_cut(int batch, int slots, int streams, int longest, int total, PartsAt parts_at) {
+    const KeyCut none{longest, batch};
+    if (slots <= batch) return none;
+    int size = total / slots > 1 ? total / slots : 1, parts = batch;
+    for (;;) {  // ends: at size >= longest every sequence has one part
+        parts = parts_at(size);
+        if (size >= longest || parts <= slots) break;
+        size += size >> 3 > 1 ? size >> 3 : 1;
+    }
+    if (key_cut_cost(parts, size, total, streams) * 100 > key_cut_cost(batch, longest, total, streams) * 92) return none;
+    return KeyCut{size, parts};
+}
+
+// First place of sequence b in the table: the parts of sequences with larger ones lie in front (equal ones by index).
+template <class Chunks, class Parts>
+constexpr int key_first_place(int b, int own_chunks, int batch, Chunks part_chunks_of, Parts parts_of) {
+    int first = 0;
+    for (int i = 0; i < batch; ++i) {
+        const int other = part_chunks_of(i), n = parts_of(i);
+        first += other > own_chunks || (other == own_chunks && i < b) ? n : 0;
+    }
+    return first;
 }
 
 }  // namespace space

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "space_attn_plan.h"
 #include "space_wide_plan.h"
 
 namespace space {
@@ -145,12 +146,7 @@ struct LayoutDev {
     int L, G;
 };
 
-// A workgroup's share of a batch in the key-split attention: part `part` of n_parts over the keys of sequence b, `len` cached
-// ones; b < 0: none.  The table holds the parts of every (head, query group), largest first.
-constexpr int kMaxKeyParts = 16, kMaxKeySlots = 512;
-struct KeyPart {
-    int b, part, n_parts, len;
-};
+// What the embedding launch needs to make the table of a batch's attention workgroups (space_attn_plan.h).
 struct KeyPlan {
     KeyPart* table;
     int slots;  // entries, at least batch; 0: no plan

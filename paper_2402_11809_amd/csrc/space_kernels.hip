@@ -14,7 +14,6 @@
 // The contraction is order independent, so any assignment of slots to real indices is fine as
 // long as A and B agree.
 #include "space_kernels.h"
-#include "space_attn_plan.h"
 #include "space_device.h"
 
 #include <limits.h>
@@ -712,48 +711,29 @@ __device__ __forceinline__ void norm_row_tail(const f32x4 (&v)[2], float ss, flo
     }
 }
 
-// How the key-split attention of a batch deals its workgroups out by length (KeyPlan); one wave, once per forward: made by every
-// workgroup for itself it cost them 1 - 2 us a layer.  Every sequence gets one part, or, with more slots than sequences, the
-// slots are dealt out so that the largest part is as small as they allow (a part has at least four chunks, so that no wave of it is
-// without one; at most kMaxKeyParts).  What a CU spends on a part is its chunks and, worth kPartStaging of these, the
-// staging of the block; beyond a workgroup per CU the mean over the CUs counts as well, and a cut has to be 8 % ahead of none.
-constexpr int kPartStaging = 16;
+// The table of a batch's attention workgroups (space_attn_plan.h), one sequence per lane of one wave, once per forward: made by
+// every workgroup for itself it cost them 1 - 2 us a layer.
 __device__ __forceinline__ void make_key_plan(const KeyPlan& kp, const int32_t* kv_len) {
     const int lane = threadIdx.x & 63, batch = kp.batch;
     const int len = lane < batch ? min(max(kv_len[lane], 0), kp.capacity) : 0;
-    const int chunks = (len + kAttnKeys - 1) / kAttnKeys, w = lane < batch ? chunks + kp.n_blk : 0;
+    const KeySeq own = lane < batch ? key_seq((len + kAttnKeys - 1) / kAttnKeys, kp.n_blk) : KeySeq{0, 1};
     int longest = 0, total = 0;
     for (int i = 0; i < batch; ++i) {
-        const int v = __builtin_amdgcn_readlane(w, i);
+        const int v = __builtin_amdgcn_readlane(own.chunks, i);
         longest = max(longest, v);
         total += v;
     }
-    const int most = max(min(chunks >> 2, kMaxKeyParts), 1);
-    int size = max(total / kp.slots, 1), n = lane < batch ? 1 : 0, parts = batch;
-    if (kp.slots > batch) {
-        for (;;) {  // ends: at size >= longest every sequence has one part
-            n = lane < batch ? size >= longest ? 1 : min((w + size - 1) / size, most) : 0;
-            parts = 0;
-            for (int i = 0; i < batch; ++i) parts += __builtin_amdgcn_readlane(n, i);
-            if (size >= longest || parts <= kp.slots) break;
-            size += max(size >> 3, 1);
-        }
-        auto cost = [&](int k, int largest) {
-            return max(largest + kPartStaging, k * kp.streams > 256 ? (total + k * kPartStaging) * kp.streams / 232 : 0);
-        };
-        if (cost(parts, size) * 100 > cost(batch, longest) * 92) {
-            n = min(n, 1);
-            parts = batch;
-        }
-    }
-    const int part = n ? (w + n - 1) / n : 0;
-    int first = 0;  // parts of sequences with larger ones
-    for (int i = 0; i < batch; ++i) {
-        const int other = __builtin_amdgcn_readlane(part, i), others = __builtin_amdgcn_readlane(n, i);
-        first += other > part || (other == part && i < lane) ? others : 0;
-    }
+    const KeyCut cut = key_cut(batch, kp.slots, kp.streams, longest, total, [&](int size) {
+        const int n = key_parts(own, size, longest);
+        int parts = 0;
+        for (int i = 0; i < batch; ++i) parts += __builtin_amdgcn_readlane(n, i);
+        return parts;
+    });
+    const int n = key_parts(own, cut.size, longest), part = key_part_chunks(own, n);
+    const int first = key_first_place(lane, part, batch, [&](int i) { return __builtin_amdgcn_readlane(part, i); },
+                                      [&](int i) { return __builtin_amdgcn_readlane(n, i); });
     for (int j = 0; j < n; ++j) kp.table[first + j] = KeyPart{lane, j, n, len};
-    for (int r = parts + lane; r < kp.slots; r += 64) kp.table[r].b = -1;
+    for (int r = cut.parts + lane; r < kp.slots; r += 64) kp.table[r].b = -1;
 }
 
 // One workgroup per block row: the embedding row (the mask embedding on mask rows) becomes the residual

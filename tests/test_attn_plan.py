@@ -1,4 +1,5 @@
-"""CPU check of how the workgroups of a batch's attention are paired on the CUs (csrc/space_attn_plan.h)."""
+"""CPU checks of how the workgroups of a batch's attention are paired on the CUs and how its keys are cut by length
+(csrc/space_attn_plan.h)."""
 import os
 import shutil
 import subprocess
@@ -33,16 +34,101 @@ int main() {
 }
 """
 
+_TABLE_PROGRAM = r"""
+#include <algorithm>
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "space_attn_plan.h"
+using namespace space;
 
-def test_every_place_takes_one_item(tmp_path):
-    """Head counts and batches of every size: no item of the table is left out, taken twice or outside it."""
+static long tables = 0, cuts = 0, full = 0, wrong = 0;
+
+static void check(const std::vector<int>& lens, int block_chunks, int slots, int streams) {
+    const int batch = (int)lens.size();
+    std::vector<KeySeq> seq;
+    int longest = 0, total = 0;
+    for (int len : lens) {
+        seq.push_back(key_seq((len + 31) / 32, block_chunks));
+        longest = std::max(longest, seq.back().chunks);
+        total += seq.back().chunks;
+    }
+    const KeyCut cut = key_cut(batch, slots, streams, longest, total, [&](int size) {
+        int parts = 0;
+        for (const KeySeq& s : seq) parts += key_parts(s, size, longest);
+        return parts;
+    });
+    std::vector<int> n, part;
+    for (const KeySeq& s : seq) {
+        n.push_back(key_parts(s, cut.size, longest));
+        part.push_back(key_part_chunks(s, n.back()));
+    }
+    std::vector<KeyPart> table(slots, KeyPart{-2, 0, 0, 0});
+    bool ok = cut.parts <= slots && slots <= kMaxKeySlots;
+    int parts = 0, largest = 0;
+    for (int b = 0; b < batch; ++b) {
+        const int first = key_first_place(b, part[b], batch, [&](int i) { return part[i]; }, [&](int i) { return n[i]; });
+        ok = ok && n[b] >= 1 && n[b] <= kMaxKeyParts && first >= 0 && first + n[b] <= cut.parts;
+        ok = ok && (n[b] == 1 || ((lens[b] + 31) / 32 >= 4 * n[b] && part[b] >= 4));  // every wave has a cached chunk
+        for (int j = 0; ok && j < n[b]; ++j) {
+            ok = table[first + j].b == -2;  // nobody else's place
+            table[first + j] = KeyPart{b, j, n[b], lens[b]};
+        }
+        parts += n[b];
+        largest = std::max(largest, part[b]);
+    }
+    ok = ok && parts == cut.parts;
+    for (int r = 0; ok && r < slots; ++r) ok = (table[r].b >= 0) == (r < parts);  // the rest is marked as left over
+    for (int r = 1; ok && r < parts; ++r) ok = part[table[r].b] <= part[table[r - 1].b];  // largest first
+    const bool cutting = parts > batch;
+    ok = ok && (!cutting || (slots > batch && largest < longest));
+    ++tables;
+    cuts += cutting;
+    full += parts == slots;
+    if (!ok && wrong++ < 5) printf("batch %d, block %d, slots %d, streams %d: wrong table\n", batch, block_chunks, slots, streams);
+}
+
+int main() {
+    std::mt19937 rng(1);
+    auto upto = [&](int n) { return (int)(rng() % (unsigned)n); };
+    for (int streams = 1; streams <= 512; streams += streams < 72 ? 1 : 8)
+        for (int batch = 2; batch <= 64; ++batch)
+            for (int kind = 0; kind < 6; ++kind) {
+                std::vector<int> lens(batch);
+                const int most = 1 << (6 + upto(11));
+                for (int b = 0; b < batch; ++b)
+                    lens[b] = kind == 0 ? most : kind == 1 ? upto(most) : kind == 2 ? (b == batch / 2 ? most : upto(40))
+                              : kind == 3 ? 0 : kind == 4 ? most * b / batch : (b & 1 ? most : most / 3);
+                const int slots[] = {batch, batch + 1, 256 / streams, 512 / streams, batch + upto(512)};
+                for (int s : slots)
+                    if (s >= batch && s <= kMaxKeySlots) check(lens, 1 + upto(32), s, streams);
+            }
+    printf("%ld tables, %ld with cuts, %ld without a slot to spare, %ld wrong\n", tables, cuts, full, wrong);
+    return wrong || tables < 10000 || cuts < 1000 || full < 1000;
+}
+"""
+
+
+def _run(tmp_path, program):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         pytest.skip("no C++ compiler")
     src = tmp_path / "attn_plan.cpp"
-    src.write_text(_PROGRAM)
+    src.write_text(program)
     exe = tmp_path / "attn_plan"
-    subprocess.run([cxx, "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2402_11809_amd", "csrc"), str(src), "-o", str(exe)],
+    subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2402_11809_amd", "csrc"), str(src), "-o", str(exe)],
                    check=True)
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, out.stdout
+
+
+def test_every_place_takes_one_item(tmp_path):
+    """Head counts and batches of every size: no item of the table is left out, taken twice or outside it."""
+    _run(tmp_path, _PROGRAM)
+
+
+def test_every_part_has_one_place_in_the_table(tmp_path):
+    """Batches of 2 to 64 sequences (equal, ragged, one long, empty, ascending, two lengths), blocks of 1 to 32 chunks and every
+    number of slots: the parts fit the slots, every part of every sequence has one place, those of a sequence lie side by side, larger
+    ones in front; a sequence is cut into at most 16 parts of at least four cached chunks; left-over slots are at the end."""
+    _run(tmp_path, _TABLE_PROGRAM)

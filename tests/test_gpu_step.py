@@ -430,7 +430,7 @@ def test_measured_cut_and_split_stay_within_rounding(torch_mod, B, k):
 
 
 def test_every_row_cut_gives_the_same_bits(torch_mod):
-    """288 rows = 9 groups of 32 rows, cut in every piece size and both launch orders (forced through
+    """288 rows = 9 groups of 32 rows, cut in every piece size and all launch orders (forced through
     SPACE_TUNE widecut=): logits, indices and accepted counts equal the default cut's bit for bit."""
     torch = torch_mod
     from paper_2402_11809_amd import binding, layout as lo
@@ -443,7 +443,8 @@ def test_every_row_cut_gives_the_same_bits(torch_mod):
     om = gc.oracle_model(shape, w)
     okvs = [gc.synthetic_oracle_kv(om, seed=60 + b, ctx=9 * b + 4, std=0.5) for b in range(B)]
     ref = None
-    for cut in (None, "2:0:0:1:0", "0:3:0:0:0", "0:3:0:0:1", "0:1:3:0:1", "0:0:4:1:0", "1:0:2:1:1", "0:0:0:9:1", "1:1:1:0:0"):
+    for cut in (None, "2:0:0:1:0", "0:3:0:0:0", "0:3:0:0:1", "0:1:3:0:1", "0:0:4:1:0", "1:0:2:1:1", "0:0:0:9:1", "1:1:1:0:0",
+                "2:0:0:1:2", "0:1:3:0:2", "1:1:1:0:2"):
         gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune=None if cut is None else "widecut=" + cut)
         cache = binding.KVCache(gm, B, 160)
         for b in range(B):
@@ -799,7 +800,7 @@ def test_query_tiles_per_workgroup_of_long_blocks(torch_mod, shape_name, B, k, c
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=6), B, k, None, gc.LOGIT_TIGHT, ctxs=ctxs, capacity=736)
 
 
-@pytest.mark.parametrize("cut", ["2:0:0:1:0", "0:3:0:0:1", "0:0:4:1:0", "0:0:0:9:1", "1:1:1:0:0"])
+@pytest.mark.parametrize("cut", ["2:0:0:1:0", "0:3:0:0:1", "0:0:4:1:0", "0:0:0:9:1", "1:1:1:0:0", "1:1:1:0:2", "2:0:0:1:2"])
 def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
     """As the test with contractions that are never split, at 1024 wide (32 and 43 contraction tiles): 288 rows,
     where the planner takes two partial sums for QKV, O and down.  A forced cut keeps the partial sums of the default
@@ -900,6 +901,36 @@ def test_keys_of_a_batch_cut_by_length(torch_mod, shape_name, B, k, order):
     toks = np.random.default_rng(16).integers(0, shape.vocab, size=(B, spec.n_rows)).astype(np.int32)
     got = [_run_step(torch, gm, cache, spec, toks, batch=B).logits.cpu().numpy().copy() for _ in range(3)]
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("shape_name,B,rows,order", [("gqa-small", 9, 112, "one-long"), ("gqa-small", 6, 97, "ragged"), ("gqa-small", 24, 112, "ragged"),
+                                                     ("gqa-small", 12, 130, "equal"), ("gqa128", 5, 200, "one-long")])
+def test_prompt_chunks_of_a_batch_dealt_out_by_length(torch_mod, shape_name, B, rows, order):
+    """Prompt chunks (three to seven query groups) of several sequences behind contexts of 0 to 700 positions: keys cut by length and
+    merged per query group, left-over slots, more workgroups than fit at once, equal lengths.  The keys and values that
+    the second layer stores, i.e. what the first layer's attention made of the chunk, against the oracle's prefill."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name]
+    w = all_weights(shape, seed=20)
+    lens = {"ragged": [(97 * b * b) % 701 for b in range(B)], "one-long": [9 * b for b in range(B - 1)] + [700], "equal": [600] * B}[order]
+    lens[B // 2] = 680
+    spec = lo.prefill_layout(rows)
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=1024)
+    om = gc.oracle_model(shape, w)
+    cache = gm.kv_cache(B, 928)
+    okvs = [gc.synthetic_oracle_kv(om, seed=30 + b, ctx=c, std=0.5) for b, c in enumerate(lens)]
+    for b in range(B):
+        gc.upload_oracle_kv(torch, cache, b, okvs[b])
+    toks = np.random.default_rng(21).integers(0, shape.vocab, size=(B, rows)).astype(np.int32)
+    gm.prefill(torch.from_numpy(toks).cuda(), gm.layout(spec), cache)
+    torch.cuda.synchronize()
+    assert gm.device_faults() == 0
+    for b, c in enumerate(lens):
+        so.prefill(om, okvs[b], toks[b])
+        gk, gv = gc.download_kv_rows(cache, 1, b, c, c + rows)
+        gc.assert_bf16_close(gk, okvs[b].k[1][c:], f"seq {b} K", min_same=0.9)
+        gc.assert_bf16_close(gv, okvs[b].v[1][c:], f"seq {b} V", min_same=0.9)
 
 
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])

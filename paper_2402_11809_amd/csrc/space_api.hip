@@ -112,7 +112,7 @@ struct space_ctx {
     // SPACE_TUNE widetail=: 0 = no pieces that are cut over the contraction, P:N = the last P pieces per XCD in N parts
     int wide_tail = 1;
     WideTail wide_tail_force{};
-    float* tail_sums = nullptr;  // their sums and arrival counts (GemmLaunch)
+    float* tail_sums = nullptr;  // their sums (within part) and arrival counts (GemmLaunch)
     int32_t* tail_count = nullptr;  // (within counts)
     std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
@@ -357,10 +357,10 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
             }
         }
     }
+    bool may_tail = false;  // pieces of a projection may be cut over the contraction
     if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv)) {
         max_splits = std::max(max_splits, 4);
-        const bool tails = ctx->wide_tail_force.pieces || (ctx->wide_tail && ceil_div(std::max(std::max(d, hd), f), kTileK) >= kWideTailMinK);
-        if (tails && dev_alloc(ctx, &ctx->tail_sums, 8 * kWideTailSlots * kWideTailFloats, false)) ctx->err.clear();  // 32 MB; no tails without
+        may_tail = ctx->wide_tail_force.pieces || (ctx->wide_tail && ceil_div(std::max(std::max(d, hd), f), kTileK) >= kWideTailMinK);
     }
     ctx->part_splits_max = max_splits;
     const size_t plane_tile = 2 * 64 * 8;  // hi + lo plane of one 16 x 32 activation tile, in elements
@@ -369,7 +369,17 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     if ((rc = dev_alloc(ctx, &ctx->x, M * d, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->ss, (size_t)kResidMaxGroups * kResidMaxRows, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->xn, rt * ctx->kt_d * plane_tile, true))) return rc;
-    if ((rc = dev_alloc(ctx, &ctx->part, ctx->part_stride * ctx->part_splits_max, true))) return rc;
+    // A projection with such pieces has one complete sum per output, so their sums lie where further partial sums would; the few
+    // MB that short contexts add for them may fail to be there (no such pieces then).
+    const size_t part_n = ctx->part_stride * ctx->part_splits_max, tail_at = (ctx->part_stride + 63) / 64 * 64;
+    const size_t tail_n = tail_at + 8 * kWideTailSlots * kWideTailFloats;
+    if (may_tail && tail_n > part_n && (rc = dev_alloc(ctx, &ctx->part, tail_n, true))) {
+        if (rc != SPACE_ENOMEM) return rc;
+        ctx->err.clear();
+        may_tail = false;
+    }
+    if (!ctx->part && (rc = dev_alloc(ctx, &ctx->part, part_n, true))) return rc;
+    if (may_tail) ctx->tail_sums = ctx->part + tail_at;
     if ((rc = dev_alloc(ctx, &ctx->q, 2 * ctx->q_plane, true))) return rc;
     // block K/V staging: one slice per head, or one per (head, query tile) on the fused path
     const size_t stage_rows = std::max<size_t>(ctx->lp_max, (size_t)(kHeadAttnMaxRows / 16) * round_up(kHeadAttnMaxRows, kAttnKeys));
@@ -386,12 +396,13 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
         ctx->attn_wg_max = std::max(ctx->attn_wg_max, wg);
     }
     if ((rc = dev_alloc(ctx, &ctx->o_part, bh * wg_rows * c.head_dim, true))) return rc;
-    if ((rc = dev_alloc(ctx, &ctx->ml_part, bh * wg_rows * 2, true))) return rc;
     ctx->o_part_rows = bh * wg_rows;
     const size_t n_attn = bh * ceil_div(c.max_rows, 16);  // (sequence, head, query group) triples
     ctx->n_counts = (int)n_attn + 8 * kWideTailSlots;
-    const size_t count_parts = ceil_div(ctx->n_counts * (int)sizeof(int32_t), (int)sizeof(KeyPart));
-    if ((rc = dev_alloc(ctx, &ctx->key_plan, (size_t)kMaxKeySlots + count_parts, true))) return rc;
+    // one allocation: maxima and sums of the partial attention outputs, the table of a batch's workgroups, arrival counts
+    const size_t ml_n = (bh * wg_rows * 2 + 3) / 4 * 4, table_n = kMaxKeySlots * sizeof(KeyPart) / sizeof(float);
+    if ((rc = dev_alloc(ctx, &ctx->ml_part, ml_n + table_n + ctx->n_counts, true))) return rc;
+    ctx->key_plan = (KeyPart*)(ctx->ml_part + ml_n);
     ctx->counts = (int32_t*)(ctx->key_plan + kMaxKeySlots);
     ctx->tail_count = ctx->counts + n_attn;
     if ((rc = dev_alloc(ctx, &ctx->arg_val, M * ctx->arg_groups, true))) return rc;

@@ -991,6 +991,27 @@ def test_tuned_contexts_keep_the_planned_tail(one_layer_7b):
         assert np.array_equal(one_layer_7b(tuned=True), plain)
 
 
+def test_tails_take_no_memory_of_their_own(torch_mod):
+    """A context of 288 rows at 7B width, whose partial sums of split contractions have room for those of the tails: as much device memory
+    as one without tails (allocations are whole pages of 2 MB)."""
+    torch = torch_mod
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["tiny"], name="7b-wide", n_layers=1, d_model=4096, n_heads=32, head_dim=128, ffn=256, vocab=300)
+    w = all_weights(shape, seed=22)
+
+    def free():
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    models, taken = [], []
+    for tune in (None, "widetail=0", None):  # the first one also pays for what the process allocates once
+        before = free()
+        models.append(gc.make_gpu_model(shape, w, max_batch=8, max_rows=36, max_ctx=128, tune=tune))
+        taken.append(before - free())
+    assert abs(taken[2] - taken[1]) <= 4 << 20, taken
+
+
 def test_forced_tail_holds_where_rows_are_tuned(one_layer_7b):
     """SPACE_TUNE widetail=P:N is applied whether or not the row count was tuned (nothing else is 10 % ahead there: previous
     test)."""

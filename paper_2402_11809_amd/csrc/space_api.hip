@@ -814,7 +814,8 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         return launch_gemm_resid(r, s);
     };
     // Few rows again, but with split sums: a row's columns are shared by workgroups where it has more than two of them
-    // (steps of 2 layers, 36 rows: 1024 wide 103.5 / 103.8 us, 512 wide 88.8 / 89.5, 4096 wide 277.8 / 274.8).
+    // (steps of 2 layers, 36 rows, a workgroup per row / shared: 512 wide 88.8 / 89.5 us, 1024 wide 103.5 / 103.8, 2560 wide
+    // level, beyond that ahead: at resid_part_kernel).
     const bool norm_parts = !resid && M <= kResidMaxRows && M < wide_from && d > 2048;
     auto add_norm = [&](int splits, const uint16_t* norm_w) {
         if (!norm_parts) return launch_resid_norm(ctx->x, ctx->part, splits, ctx->part_stride, d, norm_w, c.rms_eps, M, d, ctx->xn, xs, s);

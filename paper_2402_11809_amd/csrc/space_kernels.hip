@@ -859,9 +859,11 @@ hipError_t launch_resid_norm(float* x, const float* part, int splits, size_t spl
 
 // The same for up to kResidMaxRows rows, without the row's factor (as gemm_resid_kernel leaves it): nothing has to wait
 // for the whole row, so a row is shared by workgroups of 1024 columns.  What bounds it is how fast one CU gets the row's
-// partial sums, 5 to 9 times 16 KB at 4096 columns.  Step of two 7B layers, 36 rows 277.8 -> 274.8 us (the launch 5.4 -> 4.4,
-// 0.3 more in the projections behind), 16 rows 238.7 -> 235.8, all 32 layers 3653 -> 3579; one 70B layer 419.6 ->
-// 416.1.
+// partial sums, 5 to 9 times 16 KB at 4096 columns.  In traces the launch goes 5.5 -> 5.2 us at 4096 columns, 5.3 -> 5.1 at 5120
+// and 7.8 -> 5.2 at 8192, and the next one need not wait for its slowest row; the projections behind pay for the factor.  Steps of
+// two layers, a workgroup per row / shared, in turn: 36 rows 2560 wide 189.7 / 189.7 us, 3072 230.7 / 230.0, 4096 280.2 / 277.9, 5120
+// 366.1 / 365.1, 6144 530.0 / 528.2, 8192 708.7 / 703.8; 16 rows 154.1 / 152.6, 190.1 / 188.1, 240.2 / 237.0, 319.2 /
+// 316.9, 450.5 / 445.7, 655.3 / 649.5; all 32 layers of 7B, 36 rows, 3649 / 3603.
 constexpr int kScaleThreads = 256;
 __global__ __launch_bounds__(kScaleThreads) void resid_part_kernel(float* __restrict__ x, const float* __restrict__ part, int splits,
                                                                    size_t split_stride, int ldp, const uint16_t* __restrict__ w, int m,
@@ -2302,8 +2304,10 @@ static int attention_query_tiles(const AttnLaunch& a) {
 // sequence leaves one or two each, i.e. where a long sequence cannot be given more, and the chip has room for more workgroups at
 // once.  Attention in us per layer, equal parts / by length (7B, 36 rows unless stated, 100 .. 4000 positions): 8 sequences
 // 92 / 67, 6 of them 65 / 55, 5 of 25 rows 31.9 / 26.8, 4 of 81 rows 54 / 42, 3 of them 35.9 / 31.4, 8 of 16 rows 44 / 30, 6 of 9 rows
-// 48 / 36; 13B, 3, 6 and 8 of them 40.9 / 33.8, 60.9 / 55.4, 51 / 38; 70B, 6 of 16 rows 36 / 30; of equal lengths level (3 of them
-// 30.8 / 30.6, 6 39.7 / 39.9, 8 47.1 / 47.8, 8 of 16 rows 37.5 / 38.1).  With four parts each anyway there is nothing to gain (2
+// 48 / 36; 13B, 3, 6 and 8 of them 40.9 / 33.8, 60.9 / 55.4, 51 / 38; 70B, 6 of 16 rows 36 / 30.  Of equal
+// lengths 3 of them 30.8 / 30.6, 6 39.7 / 39.9, 8 47.1 / 47.8, 8 of 16 rows 37.5 / 38.1: a workgroup knows its sequence only when
+// the table is there (whole steps of 8 equal sequences of 9 rows, 700 positions: two layers 373.1 / 374.4, six 973.9 /
+// 976.2, i.e. 0.4 us a layer).  With four parts each anyway there is nothing to gain (2
 // sequences 24.9 / 25.1 and 23.5 / 24.5, 8 with 8 heads 23.3 / 23.8), and a lone sequence is better merged by all CUs
 // (attn_combine_kernel: 7B 23.5 / 26.8).
 static int attention_slots(const AttnLaunch& a, int QG, int TQ) {
@@ -2759,7 +2763,8 @@ __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K
 // L2 or the cache behind it, 1 - 2 us): four rows to a CU, so that up to 1024 rows read at the same time.  648 rows, 50
 // kept: 37.8 -> 25.6 us (1.3 rounds of the first form).  The rule, rows up to 512, is where the first form needs a
 // second round (both launches of a call, first / second form: 486 rows, 10 kept, 21.8 / 23.1; 36 rows 12.0 / 13.2; 567
-// rows, 50 kept, 43.8 / 31.0).
+// rows, 50 kept, 43.8 / 31.0).  (The second form does not quite fit the 64 registers that four rows to a CU leave: 6 of them
+// spill, 16 bytes a thread.)
 template <int NT, bool HELD>
 __global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
     TopLds& s = top_lds();

@@ -162,7 +162,8 @@ struct WideTail {
 // A part costs its share of the piece and 3 us to write the sums and count itself; the one that ends last another
 // 2 us, and 2 us to read each part's sums: a wave has room for one part's in flight.  (Measured at 7B: 256 rows, O and down, all
 // pieces in 8 parts 19 -> 35 and 42 -> 54 us; QKV at 208 rows, 12 of 18 pieces in 2 parts 49 -> 50; but gate / up, one piece
-// of 33 in 4 to 16 parts, 288 rows 89 -> 82 and 333 rows 107 -> 94: there all of it lies beside whole pieces.)
+// of 33 in 4 to 16 parts, 288 rows 89 -> 82 and 333 rows 107 -> 94: there all of it lies beside whole pieces.  These are launches
+// whose weights come from memory; in two layers run again and again, most of them out of the cache behind L2, 288 rows are level.)
 inline int64_t wide_part_cost(int g, int kt, int parts, bool last) {
     return wide_piece_cost(g, round_up(ceil_div(kt, parts), kWideDepth)) + 220 + (last ? 147 + 147 * parts : 0);
 }
@@ -174,7 +175,9 @@ inline int64_t wide_part_cost(int g, int kt, int parts, bool last) {
 // the last size.  Measured, without / with: 7B gate / up at 208 and 224 rows 84 / 74 us, 333 and 352 rows 113 / 99, QKV at
 // 704 rows 118 / 113; 13B gate / up at 288 and 333 rows 133 / 122 and 159 / 148; 70B gate / up at 512 and 896 rows 688 /
 // 635 and 1203 / 1117.  5 to 10 % ahead in the model is within what cards differ by: 7B QKV at 648 and 1024 rows 102.4 / 101.7 and
-// 161 / 157 on one, 108.9 / 113.0 and level on another that holds a lower clock.
+// 161 / 157 on one, 108.9 / 113.0 and level on another that holds a lower clock.  Whole prompts of six layers, us a
+// layer: 7B 208 rows -4.4, 288 -3.2, 320 -5.4, 333 and 352 -11.6; 13B 288 rows -5.5, 333 and 352 -4.2; level (-2.6 .. +1.7,
+// which is also what runs differ by) at the other 23 of 32 row counts from 208 to 896.
 inline bool plan_wide_tail(int n_groups, int n, int k_tiles, int m, const WideCut& c, WideCut* cut, WideTail* tail) {
     const int groups = ceil_div(ceil_div(m, 16), 2), gk8 = ceil_div(n_groups, 8);
     if (groups > kWideSearchGroups || k_tiles < kWideTailMinK) return false;

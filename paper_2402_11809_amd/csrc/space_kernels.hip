@@ -2527,8 +2527,9 @@ hipError_t launch_verify(const VerifyLaunch& v, hipStream_t s) {
 // ------------------------------------------------------------------------------------------
 // verification by rejection sampling (Algorithm 1 as printed; appendix "Random Sampling")
 // ------------------------------------------------------------------------------------------
-// Kernel 1, one workgroup per block row: the top_k largest logits in descending order (ties: lowest
-// id), softmax over them, the shortest prefix whose mass reaches top_p, renormalised.  The top_k-th largest of 256
+// One workgroup per block row: the top_k largest logits in descending order (ties: lowest
+// id), softmax over them, the shortest prefix whose mass reaches top_p, renormalised; the workgroup that ends last of a
+// sequence's goes on with the verification (sample_verify, below).  The top_k-th largest of 256
 // group maxima (a group: the elements of two or four threads) bounds the top_k-th largest element from below, so the
 // elements at or above it -- about top_k and a few more -- are all that has to be ordered: they go to LDS and each
 // finds its place by counting.  What that costs does not grow with top_k, unlike a round with two barriers per kept
@@ -2758,15 +2759,196 @@ __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K
     topk_many_equal<NT>(x, V, K, bound, n);
 }
 
+// Whether this is the last of n arrivals of call number `call`.  The count is 0 between launches; should calls have
+// met on it that ran at the same time, the next one, which has a higher number, starts afresh all the same.
+__device__ __forceinline__ bool arrives_last(unsigned long long* count, uint32_t call, int n) {
+    const unsigned long long none = (unsigned long long)call << 32;
+    __hip_atomic_fetch_max(count, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == none + n - 1;
+    if (last) __hip_atomic_store(count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
+
+// Lines 6-22 of Algorithm 1 over the lists of a sequence's rows, by the workgroup of these rows that ends last: lists go through
+// memory with stores and loads that pass by the caches other XCDs do not see, and nobody waits for anybody (as in the merge of
+// attn_sar_kernel).  A launch of its own behind the rows cost a kernel boundary and the trips for what does not depend on the
+// rows, which now happen while wave 0 still computes: one sequence, k = 5, 10 kept, 13.3 -> 12.1 us; 8 sequences, k = 8, 50
+// kept, 32.2 -> 29.7 (34.9 with the counts of all sequences on one 128-byte line: 1300 atomics that wait for each other).
+//
+// A wave holds a list, one kept token per lane: a token is found by one comparison in all lanes, and the sums of the draws
+// add the lanes up in list order.  The test of every candidate only needs its own row's list, so the waves make
+// them side by side and the first rejection is looked up afterwards.
+struct SampleList {
+    int id;
+    float p;
+    int n;
+};
+__device__ __forceinline__ float sample_prob_of(const SampleList& l, int token) {
+    const int lane = threadIdx.x & 63;
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(lane < l.n && l.id == token);
+    return hit ? lane_value(l.p, __builtin_ctzll(hit)) : 0.f;
+}
+__device__ __forceinline__ int sample_draw(const SampleList& l, float u, float* p_out) {
+    float run = 0.f;
+    int at = l.n - 1;
+    for (int j = 0; j < l.n; ++j) {  // (mostly a few: the likely tokens are in front)
+        run += lane_value(l.p, j);
+        if (u < run) { at = j; break; }
+    }
+    *p_out = lane_value(l.p, at);
+    return __builtin_amdgcn_readlane(l.id, at);
+}
+
+struct VerifyLds {
+    static constexpr int kRows = 16 * kMaxRowTiles;
+    int extra, emit_n, fin;
+    int new_cand[kRows], tok[kRows], real[kRows], nmask[kRows];
+    float u[2 * kRows], pc[kRows], ratio[kRows];
+};
+
+// What the verification of sequence b reads and no row changes, by threads first, first + step, ...
+__device__ __forceinline__ void sample_facts(const SampleLaunch& v, VerifyLds& s, int b, int first, int step) {
+    const int L = v.lay.L, G = v.lay.G, NU = G + v.max_cands;
+    if (first == 0 && v.emit && v.emit_len) {
+        s.emit_n = v.emit_len[b];
+        s.fin = v.finished && v.finished[b] != 0;
+    }
+    for (int i = first; i < L; i += step) s.tok[i] = v.tokens[(size_t)b * L + i];
+    for (int i = first; i < G; i += step) {
+        s.real[i] = v.lay.real_row[i];
+        s.nmask[i] = v.lay.n_mask[i];
+    }
+    for (int i = first; i < NU; i += step) s.u[i] = v.uniforms[(size_t)b * NU + i];
+    for (int i = first; i < v.max_cands; i += step) s.pc[i] = v.p_c[(size_t)b * v.max_cands + i];
+}
+
+template <int W>  // waves
+__device__ __forceinline__ void sample_verify(const SampleLaunch& v, VerifyLds& s, int b) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int L = v.lay.L, G = v.lay.G, K = v.top_k;
+    auto list_of = [&](int row) {  // row: the same in all lanes; places behind the list's end may hold anything
+        SampleList l;
+        const size_t at = ((size_t)b * L + row) * kMaxTopK + lane;  // kMaxTopK lanes
+        const int id = __hip_atomic_load(v.row_ids + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float p = __hip_atomic_load(v.row_probs + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        l.n = __builtin_amdgcn_readfirstlane(__hip_atomic_load(v.row_n + (size_t)b * L + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        l.id = lane < l.n ? id : -1;
+        l.p = lane < l.n ? p : 0.f;
+        return l;
+    };
+    static_assert(kMaxTopK == 64, "a list per wave");
+    for (int i = 1 + wave; i < G; i += W) {
+        const SampleList l = list_of(__builtin_amdgcn_readfirstlane(s.real[i - 1]));
+        const float ratio = sample_prob_of(l, s.tok[s.real[i]]) / s.pc[i - 1];
+        if (lane == 0) s.ratio[i] = ratio;
+    }
+    __syncthreads();
+    int acc = G - 1;  // accepted candidates: all in front of the first whose test fails
+    for (int i0 = 1; i0 < G; i0 += 64) {
+        const int i = i0 + lane;
+        const uint64_t no = __builtin_amdgcn_ballot_w64(i < G && !(s.u[min(i, G - 1) - 1] <= s.ratio[min(i, G - 1)]));
+        if (no) {
+            acc = i0 + __builtin_ctzll(no) - 1;
+            break;
+        }
+    }
+    const int rejected = acc < G - 1 ? acc + 1 : 0;
+    if (v.ratios)
+        for (int i = 1 + threadIdx.x; i < G; i += blockDim.x)
+            v.ratios[(size_t)b * (G - 1) + (i - 1)] = (!rejected || i <= rejected) ? s.ratio[i] : -1.f;
+    const int last = __builtin_amdgcn_readfirstlane(s.real[acc]), nm = __builtin_amdgcn_readfirstlane(s.nmask[acc]);
+    // new_ids / new_probs may lie on draft_ids / draft_probs: what is needed of these is read before the other waves write
+    const bool use_residual = v.residual && rejected && v.draft_ids && v.draft_probs;
+    int did = -1;
+    float dp = 0.f;
+    if (use_residual) {
+        if (wave == 0 && lane < K) {
+            const size_t d0 = ((size_t)b * v.max_cands + (rejected - 1)) * K;
+            did = v.draft_ids[d0 + lane];
+            dp = v.draft_probs[d0 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {  // the extra token
+        SampleList l = list_of(last);
+        if (use_residual) {
+            const uint64_t end = __builtin_amdgcn_ballot_w64(did < 0 || lane >= K);
+            const int dn = end ? __builtin_ctzll(end) : 64;
+            float d = 0.f;
+            bool found = false;
+            for_lanes(dn, [&](int q) {
+                const bool hit = !found && q < dn && __builtin_amdgcn_readlane(did, q) == l.id;
+                const float pq = lane_value(dp, q);
+                d = hit ? pq : d;
+                found |= hit;
+            });
+            float res = l.p - d;
+            res = (lane < l.n && res > 0.f) ? res : 0.f;
+            const float sum = lanes_sum(res, l.n);
+            if (sum > 0.f) l.p = res / sum;
+        }
+        float p_extra;
+        const int extra = sample_draw(l, s.u[G - 1], &p_extra);
+        if (lane == 0) {
+            s.extra = extra;
+            v.accepted_ws[b] = acc;
+            v.accepted_len[b] = acc;
+            v.extra[b] = extra;
+            if (v.emit && v.emit_len) {
+                int n = s.emit_n;
+                bool fin = s.fin != 0;
+                for (int i = 1; i <= acc + 1 && !fin; ++i) {  // accepted candidates, then the extra token
+                    const int t = i <= acc ? s.tok[s.real[i]] : extra;
+                    if (v.eos_id >= 0 && t == v.eos_id) { fin = true; break; }
+                    if (n < v.emit_cap) v.emit[(size_t)b * v.emit_cap + n++] = t;
+                }
+                v.emit_len[b] = n;
+                if (v.finished) v.finished[b] = fin;
+            }
+        }
+    } else {  // the new candidates: the j-th is drawn from the j-th mask row behind the last accepted row
+        for (int j = wave - 1; j < v.max_cands; j += W - 1) {
+            int t = -1;
+            float pt = 0.f;
+            SampleList l = {-1, 0.f, 0};
+            if (j < nm) {
+                l = list_of(last + 1 + j);
+                t = sample_draw(l, s.u[G + j], &pt);
+            }
+            const size_t o = ((size_t)b * v.max_cands + j) * K;
+            if (lane < K) {
+                if (v.new_ids) v.new_ids[o + lane] = l.id;
+                if (v.new_probs) v.new_probs[o + lane] = l.p;
+            }
+            if (lane == 0) {
+                v.new_cands[(size_t)b * v.max_cands + j] = t;
+                v.new_pc[(size_t)b * v.max_cands + j] = pt;
+                s.new_cand[j] = t;
+            }
+        }
+    }
+    __syncthreads();
+    if (v.next_tokens)
+        for (int r = threadIdx.x; r < v.next.L; r += blockDim.x) {
+            const int inf = v.next.info[r], g = inf >> 1;
+            int tok;
+            if (inf & 1) tok = v.mask_id;
+            else if (g == 0) tok = s.extra;
+            else tok = (g - 1 < nm) ? s.new_cand[g - 1] : 0;
+            v.next_tokens[(size_t)b * v.next.L + r] = tok;
+        }
+}
+
 // HELD: 1024 threads keep the first 32768 elements of the row in registers, two rows to a CU.  Else 512 threads keep
 // the maxima of the eighths of their first 64 elements and read those eighths again that reach the bound (out of
 // L2 or the cache behind it, 1 - 2 us): four rows to a CU, so that up to 1024 rows read at the same time.  648 rows, 50
 // kept: 37.8 -> 25.6 us (1.3 rounds of the first form).  The rule, rows up to 512, is where the first form needs a
-// second round (both launches of a call, first / second form: 486 rows, 10 kept, 21.8 / 23.1; 36 rows 12.0 / 13.2; 567
-// rows, 50 kept, 43.8 / 31.0).  (The second form does not quite fit the 64 registers that four rows to a CU leave: 6 of them
-// spill, 16 bytes a thread.)
+// second round (calls with the verification in a launch of its own, first / second form: 486 rows, 10 kept, 21.8 / 23.1; 36 rows
+// 12.0 / 13.2; 567 rows, 50 kept, 43.8 / 31.0).  (The second form does not quite fit the 64 registers that four rows to a CU leave:
+// 8 of them spill.)
 template <int NT, bool HELD>
-__global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
+__global__ __launch_bounds__(NT, 8) void sample_rows_kernel(SampleLaunch a) {
     TopLds& s = top_lds();
     const int r = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const size_t row = (size_t)b * a.lay.L + r;
@@ -2781,7 +2963,7 @@ __global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
 #pragma unroll
         for (int j = 0; j < kTopHeld; ++j) {
             const int i = tid + j * NT;
-            cache[j] = i < V ? __builtin_nontemporal_load(x + i) : -INFINITY;  // (both launches, 486 rows, 10 kept: 22.0 -> 20.9 us)
+            cache[j] = i < V ? __builtin_nontemporal_load(x + i) : -INFINITY;  // (486 rows, 10 kept: 22.0 -> 20.9 us)
         }
     } else {
 #pragma unroll
@@ -2871,6 +3053,8 @@ __global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
         topk_place<NT>(n, K);
     else
         topk_rare<NT>(x, V, K, bound, mine > bound);
+    __shared__ VerifyLds facts;
+    __shared__ int s_last;
     if (tid < 64) {  // lane j: the j-th kept token
         const float e = lane < K ? expf(s.top_v[min(lane, K - 1)] - s.top_v[0]) : 0.f;
         const float p = e / lanes_sum(e, K);
@@ -2879,188 +3063,28 @@ __global__ __launch_bounds__(NT, 8) void topk_warp_kernel(SampleLaunch a) {
         const int keep = reached ? __builtin_ctzll(reached) + 1 : K;
         const float mass = lane_value(run, __builtin_amdgcn_readfirstlane(keep - 1));
         if (lane < keep) {
-            a.row_ids[row * kMaxTopK + lane] = s.top_i[lane];
-            a.row_probs[row * kMaxTopK + lane] = p / mass;
+            __hip_atomic_store(a.row_ids + row * kMaxTopK + lane, s.top_i[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.row_probs + row * kMaxTopK + lane, p / mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (lane == 0) a.row_n[row] = keep;
-    }
-}
-
-// Kernel 2, one workgroup per sequence: lines 6-22 of Algorithm 1 over the lists.  A wave holds a list, one
-// kept token per lane: a token is found by one comparison in all lanes, and the sums of the draws add
-// the lanes up in list order.  The test of every candidate only needs its own row's list, so the waves make
-// them side by side and the first rejection is looked up afterwards.  8 sequences, k = 8, 50 kept: 5.7 us
-// (17.7 when one thread walked lists staged in LDS); one sequence, k = 5, 10 kept: 4.0 (6.4).
-struct SampleList {
-    int id;
-    float p;
-    int n;
-};
-__device__ __forceinline__ float sample_prob_of(const SampleList& l, int token) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t hit = __builtin_amdgcn_ballot_w64(lane < l.n && l.id == token);
-    return hit ? lane_value(l.p, __builtin_ctzll(hit)) : 0.f;
-}
-__device__ __forceinline__ int sample_draw(const SampleList& l, float u, float* p_out) {
-    float run = 0.f;
-    int at = l.n - 1;
-    for (int j = 0; j < l.n; ++j) {  // (mostly a few: the likely tokens are in front)
-        run += lane_value(l.p, j);
-        if (u < run) { at = j; break; }
-    }
-    *p_out = lane_value(l.p, at);
-    return __builtin_amdgcn_readlane(l.id, at);
-}
-
-constexpr int kSampleWaves = 8;
-__global__ __launch_bounds__(64 * kSampleWaves) void sample_verify_kernel(SampleLaunch v) {
-    constexpr int kRows = 16 * kMaxRowTiles;
-    __shared__ int s_extra, s_emit_n, s_fin;
-    __shared__ int s_new[kRows], s_tok[kRows], s_n[kRows], s_real[kRows], s_nmask[kRows];
-    __shared__ float s_u[2 * kRows], s_pc[kRows], s_ratio[kRows];
-    const int b = blockIdx.x, lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int L = v.lay.L, G = v.lay.G, K = v.top_k;
-    const int NU = G + v.max_cands;
-    // everything but the lists goes to LDS with independent loads
-    if (threadIdx.x == 0 && v.emit && v.emit_len) {
-        s_emit_n = v.emit_len[b];
-        s_fin = v.finished && v.finished[b] != 0;
-    }
-    for (int i = threadIdx.x; i < L; i += blockDim.x) {
-        s_tok[i] = v.tokens[(size_t)b * L + i];
-        s_n[i] = v.row_n[(size_t)b * L + i];
-    }
-    for (int i = threadIdx.x; i < G; i += blockDim.x) {
-        s_real[i] = v.lay.real_row[i];
-        s_nmask[i] = v.lay.n_mask[i];
-    }
-    for (int i = threadIdx.x; i < NU; i += blockDim.x) s_u[i] = v.uniforms[(size_t)b * NU + i];
-    for (int i = threadIdx.x; i < v.max_cands; i += blockDim.x) s_pc[i] = v.p_c[(size_t)b * v.max_cands + i];
-    __syncthreads();
-    auto list_of = [&](int row) {  // row: the same in all lanes
-        SampleList l;
-        l.n = __builtin_amdgcn_readfirstlane(s_n[row]);
-        const size_t at = ((size_t)b * L + row) * kMaxTopK + lane;  // kMaxTopK lanes
-        l.id = lane < l.n ? v.row_ids[at] : -1;
-        l.p = lane < l.n ? v.row_probs[at] : 0.f;
-        return l;
-    };
-    static_assert(kMaxTopK == 64, "a list per wave");
-    for (int i = 1 + wave; i < G; i += kSampleWaves) {
-        const SampleList l = list_of(__builtin_amdgcn_readfirstlane(s_real[i - 1]));
-        const float ratio = sample_prob_of(l, s_tok[s_real[i]]) / s_pc[i - 1];
-        if (lane == 0) s_ratio[i] = ratio;
+        if (lane == 0) __hip_atomic_store(a.row_n + row, keep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave made all of the row's stores
+        if (lane == 0) s_last = arrives_last(a.arrived + (size_t)b * kArrivedStride, a.call, a.lay.L);
+    } else {
+        sample_facts(a, facts, b, tid - 64, NT - 64);
     }
     __syncthreads();
-    int acc = G - 1;  // accepted candidates: all in front of the first whose test fails
-    for (int i0 = 1; i0 < G; i0 += 64) {
-        const int i = i0 + lane;
-        const uint64_t no = __builtin_amdgcn_ballot_w64(i < G && !(s_u[min(i, G - 1) - 1] <= s_ratio[min(i, G - 1)]));
-        if (no) {
-            acc = i0 + __builtin_ctzll(no) - 1;
-            break;
-        }
-    }
-    const int rejected = acc < G - 1 ? acc + 1 : 0;
-    if (v.ratios)
-        for (int i = 1 + threadIdx.x; i < G; i += blockDim.x)
-            v.ratios[(size_t)b * (G - 1) + (i - 1)] = (!rejected || i <= rejected) ? s_ratio[i] : -1.f;
-    const int last = __builtin_amdgcn_readfirstlane(s_real[acc]), nm = __builtin_amdgcn_readfirstlane(s_nmask[acc]);
-    // new_ids / new_probs may lie on draft_ids / draft_probs: what is needed of these is read before the other waves write
-    const bool use_residual = v.residual && rejected && v.draft_ids && v.draft_probs;
-    int did = -1;
-    float dp = 0.f;
-    if (use_residual) {
-        if (wave == 0 && lane < K) {
-            const size_t d0 = ((size_t)b * v.max_cands + (rejected - 1)) * K;
-            did = v.draft_ids[d0 + lane];
-            dp = v.draft_probs[d0 + lane];
-        }
-        __syncthreads();
-    }
-    if (wave == 0) {  // the extra token
-        SampleList l = list_of(last);
-        if (use_residual) {
-            const uint64_t end = __builtin_amdgcn_ballot_w64(did < 0 || lane >= K);
-            const int dn = end ? __builtin_ctzll(end) : 64;
-            float d = 0.f;
-            bool found = false;
-            for_lanes(dn, [&](int q) {
-                const bool hit = !found && q < dn && __builtin_amdgcn_readlane(did, q) == l.id;
-                const float pq = lane_value(dp, q);
-                d = hit ? pq : d;
-                found |= hit;
-            });
-            float res = l.p - d;
-            res = (lane < l.n && res > 0.f) ? res : 0.f;
-            const float sum = lanes_sum(res, l.n);
-            if (sum > 0.f) l.p = res / sum;
-        }
-        float p_extra;
-        const int extra = sample_draw(l, s_u[G - 1], &p_extra);
-        if (lane == 0) {
-            s_extra = extra;
-            v.accepted_ws[b] = acc;
-            v.accepted_len[b] = acc;
-            v.extra[b] = extra;
-            if (v.emit && v.emit_len) {
-                int n = s_emit_n;
-                bool fin = s_fin != 0;
-                for (int i = 1; i <= acc + 1 && !fin; ++i) {  // accepted candidates, then the extra token
-                    const int t = i <= acc ? s_tok[s_real[i]] : extra;
-                    if (v.eos_id >= 0 && t == v.eos_id) { fin = true; break; }
-                    if (n < v.emit_cap) v.emit[(size_t)b * v.emit_cap + n++] = t;
-                }
-                v.emit_len[b] = n;
-                if (v.finished) v.finished[b] = fin;
-            }
-        }
-    } else {  // the new candidates: the j-th is drawn from the j-th mask row behind the last accepted row
-        for (int j = wave - 1; j < v.max_cands; j += kSampleWaves - 1) {
-            int t = -1;
-            float pt = 0.f;
-            SampleList l = {-1, 0.f, 0};
-            if (j < nm) {
-                l = list_of(last + 1 + j);
-                t = sample_draw(l, s_u[G + j], &pt);
-            }
-            const size_t o = ((size_t)b * v.max_cands + j) * K;
-            if (lane < K) {
-                if (v.new_ids) v.new_ids[o + lane] = l.id;
-                if (v.new_probs) v.new_probs[o + lane] = l.p;
-            }
-            if (lane == 0) {
-                v.new_cands[(size_t)b * v.max_cands + j] = t;
-                v.new_pc[(size_t)b * v.max_cands + j] = pt;
-                s_new[j] = t;
-            }
-        }
-    }
-    __syncthreads();
-    if (v.next_tokens)
-        for (int r = threadIdx.x; r < v.next.L; r += blockDim.x) {
-            const int inf = v.next.info[r], g = inf >> 1;
-            int tok;
-            if (inf & 1) tok = v.mask_id;
-            else if (g == 0) tok = s_extra;
-            else tok = (g - 1 < nm) ? s_new[g - 1] : 0;
-            v.next_tokens[(size_t)b * v.next.L + r] = tok;
-        }
+    if (s_last) sample_verify<NT / 64>(a, facts, b);
 }
 
 hipError_t launch_sample_verify(const SampleLaunch& v, hipStream_t s) {
     if (v.top_k < 1 || v.top_k > kMaxTopK || !(v.top_p > 0.f) || v.top_p > 1.f || v.lay.L < 1 || v.lay.G < 1 ||
         v.max_cands < 1 || v.max_cands > 16 * kMaxRowTiles)
         return hipErrorInvalidValue;
-    // both kernels keep per-row facts in LDS arrays of 96 entries (uniforms: 192): check before either is enqueued
+    // per-row facts are kept in LDS arrays of 96 entries (uniforms: 192)
     if (v.lay.L > 16 * kMaxRowTiles || v.lay.G + v.max_cands > 2 * 16 * kMaxRowTiles) return hipErrorInvalidValue;
     const dim3 rows(v.lay.L, v.batch);
-    if (v.lay.L * v.batch <= 512) hipLaunchKernelGGL((topk_warp_kernel<1024, true>), rows, dim3(1024), 0, s, v);
-    else hipLaunchKernelGGL((topk_warp_kernel<512, false>), rows, dim3(512), 0, s, v);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(sample_verify_kernel, dim3(v.batch), dim3(64 * kSampleWaves), 0, s, v);
+    if (v.lay.L * v.batch <= 512) hipLaunchKernelGGL((sample_rows_kernel<1024, true>), rows, dim3(1024), 0, s, v);
+    else hipLaunchKernelGGL((sample_rows_kernel<512, false>), rows, dim3(512), 0, s, v);
     return hipGetLastError();
 }
 

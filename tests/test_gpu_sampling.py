@@ -583,3 +583,62 @@ def test_more_rows_than_are_held_at_once(torch_mod, V, top_k):
     assert B * (k + 1) > 512
     for whole, a, b in zip(call(0, B), call(0, 28), call(28, B)):
         assert whole.tobytes() == np.concatenate([a, b]).tobytes()
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_rows_that_end_last_verify_whatever_call_came_before(torch_mod, static):
+    """Calls of other block lengths, batches and launch forms (up to and beyond 512 rows) in turn on one context, then replays of
+    a graph that holds two of them with eager calls in between: every call's outputs are those of the first such
+    call on a context of its own, bit for bit (the arrival counts of the rows come back to where they were)."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    V = 700
+    shape = dataclasses.replace(SHAPES["tiny"], vocab=V, n_layers=1)
+    w = all_weights(shape, seed=0)
+    names = ("accepted_len", "extra", "new_cands", "new_pc", "new_ids", "new_probs", "next_tokens", "ratios")
+    rng = np.random.default_rng(17)
+    calls = []
+    for B, k, top_k in ((1, 1, 1), (8, 8, 50), (3, 5, 10), (11, 6, 64)):  # 4, 648, 108, 539 rows
+        spec = lo.paper_layout(k)
+        P = torch.from_numpy((rng.standard_normal((B, spec.n_rows, V)) * 2.5).astype(np.float32)).cuda()
+        toks = P.argmax(2).int().roll(1, 1).contiguous()
+        p_c = torch.from_numpy(rng.uniform(0.02, 0.5, (B, k)).astype(np.float32)).cuda()
+        u = torch.from_numpy(rng.uniform(0.0, 1.0, (B, spec.n_groups + k)).astype(np.float32)).cuda()
+        calls.append((B, spec, k, top_k, P, toks, p_c, u))
+
+    def issue(gm, out, lay, c):
+        gm.sample_verify(c[4], c[5], lay, c[6], c[7], out, top_k=c[3], top_p=0.95, next_layout=lay, static=static)
+
+    def make(gm, c):
+        return binding.SampleOut(gm, c[0], c[1].n_groups, c[2], c[3], next_rows=c[1].n_rows), gm.layout(c[1])
+
+    def read(out):
+        torch.cuda.synchronize()
+        return [getattr(out, n).cpu().numpy().tobytes() for n in names]
+
+    ref = []
+    for c in calls:
+        gm = gc.make_gpu_model(shape, w, max_batch=16, max_rows=81, max_ctx=64)
+        out, lay = make(gm, c)
+        issue(gm, out, lay, c)
+        ref.append(read(out))
+    gm = gc.make_gpu_model(shape, w, max_batch=16, max_rows=81, max_ctx=64)
+    outs = [make(gm, c) for c in calls]
+    for i in (0, 1, 2, 3, 1, 0, 3, 3, 2):
+        issue(gm, *outs[i], calls[i])
+        assert read(outs[i][0]) == ref[i], i
+    g, held = torch.cuda.CUDAGraph(), [make(gm, calls[i]) for i in (2, 1)]
+    with torch.cuda.graph(g):
+        for (out, lay), i in zip(held, (2, 1)):
+            issue(gm, out, lay, calls[i])
+    for rep in range(4):
+        for out, _ in held:
+            for n in names:
+                getattr(out, n).zero_()
+        g.replay()
+        for (out, _), i in zip(held, (2, 1)):
+            assert read(out) == ref[i], (rep, i)
+        issue(gm, *outs[rep], calls[rep])
+        assert read(outs[rep][0]) == ref[rep]
+    assert gm.device_faults() == 0

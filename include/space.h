@@ -348,8 +348,9 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *            where a batch has so many of its workgroups that it would otherwise not be taken);
  *   resid=N  most rows (at most 48) for which O and down are computed without partial sums, norm included
  *            (0: never);
- *   wide=N   fewest rows for the many-row projection kernel (default 193; 97 for QKV), widemask=M which projections
- *            may use it (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head);
+ *   wide=N   fewest rows for the many-row projection kernel (0: never; by default what its workgroups and those of passes
+ *            of 96 rows would take decides, from 97 rows on), widemask=M which projections may use it (bit 0 QKV, 1 O, 2
+ *            gate/up, 3 down, 4 LM head);
  *   widecut=A:B:C:D:O   forces how that kernel cuts the rows of every launch whose rows make up exactly
  *            4A + 3B + 2C + D groups of 32 rows: A pieces of 128 rows, B of 96, C of 64, D of 32, launched
  *            weight group by weight group (O = 0) or all pieces of a size before any smaller one (O = 1) or any

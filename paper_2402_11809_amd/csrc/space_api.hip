@@ -102,12 +102,18 @@ struct space_ctx {
     int m_max = 0, hd = 0, hd_kv = 0, kv_heads = 0, kt_d = 0, kt_hd = 0, kt_ffn = 0, lp_max = 0, row_tiles_max = 0;
     size_t q_plane = 0;
     int part_splits_max = 8;
-    // Projections over at least wide_min_rows rows use the many-row kernel where wide_mask allows it
-    // (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head).  Measured at 7B shapes (all projections of a
-    // layer, skinny passes -> many-row kernel, in us): 128 rows 193 -> 210 (but QKV alone 47 -> 33), 192
-    // rows 205 -> 224 (QKV level), 208 rows 286 -> 238, 288 rows 296 -> 260, 384 rows 381 -> 340, 512 rows
-    // 521 -> 370, 1024 rows 1015 -> 640: from the third 96-row pass on, and for QKV from the second.
-    int wide_min_rows = 193, wide_min_rows_qkv = 97, wide_mask = 31;
+    // Which projections use the many-row kernel: those of wide_mask (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head) over at
+    // least wide_min_rows rows (0: none), or, at -1, where wide_is_faster says so.
+    int wide_min_rows = -1, wide_mask = 31;
+    bool wide(int cls, const PackedW& w, int m) const {
+        if (!((wide_mask >> cls) & 1) || w.bytes() >= ((size_t)1 << 32)) return false;  // (32-bit offsets)
+        if (wide_min_rows >= 0) return wide_min_rows > 0 && m >= wide_min_rows;
+        return wide_is_faster(w.groups, w.splits, w.lq, w.r_pack, m, cls == 0 || cls == 1 || cls == 3);
+    }
+    bool any_wide(int m) const {
+        const LayerPacked& l = layers[0];
+        return wide(0, l.qkv, m) || wide(1, l.o, m) || wide(2, l.gate_up, m) || wide(3, l.down, m) || wide(4, lm, m);
+    }
     // How the many-row kernel cuts the rows of (projection class, row count) and in how many parts it sums the
     // contraction, where space_tune_rows has found something faster than the planner's choice; key = class << 32 | rows.
     struct WideTuned { WideParts parts; int ksplit; };
@@ -342,7 +348,7 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
             if (sscanf(p + 7, "%d", &n) == 1 && n >= 0 && n <= 4) ctx->wide_ks = n;
         }
         if (const char* p = strstr(e, "wide=")) {
-            if (sscanf(p + 5, "%d", &n) == 1 && n >= 0) ctx->wide_min_rows = ctx->wide_min_rows_qkv = n;
+            if (sscanf(p + 5, "%d", &n) == 1 && n >= 0) ctx->wide_min_rows = n;
         }
         if (const char* p = strstr(e, "widemask=")) {
             if (sscanf(p + 9, "%d", &n) == 1 && n >= 0) ctx->wide_mask = n;
@@ -363,7 +369,7 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
         }
     }
     bool may_tail = false;  // pieces of a projection may be cut over the contraction
-    if ((ctx->wide_min_rows > 0 && ctx->m_max >= ctx->wide_min_rows) || (ctx->wide_min_rows_qkv > 0 && ctx->m_max >= ctx->wide_min_rows_qkv)) {
+    if (ctx->any_wide(ctx->m_max)) {  // (and nothing that is not wide at that many rows is at fewer)
         max_splits = std::max(max_splits, 4);
         may_tail = ctx->wide_tail_force.pieces || (ctx->wide_tail && ceil_div(std::max(std::max(d, hd), f), kTileK) >= kWideTailMinK);
     }
@@ -481,7 +487,7 @@ void free_ctx(space_ctx* ctx) {
 // (EPI_ARGMAX: *groups_used).
 int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t* x, int m, float* out, int ldo,
              size_t split_stride, uint16_t* h, int ffn, float* logits, hipStream_t s, int* splits_used = nullptr,
-             int* groups_used = nullptr, int wide_from = 0, int cls = -1, const WidePlan* force_plan = nullptr,
+             int* groups_used = nullptr, bool wide = false, int cls = -1, const WidePlan* force_plan = nullptr,
              const float* ss = nullptr, int ss_n = 0) {
     const int pass_rows = 16 * kMaxRowTiles;
     GemmLaunch g{};
@@ -511,7 +517,7 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
         g.arg_idx = ctx->arg_idx;
         g.arg_groups = ctx->arg_groups;
     }
-    if (wide_from > 0 && m >= wide_from) {  // wide_from: fewest rows for the many-row kernel, 0 = never
+    if (wide) {
         // The cut of the rows changes no result, only the time; the number of partial sums over the
         // contraction (measured too, for the plain-sum projections) and a tail change the order of the fp32 sums.
         const uint64_t key = ((uint64_t)cls << 32) | (uint32_t)m;
@@ -785,9 +791,8 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     sched.qkv = L <= kHeadAttnMaxRows ? ctx->part : nullptr;
     sched.plan = ctx->key_plan; sched.part_rows = (long long)ctx->o_part_rows; sched.part_count = ctx->counts;
     const KeyPlan key_plan = head_attn ? KeyPlan{} : schedule_attention(&sched);
-    const int wide_from = std::min(ctx->wide_min_rows > 0 ? ctx->wide_min_rows : INT_MAX,
-                                   ctx->wide_min_rows_qkv > 0 ? ctx->wide_min_rows_qkv : INT_MAX);
-    const bool counted = key_plan.slots > B || M >= wide_from;  // some launch of this forward counts arrivals
+    const bool any_wide = ctx->any_wide(M);
+    const bool counted = key_plan.slots > B || any_wide;  // some launch of this forward counts arrivals
     {
         TimedScope ts(ctx, SPACE_K_EMBED, s);
         HIP_TRY(ctx, launch_embed(tokens, ctx->embed, c.vocab, d, lay, kv->len, B, ctx->cos_tab, ctx->sin_tab, ctx->n_pos, dh,
@@ -810,7 +815,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const size_t plane_bytes = (size_t)M * kTileK * 4 * std::max(ctx->layers[0].o.k_tiles, ctx->layers[0].down.k_tiles);
     const bool few = ctx->resid_max_rows >= 0 ? M <= ctx->resid_max_rows
                                               : plane_bytes <= 100 * 1024 || M <= (groups_o >= 192 ? 9 : 4);
-    const bool resid = few && M <= kResidMaxRows && M < wide_from && groups_o > 0 && groups_dn > 0;
+    const bool resid = few && M <= kResidMaxRows && !any_wide && groups_o > 0 && groups_dn > 0;
     const float* ss = nullptr;  // set while xn holds rows without their factor
     int ss_n = 0;
     auto project_resid = [&](const PackedW& w, const uint16_t* in, const uint16_t* norm_w, int groups) {
@@ -823,7 +828,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     // Few rows again, but with split sums: a row's columns are shared by workgroups where it has more than two of them
     // (steps of 2 layers, 36 rows, a workgroup per row / shared: 512 wide 88.8 / 89.5 us, 1024 wide 103.5 / 103.8, 2560 wide
     // level, beyond that ahead: at resid_part_kernel).
-    const bool norm_parts = !resid && M <= kResidMaxRows && M < wide_from && d > 2048;
+    const bool norm_parts = !resid && M <= kResidMaxRows && !any_wide && d > 2048;
     auto add_norm = [&](int splits, const uint16_t* norm_w) {
         if (!norm_parts) return launch_resid_norm(ctx->x, ctx->part, splits, ctx->part_stride, d, norm_w, c.rms_eps, M, d, ctx->xn, xs, s);
         ss = ctx->ss;
@@ -837,7 +842,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_QKV, s);
             if ((rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, M, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0,
-                               nullptr, s, &s_qkv, nullptr, (ctx->wide_mask & 1) ? ctx->wide_min_rows_qkv : 0, 0, nullptr, ss, ss_n)))
+                               nullptr, s, &s_qkv, nullptr, ctx->wide(0, lp.qkv, M), 0, nullptr, ss, ss_n)))
                 return rc;
         }
         uint16_t* kc_l = (uint16_t*)kv->k + kv_layer * l;
@@ -900,7 +905,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         } else {
             TimedScope ts(ctx, SPACE_K_O, s);
             if ((rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, M, ctx->part, d, ctx->part_stride, nullptr, 0,
-                               nullptr, s, &s_o, nullptr, (ctx->wide_mask & 2) ? ctx->wide_min_rows : 0, 1)))
+                               nullptr, s, &s_o, nullptr, ctx->wide(1, lp.o, M), 1)))
                 return rc;
         }
         if (!resid) {
@@ -910,7 +915,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_GATE_UP, s);
             if ((rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, M, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr,
-                               (ctx->wide_mask & 4) ? ctx->wide_min_rows : 0, 2, nullptr, ss, ss_n)))
+                               ctx->wide(2, lp.gate_up, M), 2, nullptr, ss, ss_n)))
                 return rc;
         }
         const uint16_t* next_norm = (l + 1 < c.n_layers) ? ctx->layers[l + 1].attn_norm : ctx->final_norm;
@@ -922,7 +927,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
         {
             TimedScope ts(ctx, SPACE_K_DOWN, s);
             if ((rc = run_gemm(ctx, lp.down, EPI_F32, ctx->h, M, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr,
-                               s, &s_dn, nullptr, (ctx->wide_mask & 8) ? ctx->wide_min_rows : 0, 3)))
+                               s, &s_dn, nullptr, ctx->wide(3, lp.down, M), 3)))
                 return rc;
         }
         {
@@ -939,7 +944,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     {
         TimedScope ts(ctx, SPACE_K_LM_HEAD, s);
         if ((rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, M, nullptr, c.vocab, 0, nullptr, 0, out->logits, s, nullptr,
-                           &lm_groups, (ctx->wide_mask & 16) ? ctx->wide_min_rows : 0, 4, nullptr, ss, ss_n)))
+                           &lm_groups, ctx->wide(4, ctx->lm, M), 4, nullptr, ss, ss_n)))
             return rc;
     }
 
@@ -1166,8 +1171,8 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(ctx, SPACE_EHIP, "hipEventCreate"); }
     int rc = SPACE_OK;
     for (int cls = 0; cls < 5 && rc == SPACE_OK; ++cls) {
-        const int from = !(ctx->wide_mask & (1 << cls)) ? 0 : cls == 0 ? ctx->wide_min_rows_qkv : ctx->wide_min_rows;
-        if (from <= 0 || rows < from) continue;
+        const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
+        if (!ctx->wide(cls, pw, rows)) continue;
         // The projections whose output is a plain sum also try other numbers of partial sums over the
         // contraction (0: the cost model's).  Whoever reads the partial sums (the attention's staging
         // work, the norm kernels) pays for each of them, which a measurement of the projection alone does
@@ -1178,7 +1183,6 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         // differ from run to run, and with it the order of the sums.
         WidePlan own, base;  // without such pieces; with them, where the planner cuts any
         {
-            const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
             own = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max);
             base = plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, 0, nullptr, ctx->tail_sums && ctx->wide_tail);
             cands[0] = own.parts;
@@ -1191,18 +1195,17 @@ int space_tune_rows(space_ctx* ctx, int32_t rows, void* stream) {
         for (int i = kc == 0 ? first : 0; i < (int)cands.size() && rc == SPACE_OK; ++i) {
             const int ks = kc == 0 ? own.ksplit : ks_cands[kc];
             if (ks > ctx->part_splits_max || (kc > 0 && ks == own.ksplit)) continue;
-            const PackedW& pw = cls == 0 ? have[0]->qkv : cls == 1 ? have[0]->o : cls == 2 ? have[0]->gate_up : cls == 3 ? have[0]->down : ctx->lm;
             const WidePlan cand = i < 0 ? base : plan_gemm_wide(pw, rows, plain ? EPI_F32 : EPI_SWIGLU, ctx->part_splits_max, ks, &cands[i]);
             float ms_min = 0.f;
             for (int rep = 0; rep < 4 && rc == SPACE_OK; ++rep) {  // the first one warms up
                 if (hipEventRecord(e0, s) != hipSuccess) { rc = fail(ctx, SPACE_EHIP, "hipEventRecord"); break; }
                 const LayerPacked& lp = *have[turn++ % have.size()];
                 switch (cls) {
-                    case 0: rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, rows, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
-                    case 1: rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
-                    case 2: rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, rows, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
-                    case 3: rc = run_gemm(ctx, lp.down, EPI_F32, ctx->h, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
-                    default: rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, rows, nullptr, c.vocab, 0, nullptr, 0, nullptr, s, nullptr, nullptr, 1, -1, &cand); break;
+                    case 0: rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, rows, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, true, -1, &cand); break;
+                    case 1: rc = run_gemm(ctx, lp.o, EPI_F32, ctx->attn_out, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, true, -1, &cand); break;
+                    case 2: rc = run_gemm(ctx, lp.gate_up, EPI_SWIGLU, ctx->xn, rows, nullptr, 0, 0, ctx->h, c.ffn, nullptr, s, nullptr, nullptr, true, -1, &cand); break;
+                    case 3: rc = run_gemm(ctx, lp.down, EPI_F32, ctx->h, rows, ctx->part, d, ctx->part_stride, nullptr, 0, nullptr, s, nullptr, nullptr, true, -1, &cand); break;
+                    default: rc = run_gemm(ctx, ctx->lm, EPI_ARGMAX, ctx->xn, rows, nullptr, c.vocab, 0, nullptr, 0, nullptr, s, nullptr, nullptr, true, -1, &cand); break;
                 }
                 if (rc != SPACE_OK) break;
                 float ms = 0.f;

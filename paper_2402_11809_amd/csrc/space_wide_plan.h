@@ -11,6 +11,24 @@ inline int round_up(int a, int b) { return ceil_div(a, b) * b; }
 constexpr int kWideDepth = 2;          // weight tiles in flight per wave and tile row: partial sums are whole rounds of them
 constexpr int kWideSearchGroups = 32;  // longest blocks (in groups of 32 rows) whose cuts are compared
 
+// Whether the many-row kernel takes a projection over m rows, or the weight-streaming kernel in passes of 96 rows.  The
+// passes cost next to nothing while all their workgroups run at once, one per CU, and a round each beyond; the many-row
+// kernel has a fixed cost of 3 - 5 us more and fewer, larger workgroups, but uses the matrix unit better and shares the operand
+// planes.  So: from the second round of workgroups on, or from the third where a round is short and the sums have to be
+// complete (the many-row kernel then cannot be cut over the contraction and has few workgroups: gate / up of a 1024-wide model
+// at 128 rows, 352 workgroups of 8 rounds, 12.1 us in passes against 15.1).  Measured on 9 shapes from 256 to 8192 wide, all
+// projections, 12 row counts from 100 to 1000, passes / many-row kernel in us: 128 rows, 256 wide down 6.8 / 12.0; 1024 wide QKV 8.0 /
+// 10.4; 2048 wide QKV 23.0 / 13.7; 7B gate / up 79.8 / 60.4, LM head 110 / 72; 70B down 176 / 125; 288 rows, 256 wide QKV 5.1 / 7.7;
+// 1024 wide LM head of 32000 69.5 / 44.9; 800 rows, 512 wide gate / up 14.6 / 10.4.  Over all of them this rule is 0.3 % behind
+// the better of the two, fixed lines at 97 and 193 rows 13 and 12 %.
+//   groups, splits, lq, r_pack  how the matrix is packed (PackedW);  plain: the sums may be partial ones
+constexpr int kPassRows = 96;
+inline bool wide_is_faster(int groups, int splits, int lq, int r_pack, int m, bool plain) {
+    if (m <= kPassRows) return false;
+    const long long wgs = (long long)groups * splits * ceil_div(m, kPassRows);
+    return wgs > 512 || (wgs > 256 && (plain || lq * (r_pack + 12) > 128));
+}
+
 // How the rows of every weight group are cut: count[c] pieces of 4 - c groups of two row tiles (8, 6, 4,
 // 2 row tiles), laid end to end in this order; the groups add up to ceil(ceil(m / 16) / 2).
 struct WideParts {

@@ -361,11 +361,21 @@ def test_pieces_cut_over_the_contraction(torch_mod, shape_name, B, k, tail):
 
 @pytest.mark.parametrize("shape_name,B,k", [("small128", 3, 5), ("small128", 6, 5), ("gqa128", 2, 8), ("small128", 8, 5)])
 def test_library_switches_between_the_projection_kernels_by_itself(torch_mod, shape_name, B, k):
-    """Row counts on both sides of the library's own switch points, nothing forced: 108 and 162 rows (only
-    the QKV projection takes the many-row kernel, the others run as two skinny passes), 216 rows (two
-    passes of the many-row kernel, the second short) and 288 rows (three, the last of two row tiles)."""
+    """Row counts of two and three passes of the skinny kernel on small models, nothing forced: 108, 162, 216 and 288
+    rows (all in passes there: which projections take the many-row kernel is the rounds of workgroups, see the next
+    test)."""
     shape = SHAPES[shape_name]
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=3), B, k, None, gc.LOGIT_TIGHT)
+
+
+@pytest.mark.parametrize("B,k", [(6, 3), (2, 6), (12, 3), (13, 3), (9, 5)])
+def test_projection_kernels_by_rounds_of_workgroups(torch_mod, B, k):
+    """Where the many-row kernel takes over, per projection and nothing forced: 96 rows (one pass: none), 98 and 192 rows (two
+    passes: gate / up in 376 short workgroups stays with them, the LM head in 258 long ones and QKV in 384 do not), 208 and
+    324 rows (three and four: gate / up goes too, O and down stay until theirs exceed a workgroup per CU)."""
+    import dataclasses
+    shape = dataclasses.replace(SHAPES["gqa128"], n_layers=1, n_kv_heads=8, ffn=6000, vocab=16500)
+    _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=4), B, k, None, gc.LOGIT_TIGHT)
 
 
 @pytest.mark.parametrize("shape_name,B,k,ctxs,tune", [

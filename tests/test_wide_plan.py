@@ -174,3 +174,29 @@ def test_tails_fit_and_are_ahead(tmp_path):
     plans, tails, bad, behind, worst = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split()
     assert int(plans) > 4000 and int(tails) > 100 and int(bad) == 0 and int(behind) == 0
     assert float(worst) < 200, worst
+
+
+_RULE = r"""
+#include <cstdio>
+#include "space_wide_plan.h"
+using namespace space;
+int main() {
+    int groups, splits, lq, r, m, plain;
+    while (scanf("%d %d %d %d %d %d", &groups, &splits, &lq, &r, &m, &plain) == 6) printf("%d", wide_is_faster(groups, splits, lq, r, m, plain));
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs a host compiler")
+def test_which_projection_kernel(tmp_path):
+    """wide_is_faster at its lines: one pass (never), 256 and 257 workgroups of two passes, 512 and 513 of three, long and short
+    workgroups, more passes than 32 bits of workgroups would hold."""
+    src = tmp_path / "rule.cpp"
+    src.write_text(_RULE)
+    subprocess.run(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2402_11809_amd", "csrc"), str(src), "-o", str(tmp_path / "rule")], check=True)
+    cases = [((1000, 8, 64, 8, 96, 1), 0), ((1000, 1, 64, 8, 97, 0), 1),
+             ((128, 1, 64, 8, 192, 1), 0), ((64, 2, 64, 8, 192, 1), 0), ((129, 1, 2, 2, 192, 1), 1), ((129, 1, 64, 8, 97, 0), 1),
+             ((256, 1, 8, 4, 192, 0), 0), ((257, 1, 8, 4, 192, 0), 1), ((256, 1, 8, 5, 192, 0), 1), ((171, 1, 2, 2, 193, 0), 1),
+             ((170, 1, 2, 2, 193, 0), 0), ((1 << 20, 8, 64, 8, 1 << 16, 0), 1)]
+    out = subprocess.run([str(tmp_path / "rule")], input="\n".join(" ".join(map(str, c)) for c, _ in cases), capture_output=True, text=True, check=True)
+    assert out.stdout == "".join(str(w) for _, w in cases)

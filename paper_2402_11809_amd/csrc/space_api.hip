@@ -105,10 +105,10 @@ struct space_ctx {
     // Which projections use the many-row kernel: those of wide_mask (bit 0 QKV, 1 O, 2 gate/up, 3 down, 4 LM head) over at
     // least wide_min_rows rows (0: none), or, at -1, where wide_is_faster says so.
     int wide_min_rows = -1, wide_mask = 31;
-    bool wide(int cls, const PackedW& w, int m) const {
+    bool wide(int cls, const PackedW& w, int m, int tile0 = 0) const {  // (tile0: GemmLaunch)
         if (!((wide_mask >> cls) & 1) || w.bytes() >= ((size_t)1 << 32)) return false;  // (32-bit offsets)
         if (wide_min_rows >= 0) return wide_min_rows > 0 && m >= wide_min_rows;
-        return wide_is_faster(w.groups, w.splits, w.lq, w.r_pack, m, cls == 0 || cls == 1 || cls == 3);
+        return wide_is_faster(w.groups - tile0 / w.r_pack, w.splits, w.lq, w.r_pack, m, cls == 0 || cls == 1 || cls == 3);
     }
     bool any_wide(int m) const {
         const LayerPacked& l = layers[0];
@@ -123,7 +123,7 @@ struct space_ctx {
     WideTail wide_tail_force{};
     float* tail_sums = nullptr;  // their sums (within part) and arrival counts (GemmLaunch)
     int32_t* tail_count = nullptr;  // (within counts)
-    std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key (at most 5 * m_max)
+    std::map<uint64_t, WidePlan> wide_plans;  // plans made so far, same key, class 5 the keys and values alone (at most 6 * m_max)
     // SPACE_TUNE widecut=: a cut forced on every launch of the many-row kernel whose rows make up exactly
     // wide_cut_groups groups of two row tiles (0: none)
     WideParts wide_cut{};
@@ -488,7 +488,7 @@ void free_ctx(space_ctx* ctx) {
 int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t* x, int m, float* out, int ldo,
              size_t split_stride, uint16_t* h, int ffn, float* logits, hipStream_t s, int* splits_used = nullptr,
              int* groups_used = nullptr, bool wide = false, int cls = -1, const WidePlan* force_plan = nullptr,
-             const float* ss = nullptr, int ss_n = 0) {
+             const float* ss = nullptr, int ss_n = 0, int tile0 = 0) {
     const int pass_rows = 16 * kMaxRowTiles;
     GemmLaunch g{};
     g.w = w;
@@ -498,6 +498,7 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
     g.m = m;
     g.passes = ceil_div(m, pass_rows);
     g.tiles_per_wave = gemm_tiles_per_wave(w, m);
+    g.tile0 = wide ? tile0 : tile0 / w.r_pack * w.r_pack;
     g.ldo = ldo;
     g.split_stride = split_stride;
     if (ss) {  // rows without their norm factor (never with the many-row kernel: see step_impl)
@@ -532,7 +533,7 @@ int run_gemm(space_ctx* ctx, const PackedW& w, GemmEpilogue epi, const uint16_t*
             const auto it = cls >= 0 && !knob ? ctx->wide_parts.find(key) : ctx->wide_parts.end();
             const space_ctx::WideTuned* tuned = it != ctx->wide_parts.end() ? &it->second : nullptr;
             p = plan_gemm_wide(w, m, epi, ctx->part_splits_max, ctx->wide_ks > 0 ? ctx->wide_ks : tuned ? tuned->ksplit : 0,
-                               tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr, ctx->tail_sums && ctx->wide_tail);
+                               tuned ? &tuned->parts : knob ? &ctx->wide_cut : nullptr, ctx->tail_sums && ctx->wide_tail, tile0);
             if (ctx->wide_tail_force.pieces && !knob && p.ksplit == 1 && ctx->tail_sums) {
                 WidePlan f = p;
                 f.tail = ctx->wide_tail_force;
@@ -839,16 +840,19 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerPacked& lp = ctx->layers[l];
         int s_qkv = 1, s_o = 1, s_dn = 1;
+        // The last layer of a prompt chunk only has to leave its keys and values behind: the queries' rows of the matrix are
+        // skipped (a plan of its own), and so are their rotary work and the block's staging (7B, 4 layers: 1024 rows 2548 -> 2472
+        // us, 333 rows 999 -> 972; 2 layers of 17 .. 64 rows 1 - 3 %).
+        const bool kv_only = !out && l + 1 == c.n_layers;
+        const int qkv_tile0 = kv_only ? hd / kTileN : 0;
         {
             TimedScope ts(ctx, SPACE_K_QKV, s);
             if ((rc = run_gemm(ctx, lp.qkv, EPI_F32, ctx->xn, M, ctx->part, hd + 2 * ctx->hd_kv, ctx->part_stride, nullptr, 0,
-                               nullptr, s, &s_qkv, nullptr, ctx->wide(0, lp.qkv, M), 0, nullptr, ss, ss_n)))
+                               nullptr, s, &s_qkv, nullptr, ctx->wide(0, lp.qkv, M, qkv_tile0), kv_only ? 5 : 0, nullptr, ss, ss_n, qkv_tile0)))
                 return rc;
         }
         uint16_t* kc_l = (uint16_t*)kv->k + kv_layer * l;
         uint16_t* vc_l = (uint16_t*)kv->v + kv_layer * l;
-        // the last layer of a prompt chunk only has to leave its keys and values behind
-        const bool kv_only = !out && l + 1 == c.n_layers;
         if (head_attn && !kv_only) {
             HeadAttnLaunch ha{};
             ha.qkv = ctx->part; ha.splits = s_qkv; ha.split_stride = ctx->part_stride;
@@ -865,6 +869,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
             rs.splits = s_qkv;
             rs.split_stride = ctx->part_stride;
             rs.m = M; rs.batch = B; rs.L = L; rs.Lp = Lp; rs.n_heads = c.n_heads; rs.n_kv_heads = ctx->kv_heads; rs.head_dim = dh;
+            rs.kv_only = kv_only;
             rs.cos_t = ctx->cos_t; rs.sin_t = ctx->sin_t; rs.pos = ctx->pos; rs.info = lay.info;
             rs.q = ctx->q; rs.q_plane = ctx->q_plane; rs.kblk = ctx->kblk; rs.vblk = ctx->vblk;
             rs.kc = kc_l;

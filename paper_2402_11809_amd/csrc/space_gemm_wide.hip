@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64 * W, 2 * W / 4) void gemm_wide_kernel(GemmLaunch
     }
 
     // weights: tile (nt, kt) of the packed matrix sits at tile index ck(kt) + cr(nt)
-    const int nt0 = (bx * W + wave) * R;
+    const int nt0 = g.tile0 + (bx * W + wave) * R;
     const int nt_last = g.w.groups * g.w.r_pack - 1;  // padded tile grid
     // buffer loads: resource of the whole packed matrix (under 4 GB, the host checks) + the tile's byte
     // offset in a scalar register + the lane's 16 bytes: no 64-bit address arithmetic per load
@@ -440,13 +440,14 @@ hipError_t launch_wide_r(const GemmLaunch& g, const WidePlan& p, hipStream_t s) 
 }  // namespace
 
 WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit, const WideParts* cut,
-                        bool may_tail) {
+                        bool may_tail, int tile0) {
     WidePlan p{};
     p.tiles_per_wave = kWideTiles;
-    p.n_groups = ceil_div(w.n_tiles, kWideWaves * kWideTiles);
+    p.n_groups = ceil_div(w.n_tiles - tile0, kWideWaves * kWideTiles);
+    const int n = w.n - tile0 * kTileN;
     const int smax = (epi == EPI_F32) ? (max_splits < 4 ? max_splits : 4) : 1;
-    WideCut c = plan_wide_cut(p.n_groups, w.n, w.k_tiles, m, smax, epi == EPI_F32 ? force_ksplit : 0, cut);
-    if (may_tail && !cut && (force_ksplit <= 0 || epi != EPI_F32)) plan_wide_tail(p.n_groups, w.n, w.k_tiles, m, c, &c, &p.tail);
+    WideCut c = plan_wide_cut(p.n_groups, n, w.k_tiles, m, smax, epi == EPI_F32 ? force_ksplit : 0, cut);
+    if (may_tail && !cut && (force_ksplit <= 0 || epi != EPI_F32)) plan_wide_tail(p.n_groups, n, w.k_tiles, m, c, &c, &p.tail);
     p.parts = c.parts;
     p.kt_per_split = round_up(ceil_div(w.k_tiles, c.ksplit), kWideDepth);
     p.ksplit = ceil_div(w.k_tiles, p.kt_per_split);  // no empty split
@@ -473,9 +474,10 @@ hipError_t launch_gemm_wide(const GemmLaunch& g0, const WidePlan& p, GemmEpilogu
         return hipErrorInvalidValue;
     if (p.ksplit < 1 || p.kt_per_split < 1 || p.kt_per_split % kWideDepth || (p.ksplit - 1) * p.kt_per_split >= g.w.k_tiles ||
         p.ksplit * p.kt_per_split < g.w.k_tiles || round_up(g.w.k_tiles, kWideDepth) > g.w.k_tiles_pad() ||
-        p.n_groups != ceil_div(g.w.n_tiles, kWideWaves * p.tiles_per_wave))
+        p.n_groups != ceil_div(g.w.n_tiles - g.tile0, kWideWaves * p.tiles_per_wave))
         return hipErrorInvalidValue;
     if (epi != EPI_F32 && p.ksplit != 1) return hipErrorInvalidValue;
+    if (g.tile0 < 0 || g.tile0 >= g.w.n_tiles || (g.tile0 && epi != EPI_F32)) return hipErrorInvalidValue;
     if (g.w.bytes() >= ((size_t)1 << 32)) return hipErrorInvalidValue;  // the kernel addresses the matrix with 32-bit byte offsets
     if (epi == EPI_ARGMAX && p.n_groups > g.arg_groups) return hipErrorInvalidValue;
     if (p.tiles_per_wave != kWideTiles) return hipErrorInvalidValue;

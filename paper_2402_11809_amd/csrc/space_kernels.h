@@ -61,6 +61,7 @@ struct GemmLaunch {
     int m;              // rows of this launch, starting at row_tile0 * 16: 1 .. 96, or up to 96 * passes
     int passes;         // 1, or the number of 96-row passes that share this launch (then row_tile0 == 0)
     int tiles_per_wave; // weight tiles per wave, gemm_tiles_per_wave(w, rows of the whole matrix)
+    int tile0;          // first weight tile: rows of w in front of it are left out (EPI_F32; weight-streaming kernel: whole groups)
     // EPI_F32: out[s][m][ldo] fp32 partial sums
     float* out;
     int ldo;
@@ -132,7 +133,7 @@ struct WidePlan {
 // cut of the rows instead of the model's, with the partial sums that the model's has; may_tail: pieces may be cut over
 // the contraction where neither is forced (GemmLaunch::tail_sums)
 WidePlan plan_gemm_wide(const PackedW& w, int m, GemmEpilogue epi, int max_splits, int force_ksplit = 0,
-                        const WideParts* cut = nullptr, bool may_tail = false);
+                        const WideParts* cut = nullptr, bool may_tail = false, int tile0 = 0);
 // A tail's pieces lie in the launch, its slots in the buffers, and every part has contraction tiles.
 bool wide_tail_fits(int k_tiles, const WidePlan& p);
 // g.passes and g.tiles_per_wave are ignored (the plan's pieces are used); g.row_tile0 must be 0.
@@ -191,6 +192,7 @@ struct RopeStore {
     int splits;
     size_t split_stride;
     int m, batch, L, Lp, n_heads, n_kv_heads, head_dim;
+    bool kv_only;  // only the cache slots are wanted: no queries (they are not there), no block staging
     const float* cos_t;
     const float* sin_t;
     const int32_t* pos;

@@ -126,14 +126,14 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
         // launch.  Workgroup index -> XCD is index % 8, so the passes of one weight group get indices
         // that differ by 8: they run on the same XCD at about the same time and the weight tiles
         // cross HBM once (ordinary loads below, so that L2 keeps them for the sibling passes).
-        const int q = blockIdx.x >> 3, n_gs = (g.w.groups * g.w.r_pack / R) * g.w.splits;
+        const int q = blockIdx.x >> 3, n_gs = ((g.w.groups * g.w.r_pack - g.tile0) / R) * g.w.splits;
         pass = q % g.passes;
         const int gi = (q / g.passes) * 8 + (blockIdx.x & 7);
         if (gi >= n_gs) return;
         bx = gi % (n_gs / g.w.splits);
         s = gi / (n_gs / g.w.splits);
     }
-    const int nt0 = bx * R;
+    const int nt0 = g.tile0 + bx * R;
     const int row_tile0 = g.row_tile0 + pass * T;
     const int m_rows = T >= 4 ? min(g.m - pass * 16 * T, 16 * T) : g.m;  // rows of this pass
     const int t_run = T >= 4 ? (m_rows + 15) >> 4 : T;                    // its row tiles, 1 .. T
@@ -378,10 +378,11 @@ int gemm_tiles_per_wave(const PackedW& w, int total_rows) {
     return w.r_pack;
 }
 int gemm_groups(const PackedW& w, int tiles_per_wave) { return w.groups * w.r_pack / tiles_per_wave; }
+static int gemm_groups(const GemmLaunch& g, int tiles_per_wave) { return (g.w.groups * g.w.r_pack - g.tile0) / tiles_per_wave; }
 
 template <int EPI, int R, int D>
 static hipError_t launch_gemm_small(const GemmLaunch& g, hipStream_t s) {  // at most 3 row tiles
-    const dim3 grid(gemm_groups(g.w, R), g.w.splits), block(256);
+    const dim3 grid(gemm_groups(g, R), g.w.splits), block(256);
     if (g.ss && g.ss_n <= kSsFew) {
         switch (ceil_div(g.m, 16)) {
             case 1: hipLaunchKernelGGL((gemm_skinny_kernel<1, R, EPI, D, 2>), grid, block, 0, s, g); break;
@@ -412,8 +413,8 @@ static hipError_t launch_gemm_small(const GemmLaunch& g, hipStream_t s) {  // at
 template <int EPI, int R>
 static hipError_t launch_gemm_large(const GemmLaunch& g, hipStream_t s) {  // 4 to 6 row tiles per pass
     const dim3 block(256);
-    dim3 grid(gemm_groups(g.w, R), g.w.splits);
-    if (g.passes > 1) grid = dim3(8 * ceil_div(gemm_groups(g.w, R) * g.w.splits, 8) * g.passes);
+    dim3 grid(gemm_groups(g, R), g.w.splits);
+    if (g.passes > 1) grid = dim3(8 * ceil_div(gemm_groups(g, R) * g.w.splits, 8) * g.passes);
     switch (g.passes > 1 ? kMaxRowTiles : ceil_div(g.m, 16)) {
         case 4: hipLaunchKernelGGL((gemm_skinny_kernel<4, R, EPI, 2>), grid, block, 0, s, g); break;
         case 5: hipLaunchKernelGGL((gemm_skinny_kernel<5, R, EPI, 2>), grid, block, 0, s, g); break;
@@ -451,6 +452,7 @@ hipError_t launch_gemm(const GemmLaunch& g, GemmEpilogue epi, hipStream_t s) {
     if (epi != EPI_F32 && g.w.splits != 1) return hipErrorInvalidValue;
     if (g.row_tile0 < 0 || g.row_tile0 + ceil_div(g.m, 16) > g.xs.row_tiles || g.xs.last_cols < 1 || g.xs.last_cols > 16) return hipErrorInvalidValue;
     if (g.tiles_per_wave > g.w.r_pack || g.w.r_pack % g.tiles_per_wave) return hipErrorInvalidValue;
+    if (g.tile0 < 0 || g.tile0 >= g.w.n_tiles || g.tile0 % g.w.r_pack || (g.tile0 && epi != EPI_F32)) return hipErrorInvalidValue;
     if (g.ss && (g.m > kResidMaxRows || g.passes != 1 || g.row_tile0 != 0 || g.ss_n < 1 || g.ss_n > kResidMaxGroups)) return hipErrorInvalidValue;
     switch (epi) {
         case EPI_F32: return launch_gemm_t<EPI_F32>(g, s);
@@ -942,7 +944,7 @@ __global__ __launch_bounds__(64) void rope_store_kernel(RopeStore a) {
     for (int s = 0; s < 8; ++s) {
         if (s < a.splits) {
             const float* p = base + (size_t)s * a.split_stride;
-            q0 += p[0]; q1 += p[half];
+            if (!a.kv_only) { q0 += p[0]; q1 += p[half]; }
             if (kv_head) {
                 k0 += p[hd]; k1 += p[hd + half];
                 v0 += p[hd + Hkv * dh]; v1 += p[hd + Hkv * dh + half];
@@ -950,19 +952,23 @@ __global__ __launch_bounds__(64) void rope_store_kernel(RopeStore a) {
         }
     }
     const float c = a.cos_t[(size_t)row * half + i], sn = a.sin_t[(size_t)row * half + i];
-    const float qra = q0 * c - q1 * sn, qrb = q1 * c + q0 * sn;
-    const uint16_t qa = f2bf(qra), qb = f2bf(qrb);
-    uint16_t* qo = a.q + (((size_t)b * H + h) * a.L + r) * dh;
-    qo[i] = qa; qo[i + half] = qb;
-    qo[a.q_plane + i] = f2bf(qra - bf2f(qa)); qo[a.q_plane + i + half] = f2bf(qrb - bf2f(qb));
+    if (!a.kv_only) {
+        const float qra = q0 * c - q1 * sn, qrb = q1 * c + q0 * sn;
+        const uint16_t qa = f2bf(qra), qb = f2bf(qrb);
+        uint16_t* qo = a.q + (((size_t)b * H + h) * a.L + r) * dh;
+        qo[i] = qa; qo[i + half] = qb;
+        qo[a.q_plane + i] = f2bf(qra - bf2f(qa)); qo[a.q_plane + i + half] = f2bf(qrb - bf2f(qb));
+    }
     if (!kv_head) return;
     const uint16_t ka = f2bf(k0 * c - k1 * sn), kb = f2bf(k1 * c + k0 * sn);
     const uint16_t va = f2bf(v0), vb = f2bf(v1);
-    const size_t bh = (size_t)b * Hkv + h;
-    uint16_t* ko = a.kblk + (bh * a.Lp + r) * dh;
-    ko[i] = ka; ko[i + half] = kb;
-    uint16_t* vo = a.vblk + ((bh * Lb + r / kAttnKeys) * dh) * kAttnKeys + (r % kAttnKeys);
-    vo[(size_t)i * kAttnKeys] = va; vo[(size_t)(i + half) * kAttnKeys] = vb;
+    if (!a.kv_only) {
+        const size_t bh = (size_t)b * Hkv + h;
+        uint16_t* ko = a.kblk + (bh * a.Lp + r) * dh;
+        ko[i] = ka; ko[i + half] = kb;
+        uint16_t* vo = a.vblk + ((bh * Lb + r / kAttnKeys) * dh) * kAttnKeys + (r % kAttnKeys);
+        vo[(size_t)i * kAttnKeys] = va; vo[(size_t)(i + half) * kAttnKeys] = vb;
+    }
     if (to_cache) {
         bool bad = false;
         const size_t run = a.paging.table
@@ -983,7 +989,7 @@ __global__ __launch_bounds__(64) void rope_store_kernel(RopeStore a) {
 // row, spent a memory round trip on each (33 us for 1024 rows of a 7B layer).  V goes to an LDS tile first
 // and leaves it transposed, 32 rows of one dimension side by side: written straight from the items every
 // 2-byte element of V would open a 64-byte line of its own.
-template <int DH>
+template <int DH, bool KVONLY>
 __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
     constexpr int half = DH / 2, IPR = half / 4, NI = kAttnKeys * IPR / 256;
     static_assert(kAttnKeys * IPR % 256 == 0, "whole items per thread");
@@ -1027,8 +1033,8 @@ __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
         for (int it = 0; it < NI; ++it)
 #pragma unroll
             for (int sp = 0; sp < S; ++sp) {
-                tq0[it][sp] = *(const f4*)(qp[it] + sp * ss);
-                tq1[it][sp] = *(const f4*)(qp[it] + sp * ss + half);
+                tq0[it][sp] = KVONLY ? z4 : *(const f4*)(qp[it] + sp * ss);
+                tq1[it][sp] = KVONLY ? z4 : *(const f4*)(qp[it] + sp * ss + half);
             }
         if (kv_head) {
 #pragma unroll
@@ -1060,8 +1066,8 @@ __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
             f4 t0[NI], t1[NI], t2[NI], t3[NI], t4[NI], t5[NI];
 #pragma unroll
             for (int it = 0; it < NI; ++it) {
-                t0[it] = *(const f4*)(qp[it] + sp * ss);
-                t1[it] = *(const f4*)(qp[it] + sp * ss + half);
+                t0[it] = KVONLY ? z4 : *(const f4*)(qp[it] + sp * ss);
+                t1[it] = KVONLY ? z4 : *(const f4*)(qp[it] + sp * ss + half);
             }
             if (kv_head) {
 #pragma unroll
@@ -1093,19 +1099,21 @@ __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
             if (it_on[it] && !it_mask[it] && !to_cache && h == 0) atomicAdd(a.faults, 1);
         }
         if (!it_on[it]) continue;
-        uint32_t ah[4], al[4], bh_[4], bl[4];
+        if (!KVONLY) {
+            uint32_t ah[4], al[4], bh_[4], bl[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float ra = q0[it][e] * cs[it][e] - q1[it][e] * sn[it][e], rb = q1[it][e] * cs[it][e] + q0[it][e] * sn[it][e];
-            const uint16_t ha = f2bf(ra), hb = f2bf(rb);
-            ah[e] = ha; al[e] = f2bf(ra - bf2f(ha));
-            bh_[e] = hb; bl[e] = f2bf(rb - bf2f(hb));
+            for (int e = 0; e < 4; ++e) {
+                const float ra = q0[it][e] * cs[it][e] - q1[it][e] * sn[it][e], rb = q1[it][e] * cs[it][e] + q0[it][e] * sn[it][e];
+                const uint16_t ha = f2bf(ra), hb = f2bf(rb);
+                ah[e] = ha; al[e] = f2bf(ra - bf2f(ha));
+                bh_[e] = hb; bl[e] = f2bf(rb - bf2f(hb));
+            }
+            uint16_t* qo = a.q + (((size_t)b * H + h) * a.L + r) * DH + i;
+            *(u32x2*)qo = u32x2{ah[0] | (ah[1] << 16), ah[2] | (ah[3] << 16)};
+            *(u32x2*)(qo + half) = u32x2{bh_[0] | (bh_[1] << 16), bh_[2] | (bh_[3] << 16)};
+            *(u32x2*)(qo + a.q_plane) = u32x2{al[0] | (al[1] << 16), al[2] | (al[3] << 16)};
+            *(u32x2*)(qo + a.q_plane + half) = u32x2{bl[0] | (bl[1] << 16), bl[2] | (bl[3] << 16)};
         }
-        uint16_t* qo = a.q + (((size_t)b * H + h) * a.L + r) * DH + i;
-        *(u32x2*)qo = u32x2{ah[0] | (ah[1] << 16), ah[2] | (ah[3] << 16)};
-        *(u32x2*)(qo + half) = u32x2{bh_[0] | (bh_[1] << 16), bh_[2] | (bh_[3] << 16)};
-        *(u32x2*)(qo + a.q_plane) = u32x2{al[0] | (al[1] << 16), al[2] | (al[3] << 16)};
-        *(u32x2*)(qo + a.q_plane + half) = u32x2{bl[0] | (bl[1] << 16), bl[2] | (bl[3] << 16)};
         if (!kv_head) continue;
         uint32_t ka[4], kb[4];
 #pragma unroll
@@ -1117,9 +1125,11 @@ __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
         }
         const u32x2 kav = {ka[0] | (ka[1] << 16), ka[2] | (ka[3] << 16)};
         const u32x2 kbv = {kb[0] | (kb[1] << 16), kb[2] | (kb[3] << 16)};
-        uint16_t* ko = a.kblk + (bh * a.Lp + r) * DH + i;
-        *(u32x2*)ko = kav;
-        *(u32x2*)(ko + half) = kbv;
+        if (!KVONLY) {
+            uint16_t* ko = a.kblk + (bh * a.Lp + r) * DH + i;
+            *(u32x2*)ko = kav;
+            *(u32x2*)(ko + half) = kbv;
+        }
         if (to_cache) {
             bool bad = false;
             const size_t run = a.paging.table
@@ -1145,7 +1155,7 @@ __global__ __launch_bounds__(256) void rope_store_rows_kernel(RopeStore a) {
     for (int d = tid >> 5; d < DH; d += 8) {
         if (r >= a.L) continue;
         const uint16_t v = v_tile[d][rr];
-        vo[(size_t)d * kAttnKeys] = v;
+        if (!KVONLY) vo[(size_t)d * kAttnKeys] = v;
         if (slot >= 0) vc[(size_t)d * kAttnKeys] = v;
     }
 }
@@ -1154,12 +1164,12 @@ hipError_t launch_rope_store(const RopeStore& a, hipStream_t s) {
     if (a.splits > 8 || a.head_dim > 128 || a.n_kv_heads < 1 || a.n_heads % a.n_kv_heads) return hipErrorInvalidValue;
     if (a.paging.table && (a.paging.table_stride * kAttnKeys != a.capacity || a.paging.n_pages < 1)) return hipErrorInvalidValue;
     if (a.Lp % kAttnKeys || a.Lp < a.L) return hipErrorInvalidValue;
-    if (a.L >= 2 * kAttnKeys && a.head_dim == 128)
-        hipLaunchKernelGGL(rope_store_rows_kernel<128>, dim3(a.batch * (a.Lp / kAttnKeys), a.n_heads), dim3(256), 0, s, a);
-    else if (a.L >= 2 * kAttnKeys && a.head_dim == 64)
-        hipLaunchKernelGGL(rope_store_rows_kernel<64>, dim3(a.batch * (a.Lp / kAttnKeys), a.n_heads), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(rope_store_kernel, dim3(a.m, a.n_heads), dim3(64), 0, s, a);
+    const int heads = a.kv_only ? a.n_kv_heads : a.n_heads;
+    const dim3 rows_grid(a.batch * (a.Lp / kAttnKeys), heads);
+    auto rows = [&](auto kernel) { hipLaunchKernelGGL(kernel, rows_grid, dim3(256), 0, s, a); };
+    if (a.L >= 2 * kAttnKeys && a.head_dim == 128) a.kv_only ? rows(rope_store_rows_kernel<128, true>) : rows(rope_store_rows_kernel<128, false>);
+    else if (a.L >= 2 * kAttnKeys && a.head_dim == 64) a.kv_only ? rows(rope_store_rows_kernel<64, true>) : rows(rope_store_rows_kernel<64, false>);
+    else hipLaunchKernelGGL(rope_store_kernel, dim3(a.m, heads), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

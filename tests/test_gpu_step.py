@@ -943,6 +943,36 @@ def test_prompt_chunks_of_a_batch_dealt_out_by_length(torch_mod, shape_name, B, 
         gc.assert_bf16_close(gv, okvs[b].v[1][c:], f"seq {b} V", min_same=0.9)
 
 
+@pytest.mark.parametrize("shape_name,B,rows,tune", [
+    ("tiny", 1, 9, None), ("gqa-small", 2, 40, "qkv=6:2"), ("gqa128", 1, 70, "qkv=8:1"), ("small128", 3, 50, "qkv=6:1"),
+    ("gqa-small", 1, 150, "wide=1"), ("gqa128", 2, 130, "wide=1,wideks=2"), ("small128", 1, 330, "wide=1,wideks=4"), ("tiny", 2, 300, "qkv=6:1")])
+def test_last_layer_of_a_prompt_chunk_without_queries(torch_mod, shape_name, B, rows, tune):
+    """The last layer's projection starts at the first key's weight tile (few rows: at the group of tiles that holds it, which need
+    not start there): that layer's keys and values of chunks with one, two and many query tiles and passes, in both projection
+    kernels, with partial sums, against the oracle's prefill; the layer in front keeps its own."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name].with_layers(2)
+    w = all_weights(shape, seed=23)
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=512, tune=tune)
+    om = gc.oracle_model(shape, w)
+    cache = gm.kv_cache(B, 512)
+    lens = [13 + 50 * b for b in range(B)]
+    okvs = [gc.synthetic_oracle_kv(om, seed=40 + b, ctx=c, std=0.5) for b, c in enumerate(lens)]
+    for b in range(B):
+        gc.upload_oracle_kv(torch, cache, b, okvs[b])
+    toks = np.random.default_rng(24).integers(0, shape.vocab, size=(B, rows)).astype(np.int32)
+    gm.prefill(torch.from_numpy(toks).cuda(), gm.layout(lo.prefill_layout(rows)), cache)
+    torch.cuda.synchronize()
+    assert gm.device_faults() == 0
+    for b, c in enumerate(lens):
+        so.prefill(om, okvs[b], toks[b])
+        for l in range(2):
+            gk, gv = gc.download_kv_rows(cache, l, b, c, c + rows)
+            gc.assert_bf16_close(gk, okvs[b].k[l][c:], f"layer {l} seq {b} K", min_same=0.9)
+            gc.assert_bf16_close(gv, okvs[b].v[l][c:], f"layer {l} seq {b} V", min_same=0.9)
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
     """One sequence of a batch, long enough to be cut into parts, with one cached key element that is NaN or infinite: a score of the

@@ -837,6 +837,27 @@ def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
         assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("shape_name", ["small128", "gqa128"])  # contractions of 8 and of 32 tiles (two partial sums)
+def test_row_cuts_of_the_many_row_kernel_give_the_same_bits(torch_mod, shape_name):
+    """288 rows of models whose projections would run in passes, with the many-row kernel forced: every cut of the rows gives the
+    logits of the default one bit for bit."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name]
+    w = all_weights(shape, seed=5)
+    spec = lo.paper_layout(5)
+    toks = np.random.default_rng(13).integers(0, shape.vocab, size=(8, spec.n_rows)).astype(np.int32)
+
+    def logits(tune):
+        gm = gc.make_gpu_model(shape, w, max_batch=8, max_rows=spec.n_rows, tune=tune)
+        return _run_step(torch, gm, gm.kv_cache(8, 160), spec, toks, batch=8).logits.cpu().numpy()
+
+    ref = logits("wide=1")
+    assert not np.array_equal(ref, logits("wide=0"))  # (another order of sums: the kernel is the one that was forced)
+    for cut in ("2:0:0:1:0", "0:3:0:0:0", "0:3:0:0:1", "0:1:3:0:1", "0:0:4:1:0", "0:0:0:9:1", "1:1:1:0:2", "2:0:0:1:2"):
+        assert np.array_equal(ref, logits("wide=1,widecut=" + cut)), cut
+
+
 def test_forced_cut_leaves_no_tail(torch_mod):
     """widecut= and widetail= together: the forced cut has no piece cut over the contraction, i.e. the logits are those of the
     default cut without tails, bit for bit; at another row count the forced tail still applies."""

@@ -210,6 +210,8 @@ struct RopeStore {
 hipError_t launch_rope_store(const RopeStore& a, hipStream_t s);
 
 constexpr int kHeadAttnMaxRows = 48;  // longest block the fused rotary + attention kernels take
+constexpr int kAttnSplitMaxRows = 96;  // longest block of attn_sar_kernel; longer ones (prompt chunks): attn_rows_kernel
+constexpr int kAttnGroupRows = 64;     // query rows per workgroup of attn_rows_kernel
 struct AttnLaunch {
     const uint16_t* q;
     size_t q_plane;
@@ -245,11 +247,12 @@ struct AttnLaunch {
     // rows of head_dim, and arrival counts of every (sequence, head, query group), zero between launches.
     KeyPart* plan = nullptr;
     int slots = 0;   // workgroups per (head, query group); 0: n_wg for every sequence
-    int shared = 0;  // see attention_item
+    int shared = 0;  // see attention_item (also of a lone block in attn_rows_kernel: its query groups are the places)
     long long part_rows = 0;
     int32_t* part_count = nullptr;
 };
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
+int attention_groups(int L);  // query groups (workgroups along the rows) that attention_workgroups reckons with
 int attention_workgroups(int len_bound, int L, int streams);
 // Whether the workgroups of a batch are dealt out by length (batch, L, n_heads, n_wg, cache_chunks, capacity, qkv, plan and
 // part_* are set): sets slots, shared and n_wg and returns what the embedding launch has to make, or nothing (slots 0).

@@ -1213,6 +1213,82 @@ __device__ __forceinline__ f32x4 load_through(const float* base, int off) {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 16));
 }
 
+// Keys cut by length: the workgroup that counts itself last merges the n_parts parts of its (sequence, head, query group) in part
+// order, as attn_combine_kernel does.  Part p's sums and maxima lie in slot slot0 + p, in NROW rows.  Stores and loads go
+// past the caches that other XCDs do not see, so nothing has to be written back or invalidated.  `st`: kMaxKeyParts * NROW
+// pairs in LDS, free behind the next barrier.
+template <int DH, int NROW, int NTH>
+__device__ __forceinline__ void merge_parts(const AttnLaunch& a, float* st, int& s_last, size_t slot0, int n_parts, int b, int h, int qg, int QG) {
+    constexpr int NIT = NROW * (DH / 4) / NTH;
+    static_assert(NROW * (DH / 4) % NTH == 0, "items");
+    const float* const ml = a.ml_part + slot0 * (NROW * 2);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int32_t* const count = a.part_count + (((size_t)b * a.n_heads + h) * QG + qg);
+    if (threadIdx.x == 0) {
+        const int before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = before == n_parts - 1;
+        if (s_last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
+    }
+    __syncthreads();
+    if (!s_last) return;
+    asm volatile("" ::: "memory");
+    // st: [part][row][max, sum], then the part's weight in place of the sum
+    for (int u = threadIdx.x; u < n_parts * NROW * 2; u += NTH)
+        st[u] = __hip_atomic_load(ml + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    f32x4 num[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) num[it] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();
+    if (threadIdx.x < NROW) {
+        float* const sr = st + threadIdx.x * 2;
+        float mx = -INFINITY, den = 0.f;
+        for (int p = 0; p < n_parts; ++p) mx = fmaxf(mx, sr[p * NROW * 2]);
+        for (int p = 0; p < n_parts; ++p) {
+            const float m = sr[p * NROW * 2], wgt = m == -INFINITY ? 0.f : exp2f(m - mx);
+            sr[p * NROW * 2] = wgt;
+            den += wgt * sr[p * NROW * 2 + 1];
+        }
+        // (a sum that is no number has to reach the output, as it does where one workgroup takes all keys)
+        for (int p = 0; p < n_parts; ++p) sr[p * NROW * 2 + 1] = den == 0.f ? 0.f : sr[p * NROW * 2] / den;
+    }
+    __syncthreads();
+    const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);
+    constexpr int kRowStep = NTH / (DH / 4);
+    for (int p = 0; p < n_parts; ++p) {
+        f32x4 v[NIT];
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) v[it] = load_through(a.o_part + (slot0 + p) * (NROW * DH), ((row0 + it * kRowStep) * DH + col) * 4);
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const float wgt = st[(p * NROW + row0 + it * kRowStep) * 2 + 1];
+            if (wgt != 0.f) num[it] += wgt * v[it];
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int tok = qg * NROW + row0 + it * kRowStep;
+        if (tok >= a.L) continue;
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint16_t hv = f2bf(num[it][e]);
+            hi[e] = hv;
+            lo[e] = f2bf(num[it][e] - bf2f(hv));
+        }
+        *(u32x2*)(a.out + xt_index(b * a.L + tok, h * DH + col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+        *(u32x2*)(a.out + xt_index(b * a.L + tok, h * DH + col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+    }
+}
+
+// Two values as bf16 hi and lo, packed.
+__device__ __forceinline__ void split_pair(float v0, float v1, uint32_t& hi, uint32_t& lo) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v0, v1}), bf16x2));
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v0 - __uint_as_float(hi << 16), v1 - __uint_as_float(hi & 0xffff0000u)}), bf16x2));
+}
+
 // WV waves per workgroup: 4, two workgroups to a CU (256 registers each, under half the LDS).  The kernel
 // is written for any count; 8 (one workgroup per CU) was measured and is not built: it was ahead only
 // while the 4-wave loop spilled registers, and is level with it since (one sequence of 4096 positions
@@ -1710,76 +1786,6 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     const size_t slot0 = ((size_t)h * QG + qg) * a.slots + (rank - wg);
     auto slot_o = [&](int p) { return a.o_part + (slot0 + p) * (TQ * 16 * DH); };
     auto slot_ml = [&](int p) { return a.ml_part + (slot0 + p) * (TQ * 16 * 2); };
-    // The workgroup that counts itself last merges the parts in part order, as attn_combine_kernel does.  Stores and loads go
-    // past the caches that other XCDs do not see, so nothing has to be written back or invalidated.
-    auto merge_last = [&]() {
-        constexpr int NTH = WV * 64, NROW = TQ * 16, NIT = NROW * (DH / 4) / NTH;
-        static_assert(NROW * (DH / 4) % NTH == 0 && kMaxKeyParts * NROW * 8 <= kPoolBytes, "items");
-        if (wave == 0 && g4 == 0) {
-#pragma unroll
-            for (int t = 0; t < TQ; ++t) {
-                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2, m_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2 + 1, l_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        int32_t* const count = a.part_count + (bh * QG + qg);
-        if (threadIdx.x == 0) {
-            const int before = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_last = before == n_wg - 1;
-            if (s_last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-        }
-        __syncthreads();
-        if (!s_last) return;
-        asm volatile("" ::: "memory");
-        float* const st = (float*)pool;  // [part][row][max, sum], then the part's weight in place of the sum
-        for (int u = threadIdx.x; u < n_wg * NROW * 2; u += NTH)
-            st[u] = __hip_atomic_load(slot_ml(0) + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        f32x4 num[NIT];
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) num[it] = f32x4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-        if (threadIdx.x < NROW) {
-            float* const sr = st + threadIdx.x * 2;
-            float mx = -INFINITY, den = 0.f;
-            for (int p = 0; p < n_wg; ++p) mx = fmaxf(mx, sr[p * NROW * 2]);
-            for (int p = 0; p < n_wg; ++p) {
-                const float m = sr[p * NROW * 2], wgt = m == -INFINITY ? 0.f : exp2f(m - mx);
-                sr[p * NROW * 2] = wgt;
-                den += wgt * sr[p * NROW * 2 + 1];
-            }
-            // (a sum that is no number has to reach the output, as it does where one workgroup takes all keys)
-            for (int p = 0; p < n_wg; ++p) sr[p * NROW * 2 + 1] = den == 0.f ? 0.f : sr[p * NROW * 2] / den;
-        }
-        __syncthreads();
-        const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);
-        constexpr int kRowStep = NTH / (DH / 4);
-        for (int p = 0; p < n_wg; ++p) {
-            f32x4 v[NIT];
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) v[it] = load_through(slot_o(p), ((row0 + it * kRowStep) * DH + col) * 4);
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const float wgt = st[(p * NROW + row0 + it * kRowStep) * 2 + 1];
-                if (wgt != 0.f) num[it] += wgt * v[it];
-            }
-        }
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int tok = r0 + row0 + it * kRowStep;
-            if (tok >= L) continue;
-            uint32_t hi[4], lo[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint16_t hv = f2bf(num[it][e]);
-                hi[e] = hv;
-                lo[e] = f2bf(num[it][e] - bf2f(hv));
-            }
-            *(u32x2*)(a.out + xt_index(b * L + tok, h * DH + col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
-            *(u32x2*)(a.out + xt_index(b * L + tok, h * DH + col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
-        }
-    };
 #pragma unroll
     for (int t = 0; t < TQ; ++t) {
         float mx = -INFINITY;
@@ -1835,7 +1841,16 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
         __syncthreads();
     }
     if constexpr (DEALT) {
-        if (n_wg > 1) merge_last();
+        if (n_wg == 1) return;
+        if (wave == 0 && g4 == 0) {
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) {
+                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2, m_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(slot_ml(wg) + (16 * t + c16) * 2 + 1, l_all[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        static_assert(kMaxKeyParts * TQ * 16 * 8 <= kPoolBytes, "LDS of the merge");
+        merge_parts<DH, TQ * 16, WV * 64>(a, (float*)pool, s_last, slot0, n_wg, b, h, qg, QG);
         return;
     }
     if (n_wg > 1 && wave == 0 && g4 == 0) {
@@ -1848,6 +1863,335 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
                 a.ml_part[base * 2 + 1] = l_all[t];
             }
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// attention of blocks of more than 96 rows (prompt chunks): the waves share the keys through LDS
+// ------------------------------------------------------------------------------------------
+// attn_sar_kernel gives every wave chunks of its own, straight into registers: right where the keys come from memory
+// and are used by few rows.  A prompt chunk is bound by the matrix unit and by what stands beside it: 1024 rows behind 1024 positions at
+// 7B are 51 GFLOP a layer (26 us at the rate the matrix unit sustains), but that kernel took 98, with a quarter of the
+// cycles in MFMAs, every wave by itself in a chain of memory, scores, softmax, output.  Here
+//   * a workgroup of 4 waves takes 64 rows of a head; wave w takes 32 of them (w % 2) and every second chunk of keys (w / 2), Q
+//     stays in registers, each operand tile read from LDS feeds four MFMAs;
+//   * two chunks at a time are copied from memory straight into LDS, double buffered, keys a stage ahead of values: the scores
+//     of the wave's next chunk (MFMAs) are issued between the softmax instructions of the current one, three to an MFMA;
+//   * two workgroups share a CU (70 KB of LDS, 230 registers), the longest with the shortest where that is all of the launch;
+//   * masking is skipped where Eq. 3 hides nothing, the output is rescaled only where a maximum has grown by more than 2^8.
+// Measured, us per layer at 7B, attn_sar_kernel / this one: 1024 rows behind 1024 positions 97.8 / 61.1, a prompt of 333 rows 17.8 /
+// 16.9.  Of the 61: 8 until the first stage has arrived, 50 for 49 stages per CU (1.8 us for two workgroups' stages, of which the
+// MFMAs need 1.0; 1.3 for a workgroup alone), 2 for the end.  Blocks of up to 96 rows stay with attn_sar_kernel, which keeps more keys
+// in flight: 8 sequences of 81 rows, up to 3685 positions, 81 us against 102.
+template <int DH, bool PAGED, bool DEALT>
+__global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float scale_log2e) {
+    constexpr int DS = DH / 32, DT = DH / 16, RT = 2;
+    constexpr int kRows = kAttnGroupRows;
+    static_assert(kRows == 4 * 16 * RT / 2 && 2 * DS == DT, "two waves along the rows, two along the keys");
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int rg = wave & 1, kh = wave >> 1;
+    const int h = blockIdx.y, L = a.L, H = a.n_heads, QG = (L + kRows - 1) / kRows;
+    int b, qg, n_wg = gridDim.x, wg = blockIdx.x, rank = 0, len;
+    if constexpr (DEALT) {
+        const int item = attention_item(blockIdx.z, gridDim.z, a.shared);
+        rank = item / QG;
+        qg = QG - 1 - item % QG;
+        const KeyPart kp = a.plan[rank];
+        if (kp.b < 0) return;  // whole workgroup: a slot that is left over
+        b = kp.b;
+        wg = kp.part;
+        n_wg = kp.n_parts;
+        len = kp.len;
+    } else {
+        // the later a group sits in the block the more keys it sees: these start first, and where two workgroups share a
+        // CU the longest of a lone sequence go with the shortest
+        b = blockIdx.z / QG;
+        qg = QG - 1 - (a.batch == 1 ? attention_item(blockIdx.z, QG, a.shared) : (int)blockIdx.z % QG);
+        len = min(max(a.kv_len[b], 0), a.capacity);
+    }
+    const int r0 = qg * kRows, row0 = r0 + rg * 16 * RT;
+    const size_t bh = (size_t)b * H + h;
+
+    // (requested in front of everything that waits for the length)
+    u32x4 qh[RT][DS], ql[RT][DS];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            const uint16_t* q = a.q + (bh * L + min(row0 + 16 * t + c16, L - 1)) * DH + 32 * ds + 8 * g4;
+            qh[t][ds] = *(const u32x4*)q;
+            ql[t][ds] = *(const u32x4*)(q + a.q_plane);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // keys and values of two chunks, twice, in operand order (arrays of their own, so that the compiler sees that the copies on
+    // their way do not touch what is read)
+    __shared__ u32x4 k_a[2][DT * 64], k_b[2][DT * 64], v_a[2][DT * 64], v_b[2][DT * 64];
+    __shared__ __attribute__((aligned(16))) int s_info[kMaxBlockRows];
+    __shared__ unsigned long long s_masks[kMaxBlockRows / 64];  // a bit per row: is it a mask
+    __shared__ float m_sh[4][16 * RT], l_sh[4][16 * RT];
+    __shared__ int s_last;
+
+    // in-block keys past this group's last row are invisible to all of its rows (Eq. 3 is causal)
+    const int n_cache = (len + kAttnKeys - 1) / kAttnKeys, n_blk = (min(L, r0 + kRows) + kAttnKeys - 1) / kAttnKeys;
+    const int n_chunks = n_cache + n_blk, n_stages = (n_chunks + 1) / 2;
+    const int kvh = h / (H / a.n_kv_heads);
+    const size_t bkv = (size_t)b * a.n_kv_heads + kvh;
+
+    // wave w copies the keys (w even) or the values (w odd) of chunk w / 2 of a stage; lanes as in attn_sar_kernel
+    const int cp_j = wave >> 1, cp_v = wave & 1;
+    const int lane_off = cp_v ? 2 * (c16 * kAttnKeys + 8 * g4) : 2 * ((8 * (c16 >> 2) + (c16 & 3)) * DH + 8 * g4);
+    const uint16_t* const cache = cp_v ? a.vc : a.kc;
+    const uint16_t* const block = (cp_v ? a.vblk : a.kblk) + bkv * a.Lp * DH;
+    auto base_of = [&](int stage) -> const uint16_t* {
+        const int ch = min(2 * stage + cp_j, n_chunks - 1);
+        return ch >= n_cache ? block + (size_t)(ch - n_cache) * kAttnKeys * DH
+                             : cache + kv_run_offset<PAGED>(a.paging, b, kvh, a.n_kv_heads, a.capacity, DH, ch);
+    };
+    auto copy = [&](u32x4(&to)[2][DT * 64], const uint16_t* base) {  // DT operand tiles of 1 KB either way
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, -1, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < DT; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)&to[cp_j][i * 64], 16, lane_off,
+                                                     cp_v ? i * 32 * kAttnKeys : (i / DS) * 8 * DH + (i % DS) * 64, 0, 0);
+    };
+
+    // Keys are a stage ahead of the values: the scores of a wave's next chunk are computed beside the softmax of the current one.
+    if (cp_v) {
+        copy(v_a, base_of(wg));
+    } else {
+        copy(k_a, base_of(wg));
+        copy(k_b, base_of(wg + n_wg));
+    }
+    const uint16_t* next = base_of(wg + (cp_v ? 1 : 2) * n_wg);
+    if (wg >= n_stages) {  // (only where every sequence has gridDim.x: the grid is sized for a bound of the length)
+        __builtin_amdgcn_s_waitcnt(0x0070);  // the copies write LDS
+        const int tok = r0 + (int)threadIdx.x;
+        if (threadIdx.x < kRows && tok < L) {
+            const size_t base = (bh * n_wg + wg) * L + tok;
+            a.ml_part[base * 2] = -INFINITY;
+            a.ml_part[base * 2 + 1] = 0.f;
+        }
+        return;
+    }
+    for (int i0 = wave * 64; i0 < n_blk * kAttnKeys; i0 += 256) {
+        const int word = a.info[min(i0 + lane, L - 1)];
+        s_info[i0 + lane] = word;
+        const unsigned long long bits = __builtin_amdgcn_ballot_w64(word & 1);
+        if (lane == 0) s_masks[i0 >> 6] = bits;
+    }
+
+    int my_info[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) my_info[t] = a.info[min(row0 + 16 * t + c16, L - 1)];
+    f32x4 o[DT][RT];
+    float m_w[RT], l_w[RT];  // running maximum (log2 domain) and sum of this wave's chunks
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        m_w[t] = -INFINITY;
+        l_w[t] = 0.f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    float neg_m[RT];  // what the scores are lowered by: -m_w, 0 while nothing was visible
+#pragma unroll
+    for (int t = 0; t < RT; ++t) neg_m[t] = 0.f;
+    auto scores = [&](const u32x4(&keys)[2][DT * 64], f32x4(&sc)[2][RT]) {
+        const u32x4* const tile = keys[kh] + lane;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) sc[0][t] = sc[1][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+            const u32x4 k0 = tile[ds * 64], k1 = tile[(DS + ds) * 64];
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                sc[0][t] = mfma16(k0, qh[t][ds], sc[0][t]);
+                sc[1][t] = mfma16(k1, qh[t][ds], sc[1][t]);
+            }
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                sc[0][t] = mfma16(k0, ql[t][ds], sc[0][t]);
+                sc[1][t] = mfma16(k1, ql[t][ds], sc[1][t]);
+            }
+        }
+    };
+    // the wave's chunk of a stage, whose scores are in sc; those of the next stage go to sc_next
+    auto compute = [&](int stage, f32x4(&sc)[2][RT], const u32x4(&vals)[2][DT * 64], const u32x4(&keys_next)[2][DT * 64], f32x4(&sc_next)[2][RT]) {
+        const int ch = 2 * stage + kh;
+        const bool blk = ch >= n_cache;
+        const int C = (blk ? ch - n_cache : ch) * kAttnKeys, kend = blk ? L : len;
+        // (wave uniform, and once true it stays true: nothing behind such a chunk is visible either)
+        if (ch >= n_chunks || row0 >= L || (blk && C >= row0 + 16 * RT)) return;
+        // Eq. 3 where it can hide something: at the end of the keys, and in the block's own chunks with mask rows or with keys
+        // behind the wave's first row
+        if (C + kAttnKeys > kend || (blk && (C + kAttnKeys - 1 > row0 || (unsigned)(s_masks[C >> 6] >> (C & 32)) != 0))) {
+            int kinfo[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) kinfo[j] = s_info[(blk ? C : 0) + 8 * g4 + j];
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int key = C + 8 * g4 + j;
+                    const bool vis = !blk | ((key <= row0 + 16 * t + c16) & (!(kinfo[j] & 1) | (kinfo[j] == my_info[t])));
+                    sc[j >> 2][t][j & 3] = ((key < kend) & vis) ? sc[j >> 2][t][j & 3] : -INFINITY;
+                }
+        }
+        // The maximum that the exponentials refer to follows the running one only where it has fallen behind by more than
+        // 2^8: sums and weights carry the same factor, and the output is rescaled in few chunks instead of most.
+        float m_new[RT];
+        bool moved = false;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            float cm = sc[0][t][0];
+#pragma unroll
+            for (int j = 1; j < 8; ++j) cm = fmaxf(cm, sc[j >> 2][t][j & 3]);
+            m_new[t] = row_groups_max(cm) * scale_log2e;
+            moved |= m_new[t] > m_w[t] + 8.f;
+        }
+        if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                m_new[t] = fmaxf(m_w[t], m_new[t]);
+                neg_m[t] = m_new[t] == -INFINITY ? 0.f : -m_new[t];
+                const float alpha = __builtin_amdgcn_exp2f(m_w[t] + neg_m[t]);
+                m_w[t] = m_new[t];
+                l_w[t] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) o[dt][t] *= alpha;
+            }
+        }
+        scores(keys_next, sc_next);
+        u32x4 p_hi[RT], p_lo[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            float p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(sc[j >> 2][t][j & 3], scale_log2e, neg_m[t]));
+            l_w[t] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));  // this lane's 8 keys; the lane groups at the end
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t hi, lo;
+                split_pair(p[2 * j], p[2 * j + 1], hi, lo);
+                p_hi[t][j] = hi;
+                p_lo[t][j] = lo;
+            }
+        }
+        const u32x4* const tile = vals[kh] + lane;
+#pragma unroll
+        for (int dt = 0; dt < DT; dt += 2) {  // four MFMAs lie between the two that add into the same sums
+            const u32x4 v0 = tile[dt * 64], v1 = tile[(dt + 1) * 64];
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                o[dt][t] = mfma16(v0, p_hi[t], o[dt][t]);
+                o[dt + 1][t] = mfma16(v1, p_hi[t], o[dt + 1][t]);
+            }
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                o[dt][t] = mfma16(v0, p_lo[t], o[dt][t]);
+                o[dt + 1][t] = mfma16(v1, p_lo[t], o[dt + 1][t]);
+            }
+        }
+        // the order wanted: behind every score MFMA three instructions of the softmax, which does not wait for it; LDS reads a
+        // round ahead
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int ds = 0; ds < DS; ++ds) {
+#pragma unroll
+            for (int i = 0; i < 4 * RT; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x402, 12 / DS, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; dt += 2) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 4 * RT, 0);
+            if (dt < DT - 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+    };
+    // own copies have landed and own reads are done; then everybody's
+    auto stage_end = [&]() {
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __syncthreads();
+    };
+    f32x4 sc_a[2][RT], sc_b[2][RT];
+    stage_end();
+    scores(k_a, sc_a);
+    stage_end();
+    // what a stage needs beyond the current one; an index past the end is clamped to the last chunk and copied again
+    for (int stage = wg;;) {
+        if (cp_v) copy(v_b, next);
+        else copy(k_a, next);
+        next = base_of(stage + (cp_v ? 2 : 3) * n_wg);
+        compute(stage, sc_a, v_a, k_b, sc_b);
+        stage_end();
+        stage += n_wg;
+        if (stage >= n_stages) break;
+        if (cp_v) copy(v_a, next);
+        else copy(k_b, next);
+        next = base_of(stage + (cp_v ? 2 : 3) * n_wg);
+        compute(stage, sc_b, v_b, k_a, sc_a);
+        stage_end();
+        stage += n_wg;
+        if (stage >= n_stages) break;
+    }
+
+    // The two waves of a row group exchange a row tile each: wave kh merges and writes tile kh.
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        l_w[t] = row_groups_sum(l_w[t]);
+        if (g4 == 0) {
+            m_sh[wave][16 * t + c16] = m_w[t];
+            l_sh[wave][16 * t + c16] = l_w[t];
+        }
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) ((f32x4*)(kh ? k_b : k_a)[rg])[dt * 64 + lane] = kh ? o[dt][0] : o[dt][1];
+    __syncthreads();
+    const int other = wave ^ 2, rr = rg * 16 * RT + 16 * kh + c16, tok = r0 + rr;
+    const float m_own = m_sh[wave][16 * kh + c16], m_oth = m_sh[other][16 * kh + c16];
+    const float m_all = fmaxf(m_own, m_oth), m_use = m_all == -INFINITY ? 0.f : m_all;
+    const float e_own = __builtin_amdgcn_exp2f(m_own - m_use), e_oth = __builtin_amdgcn_exp2f(m_oth - m_use);
+    const float l_all = l_sh[wave][16 * kh + c16] * e_own + l_sh[other][16 * kh + c16] * e_oth;
+    // where part p of this sequence leaves its sums (parts of a sequence lie one behind the other)
+    const size_t slot0 = ((size_t)h * QG + qg) * a.slots + (rank - wg);
+    const float wgt = l_all > 0.f ? 1.0f / l_all : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+        const f32x4 sum = (kh ? o[dt][1] : o[dt][0]) * e_own + ((const f32x4*)(kh ? k_a : k_b)[rg])[dt * 64 + lane] * e_oth;
+        if (tok >= L) continue;
+        if (n_wg == 1) {  // the only workgroup of this (sequence, head, query group): the operand planes of the output projection
+            uint32_t hi[4], lo[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = wgt * sum[e];
+                const uint16_t hv = f2bf(v);
+                hi[e] = hv;
+                lo[e] = f2bf(v - bf2f(hv));
+            }
+            const int col = h * DH + 16 * dt + 4 * g4;
+            *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+            *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+        } else if (DEALT) {
+            store_through(a.o_part + (slot0 + wg) * (kRows * DH), (rr * DH + 16 * dt + 4 * g4) * 4, sum);
+        } else {
+            *(f32x4*)(a.o_part + ((bh * n_wg + wg) * L + tok) * DH + 16 * dt + 4 * g4) = sum;
+        }
+    }
+    if (n_wg == 1) return;
+    if constexpr (DEALT) {
+        if (g4 == 0) {
+            float* const ml = a.ml_part + ((slot0 + wg) * kRows + rr) * 2;
+            __hip_atomic_store(ml, m_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(ml + 1, l_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        merge_parts<DH, kRows, 256>(a, (float*)v_a, s_last, slot0, n_wg, b, h, qg, QG);
+    } else if (g4 == 0 && tok < L) {
+        const size_t base = (bh * n_wg + wg) * L + tok;
+        a.ml_part[base * 2] = m_all;
+        a.ml_part[base * 2 + 1] = l_all;
     }
 }
 
@@ -2295,14 +2639,16 @@ int attention_workgroups(int len_bound, int L, int streams) {
     return want < cap ? want : cap;
 }
 
-// Query tiles per workgroup.  Three share every chunk of keys best (long blocks: 3 tiles 165 us, 2 tiles 184 us at
-// 1024 rows behind 3000 positions, 7B), two make more and shorter workgroups: better while all of them are on
-// the chip at once, two per CU (7B: 333 rows 17.1 -> 14.0, 400 rows 21.2 -> 16.8, 512 rows 23.0 -> 18.1 and behind
-// 1024 positions 48.7 -> 44.2; 70B: 256 rows 18.9 -> 14.1) -- unless three give every CU at most one and
-// the cached keys, which all workgroups read alike, outweigh the block's own (13B: 256 rows behind 1500
-// positions 41.0 against 48.1).  Where both make the same number of groups, two waste less on padding.
+int attention_groups(int L) { return L > kAttnSplitMaxRows ? ceil_div(L, kAttnGroupRows) : ceil_div(ceil_div(L, 16), 3); }
+
+// Query tiles per workgroup of blocks of 49 to 96 rows.  Three share every chunk of keys best, two make more and shorter
+// workgroups: better while all of them are on the chip at once, two per CU (prompts of 333 and 512 rows, when this kernel took them:
+// 17.1 -> 14.0 us, 23.0 -> 18.1) -- unless three give every CU at most one and the cached keys, which all workgroups read alike,
+// outweigh the block's own (13B behind 1500 positions 41.0 against 48.1).  Where both make the same number of groups, two waste
+// less on padding.
 static int attention_query_tiles(const AttnLaunch& a) {
     const int tiles = ceil_div(a.L, 16);
+    if (a.L > kAttnSplitMaxRows) return kAttnGroupRows / 16;
     if (tiles < 3 || a.qkv) return tiles < 3 ? tiles : 3;
     const int per = a.batch * a.n_heads * a.n_wg, wgs3 = per * ceil_div(tiles, 3), wgs2 = per * ceil_div(tiles, 2);
     if (wgs2 == wgs3) return 2;
@@ -2334,6 +2680,7 @@ KeyPlan schedule_attention(AttnLaunch* a) {
     one.n_wg = 1;  // as the launch will be
     const int TQ = attention_query_tiles(one), QG = ceil_div(ceil_div(a->L, 16), TQ), streams = a->n_heads * QG;
     a->slots = a->shared = 0;
+    if (a->batch == 1 && a->n_wg == 1) a->shared = std::max(0, attention_shared(QG, a->n_heads));
     if (!a->plan || a->batch < 2 || a->batch > 64) return p;
     a->slots = attention_slots(*a, QG, TQ);
     if (!a->slots && a->n_wg == 1 && a->batch * streams > 256) a->slots = a->batch;
@@ -2377,7 +2724,11 @@ static hipError_t launch_attention_dh(const AttnLaunch& a, hipStream_t s) {
     switch (TQ) {
         case 1: launch(std::integral_constant<int, 1>{}); break;
         case 2: launch(std::integral_constant<int, 2>{}); break;
-        default: launch(std::integral_constant<int, 3>{}); break;
+        case 3: launch(std::integral_constant<int, 3>{}); break;
+        default:
+            if (a.qkv || a.shared < (a.slots ? -1 : 0) || 2 * a.shared > (int)grid.z) return hipErrorInvalidValue;
+            if (a.slots) hipLaunchKernelGGL((attn_rows_kernel<DH, PAGED, true>), grid, block, 0, s, a, scale_log2e);
+            else hipLaunchKernelGGL((attn_rows_kernel<DH, PAGED, false>), grid, block, 0, s, a, scale_log2e);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.n_wg == 1) return e;  // a single workgroup along the keys writes the output itself

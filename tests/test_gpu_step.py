@@ -290,6 +290,71 @@ def test_long_prompt_chunks_match_oracle(torch_mod, shape_name, n_prompt, chunk)
         assert e.value.code == binding.SPACE_ESHAPE
 
 
+@pytest.mark.parametrize("shape_name,rows,k,ctxs,paged", [
+    ("tiny", 97, 0, [0], False),                # two row groups, the second one row into its second wave
+    ("gqa128", 128, 0, [31, 700], False),       # full groups, keys cut into equal parts, an empty part of the short sequence
+    ("gqa128", 129, 0, [1], True),              # a third group of one row
+    ("tiny", 321, 0, [1023], False),            # more workgroups than one round of a lone sequence's
+    ("tiny", 100, 9, [0, 45, 700], False),      # mask rows
+    ("gqa128", 121, 10, [333], True),
+    ("gqa-small", 97, 0, "ragged", False),      # a batch dealt out and cut by length, merged by whoever ends last
+    ("gqa-small", 121, 10, "ragged", True),
+])
+def test_attention_of_long_blocks(torch_mod, shape_name, rows, k, ctxs, paged):
+    """Blocks beyond 96 rows through space_prefill, prompts and blocks with mask rows, at the edges of the 64-row groups, 32-key
+    chunks and 64-key stages: the first layer's attention output of every row against the oracle's, and the keys and values of
+    the layer behind it."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import binding, layout as lo
+    shape = dataclasses.replace(SHAPES[shape_name], n_layers=2)
+    w = all_weights(shape, seed=8)
+    spec = lo.paper_layout(k) if k else lo.prefill_layout(rows)
+    assert spec.n_rows == rows
+    if ctxs == "ragged":
+        ctxs = [(151 * b) % 690 for b in range(19)] + [700]
+    B, cap = len(ctxs), -(-(max(ctxs) + spec.n_groups) // 32) * 32
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=cap)
+    om = gc.oracle_model(shape, w)
+    okvs = [gc.synthetic_oracle_kv(om, seed=30 + b, ctx=c, std=0.5) for b, c in enumerate(ctxs)]
+    cache = gm.kv_cache(B, cap)
+    for b in range(B):
+        gc.upload_oracle_kv(torch, cache, b, okvs[b])
+    kv = cache
+    if paged:
+        per = cap // 32
+        order = torch.randperm(B * per, generator=torch.Generator().manual_seed(1)).view(B, per)
+        kv = binding.PagedKV(binding.PagePool(gm, B * per), order.int().cuda().contiguous(), cache.len)
+        kv.set_len_bound(max(ctxs))
+        for b in range(B):
+            at = order[b].cuda()
+            kv.pool.k_view()[:, at] = cache.k_view()[:, b].unflatten(2, (per, 32)).transpose(1, 2)
+            kv.pool.v_view()[:, at] = cache.v_view()[:, b].transpose(1, 2)
+    rng = np.random.default_rng(11)
+    toks = rng.integers(0, shape.vocab, size=(B, rows)).astype(np.int32)
+    toks[:, spec.is_mask.astype(bool)] = shape.mask_id
+    gm.prefill(torch.from_numpy(toks).cuda(), gm.layout(spec), kv)
+    torch.cuda.synchronize()
+    assert gm.device_faults() == 0
+    hd = shape.n_heads * shape.head_dim
+    out = gc.decode_planes(gm.debug_buffer("attn_out"), B * rows, hd).reshape(B, rows, hd)
+    if paged:
+        for b in range(B):
+            at = order[b].cuda()
+            cache.k_view()[:, b] = kv.pool.k_view()[:, at].transpose(1, 2).flatten(2, 3)
+            cache.v_view()[:, b] = kv.pool.v_view()[:, at].transpose(1, 2)
+    real = gc.real_rows(spec)
+    for b, c in enumerate(ctxs):
+        trace = []
+        _, ks, vs, _ = so.block_forward_cached(om, okvs[b], toks[b].astype(np.int64), spec.is_mask.astype(bool), k=k or None, trace=trace)
+        # 2^-17 per operand and sums in 32 bits, beside the block's own keys and values that round to the other bf16 neighbour
+        # (some in ten thousand, a step of 2^-8 of one of the keys of a row)
+        assert np.abs(out[b] - trace[0]["attn_out"].reshape(rows, hd)).max() < 2e-3, b
+        got_k, got_v = gc.download_kv_rows(cache, 1, b, c, c + len(real))
+        gc.assert_bf16_close(got_k, np.asarray(ks[1])[real], f"keys of {b}", min_same=0.9)
+        gc.assert_bf16_close(got_v, np.asarray(vs[1])[real], f"values of {b}", min_same=0.9)
+
+
 def _batched_step_vs_oracle(torch, shape, w, B, k, tune, tol, threads=1, ctxs=None, capacity=160):
     from paper_2402_11809_amd import binding, layout as lo
     spec = lo.paper_layout(k)

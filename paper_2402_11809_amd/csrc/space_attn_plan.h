@@ -55,6 +55,17 @@ constexpr int key_parts(const KeySeq& s, int size, int longest) {
 }
 constexpr int key_part_chunks(const KeySeq& s, int n) { return n ? (s.chunks + n - 1) / n : 0; }
 
+// Rounds of cached chunks (a chunk per wave each) of every part but the last, which takes what is left: it also stages the block's
+// keys and values and takes its chunks, which costs as much as kBlockRounds of them (measured in a batch of 8 x 36 rows, us: staging 14
+// instead of 6, the block's chunks 2, a round 4.4 while HBM is busy; with equal parts the last ones ended 10 us behind all others).
+// No part before the last is empty.
+constexpr int kBlockRounds = 2;
+constexpr int key_part_rounds(int rounds, int n_parts) {
+    if (n_parts < 2) return rounds;
+    const int even = (rounds + kBlockRounds + n_parts - 1) / n_parts, most = rounds / (n_parts - 1);
+    return even < most ? even : most > 1 ? most : 1;
+}
+
 // What the busiest CU spends on `parts` parts of at most `largest` chunks: these and, worth kPartStaging chunks, the staging of
 // the block; beyond a workgroup per CU the mean over the CUs, of which 232 are taken to be busy, counts as well.
 constexpr int kPartStaging = 16;

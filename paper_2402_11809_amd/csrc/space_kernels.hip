@@ -1234,9 +1234,21 @@ __device__ __forceinline__ void merge_parts(const AttnLaunch& a, float* st, int&
     if (!s_last) return;
     asm volatile("" ::: "memory");
     // st: [part][row][max, sum], then the part's weight in place of the sum
+    const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);
+    constexpr int kRowStep = NTH / (DH / 4);
     for (int u = threadIdx.x; u < n_parts * NROW * 2; u += NTH)
         st[u] = __hip_atomic_load(ml + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    f32x4 num[NIT];
+    // the sums of four parts are requested at a time (a part's were, one behind the other: a trip to memory each)
+    constexpr int kAtOnce = 4;
+    f32x4 num[NIT], v[kAtOnce][NIT];
+    auto fetch = [&](int p0) {
+#pragma unroll
+        for (int p = 0; p < kAtOnce; ++p)
+#pragma unroll
+            for (int it = 0; it < NIT; ++it)
+                v[p][it] = load_through(a.o_part + (slot0 + min(p0 + p, n_parts - 1)) * (NROW * DH), ((row0 + it * kRowStep) * DH + col) * 4);
+    };
+    fetch(0);
 #pragma unroll
     for (int it = 0; it < NIT; ++it) num[it] = f32x4{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
@@ -1253,16 +1265,16 @@ __device__ __forceinline__ void merge_parts(const AttnLaunch& a, float* st, int&
         for (int p = 0; p < n_parts; ++p) sr[p * NROW * 2 + 1] = den == 0.f ? 0.f : sr[p * NROW * 2] / den;
     }
     __syncthreads();
-    const int col = (threadIdx.x % (DH / 4)) * 4, row0 = threadIdx.x / (DH / 4);
-    constexpr int kRowStep = NTH / (DH / 4);
-    for (int p = 0; p < n_parts; ++p) {
-        f32x4 v[NIT];
+    for (int p0 = 0; p0 < n_parts; p0 += kAtOnce) {
+        if (p0) fetch(p0);
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) v[it] = load_through(a.o_part + (slot0 + p) * (NROW * DH), ((row0 + it * kRowStep) * DH + col) * 4);
+        for (int p = 0; p < kAtOnce; ++p) {
+            if (p0 + p >= n_parts) break;
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const float wgt = st[(p * NROW + row0 + it * kRowStep) * 2 + 1];
-            if (wgt != 0.f) num[it] += wgt * v[it];
+            for (int it = 0; it < NIT; ++it) {
+                const float wgt = st[((p0 + p) * NROW + row0 + it * kRowStep) * 2 + 1];
+                if (wgt != 0.f) num[it] += wgt * v[p][it];
+            }
         }
     }
 #pragma unroll
@@ -1350,9 +1362,16 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     const int n_cache = (len + kAttnKeys - 1) / kAttnKeys, n_blk = (min(L, r0 + TQ * 16) + kAttnKeys - 1) / kAttnKeys;
     // FUSE: the pipelined loop runs over the cache chunks only; the last workgroup along the keys (which
     // the bound the grid was sized for usually leaves without cache chunks) takes the block's own
-    const int n_chunks = FUSE ? n_cache : n_cache + n_blk;
+    int n_chunks = FUSE ? n_cache : n_cache + n_blk;
     const bool blk_wg = FUSE && wg == n_wg - 1;
-    if (wg * WV >= n_chunks && !blk_wg) {
+    int chunk_step = n_wg * WV, chunk = wg * WV + wave;
+    if (FUSE && DEALT) {  // the last part has more to do beside the cache
+        const int per = key_part_rounds((n_cache + WV - 1) / WV, n_wg);
+        chunk_step = WV;
+        chunk = wg * per * WV + wave;
+        if (!blk_wg) n_chunks = min(n_chunks, (wg + 1) * per * WV);
+    }
+    if (!DEALT && wg * WV >= n_chunks && !blk_wg) {
         // the grid is sized for an upper bound of the length: a workgroup past the real end only
         // marks its partial as empty (the merge pass skips it)
         const int tok = r0 + (int)threadIdx.x;
@@ -1363,8 +1382,6 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
         }
         return;
     }
-    const int chunk_step = n_wg * WV;
-    int chunk = wg * WV + wave;
     // grouped-query attention: query head h reads key/value head h / (H / Hkv)
     const int kvh = h / (H / a.n_kv_heads);
     const size_t bkv = (size_t)b * a.n_kv_heads + kvh;

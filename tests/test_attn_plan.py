@@ -109,6 +109,26 @@ int main() {
 """
 
 
+_ROUNDS_PROGRAM = r"""
+#include <cstdio>
+#include "space_attn_plan.h"
+using namespace space;
+
+int main() {
+    int wrong = 0;
+    for (int chunks = 0; chunks <= 4100; ++chunks)
+        for (int n = 1; n <= key_seq(chunks, 2).most; ++n) {
+            const int rounds = (chunks + 3) / 4, per = key_part_rounds(rounds, n);
+            // every part but the last has `per` of them, and so many there are; the last no more than the others
+            const int last = rounds - (n - 1) * per;
+            const bool ok = n == 1 ? per == rounds : per >= 1 && last >= 0 && (last <= per || rounds / (n - 1) == per);
+            if (!ok && wrong++ < 5) printf("%d chunks in %d parts: %d rounds\n", chunks, n, per);
+        }
+    return wrong;
+}
+"""
+
+
 def _run(tmp_path, program):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
@@ -132,3 +152,9 @@ def test_every_part_has_one_place_in_the_table(tmp_path):
     number of slots: the parts fit the slots, every part of every sequence has one place, those of a sequence lie side by side, larger
     ones in front; a sequence is cut into at most 16 parts of at least four cached chunks; left-over slots are at the end."""
     _run(tmp_path, _TABLE_PROGRAM)
+
+
+def test_rounds_of_a_part(tmp_path):
+    """Every number of cached chunks and of parts that a sequence may have: the parts before the last are full, and the last, which also
+    has the block, is never longer than they are unless they could not be either."""
+    _run(tmp_path, _ROUNDS_PROGRAM)

@@ -403,7 +403,7 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     // (the step launches with at least n_heads * query groups streams, more with a batch)
     size_t wg_rows = 1;
     for (int L = 1; L <= c.max_rows; ++L) {
-        const int wg = attention_workgroups(c.max_ctx, L, c.n_heads * attention_groups(L));
+        const int wg = attention_workgroups(c.max_ctx, L, c.n_heads * ceil_div(ceil_div(L, 16), 3));
         wg_rows = std::max(wg_rows, (size_t)wg * L);
         ctx->attn_wg_max = std::max(ctx->attn_wg_max, wg);
     }
@@ -746,7 +746,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const XtShape xs = xt_shape(M);
     // the real lengths live on the device; the grid covers the host-side upper bound
     const int attn_chunks = ceil_div(kv->host_len_bound, kAttnKeys) + ceil_div(L, kAttnKeys);
-    const int attn_streams = B * c.n_heads * attention_groups(L);
+    const int attn_streams = B * c.n_heads * attention_groups(B, c.n_heads, L);
     const int attn_wg = attention_workgroups(kv->host_len_bound, L, attn_streams);
     const size_t kv_layer = kv->block_table ? (size_t)kv->n_pages * ctx->kv_heads * kAttnKeys * dh
                                             : (size_t)B * ctx->kv_heads * kv->capacity * dh;

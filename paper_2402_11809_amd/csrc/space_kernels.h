@@ -210,8 +210,8 @@ struct RopeStore {
 hipError_t launch_rope_store(const RopeStore& a, hipStream_t s);
 
 constexpr int kHeadAttnMaxRows = 48;  // longest block the fused rotary + attention kernels take
-constexpr int kAttnSplitMaxRows = 96;  // longest block of attn_sar_kernel; longer ones (prompt chunks): attn_rows_kernel
-constexpr int kAttnGroupRows = 64;     // query rows per workgroup of attn_rows_kernel
+constexpr int kAttnRowsMin = 192;     // blocks of more rows may go to attn_rows_kernel (attention_by_rows)
+constexpr int kAttnGroupRows = 64;    // query rows per workgroup of attn_rows_kernel
 struct AttnLaunch {
     const uint16_t* q;
     size_t q_plane;
@@ -252,7 +252,7 @@ struct AttnLaunch {
     int32_t* part_count = nullptr;
 };
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
-int attention_groups(int L);  // query groups (workgroups along the rows) that attention_workgroups reckons with
+int attention_groups(int batch, int n_heads, int L);  // query groups (workgroups along the rows) that attention_workgroups reckons with
 int attention_workgroups(int len_bound, int L, int streams);
 // Whether the workgroups of a batch are dealt out by length (batch, L, n_heads, n_wg, cache_chunks, capacity, qkv, plan and
 // part_* are set): sets slots, shared and n_wg and returns what the embedding launch has to make, or nothing (slots 0).

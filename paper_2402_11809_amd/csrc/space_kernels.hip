@@ -1881,7 +1881,7 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
 }
 
 // ------------------------------------------------------------------------------------------
-// attention of blocks of more than 96 rows (prompt chunks): the waves share the keys through LDS
+// attention of long blocks (prompt chunks, attention_by_rows): the waves share the keys through LDS
 // ------------------------------------------------------------------------------------------
 // attn_sar_kernel gives every wave chunks of its own, straight into registers: right where the keys come from memory
 // and are used by few rows.  A prompt chunk is bound by the matrix unit and by what stands beside it: 1024 rows behind 1024 positions at
@@ -1893,10 +1893,8 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
 //     of the wave's next chunk (MFMAs) are issued between the softmax instructions of the current one, three to an MFMA;
 //   * two workgroups share a CU (70 KB of LDS, 230 registers), the longest with the shortest where that is all of the launch;
 //   * masking is skipped where Eq. 3 hides nothing, the output is rescaled only where a maximum has grown by more than 2^8.
-// Measured, us per layer at 7B, attn_sar_kernel / this one: 1024 rows behind 1024 positions 97.8 / 61.1, a prompt of 333 rows 17.8 /
-// 16.9.  Of the 61: 8 until the first stage has arrived, 50 for 49 stages per CU (1.8 us for two workgroups' stages, of which the
-// MFMAs need 1.0; 1.3 for a workgroup alone), 2 for the end.  Blocks of up to 96 rows stay with attn_sar_kernel, which keeps more keys
-// in flight: 8 sequences of 81 rows, up to 3685 positions, 81 us against 102.
+// 1024 rows behind 1024 positions: 97.8 -> 61.1 us per layer.  Of these 8 go until the first stage has arrived, 50 for 49 stages per CU
+// (1.8 us for two workgroups' stages, of which the MFMAs need 1.0; 1.3 for a workgroup alone), 2 for the end.
 template <int DH, bool PAGED, bool DEALT>
 __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float scale_log2e) {
     constexpr int DS = DH / 32, DT = DH / 16, RT = 2;
@@ -1906,7 +1904,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int rg = wave & 1, kh = wave >> 1;
     const int h = blockIdx.y, L = a.L, H = a.n_heads, QG = (L + kRows - 1) / kRows;
-    int b, qg, n_wg = gridDim.x, wg = blockIdx.x, rank = 0, len;
+    int b, qg, n_wg = 1, wg = 0, rank = 0, len;
     if constexpr (DEALT) {
         const int item = attention_item(blockIdx.z, gridDim.z, a.shared);
         rank = item / QG;
@@ -1979,16 +1977,6 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
         copy(k_b, base_of(wg + n_wg));
     }
     const uint16_t* next = base_of(wg + (cp_v ? 1 : 2) * n_wg);
-    if (wg >= n_stages) {  // (only where every sequence has gridDim.x: the grid is sized for a bound of the length)
-        __builtin_amdgcn_s_waitcnt(0x0070);  // the copies write LDS
-        const int tok = r0 + (int)threadIdx.x;
-        if (threadIdx.x < kRows && tok < L) {
-            const size_t base = (bh * n_wg + wg) * L + tok;
-            a.ml_part[base * 2] = -INFINITY;
-            a.ml_part[base * 2 + 1] = 0.f;
-        }
-        return;
-    }
     for (int i0 = wave * 64; i0 < n_blk * kAttnKeys; i0 += 256) {
         const int word = a.info[min(i0 + lane, L - 1)];
         s_info[i0 + lane] = word;
@@ -2188,10 +2176,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
             const int col = h * DH + 16 * dt + 4 * g4;
             *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 0)) = u32x2{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
             *(u32x2*)(a.out + xt_index(b * L + tok, col, a.out_shape, 1)) = u32x2{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
-        } else if (DEALT) {
-            store_through(a.o_part + (slot0 + wg) * (kRows * DH), (rr * DH + 16 * dt + 4 * g4) * 4, sum);
         } else {
-            *(f32x4*)(a.o_part + ((bh * n_wg + wg) * L + tok) * DH + 16 * dt + 4 * g4) = sum;
+            store_through(a.o_part + (slot0 + wg) * (kRows * DH), (rr * DH + 16 * dt + 4 * g4) * 4, sum);
         }
     }
     if (n_wg == 1) return;
@@ -2202,10 +2188,6 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
             __hip_atomic_store(ml + 1, l_all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         merge_parts<DH, kRows, 256>(a, (float*)v_a, s_last, slot0, n_wg, b, h, qg, QG);
-    } else if (g4 == 0 && tok < L) {
-        const size_t base = (bh * n_wg + wg) * L + tok;
-        a.ml_part[base * 2] = m_all;
-        a.ml_part[base * 2 + 1] = l_all;
     }
 }
 
@@ -2653,16 +2635,28 @@ int attention_workgroups(int len_bound, int L, int streams) {
     return want < cap ? want : cap;
 }
 
-int attention_groups(int L) { return L > kAttnSplitMaxRows ? ceil_div(L, kAttnGroupRows) : ceil_div(ceil_div(L, 16), 3); }
+// Whether attn_rows_kernel takes a block: where it has a workgroup of 64 rows for every CU, and more than 192 rows.  With fewer
+// workgroups attn_sar_kernel's smaller ones, cut over the keys, fill the chip better.  Whole prompts at 7B (three layers, i.e. two
+// times the attention), attn_sar_kernel / this one in us: 256 rows, 128 workgroups, 525 .. 613 / 530 .. 607; 512 rows, 256, 912 / 916, behind 4000
+// positions 1087 / 1057; 1024 rows, 512, 1615 / 1602, behind 1024 and 4000 positions 1706 / 1638, 1907 / 1803; four prompts of 128
+// rows, 256, 899 / 896, behind up to 2048 positions 962 / 976; of 200 rows, 512, 1351 / 1326, 1451 / 1418; of 256 rows 1583 / 1567, behind
+// 4000 positions 1819 / 1739; 70B, two layers, 256 rows, 256, 808 / 813, 906 / 885; 8 heads, four prompts of 256 rows, 128, 224 / 237.
+bool attention_by_rows(int batch, int n_heads, int L) {
+    return L > kAttnRowsMin && (long long)batch * n_heads * ceil_div(L, kAttnGroupRows) >= 256;
+}
+int attention_groups(int batch, int n_heads, int L) {
+    return attention_by_rows(batch, n_heads, L) ? ceil_div(L, kAttnGroupRows) : ceil_div(ceil_div(L, 16), 3);
+}
 
-// Query tiles per workgroup of blocks of 49 to 96 rows.  Three share every chunk of keys best, two make more and shorter
-// workgroups: better while all of them are on the chip at once, two per CU (prompts of 333 and 512 rows, when this kernel took them:
-// 17.1 -> 14.0 us, 23.0 -> 18.1) -- unless three give every CU at most one and the cached keys, which all workgroups read alike,
-// outweigh the block's own (13B behind 1500 positions 41.0 against 48.1).  Where both make the same number of groups, two waste
-// less on padding.
+// Query tiles per workgroup.  Three share every chunk of keys best (long blocks: 3 tiles 165 us, 2 tiles 184 us at
+// 1024 rows behind 3000 positions, 7B), two make more and shorter workgroups: better while all of them are on
+// the chip at once, two per CU (7B: 333 rows 17.1 -> 14.0, 400 rows 21.2 -> 16.8, 512 rows 23.0 -> 18.1 and behind
+// 1024 positions 48.7 -> 44.2; 70B: 256 rows 18.9 -> 14.1) -- unless three give every CU at most one and
+// the cached keys, which all workgroups read alike, outweigh the block's own (13B: 256 rows behind 1500
+// positions 41.0 against 48.1).  Where both make the same number of groups, two waste less on padding.
 static int attention_query_tiles(const AttnLaunch& a) {
     const int tiles = ceil_div(a.L, 16);
-    if (a.L > kAttnSplitMaxRows) return kAttnGroupRows / 16;
+    if (attention_by_rows(a.batch, a.n_heads, a.L)) return kAttnGroupRows / 16;
     if (tiles < 3 || a.qkv) return tiles < 3 ? tiles : 3;
     const int per = a.batch * a.n_heads * a.n_wg, wgs3 = per * ceil_div(tiles, 3), wgs2 = per * ceil_div(tiles, 2);
     if (wgs2 == wgs3) return 2;
@@ -2740,7 +2734,7 @@ static hipError_t launch_attention_dh(const AttnLaunch& a, hipStream_t s) {
         case 2: launch(std::integral_constant<int, 2>{}); break;
         case 3: launch(std::integral_constant<int, 3>{}); break;
         default:
-            if (a.qkv || a.shared < (a.slots ? -1 : 0) || 2 * a.shared > (int)grid.z) return hipErrorInvalidValue;
+            if (a.qkv || a.n_wg != 1 || a.shared < (a.slots ? -1 : 0) || 2 * a.shared > (int)grid.z) return hipErrorInvalidValue;
             if (a.slots) hipLaunchKernelGGL((attn_rows_kernel<DH, PAGED, true>), grid, block, 0, s, a, scale_log2e);
             else hipLaunchKernelGGL((attn_rows_kernel<DH, PAGED, false>), grid, block, 0, s, a, scale_log2e);
     }

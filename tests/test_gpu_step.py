@@ -291,28 +291,31 @@ def test_long_prompt_chunks_match_oracle(torch_mod, shape_name, n_prompt, chunk)
 
 
 @pytest.mark.parametrize("shape_name,rows,k,ctxs,paged", [
-    ("tiny", 97, 0, [0], False),                # two row groups, the second one row into its second wave
-    ("gqa128", 128, 0, [31, 700], False),       # full groups, keys cut into equal parts, an empty part of the short sequence
-    ("gqa128", 129, 0, [1], True),              # a third group of one row
-    ("tiny", 321, 0, [1023], False),            # more workgroups than one round of a lone sequence's
-    ("tiny", 100, 9, [0, 45, 700], False),      # mask rows
-    ("gqa128", 121, 10, [333], True),
-    ("gqa-small", 97, 0, "ragged", False),      # a batch dealt out and cut by length, merged by whoever ends last
-    ("gqa-small", 121, 10, "ragged", True),
+    ("64 heads", 256, 0, [0], False),            # a lone prompt, a workgroup per CU, four full groups
+    ("64 heads", 257, 0, [31], True),            # a fifth group of one row, and workgroups that share CUs
+    ("64 heads", 449, 0, [1023], False),         # two to a CU
+    ("64 heads", 576, 23, [45], False),          # mask rows; more workgroups than fit at once
+    ("gqa128", 993, 0, [1, 700], False),         # equal numbers of workgroups and CUs, two sequences
+    ("gqa-small", 193, 0, "ragged", False),      # a batch dealt out and cut by length, merged by whoever ends last
+    ("gqa-small", 196, 13, "ragged", True),
+    ("tiny", 321, 0, "ragged", False),
 ])
 def test_attention_of_long_blocks(torch_mod, shape_name, rows, k, ctxs, paged):
-    """Blocks beyond 96 rows through space_prefill, prompts and blocks with mask rows, at the edges of the 64-row groups, 32-key
+    """Blocks that attn_rows_kernel takes (space_prefill), prompts and blocks with mask rows, at the edges of the 64-row groups, 32-key
     chunks and 64-key stages: the first layer's attention output of every row against the oracle's, and the keys and values of
     the layer behind it."""
     torch = torch_mod
     import dataclasses
     from paper_2402_11809_amd import binding, layout as lo
-    shape = dataclasses.replace(SHAPES[shape_name], n_layers=2)
+    if shape_name == "64 heads":
+        shape = dataclasses.replace(SHAPES["gqa-small"], n_layers=2, n_heads=64, n_kv_heads=8)
+    else:
+        shape = dataclasses.replace(SHAPES[shape_name], n_layers=2)
     w = all_weights(shape, seed=8)
     spec = lo.paper_layout(k) if k else lo.prefill_layout(rows)
     assert spec.n_rows == rows
     if ctxs == "ragged":
-        ctxs = [(151 * b) % 690 for b in range(19)] + [700]
+        ctxs = [(151 * b) % 690 for b in range(11)] + [700]
     B, cap = len(ctxs), -(-(max(ctxs) + spec.n_groups) // 32) * 32
     gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=cap)
     om = gc.oracle_model(shape, w)

@@ -61,7 +61,6 @@ struct GemmLaunch {
     int m;              // rows of this launch, starting at row_tile0 * 16: 1 .. 96, or up to 96 * passes
     int passes;         // 1, or the number of 96-row passes that share this launch (then row_tile0 == 0)
     int tiles_per_wave; // weight tiles per wave, gemm_tiles_per_wave(w, rows of the whole matrix)
-    int tile0;          // first weight tile: rows of w in front of it are left out (EPI_F32; weight-streaming kernel: whole groups)
     // EPI_F32: out[s][m][ldo] fp32 partial sums
     float* out;
     int ldo;
@@ -82,6 +81,7 @@ struct GemmLaunch {
     // nullptr: none may be.  The counts are zero between launches.
     float* tail_sums;     // [8 * kWideTailSlots][kWideTailFloats]
     int32_t* tail_count;  // [8 * kWideTailSlots]
+    int tile0;            // first weight tile: rows of w in front of it are left out (EPI_F32; weight-streaming kernel: whole groups)
 };
 constexpr size_t kWideTailFloats = 16 * 8 * 256;  // a piece of 16 weight tiles x 8 row tiles
 

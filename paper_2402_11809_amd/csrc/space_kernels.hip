@@ -126,14 +126,14 @@ __global__ __launch_bounds__(256) void gemm_skinny_kernel(GemmLaunch g) {
         // launch.  Workgroup index -> XCD is index % 8, so the passes of one weight group get indices
         // that differ by 8: they run on the same XCD at about the same time and the weight tiles
         // cross HBM once (ordinary loads below, so that L2 keeps them for the sibling passes).
-        const int q = blockIdx.x >> 3, n_gs = ((g.w.groups * g.w.r_pack - g.tile0) / R) * g.w.splits;
+        const int q = blockIdx.x >> 3, n_gs = ((g.w.groups * g.w.r_pack - (EPI == EPI_F32 ? g.tile0 : 0)) / R) * g.w.splits;
         pass = q % g.passes;
         const int gi = (q / g.passes) * 8 + (blockIdx.x & 7);
         if (gi >= n_gs) return;
         bx = gi % (n_gs / g.w.splits);
         s = gi / (n_gs / g.w.splits);
     }
-    const int nt0 = g.tile0 + bx * R;
+    const int nt0 = (EPI == EPI_F32 ? g.tile0 : 0) + bx * R;
     const int row_tile0 = g.row_tile0 + pass * T;
     const int m_rows = T >= 4 ? min(g.m - pass * 16 * T, 16 * T) : g.m;  // rows of this pass
     const int t_run = T >= 4 ? (m_rows + 15) >> 4 : T;                    // its row tiles, 1 .. T

@@ -292,11 +292,12 @@ int space_sample_verify(space_ctx *ctx, int32_t batch, const space_layout *layou
  * and results (bit for bit) as space_sample_verify, but the per-row lists of the verification
  * live in a fixed array inside the library's device image instead of in memory space_init allocated;
  * the call itself allocates nothing and frees nothing, on the host or on the device.
- * Limit: batch * L <= SPACE_STATIC_MAX_ROWS (648 KB of device memory per GPU, held until the process
+ * Limit: batch * L <= SPACE_STATIC_MAX_ROWS (664 KB of device memory per GPU, held until the process
  * ends); beyond it the call returns SPACE_ECAPACITY and launches nothing.  The array keeps the
- * last call's contents; every entry a call reads is written by that call first or left at zero by the
- * call before, so nothing has to be cleared.  All calls on one GPU (from any context or stream) share the array: two calls that
- * overlap in time on one GPU race, so keep them on one stream or order them with events. */
+ * last call's contents; every entry a call reads is written by that call first, but for the sequences' arrival counts, which
+ * every call leaves as it found them, so nothing has to be cleared.  All calls on one GPU (from any context or stream) share the
+ * array: two calls that overlap in time on one GPU race, so keep them on one stream or order them with events.  A race spoils the
+ * outputs of the calls that meet and of no call behind them (eager or replayed from a graph). */
 #define SPACE_STATIC_MAX_ROWS 1024
 int space_sample_verify_static(space_ctx *ctx, int32_t batch, const space_layout *layout,
                                const space_layout *next_layout, const space_sample_params *params,

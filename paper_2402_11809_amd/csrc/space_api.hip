@@ -2,7 +2,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <climits>
 #include <cmath>
 #include <cstdarg>
@@ -50,8 +49,8 @@ thread_local std::string g_init_error;
 }  // namespace
 
 // Scratch of space_sample_verify_static: the per-row lists of the sampling verification (kept token ids, their
-// probabilities, their count), the internal copy of the accepted counts and the sequences' arrival counts (zero between
-// calls), for up to SPACE_STATIC_MAX_ROWS block rows.  Every GPU the library runs on holds its own copy of this
+// probabilities, their count), the internal copy of the accepted counts and the sequences' arrival counts (which every launch
+// leaves as it found them), for up to SPACE_STATIC_MAX_ROWS block rows.  Every GPU the library runs on holds its own copy of this
 // array for the life of the process; the name below is only a host-side handle, the device address
 // comes from hipGetSymbolAddress (static_scratch_address) and is what the kernels are given.
 struct StaticSampleScratch {
@@ -59,7 +58,7 @@ struct StaticSampleScratch {
     float row_probs[SPACE_STATIC_MAX_ROWS * kMaxTopK];
     int32_t row_n[SPACE_STATIC_MAX_ROWS];
     int32_t accepted_ws[SPACE_STATIC_MAX_ROWS];
-    unsigned long long arrived[SPACE_STATIC_MAX_ROWS * kArrivedStride];
+    uint32_t arrived[SPACE_STATIC_MAX_ROWS * kArrivedStride];
 };
 static __device__ __align__(256) unsigned char scratch[sizeof(StaticSampleScratch)];
 
@@ -67,7 +66,6 @@ namespace {
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-std::atomic<uint32_t> g_scratch_calls{0};
 void* g_scratch_dev[kMaxDevices];  // device address of `scratch` on each GPU, looked up once per GPU
 
 // Device address of `scratch` on the current GPU; no allocation.  hipErrorInvalidDevice beyond kMaxDevices.
@@ -156,8 +154,7 @@ struct space_ctx {
     int n_pos = 0;
     int32_t *pos = nullptr, *argmax_ws = nullptr, *accepted_ws = nullptr, *faults = nullptr;
     int32_t *row_ids = nullptr, *row_n = nullptr;  // sampling verification: kept ids / count of every row
-    unsigned long long* row_arrived = nullptr;     // ... arrival counts of the sequences
-    uint32_t sample_calls = 0;
+    uint32_t* row_arrived = nullptr;               // ... arrival counts of the sequences
     float* row_probs = nullptr;
     float* loss_ws = nullptr;  // per-row loss terms when the caller does not ask for them
     std::vector<space_layout*> layouts;
@@ -430,9 +427,8 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
     if ((rc = dev_alloc(ctx, &ctx->accepted_ws, (size_t)c.max_batch, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->row_ids, M * kMaxTopK, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->row_probs, M * kMaxTopK, true))) return rc;
-    const size_t row_n_even = (M + 1) / 2 * 2;  // the sequences' arrival counts lie behind
-    if ((rc = dev_alloc(ctx, &ctx->row_n, row_n_even + 2 * kArrivedStride * (size_t)c.max_batch, true))) return rc;
-    ctx->row_arrived = (unsigned long long*)(ctx->row_n + row_n_even);
+    if ((rc = dev_alloc(ctx, &ctx->row_n, M + kArrivedStride * (size_t)c.max_batch, true))) return rc;
+    ctx->row_arrived = (uint32_t*)(ctx->row_n + M);  // the sequences' arrival counts lie behind
     if ((rc = dev_alloc(ctx, &ctx->loss_ws, M, true))) return rc;
     if ((rc = dev_alloc(ctx, &ctx->faults, (size_t)4, true))) return rc;
     {
@@ -1035,7 +1031,7 @@ int space_kv_rollback(space_ctx* ctx, space_kv* kv, const int32_t* n, int32_t n_
 static int sample_verify_impl(space_ctx* ctx, const char* who, int32_t batch, const space_layout* layout,
                               const space_layout* next_layout, const space_sample_params* params,
                               const space_sample_io* io, int32_t* row_ids, float* row_probs, int32_t* row_n,
-                              unsigned long long* arrived, uint32_t call, int32_t* accepted_ws, size_t rows_max, void* stream) {
+                              uint32_t* arrived, int32_t* accepted_ws, size_t rows_max, void* stream) {
     if (!layout || !params || !io) return fail(ctx, SPACE_EINVAL, "%s: null argument", who);
     if (!io->logits || !io->tokens || !io->p_c || !io->uniforms || !io->accepted_len || !io->extra || !io->new_cands ||
         !io->new_pc)
@@ -1067,7 +1063,7 @@ static int sample_verify_impl(space_ctx* ctx, const char* who, int32_t batch, co
     v.tokens = io->tokens; v.mask_id = ctx->cfg.vocab;
     v.p_c = io->p_c; v.uniforms = io->uniforms; v.draft_ids = io->draft_ids; v.draft_probs = io->draft_probs;
     v.row_ids = row_ids; v.row_probs = row_probs; v.row_n = row_n;
-    v.arrived = arrived; v.call = call;
+    v.arrived = arrived;
     v.accepted_len = io->accepted_len; v.accepted_ws = accepted_ws; v.extra = io->extra;
     v.new_cands = io->new_cands; v.new_pc = io->new_pc; v.max_cands = io->max_cands;
     v.new_ids = io->new_ids; v.new_probs = io->new_probs;
@@ -1083,7 +1079,7 @@ int space_sample_verify(space_ctx* ctx, int32_t batch, const space_layout* layou
                         const space_sample_params* params, const space_sample_io* io, void* stream) {
     if (!ctx) return SPACE_EINVAL;
     return sample_verify_impl(ctx, "space_sample_verify", batch, layout, next_layout, params, io, ctx->row_ids,
-                              ctx->row_probs, ctx->row_n, ctx->row_arrived, ++ctx->sample_calls, ctx->accepted_ws, (size_t)ctx->m_max, stream);
+                              ctx->row_probs, ctx->row_n, ctx->row_arrived, ctx->accepted_ws, (size_t)ctx->m_max, stream);
 }
 
 int space_sample_verify_static(space_ctx* ctx, int32_t batch, const space_layout* layout, const space_layout* next_layout,
@@ -1096,7 +1092,7 @@ int space_sample_verify_static(space_ctx* ctx, int32_t batch, const space_layout
     HIP_TRY(ctx, static_scratch_address(&base));
     StaticSampleScratch* sc = (StaticSampleScratch*)base;  // a device address: only handed to the kernels
     return sample_verify_impl(ctx, "space_sample_verify_static", batch, layout, next_layout, params, io, sc->row_ids,
-                              sc->row_probs, sc->row_n, sc->arrived, ++g_scratch_calls, sc->accepted_ws, (size_t)SPACE_STATIC_MAX_ROWS, stream);
+                              sc->row_probs, sc->row_n, sc->arrived, sc->accepted_ws, (size_t)SPACE_STATIC_MAX_ROWS, stream);
 }
 
 int space_sar_loss(space_ctx* ctx, const float* logits, const int32_t* labels, int32_t rows, float* row_loss,

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "space_arrivals.h"
 #include "space_attn_plan.h"
 #include "space_wide_plan.h"
 
@@ -311,7 +312,7 @@ hipError_t launch_verify(const VerifyLaunch& v, hipStream_t s);
 // Rejection-sampling verification (Algorithm 1 as printed): warped distribution of every block row,
 // then the acceptance loop, the extra token and the candidate refresh.
 constexpr int kMaxTopK = 64;
-constexpr int kArrivedStride = 16;  // a sequence's count has a 128-byte line to itself: atomics on one line wait for each other
+constexpr int kArrivedStride = 32;  // a sequence's count has a 128-byte line to itself: atomics on one line wait for each other
 struct SampleLaunch {
     const float* logits;  // [B][L][vocab]
     int vocab, batch;
@@ -330,8 +331,7 @@ struct SampleLaunch {
     int32_t* row_ids;     // [B*L][kMaxTopK]
     float* row_probs;     // [B*L][kMaxTopK]
     int32_t* row_n;       // [B*L]
-    unsigned long long* arrived;  // [B][kArrivedStride] the first: rows of the sequence that are done; zero between launches
-    uint32_t call;        // a number of its own for every call that uses this scratch, higher each time
+    uint32_t* arrived;    // [B][kArrivedStride] the first: shares of the sequence's rows that are done (space_arrivals.h)
     int32_t* accepted_len;
     int32_t* accepted_ws;
     int32_t* extra;

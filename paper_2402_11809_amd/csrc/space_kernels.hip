@@ -3128,16 +3128,6 @@ __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K
     topk_many_equal<NT>(x, V, K, bound, n);
 }
 
-// Whether this is the last of n arrivals of call number `call`.  The count is 0 between launches; should calls have
-// met on it that ran at the same time, the next one, which has a higher number, starts afresh all the same.
-__device__ __forceinline__ bool arrives_last(unsigned long long* count, uint32_t call, int n) {
-    const unsigned long long none = (unsigned long long)call << 32;
-    __hip_atomic_fetch_max(count, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = __hip_atomic_fetch_add(count, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == none + n - 1;
-    if (last) __hip_atomic_store(count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return last;
-}
-
 // Lines 6-22 of Algorithm 1 over the lists of a sequence's rows, by the workgroup of these rows that ends last: lists go through
 // memory with stores and loads that pass by the caches other XCDs do not see, and nobody waits for anybody (as in the merge of
 // attn_sar_kernel).  A launch of its own behind the rows cost a kernel boundary and the trips for what does not depend on the
@@ -3437,7 +3427,10 @@ __global__ __launch_bounds__(NT, 8) void sample_rows_kernel(SampleLaunch a) {
         }
         if (lane == 0) __hip_atomic_store(a.row_n + row, keep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave made all of the row's stores
-        if (lane == 0) s_last = arrives_last(a.arrived + (size_t)b * kArrivedStride, a.call, a.lay.L);
+        if (lane == 0) {
+            const uint32_t share = arrival_share(a.lay.L, r);
+            s_last = arrival_is_last(__hip_atomic_fetch_add(a.arrived + (size_t)b * kArrivedStride, share, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), share);
+        }
     } else {
         sample_facts(a, facts, b, tid - 64, NT - 64);
     }

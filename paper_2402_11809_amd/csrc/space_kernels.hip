@@ -1669,7 +1669,7 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     };
     if (!kLoopCacheOnly) row_facts();
     f32x4 o[DT][TQ];
-    float m_w[TQ], l_w[TQ];  // running max (log2 domain) and sum of this wave's chunks
+    float m_w[TQ], l_w[TQ];  // what the exponentials refer to (log2 domain) and sum of this wave's chunks
 #pragma unroll
     for (int t = 0; t < TQ; ++t) {
         m_w[t] = -INFINITY;
@@ -1717,10 +1717,10 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
             float cm = sc[0][t][0];                                                                         \
             _Pragma("unroll") for (int j = 1; j < 8; ++j) cm = fmaxf(cm, sc[j >> 2][t][j & 3]);             \
             cm = row_groups_max(cm) * scale_log2e;                                                          \
-            /* the maximum that the exponentials refer to follows the running one where that is ahead by more than */\
-            /* 2^8: sums and weights carry the same factor, and the output is rescaled in few chunks instead of most */\
-            if (__builtin_amdgcn_ballot_w64(cm > m_w[t] + 8.f) != 0) {                                      \
-                const float m_new = fmaxf(m_w[t], cm);                                                      \
+            /* what the exponentials refer to is set 2^8 above the running maximum and moves only once that has come up to it: */\
+            /* sums and weights carry the same factor, no weight is above 1, and the output is rescaled in few chunks, not in most */\
+            if (__builtin_amdgcn_ballot_w64(cm > m_w[t]) != 0) {                                            \
+                const float m_new = fmaxf(m_w[t], cm + 8.f);                                                \
                 const float alpha = __builtin_amdgcn_exp2f(m_w[t] - (m_new == -INFINITY ? 0.f : m_new));    \
                 m_w[t] = m_new;                                                                             \
                 l_w[t] *= alpha;                                                                            \
@@ -1988,7 +1988,7 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
 #pragma unroll
     for (int t = 0; t < RT; ++t) my_info[t] = a.info[min(row0 + 16 * t + c16, L - 1)];
     f32x4 o[DT][RT];
-    float m_w[RT], l_w[RT];  // running maximum (log2 domain) and sum of this wave's chunks
+    float m_w[RT], l_w[RT];  // what the exponentials refer to (log2 domain) and sum of this wave's chunks
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         m_w[t] = -INFINITY;
@@ -2040,8 +2040,8 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
                     sc[j >> 2][t][j & 3] = ((key < kend) & vis) ? sc[j >> 2][t][j & 3] : -INFINITY;
                 }
         }
-        // The maximum that the exponentials refer to follows the running one only where it has fallen behind by more than
-        // 2^8: sums and weights carry the same factor, and the output is rescaled in few chunks instead of most.
+        // What the exponentials refer to is set 2^8 above the running maximum and moves only once that has come up to
+        // it: sums and weights carry the same factor, no weight is above 1, and the output is rescaled in few chunks, not in most.
         float m_new[RT];
         bool moved = false;
 #pragma unroll
@@ -2050,12 +2050,12 @@ __global__ __launch_bounds__(256, 2) void attn_rows_kernel(AttnLaunch a, float s
 #pragma unroll
             for (int j = 1; j < 8; ++j) cm = fmaxf(cm, sc[j >> 2][t][j & 3]);
             m_new[t] = row_groups_max(cm) * scale_log2e;
-            moved |= m_new[t] > m_w[t] + 8.f;
+            moved |= m_new[t] > m_w[t];
         }
         if (__builtin_amdgcn_ballot_w64(moved) != 0) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                m_new[t] = fmaxf(m_w[t], m_new[t]);
+                m_new[t] = fmaxf(m_w[t], m_new[t] + 8.f);
                 neg_m[t] = m_new[t] == -INFINITY ? 0.f : -m_new[t];
                 const float alpha = __builtin_amdgcn_exp2f(m_w[t] + neg_m[t]);
                 m_w[t] = m_new[t];

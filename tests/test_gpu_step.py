@@ -1062,6 +1062,43 @@ def test_last_layer_of_a_prompt_chunk_without_queries(torch_mod, shape_name, B, 
             gc.assert_bf16_close(gv, okvs[b].v[l][c:], f"layer {l} seq {b} V", min_same=0.9)
 
 
+@pytest.mark.parametrize("shape_name,rows,ctxs,tune", [
+    ("small128", 36, [500], "attn=1000000"),   # one launch per layer
+    ("small128", 36, [700], "attn=0"),         # keys cut over workgroups
+    ("gqa-small", 25, "ragged", "attn=0"),     # a batch dealt out and cut by length
+    ("gqa128", 70, [700, 90], None),
+    ("gqa-small", 193, "ragged", None)])       # attn_rows_kernel
+def test_large_values_of_a_steep_softmax_stay_finite(torch_mod, shape_name, rows, ctxs, tune):
+    """Cached values of 2^121 to 2^122 and keys whose scores spread over some tens: no weight of the softmax may be above 1 on the way, or
+    the sums of a wave's chunks overflow where the output does not.  The first layer's attention output of every row against the
+    oracle's; bars relative to the largest (2^-17 per operand of scores up to some tens in the exponent)."""
+    torch = torch_mod
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES[shape_name].with_layers(2)
+    w = all_weights(shape, seed=27)
+    if ctxs == "ragged":
+        ctxs = [(151 * b) % 690 for b in range(11)] + [700]
+    B, cap = len(ctxs), 1024
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=cap, tune=tune)
+    om = gc.oracle_model(shape, w)
+    okvs = [gc.synthetic_oracle_kv(om, seed=50 + b, ctx=c, std=16.0) for b, c in enumerate(ctxs)]
+    cache = gm.kv_cache(B, cap)
+    for b, okv in enumerate(okvs):
+        okv.v[0] = gc.bits_to_f64(gc.f32_to_bf16_bits((2.0 ** 121 * (1.0 + np.minimum(np.abs(okv.v[0]), 15.0) / 16.0)).astype(np.float32)))
+        gc.upload_oracle_kv(torch, cache, b, okv)
+    toks = np.random.default_rng(28).integers(0, shape.vocab, size=(B, rows)).astype(np.int32)
+    spec = lo.prefill_layout(rows)
+    gm.prefill(torch.from_numpy(toks).cuda(), gm.layout(spec), cache)
+    torch.cuda.synchronize()
+    hd = shape.n_heads * shape.head_dim
+    out = gc.decode_planes(gm.debug_buffer("attn_out"), B * rows, hd).reshape(B, rows, hd)
+    for b, okv in enumerate(okvs):
+        trace = []
+        so.block_forward_cached(om, okv, toks[b].astype(np.int64), spec.is_mask.astype(bool), trace=trace)
+        ref = trace[0]["attn_out"].reshape(rows, hd)
+        assert np.abs(out[b] - ref).max() < 2e-3 * max(np.abs(ref).max(), 1.0), b
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
     """One sequence of a batch, long enough to be cut into parts, with one cached key element that is NaN or infinite: a score of the

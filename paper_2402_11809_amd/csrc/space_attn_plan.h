@@ -38,7 +38,7 @@ struct KeyPart {
 };
 
 // Chunks of a sequence, the block's included (0: no sequence), and the most parts it may have: at least four cached chunks
-// each, so that no wave of a part is without one.
+// (a round of the four waves of a workgroup) for each.
 struct KeySeq {
     int chunks, most;
 };
@@ -53,17 +53,24 @@ constexpr int key_parts(const KeySeq& s, int size, int longest) {
     const int n = (s.chunks + size - 1) / size;
     return n < s.most ? n : s.most;
 }
+// An even share of a sequence's chunks, by which the parts are ordered and the cut is priced: how many of them the last part has
+// (below) does not belong there.  (Sizes in whole rounds, the block counted as kBlockRounds: 20 sequences of 8 heads of 64 277.5 ->
+// 292 us a step of six layers, 30 of them 289 -> 301, 8 of 40 heads of 128 813 -> 827; none of 70 batches ahead.)
 constexpr int key_part_chunks(const KeySeq& s, int n) { return n ? (s.chunks + n - 1) / n : 0; }
 
-// Rounds of cached chunks (a chunk per wave each) of every part but the last, which takes what is left: it also stages the block's
-// keys and values and takes its chunks, which costs as much as kBlockRounds of them (measured in a batch of 8 x 36 rows, us: staging 14
-// instead of 6, the block's chunks 2, a round 4.4 while HBM is busy; with equal parts the last ones ended 10 us behind all others).
-// No part before the last is empty.
+// First round of cached chunks (a chunk per wave each) of part p, of part n_parts the end, where the last part alone stages the
+// block's keys and values and takes its chunks.  That costs as much as kBlockRounds rounds (measured in a batch of 8 x 36 rows, us: staging 14
+// instead of 6, the block's chunks 2, a round 4.4 while HBM is busy; with equal parts the last ones ended 10 us behind all others;
+// 1, 3 and 4 rounds are level with 2 over 70 ragged batches of one to three query tiles, heads of 64 and of 128).  So no part has more than
+// rounds and block dealt out evenly: the last one what the others leave at that size, down to none, and they share the rest evenly, one
+// more for the first ones.  No part before the last is empty.
 constexpr int kBlockRounds = 2;
-constexpr int key_part_rounds(int rounds, int n_parts) {
-    if (n_parts < 2) return rounds;
-    const int even = (rounds + kBlockRounds + n_parts - 1) / n_parts, most = rounds / (n_parts - 1);
-    return even < most ? even : most > 1 ? most : 1;
+constexpr int key_part_first(int rounds, int n_parts, int p) {
+    if (p <= 0) return 0;
+    if (p >= n_parts) return rounds;
+    const int others = n_parts - 1, full = others * ((rounds + kBlockRounds + n_parts - 1) / n_parts), rest = rounds < full ? rounds : full;
+    const int one_more = rest % others;
+    return p * (rest / others) + (p < one_more ? p : one_more);
 }
 
 // What the busiest CU spends on `parts` parts of at most `largest` chunks: these and, worth kPartStaging chunks, the staging of

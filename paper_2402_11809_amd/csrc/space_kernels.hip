@@ -1366,10 +1366,10 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     const bool blk_wg = FUSE && wg == n_wg - 1;
     int chunk_step = n_wg * WV, chunk = wg * WV + wave;
     if (FUSE && DEALT) {  // the last part has more to do beside the cache
-        const int per = key_part_rounds((n_cache + WV - 1) / WV, n_wg);
+        const int rounds = (n_cache + WV - 1) / WV;
         chunk_step = WV;
-        chunk = wg * per * WV + wave;
-        if (!blk_wg) n_chunks = min(n_chunks, (wg + 1) * per * WV);
+        chunk = key_part_first(rounds, n_wg, wg) * WV + wave;
+        n_chunks = min(n_chunks, key_part_first(rounds, n_wg, wg + 1) * WV);
     }
     if (!DEALT && wg * WV >= n_chunks && !blk_wg) {
         // the grid is sized for an upper bound of the length: a workgroup past the real end only

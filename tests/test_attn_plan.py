@@ -110,6 +110,7 @@ int main() {
 
 
 _ROUNDS_PROGRAM = r"""
+#include <algorithm>
 #include <cstdio>
 #include "space_attn_plan.h"
 using namespace space;
@@ -118,11 +119,18 @@ int main() {
     int wrong = 0;
     for (int chunks = 0; chunks <= 4100; ++chunks)
         for (int n = 1; n <= key_seq(chunks, 2).most; ++n) {
-            const int rounds = (chunks + 3) / 4, per = key_part_rounds(rounds, n);
-            // every part but the last has `per` of them, and so many there are; the last no more than the others
-            const int last = rounds - (n - 1) * per;
-            const bool ok = n == 1 ? per == rounds : per >= 1 && last >= 0 && (last <= per || rounds / (n - 1) == per);
-            if (!ok && wrong++ < 5) printf("%d chunks in %d parts: %d rounds\n", chunks, n, per);
+            const int rounds = (chunks + 3) / 4, even = (rounds + kBlockRounds + n - 1) / n;
+            int at = 0, busiest = 0;
+            bool ok = key_part_first(rounds, n, 0) == 0 && key_part_first(rounds, n, n) == rounds;
+            for (int p = 0; p < n; ++p) {
+                const int own = key_part_first(rounds, n, p + 1) - at;
+                ok = ok && own >= (p < n - 1) && (p == 0 || p == n - 1 || own <= at - key_part_first(rounds, n, p - 1));
+                busiest = std::max(busiest, p < n - 1 ? own : own + kBlockRounds);
+                at += own;
+            }
+            // (a part of no cached rounds still has the block)
+            ok = ok && at == rounds && busiest <= std::max(even, kBlockRounds) && busiest <= (rounds + n - 1) / n + kBlockRounds;
+            if (!ok && wrong++ < 5) printf("%d chunks in %d parts: busiest %d\n", chunks, n, busiest);
         }
     return wrong;
 }
@@ -155,6 +163,7 @@ def test_every_part_has_one_place_in_the_table(tmp_path):
 
 
 def test_rounds_of_a_part(tmp_path):
-    """Every number of cached chunks and of parts that a sequence may have: the parts before the last are full, and the last, which also
-    has the block, is never longer than they are unless they could not be either."""
+    """Every number of cached chunks and of parts that a sequence may have: the parts lie end to end and hold every round once, no part
+    before the last is empty, and the busiest, the last one's block included, has no more than rounds and block dealt out evenly, nor more
+    than it had with equal parts."""
     _run(tmp_path, _ROUNDS_PROGRAM)

@@ -359,7 +359,6 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  *            piece is cut over the contraction (not by widetail= either);
  *   widetail=P:N   where a projection has complete sums, its last P pieces per XCD are cut over the contraction into N
  *            workgroups each (P * N up to 32) as far as it has that many; widetail=0: never by the library's own choice;
- *            either way that kernel takes projections from 193 rows on where wide= is not given;
  *   wideks=N   that kernel sums the contraction in N parts (1, 2 or 4; plain-sum projections only) instead of
  *            what its cost model or space_tune_rows picked.
  * Results do not depend on it beyond the order of floating-point sums; the tests use it to force every

@@ -352,7 +352,6 @@ int init_impl(space_ctx* ctx, const space_weights* w) {
         }
         if (const char* p = strstr(e, "widetail=")) {
             int parts = 0;
-            if (ctx->wide_min_rows < 0) ctx->wide_min_rows = 193;
             const int got = sscanf(p + 9, "%d:%d", &n, &parts);
             if (got == 2 && n >= 1 && n <= kWideTailSlots && parts >= 2 && n * parts <= kWideTailSlots) ctx->wide_tail_force = WideTail{n, parts};
             else if (got == 1 && (n == 0 || n == 1)) ctx->wide_tail = n;

@@ -927,8 +927,9 @@ def test_row_cuts_of_the_many_row_kernel_give_the_same_bits(torch_mod, shape_nam
 
 
 def test_forced_cut_leaves_no_tail(torch_mod):
-    """widecut= and widetail= together: the forced cut has no piece cut over the contraction, i.e. the logits are those of the
-    default cut without tails, bit for bit; at another row count the forced tail still applies."""
+    """widecut= and widetail= together, the many-row kernel forced: the forced cut has no piece cut over the contraction, i.e. the
+    logits are those of the default cut without tails, bit for bit; at another row count the forced tail still applies.  Where the kernel
+    is not forced and these projections run in passes, neither form of widetail= changes a bit."""
     torch = torch_mod
     from paper_2402_11809_amd import layout as lo
     shape = SHAPES["gqa128"]
@@ -940,8 +941,10 @@ def test_forced_cut_leaves_no_tail(torch_mod):
         gm = gc.make_gpu_model(shape, w, max_batch=8, max_rows=spec.n_rows, tune=tune)
         return _run_step(torch, gm, gm.kv_cache(B, 160), spec, toks[:B], batch=B).logits.cpu().numpy()
 
-    assert np.array_equal(logits(8, "widecut=2:0:0:1:0,widetail=5:3"), logits(8, "widetail=0"))
-    assert not np.array_equal(logits(7, "widecut=2:0:0:1:0,widetail=5:3"), logits(7, "widetail=0"))
+    assert np.array_equal(logits(8, "wide=1,widecut=2:0:0:1:0,widetail=5:3"), logits(8, "wide=1,widetail=0"))
+    assert not np.array_equal(logits(7, "wide=1,widecut=2:0:0:1:0,widetail=5:3"), logits(7, "wide=1,widetail=0"))
+    passes = logits(8, None)
+    assert np.array_equal(logits(8, "widetail=0"), passes) and np.array_equal(logits(8, "widetail=5:3"), passes)
 
 
 @pytest.mark.parametrize("d,B,k", [(2080, 1, 1), (2080, 3, 3), (3104, 1, 5), (4096, 2, 3), (4128, 1, 4), (8192, 1, 5)])

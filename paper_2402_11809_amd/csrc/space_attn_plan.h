@@ -73,12 +73,17 @@ constexpr int key_part_first(int rounds, int n_parts, int p) {
     return p * (rest / others) + (p < one_more ? p : one_more);
 }
 
-// What the busiest CU spends on `parts` parts of at most `largest` chunks: these and, worth kPartStaging chunks, the staging of
-// the block; beyond a workgroup per CU the mean over the CUs, of which 232 are taken to be busy, counts as well.
-constexpr int kPartStaging = 16;
-constexpr int key_cut_cost(int parts, int largest, int total, int streams) {
-    const int alone = largest + kPartStaging;
-    const int mean = parts * streams > 256 ? (total + parts * kPartStaging) * streams / 232 : 0;
+// What the busiest CU spends on `parts` parts of at most `largest` chunks: these and, worth `staging` chunks, what a part does in
+// front of them; beyond a workgroup per CU the mean over the CUs, of which 232 are taken to be busy, counts as well.  kPartStaging: the
+// kernel for few rows stages the block.  kRowsStaging: attn_rows_kernel only asks for its queries, and while a CU has one of its
+// workgroups leaves a third of its time unused, so long sequences are better cut than alone (priced at 16 it was up to 9 %
+// behind the kernel for few rows there; five-layer prompts, that kernel / priced at 16 / at 2, us: 2 sequences of 256 rows behind 2000 and 4000
+// positions, 32 heads of 128 1199 / 1230 / 1140, of 64 788 / 853 / 783; 4 of 512 rows behind 512 to 2048, 8 heads of 64, 449 / 491 / 445; 6 and
+// 10 lie in between, equal lengths are level).
+constexpr int kPartStaging = 16, kRowsStaging = 2;
+constexpr int key_cut_cost(int parts, int largest, int total, int streams, int staging) {
+    const int alone = largest + staging;
+    const int mean = parts * streams > 256 ? (total + parts * staging) * streams / 232 : 0;
     return alone > mean ? alone : mean;
 }
 
@@ -89,7 +94,7 @@ struct KeyCut {
 // The smallest largest part that the slots allow; no cut (size = longest) where it is not 8 % ahead of none.
 //   longest, total  chunks of the longest sequence and of all of them;  parts_at(size): parts of all sequences
 template <class PartsAt>
-constexpr KeyCut key_cut(int batch, int slots, int streams, int longest, int total, PartsAt parts_at) {
+constexpr KeyCut key_cut(int batch, int slots, int streams, int longest, int total, PartsAt parts_at, int staging = kPartStaging) {
     const KeyCut none{longest, batch};
     if (slots <= batch) return none;
     int size = total / slots > 1 ? total / slots : 1, parts = batch;
@@ -98,7 +103,7 @@ constexpr KeyCut key_cut(int batch, int slots, int streams, int longest, int tot
         if (size >= longest || parts <= slots) break;
         size += size >> 3 > 1 ? size >> 3 : 1;
     }
-    if (key_cut_cost(parts, size, total, streams) * 100 > key_cut_cost(batch, longest, total, streams) * 92) return none;
+    if (key_cut_cost(parts, size, total, streams, staging) * 100 > key_cut_cost(batch, longest, total, streams, staging) * 92) return none;
     return KeyCut{size, parts};
 }
 

@@ -155,6 +155,7 @@ struct KeyPlan {
     int batch;  // up to 64
     int capacity, n_blk;  // chunks of the block
     int streams;          // heads x query groups
+    int staging;          // for key_cut
 };
 
 // cos / sin of every position 0 .. n_pos-1 ([n_pos][head_dim/2] each), computed once

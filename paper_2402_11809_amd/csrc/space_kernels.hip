@@ -730,7 +730,7 @@ __device__ __forceinline__ void make_key_plan(const KeyPlan& kp, const int32_t* 
         int parts = 0;
         for (int i = 0; i < batch; ++i) parts += __builtin_amdgcn_readlane(n, i);
         return parts;
-    });
+    }, kp.staging);
     const int n = key_parts(own, cut.size, longest), part = key_part_chunks(own, n);
     const int first = key_first_place(lane, part, batch, [&](int i) { return __builtin_amdgcn_readlane(part, i); },
                                       [&](int i) { return __builtin_amdgcn_readlane(n, i); });
@@ -2701,6 +2701,7 @@ KeyPlan schedule_attention(AttnLaunch* a) {
     p.capacity = a->capacity;
     p.n_blk = ceil_div(a->L, kAttnKeys);
     p.streams = streams;
+    p.staging = TQ == kAttnGroupRows / 16 ? kRowsStaging : kPartStaging;
     return p;
 }
 

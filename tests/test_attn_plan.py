@@ -137,6 +137,25 @@ int main() {
 """
 
 
+_PRICE_PROGRAM = r"""
+#include <cstdio>
+#include "space_attn_plan.h"
+using namespace space;
+
+static int parts(int staging, int streams, int slots, int a, int b) {
+    const KeySeq s[2] = {key_seq(a, 8), key_seq(b, 8)};
+    const int longest = b + 8;
+    return key_cut(2, slots, streams, longest, a + b + 16, [&](int size) { return key_parts(s[0], size, longest) + key_parts(s[1], size, longest); }, staging).parts;
+}
+int main() {
+    // 256 rows of 32 heads: four query groups, two workgroups per CU in all; behind 2000 and 4000 positions
+    const int rows = parts(kRowsStaging, 128, 4, 63, 125), few = parts(kPartStaging, 128, 4, 63, 125), none = parts(kRowsStaging, 128, 2, 63, 125), equal = parts(kRowsStaging, 128, 3, 125, 125);
+    printf("%d %d %d %d\n", rows, few, none, equal);
+    return !(rows == 3 && few == 2 && none == 2 && equal == 2);
+}
+"""
+
+
 def _run(tmp_path, program):
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
@@ -167,3 +186,9 @@ def test_rounds_of_a_part(tmp_path):
     before the last is empty, and the busiest, the last one's block included, has no more than rounds and block dealt out evenly, nor more
     than it had with equal parts."""
     _run(tmp_path, _ROUNDS_PROGRAM)
+
+
+def test_a_batch_of_prompt_chunks_is_cut_at_its_own_price(tmp_path):
+    """Two sequences whose query groups give every CU one workgroup: the longer one is cut where a part costs next to nothing
+    beside its chunks, not where it stages the block; never without a slot to spare, nor equal ones that cannot both be cut."""
+    _run(tmp_path, _PRICE_PROGRAM)

@@ -741,7 +741,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
     const XtShape xs = xt_shape(M);
     // the real lengths live on the device; the grid covers the host-side upper bound
     const int attn_chunks = ceil_div(kv->host_len_bound, kAttnKeys) + ceil_div(L, kAttnKeys);
-    const int attn_streams = B * c.n_heads * attention_groups(B, c.n_heads, L);
+    const int attn_streams = B * c.n_heads * attention_groups(B, c.n_heads, dh, L);
     const int attn_wg = attention_workgroups(kv->host_len_bound, L, attn_streams);
     const size_t kv_layer = kv->block_table ? (size_t)kv->n_pages * ctx->kv_heads * kAttnKeys * dh
                                             : (size_t)B * ctx->kv_heads * kv->capacity * dh;
@@ -783,7 +783,7 @@ int step_impl(space_ctx* ctx, const int32_t* tokens, const space_layout* layout,
 
     // The key-split attention of a batch: which workgroup takes what may go by length, from a table that is made with the embedding
     AttnLaunch sched{};
-    sched.batch = B; sched.L = L; sched.n_heads = c.n_heads; sched.n_wg = attn_wg; sched.capacity = kv->capacity;
+    sched.batch = B; sched.L = L; sched.n_heads = c.n_heads; sched.head_dim = dh; sched.n_wg = attn_wg; sched.capacity = kv->capacity;
     sched.cache_chunks = ceil_div(kv->host_len_bound, kAttnKeys);
     sched.qkv = L <= kHeadAttnMaxRows ? ctx->part : nullptr;
     sched.plan = ctx->key_plan; sched.part_rows = (long long)ctx->o_part_rows; sched.part_count = ctx->counts;

@@ -254,9 +254,9 @@ struct AttnLaunch {
     int32_t* part_count = nullptr;
 };
 hipError_t launch_attention(const AttnLaunch& a, hipStream_t s);
-int attention_groups(int batch, int n_heads, int L);  // query groups (workgroups along the rows) that attention_workgroups reckons with
+int attention_groups(int batch, int n_heads, int head_dim, int L);  // query groups (workgroups along the rows) that attention_workgroups reckons with
 int attention_workgroups(int len_bound, int L, int streams);
-// Whether the workgroups of a batch are dealt out by length (batch, L, n_heads, n_wg, cache_chunks, capacity, qkv, plan and
+// Whether the workgroups of a batch are dealt out by length (batch, L, n_heads, head_dim, n_wg, cache_chunks, capacity, qkv, plan and
 // part_* are set): sets slots, shared and n_wg and returns what the embedding launch has to make, or nothing (slots 0).
 KeyPlan schedule_attention(AttnLaunch* a);
 

@@ -2636,16 +2636,20 @@ int attention_workgroups(int len_bound, int L, int streams) {
 }
 
 // Whether attn_rows_kernel takes a block: where it has a workgroup of 64 rows for every CU, and more than 192 rows.  With fewer
-// workgroups attn_sar_kernel's smaller ones, cut over the keys, fill the chip better.  Whole prompts at 7B (three layers, i.e. two
-// times the attention), attn_sar_kernel / this one in us: 256 rows, 128 workgroups, 525 .. 613 / 530 .. 607; 512 rows, 256, 912 / 916, behind 4000
-// positions 1087 / 1057; 1024 rows, 512, 1615 / 1602, behind 1024 and 4000 positions 1706 / 1638, 1907 / 1803; four prompts of 128
-// rows, 256, 899 / 896, behind up to 2048 positions 962 / 976; of 200 rows, 512, 1351 / 1326, 1451 / 1418; of 256 rows 1583 / 1567, behind
-// 4000 positions 1819 / 1739; 70B, two layers, 256 rows, 256, 808 / 813, 906 / 885; 8 heads, four prompts of 256 rows, 128, 224 / 237.
-bool attention_by_rows(int batch, int n_heads, int L) {
-    return L > kAttnRowsMin && (long long)batch * n_heads * ceil_div(L, kAttnGroupRows) >= 256;
+// workgroups attn_sar_kernel's smaller ones, cut over the keys, fill the chip better (7B, three layers, attn_sar_kernel / this one in
+// us: 256 rows, 128 workgroups, 525 .. 613 / 530 .. 607; 8 heads, four prompts of 256 rows, 128, 224 / 237; four prompts of 128 rows, 256,
+// 899 / 896, behind up to 2048 positions 962 / 976).  Prompts of five layers, i.e. four times the attention, with an empty cache and behind
+// 4000 positions: 32 heads, 512 rows, 256 workgroups, 928 / 920, 1282 / 1230; 1024 rows, 512, 1597 / 1549, 2183 / 1976; two of 256 rows,
+// 256, 913 / 906, 1199 / 1140; four of 200, 512, 1284 / 1250, 1636 / 1593; three of 200, 384, 1010 / 1003, 1267 / 1307 (behind 4000 and two
+// short ones 1204 / 1168); 64 heads, 256 rows, 256, 637 / 630, 1000 / 935.  Of heads of 64 a lone block needs more than a workgroup per
+// CU, since a chunk then has half the matrix work beside the same softmax: 512 rows, 256, 635 / 638, 817 / 850; 576 rows, 288, 717 / 702, 926 /
+// 945 (behind 2048 820 / 815); 768 rows, 384, 846 / 827, 1068 / 1078.  A batch has it by being cut over the keys.
+static bool attention_by_rows(int batch, int n_heads, int head_dim, int L) {
+    const long long wgs = (long long)batch * n_heads * ceil_div(L, kAttnGroupRows);
+    return L > kAttnRowsMin && wgs >= (batch == 1 && head_dim < 128 ? 288 : 256);
 }
-int attention_groups(int batch, int n_heads, int L) {
-    return attention_by_rows(batch, n_heads, L) ? ceil_div(L, kAttnGroupRows) : ceil_div(ceil_div(L, 16), 3);
+int attention_groups(int batch, int n_heads, int head_dim, int L) {
+    return attention_by_rows(batch, n_heads, head_dim, L) ? ceil_div(L, kAttnGroupRows) : ceil_div(ceil_div(L, 16), 3);
 }
 
 // Query tiles per workgroup.  Three share every chunk of keys best (long blocks: 3 tiles 165 us, 2 tiles 184 us at
@@ -2656,7 +2660,7 @@ int attention_groups(int batch, int n_heads, int L) {
 // positions 41.0 against 48.1).  Where both make the same number of groups, two waste less on padding.
 static int attention_query_tiles(const AttnLaunch& a) {
     const int tiles = ceil_div(a.L, 16);
-    if (attention_by_rows(a.batch, a.n_heads, a.L)) return kAttnGroupRows / 16;
+    if (attention_by_rows(a.batch, a.n_heads, a.head_dim, a.L)) return kAttnGroupRows / 16;
     if (tiles < 3 || a.qkv) return tiles < 3 ? tiles : 3;
     const int per = a.batch * a.n_heads * a.n_wg, wgs3 = per * ceil_div(tiles, 3), wgs2 = per * ceil_div(tiles, 2);
     if (wgs2 == wgs3) return 2;

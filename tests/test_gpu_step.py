@@ -291,8 +291,9 @@ def test_long_prompt_chunks_match_oracle(torch_mod, shape_name, n_prompt, chunk)
 
 
 @pytest.mark.parametrize("shape_name,rows,k,ctxs,paged", [
-    ("64 heads", 256, 0, [0], False),            # a lone prompt, a workgroup per CU, four full groups
+    ("64 heads", 256, 0, [40], False),           # heads of 64: a workgroup per CU, one too few (attn_sar_kernel)
     ("64 heads", 257, 0, [31], True),            # a fifth group of one row, and workgroups that share CUs
+    ("64 heads of 128", 256, 0, [0], False),     # a lone prompt, a workgroup per CU, four full groups
     ("64 heads", 449, 0, [1023], False),         # two to a CU
     ("64 heads", 576, 23, [45], False),          # mask rows; more workgroups than fit at once
     ("gqa128", 993, 0, [1, 700], False),         # equal numbers of workgroups and CUs, two sequences
@@ -301,14 +302,14 @@ def test_long_prompt_chunks_match_oracle(torch_mod, shape_name, n_prompt, chunk)
     ("tiny", 321, 0, "ragged", False),
 ])
 def test_attention_of_long_blocks(torch_mod, shape_name, rows, k, ctxs, paged):
-    """Blocks that attn_rows_kernel takes (space_prefill), prompts and blocks with mask rows, at the edges of the 64-row groups, 32-key
+    """Blocks that attn_rows_kernel takes (space_prefill) and one that it does not, prompts and blocks with mask rows, at the edges of the 64-row groups, 32-key
     chunks and 64-key stages: the first layer's attention output of every row against the oracle's, and the keys and values of
     the layer behind it."""
     torch = torch_mod
     import dataclasses
     from paper_2402_11809_amd import binding, layout as lo
-    if shape_name == "64 heads":
-        shape = dataclasses.replace(SHAPES["gqa-small"], n_layers=2, n_heads=64, n_kv_heads=8)
+    if shape_name.startswith("64 heads"):
+        shape = dataclasses.replace(SHAPES["gqa-small"], n_layers=2, n_heads=64, n_kv_heads=8, head_dim=128 if "128" in shape_name else 64)
     else:
         shape = dataclasses.replace(SHAPES[shape_name], n_layers=2)
     w = all_weights(shape, seed=8)

@@ -375,7 +375,8 @@ int space_sar_loss(space_ctx *ctx, const float *logits, const int32_t *labels, i
  * The cut of the rows changes no result (every output element is computed by the same instructions in the same
  * order); the number of partial sums and pieces cut over the contraction change the order of the fp32 additions, i.e.
  * results of a tuned context can differ from an untuned one's in the last bits, as they do between any two tilings, where
- * something is that far ahead.  Unlike the other calls it waits for the
+ * something is that far ahead.  The last layer of a prompt chunk projects keys and values alone; that launch, smaller than
+ * the QKV projection that is measured, keeps the library's own choice.  Unlike the other calls it waits for the
  * stream (a few tens of milliseconds) and must not be called on a stream that is being captured
  * (SPACE_EINVAL).  rows: 1..max_batch*max_rows, else SPACE_ESHAPE.  Row counts below the many-row kernel's
  * switch points and contexts without a loaded layer return SPACE_OK without doing anything. */

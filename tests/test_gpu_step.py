@@ -297,6 +297,8 @@ def test_long_prompt_chunks_match_oracle(torch_mod, shape_name, n_prompt, chunk)
     ("64 heads", 449, 0, [1023], False),         # two to a CU
     ("64 heads", 576, 23, [45], False),          # mask rows; more workgroups than fit at once
     ("gqa128", 993, 0, [1, 700], False),         # equal numbers of workgroups and CUs, two sequences
+    ("64 heads of 128", 321, 0, [700], True),    # heads of 128 over pages, six groups
+    ("gqa128", 257, 0, "ragged", True),          # ... dealt out and cut by length
     ("gqa-small", 193, 0, "ragged", False),      # a batch dealt out and cut by length, merged by whoever ends last
     ("gqa-small", 196, 13, "ragged", True),
     ("tiny", 321, 0, "ragged", False),
@@ -429,10 +431,9 @@ def test_pieces_cut_over_the_contraction(torch_mod, shape_name, B, k, tail):
 
 
 @pytest.mark.parametrize("shape_name,B,k", [("small128", 3, 5), ("small128", 6, 5), ("gqa128", 2, 8), ("small128", 8, 5)])
-def test_library_switches_between_the_projection_kernels_by_itself(torch_mod, shape_name, B, k):
-    """Row counts of two and three passes of the skinny kernel on small models, nothing forced: 108, 162, 216 and 288
-    rows (all in passes there: which projections take the many-row kernel is the rounds of workgroups, see the next
-    test)."""
+def test_two_and_three_passes_on_small_models(torch_mod, shape_name, B, k):
+    """Row counts of two and three passes of the weight-streaming kernel on small models, nothing forced: 108, 162, 216 and 288
+    rows, all in passes (which projections take the many-row kernel by themselves: the next test)."""
     shape = SHAPES[shape_name]
     _batched_step_vs_oracle(torch_mod, shape, all_weights(shape, seed=3), B, k, None, gc.LOGIT_TIGHT)
 
@@ -471,8 +472,8 @@ def test_measured_cut_and_split_stay_within_rounding(torch_mod, B, k):
     no bit (next test); the number of partial sums reorders fp32 additions, so whatever it picks, the
     logits stay within 1e-3 of the untuned step's (a reordered sum can move a key or value across a bf16
     rounding boundary, which shows downstream), and indices and accepted counts are the same wherever
-    the untuned step's top two logits are more than 1e-3 apart.  216 rows (all projections), 162 rows (QKV
-    only) and 288 rows; also the call's error paths."""
+    the untuned step's top two logits are more than 1e-3 apart.  216, 162 and 288 rows, with the many-row kernel forced (these
+    projections would run in passes, which are not measured); also the call's error paths."""
     torch = torch_mod
     from paper_2402_11809_amd import binding, layout as lo
     shape = SHAPES["small128"]
@@ -482,8 +483,8 @@ def test_measured_cut_and_split_stay_within_rounding(torch_mod, B, k):
     rng = np.random.default_rng(12)
     toks = rng.integers(0, shape.vocab, size=(B, L)).astype(np.int32)
     results = []
-    for tuned in (False, True):
-        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L)
+    for tuned, tune in ((False, "wide=1"), (True, "wide=1"), (False, "wide=0")):
+        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune=tune)
         if tuned:
             gm.tune_rows(B * L)
             gm.tune_rows(B * L)  # a second request for the same count is a no-op
@@ -499,7 +500,8 @@ def test_measured_cut_and_split_stay_within_rounding(torch_mod, B, k):
             gc.upload_oracle_kv(torch, cache, b, gc.synthetic_oracle_kv(om, seed=40 + b, ctx=11 * b + 5, std=0.5))
         out = _run_step(torch, gm, cache, spec, toks, batch=B)
         results.append((out.logits.cpu().numpy().copy(), out.argmax.cpu().numpy().copy(), out.accepted_len.cpu().numpy().copy()))
-    (l0, a0, n0), (l1, a1, n1) = results
+    (l0, a0, n0), (l1, a1, n1), (passes, _, _) = results
+    assert not np.array_equal(l0, passes)  # (another order of sums: what was measured is the many-row kernel)
     assert np.abs(l0 - l1).max() < 1e-3
     top2 = np.sort(l0, axis=-1)[..., -2:]
     clear = (top2[..., 1] - top2[..., 0]) > 1e-3
@@ -509,8 +511,8 @@ def test_measured_cut_and_split_stay_within_rounding(torch_mod, B, k):
 
 
 def test_every_row_cut_gives_the_same_bits(torch_mod):
-    """288 rows = 9 groups of 32 rows, cut in every piece size and all launch orders (forced through
-    SPACE_TUNE widecut=): logits, indices and accepted counts equal the default cut's bit for bit."""
+    """288 rows = 9 groups of 32 rows, cut in every piece size and all launch orders (forced through SPACE_TUNE widecut=,
+    and the many-row kernel through wide=): logits, indices and accepted counts equal the default cut's bit for bit."""
     torch = torch_mod
     from paper_2402_11809_amd import binding, layout as lo
     shape = SHAPES["small128"]
@@ -524,7 +526,7 @@ def test_every_row_cut_gives_the_same_bits(torch_mod):
     ref = None
     for cut in (None, "2:0:0:1:0", "0:3:0:0:0", "0:3:0:0:1", "0:1:3:0:1", "0:0:4:1:0", "1:0:2:1:1", "0:0:0:9:1", "1:1:1:0:0",
                 "2:0:0:1:2", "0:1:3:0:2", "1:1:1:0:2"):
-        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune=None if cut is None else "widecut=" + cut)
+        gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune="wide=1" if cut is None else "wide=1,widecut=" + cut)
         cache = binding.KVCache(gm, B, 160)
         for b in range(B):
             gc.upload_oracle_kv(torch, cache, b, okvs[b])
@@ -881,8 +883,8 @@ def test_query_tiles_per_workgroup_of_long_blocks(torch_mod, shape_name, B, k, c
 
 @pytest.mark.parametrize("cut", ["2:0:0:1:0", "0:3:0:0:1", "0:0:4:1:0", "0:0:0:9:1", "1:1:1:0:0", "1:1:1:0:2", "2:0:0:1:2"])
 def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
-    """As the test with contractions that are never split, at 1024 wide (32 and 43 contraction tiles): 288 rows,
-    where the planner takes two partial sums for QKV, O and down.  A forced cut keeps the partial sums of the default
+    """As the test with contractions that are never split, at 1024 wide (32 and 43 contraction tiles): 288 rows with the many-row
+    kernel forced, where its planner takes two partial sums for QKV, O and down.  A forced cut keeps the partial sums of the default
     one, so logits, indices and accepted counts are equal bit for bit."""
     torch = torch_mod
     from paper_2402_11809_amd import layout as lo
@@ -895,7 +897,7 @@ def test_row_cuts_of_split_contractions_give_the_same_bits(torch_mod, cut):
     om = gc.oracle_model(shape, w)
     okvs = [gc.synthetic_oracle_kv(om, seed=80 + b, ctx=9 * b + 4, std=0.5) for b in range(B)]
     got = []
-    for tune in (None, "widecut=" + cut):
+    for tune in ("wide=1", "wide=1,widecut=" + cut):
         gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=L, tune=tune)
         cache = gm.kv_cache(B, 160)
         for b in range(B):
@@ -1036,18 +1038,21 @@ def test_prompt_chunks_of_a_batch_dealt_out_by_length(torch_mod, shape_name, B, 
         gc.assert_bf16_close(gv, okvs[b].v[1][c:], f"seq {b} V", min_same=0.9)
 
 
-@pytest.mark.parametrize("shape_name,B,rows,tune", [
-    ("tiny", 1, 9, None), ("gqa-small", 2, 40, "qkv=6:2"), ("gqa128", 1, 70, "qkv=8:1"), ("small128", 3, 50, "qkv=6:1"),
-    ("gqa-small", 1, 150, "wide=1"), ("gqa128", 2, 130, "wide=1,wideks=2"), ("small128", 1, 330, "wide=1,wideks=4"), ("tiny", 2, 300, "qkv=6:1")])
-def test_last_layer_of_a_prompt_chunk_without_queries(torch_mod, shape_name, B, rows, tune):
+@pytest.mark.parametrize("shape_name,B,rows,tune,tuned", [
+    ("tiny", 1, 9, None, False), ("gqa-small", 2, 40, "qkv=6:2", False), ("gqa128", 1, 70, "qkv=8:1", False), ("small128", 3, 50, "qkv=6:1", False),
+    ("gqa-small", 1, 150, "wide=1", False), ("gqa128", 2, 130, "wide=1,wideks=2", False), ("small128", 1, 330, "wide=1,wideks=4", False),
+    ("tiny", 2, 300, "qkv=6:1", False), ("gqa128", 1, 200, "wide=1", True), ("gqa-small", 2, 161, "wide=1,wideks=2", True)])
+def test_last_layer_of_a_prompt_chunk_without_queries(torch_mod, shape_name, B, rows, tune, tuned):
     """The last layer's projection starts at the first key's weight tile (few rows: at the group of tiles that holds it, which need
     not start there): that layer's keys and values of chunks with one, two and many query tiles and passes, in both projection
-    kernels, with partial sums, against the oracle's prefill; the layer in front keeps its own."""
+    kernels, with partial sums, in tuned contexts (which leave that launch as it is planned) too, against the oracle's prefill; the layer in front keeps its own."""
     torch = torch_mod
     from paper_2402_11809_amd import layout as lo
     shape = SHAPES[shape_name].with_layers(2)
     w = all_weights(shape, seed=23)
     gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=512, tune=tune)
+    if tuned:
+        gm.tune_rows(B * rows)
     om = gc.oracle_model(shape, w)
     cache = gm.kv_cache(B, 512)
     lens = [13 + 50 * b for b in range(B)]
@@ -1129,6 +1134,46 @@ def test_a_key_that_is_no_number_shows_through_the_merge(torch_mod, value):
     assert np.isnan(got[long_one]).all()
     others = [b for b in range(B) if b != long_one]
     assert np.array_equal(got[others], clean[others])
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("shape_name,rows,ctxs", [("64 heads", 257, [400]), ("gqa-small", 193, "ragged")])
+def test_a_key_that_is_no_number_shows_in_long_blocks(torch_mod, shape_name, rows, ctxs, value):
+    """attn_rows_kernel, one workgroup for all keys and parts merged by whoever ends last, with one cached key element that is NaN or
+    infinite: the attention output of every row and head of that sequence is NaN where the softmax is (infinite keys: unless both
+    halves of the query's element are negative, when the key has no weight), and the other sequences' keep their bits."""
+    torch = torch_mod
+    import dataclasses
+    from paper_2402_11809_amd import layout as lo
+    shape = SHAPES["gqa-small"].with_layers(2)
+    if shape_name == "64 heads":
+        shape = dataclasses.replace(shape, n_heads=64, n_kv_heads=8)
+    if ctxs == "ragged":
+        ctxs = [(151 * b) % 690 for b in range(11)] + [700]
+    B, hd, one = len(ctxs), shape.n_heads * shape.head_dim, len(ctxs) - 1
+    w = all_weights(shape, seed=8)
+    gm = gc.make_gpu_model(shape, w, max_batch=B, max_rows=rows, max_ctx=1024)
+    om = gc.oracle_model(shape, w)
+    cache = gm.kv_cache(B, 1024)
+    for b, c in enumerate(ctxs):
+        gc.upload_oracle_kv(torch, cache, b, gc.synthetic_oracle_kv(om, seed=30 + b, ctx=c, std=0.5))
+    toks = torch.from_numpy(np.random.default_rng(11).integers(0, shape.vocab, size=(B, rows)).astype(np.int32)).cuda()
+
+    def attention():
+        gm.prefill(toks, gm.layout(lo.prefill_layout(rows)), cache)
+        torch.cuda.synchronize()
+        return gc.decode_planes(gm.debug_buffer("attn_out"), B * rows, hd).reshape(B, rows, shape.n_heads, shape.head_dim)
+
+    clean = attention()
+    cache.k_view()[0, one, :, 333, 0] = value
+    got = attention()
+    q = gc.bits_to_f64(gm.debug_buffer("q")[: 2 * B * rows * hd]).reshape(2, B, shape.n_heads, rows, shape.head_dim)
+    hi, lo_ = (q[plane, one, :, :, 0].T for plane in (0, 1))  # [row, head]
+    assert np.isfinite(clean).all()
+    hit = np.ones_like(hi, dtype=bool) if np.isnan(value) else ~((hi < 0) & (lo_ < 0))
+    assert hit.any() and (np.isnan(value) or not hit.all())
+    assert np.isnan(got[one][hit]).all() and np.isfinite(got[one][~hit]).all()
+    assert np.array_equal(got[:one], clean[:one])
 
 
 @pytest.fixture(scope="module")

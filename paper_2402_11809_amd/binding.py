@@ -375,7 +375,7 @@ class Model:
                       next_layout: Optional[Layout] = None, stream=None, static: bool = False) -> None:
         """space_sample_verify (static=True: space_sample_verify_static, same arguments): logits float32 [batch, L, vocab], tokens int32 [batch, L], p_c float32
         [batch, max_cands], uniforms float32 [batch, G + max_cands], all CUDA and contiguous."""
-        # A call is two launches of 8 and 4 us, so what stands in front of them counts: the struct is filled without a
+        # A call is one launch of about 12 us, so what stands in front of them counts: the struct is filled without a
         # call per pointer, and a field that is not given costs a comparison.
         import torch
         f32, batch = torch.float32, tokens.shape[0]

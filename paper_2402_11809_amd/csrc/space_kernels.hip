@@ -1679,7 +1679,7 @@ __global__ __launch_bounds__(WV * 64, WV == 4 ? 2 : 1) void attn_sar_kernel(Attn
     }
 
 // (The softmax: exponents in one fused multiply-add, values rounded and packed in pairs, the output rescaled only where a maximum has
-// grown by more than 2^8.  8 sequences of 81 rows 86 -> 82.5 us per layer, of 36 rows 70.6 -> 68.9; lone sequences level.)
+// grown by more than 2^8.  8 sequences of 81 rows 81.9 -> 77.7 us per layer, traced in turn on one box; lone sequences level.)
 // AFTER_PV runs at the end, when the value operands are free: the place where the values of the next
 // chunk are requested into the same registers.
 #define SPACE_ATTN_COMPUTE2(AK, AV, C, KEND, BLK, AFTER_PV)                                                 \
@@ -3134,8 +3134,8 @@ __device__ __noinline__ void topk_rare(const float* __restrict__ x, int V, int K
 }
 
 // Lines 6-22 of Algorithm 1 over the lists of a sequence's rows, by the workgroup of these rows that ends last: lists go through
-// memory with stores and loads that pass by the caches other XCDs do not see, and nobody waits for anybody (as in the merge of
-// attn_sar_kernel).  A launch of its own behind the rows cost a kernel boundary and the trips for what does not depend on the
+// memory with stores and loads that pass by the caches other XCDs do not see, and nobody waits for anybody (as in
+// merge_parts).  A launch of its own behind the rows cost a kernel boundary and the trips for what does not depend on the
 // rows, which now happen while wave 0 still computes: one sequence, k = 5, 10 kept, 13.3 -> 12.1 us; 8 sequences, k = 8, 50
 // kept, 32.2 -> 29.7 (34.9 with the counts of all sequences on one 128-byte line: 1300 atomics that wait for each other).
 //

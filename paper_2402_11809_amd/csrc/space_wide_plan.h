@@ -16,10 +16,12 @@ constexpr int kWideSearchGroups = 32;  // longest blocks (in groups of 32 rows) 
 // kernel has a fixed cost of 3 - 5 us more and fewer, larger workgroups, but uses the matrix unit better and shares the operand
 // planes.  So: from the second round of workgroups on, or from the third where a round is short and the sums have to be
 // complete (the many-row kernel then cannot be cut over the contraction and has few workgroups: gate / up of a 1024-wide model
-// at 128 rows, 352 workgroups of 8 rounds, 12.1 us in passes against 15.1).  Measured on 9 shapes from 256 to 8192 wide, all
+// at 128 rows, 352 workgroups of 8 rounds, 12.1 us in passes against 15.1).  Short: a wave requests at most 128 tiles of 1 KB in its lq
+// contraction tiles, r_pack of weights and 12 of operands (6 row tiles, two planes) each; the line
+// lies between that gate / up, 112 tiles, and the LM head of 32000 of the same model, 160.  Measured on 9 shapes from 256 to 8192 wide, all
 // projections, 12 row counts from 100 to 1000, passes / many-row kernel in us: 128 rows, 256 wide down 6.8 / 12.0; 1024 wide QKV 8.0 /
 // 10.4; 2048 wide QKV 23.0 / 13.7; 7B gate / up 79.8 / 60.4, LM head 110 / 72; 70B down 176 / 125; 288 rows, 256 wide QKV 5.1 / 7.7;
-// 1024 wide LM head of 32000 69.5 / 44.9; 800 rows, 512 wide gate / up 14.6 / 10.4.  Over all of them this rule is 0.3 % behind
+// 1024 wide LM head of 32000 69.5 / 44.9; 800 rows, 512 wide gate / up 14.6 / 10.4.  Over all of them, on which the rule was made, it is 0.3 % behind
 // the better of the two, fixed lines at 97 and 193 rows 13 and 12 %.
 //   groups, splits, lq, r_pack  how the matrix is packed (PackedW);  plain: the sums may be partial ones
 constexpr int kPassRows = 96;
